@@ -11,6 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblqsgd.so")
 SOURCES = ["lqsgd_plan.cpp", "lqsgd_api.cpp", "lqsgd_kernels.hip"]
+KERNEL_PARTS = 6        # the kernel file is compiled in this many parts side by side (LQSGD_PART in the file)
 
 
 def hipcc() -> str:
@@ -33,10 +34,12 @@ def build(verbose: bool = True, extra=(), out: str = LIB) -> str:
     # the feature and says so, which is harmless.
     dev = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
     procs = []
-    for src in SOURCES:
-        obj = os.path.join(bdir, os.path.splitext(src)[0] + ".o")
+    units = [(s, None) for s in SOURCES if not s.endswith(".hip")]
+    units += [(s, k) for s in SOURCES if s.endswith(".hip") for k in range(KERNEL_PARTS)]
+    for src, part in units:
+        obj = os.path.join(bdir, os.path.splitext(src)[0] + ("" if part is None else "_%d" % part) + ".o")
         objs.append(obj)
-        cmd = [hipcc()] + common + (dev if src.endswith(".hip") else []) + list(extra) + \
+        cmd = [hipcc()] + common + (dev + ["-DLQSGD_PART=%d" % part] if part is not None else []) + list(extra) + \
               ["-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)

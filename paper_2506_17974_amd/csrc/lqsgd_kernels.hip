@@ -27,10 +27,21 @@
 #include <cstdlib>
 #include <type_traits>
 
+// The kernels are templates and most of the build is their instantiation, so the file is compiled
+// several times side by side, each time with the launchers of one part (LQSGD_PART = 0 .. 5) and
+// with them the kernels that those launch.  Without the macro it is one whole translation unit.
+#ifdef LQSGD_PART
+#define LQSGD_HAS(part) (LQSGD_PART == (part))
+#else
+#define LQSGD_HAS(part) 1
+#endif
+
+#if LQSGD_HAS(0)
 // Scratch block of lqsgd_step_static (see static_scratch() below): device memory that is part of
 // the code object, one copy per GPU.  In host code this name is a handle for hipGetSymbolAddress,
 // never an address.
 static __device__ __align__(256) unsigned char scratch[LQSGD_STATIC_SCRATCH_BYTES];
+#endif
 
 namespace lqsgd {
 namespace {
@@ -891,7 +902,7 @@ __global__ __launch_bounds__(256) void orth_wide_kernel(DevArgs a, int j, int ns
 // Every wait is bounded; if one ever expires the workgroup raises the status
 // word and carries on, so the kernel always ends.
 // ---------------------------------------------------------------------------
-constexpr unsigned kTablePolls = 1u << 20;      // default bound of a wait (about a second)
+[[maybe_unused]] constexpr unsigned kTablePolls = 1u << 20;      // default bound of a wait (about a second)
 constexpr int kCoopMaxSlices = 64;               // rows <= 16384 per factor in this form
 
 __device__ __forceinline__ unsigned long long table_load(const unsigned long long* p) {
@@ -2922,17 +2933,18 @@ __global__ __launch_bounds__(256, 2) void orth_chol_kernel(DevArgs a, int nslice
 // Every launcher notes the device function it has just launched, template arguments included, in
 // the form a profiler's kernel list shows it (without namespaces and parameter list), so that a
 // timing slot of the API can be matched to a profile.
-namespace {
-thread_local char g_launched[96] = "";
-__attribute__((format(printf, 1, 2))) void note_kernel(const char* fmt, ...) {
+__attribute__((format(printf, 1, 2))) void note_kernel(const char* fmt, ...);
+#if LQSGD_HAS(0)
+static thread_local char g_launched[96] = "";
+void note_kernel(const char* fmt, ...) {
   va_list ap;
   va_start(ap, fmt);
   std::vsnprintf(g_launched, sizeof g_launched, fmt, ap);
   va_end(ap);
 }
-const char* tf(bool b) { return b ? "true" : "false"; }
-}  // namespace
 const char* last_launched_kernel() { return g_launched; }
+#endif
+static inline const char* tf(bool b) { return b ? "true" : "false"; }
 
 #define LQSGD_RP_SWITCH(RPV, CALL)            \
   switch (RPV) {                              \
@@ -2950,6 +2962,7 @@ const char* last_launched_kernel() { return g_launched; }
   if ((RPV) == 64) { constexpr int RP = 64; CALL; } else \
     LQSGD_RP_SWITCH(RPV, CALL)
 
+#if LQSGD_HAS(1)
 hipError_t launch_add_project(int rp, const DevArgs& a, const Tile* tiles, int ntiles, int fuse_residual, int reverse,
                               hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
@@ -2968,7 +2981,9 @@ hipError_t launch_add_project(int rp, const DevArgs& a, const Tile* tiles, int n
   note_kernel("add_project_kernel<%d, %s, %s, %s>", rp, tf(fuse_residual), tf(a.g_bf16), tf(a.nt_store));
   return hipGetLastError();
 }
+#endif
 
+#if LQSGD_HAS(4)
 // Register-resident Gram-Schmidt where rows-per-lane x rank fits the register
 // file comfortably; the in-memory kernel otherwise.
 template <int RP, int RPT, int BS>
@@ -3041,7 +3056,9 @@ bool launch_orth_coop(int rp, int nslice, int max_rank, const DevArgs& a, int nb
     default: return false;
   }
 }
+#endif
 
+#if LQSGD_HAS(5)
 // The Cholesky-QR form in one cooperative launch; false (nothing launched) if the grid cannot be
 // resident at once or the stream is being captured.
 template <int RP>
@@ -3109,6 +3126,20 @@ int chol_entries(int rp) {
   return rp == 8 ? CholShape<8>::NE : rp == 16 ? CholShape<16>::NE : rp == 32 ? CholShape<32>::NE : rp == 64 ? CholShape<64>::NE : 0;
 }
 
+// The Cholesky-QR Gram-Schmidt of every pair: in one cooperative launch, or else in several launches.
+hipError_t launch_orth_chol(int rp, int nslice, int max_rank, const DevArgs& a, int nblocks, CoopState* coop, hipStream_t s) {
+  if (launch_orth_chol_coop(rp, nslice, max_rank, a, nblocks, coop, s)) return hipSuccess;
+  if (rp == 8) launch_orth_chol_split<8>(nslice, max_rank, a, nblocks, s);
+  else if (rp == 16) launch_orth_chol_split<16>(nslice, max_rank, a, nblocks, s);
+  else if (rp == 32) launch_orth_chol_split<32>(nslice, max_rank, a, nblocks, s);
+  else launch_orth_chol_split<64>(nslice, max_rank, a, nblocks, s);
+  return hipGetLastError();
+}
+#endif
+
+hipError_t launch_orth_chol(int rp, int nslice, int max_rank, const DevArgs& a, int nblocks, CoopState* coop, hipStream_t s);
+
+#if LQSGD_HAS(4)
 hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, CoopState* coop, hipStream_t s) {
   if (a.L <= 0) return hipSuccess;
   const dim3 grid(a.L * a.W);
@@ -3124,12 +3155,7 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, Coo
     constexpr bool chol = true;
 #endif
     if (chol && rp >= 8 && a.chol_part && a.chol_redo) {
-      if (launch_orth_chol_coop(rp, nslice, max_rank, a, (int)grid.x * nslice, coop, s)) return hipSuccess;
-      if (rp == 8) launch_orth_chol_split<8>(nslice, max_rank, a, (int)grid.x * nslice, s);
-      else if (rp == 16) launch_orth_chol_split<16>(nslice, max_rank, a, (int)grid.x * nslice, s);
-      else if (rp == 32) launch_orth_chol_split<32>(nslice, max_rank, a, (int)grid.x * nslice, s);
-      else launch_orth_chol_split<64>(nslice, max_rank, a, (int)grid.x * nslice, s);
-      return hipGetLastError();
+      return launch_orth_chol(rp, nslice, max_rank, a, (int)grid.x * nslice, coop, s);
     }
     if (launch_orth_coop(rp, nslice, max_rank, a, (int)grid.x * nslice, coop, s)) return hipSuccess;
     for (int j = 0; j <= max_rank; ++j) {
@@ -3152,7 +3178,9 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, Coo
   }
   return hipGetLastError();
 }
+#endif
 
+#if LQSGD_HAS(0)
 hipError_t launch_exchange(int mode, int phase, const DevArgs& a, const XTile* tiles, int ntiles, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   const dim3 grid(ntiles), block(256);
@@ -3165,7 +3193,9 @@ hipError_t launch_exchange(int mode, int phase, const DevArgs& a, const XTile* t
   note_kernel("exchange_kernel<%d>", mode);
   return hipGetLastError();
 }
+#endif
 
+#if LQSGD_HAS(1)
 hipError_t launch_back_project(int rp, const DevArgs& a, const Tile* tiles, int ntiles, const VTile* vtiles, int nvtiles,
                                int reverse, hipStream_t s) {
   if (ntiles + nvtiles <= 0) return hipSuccess;
@@ -3185,14 +3215,18 @@ hipError_t launch_back_project_mfma(int rp, const DevArgs& a, const Tile* tiles,
   note_kernel("back_project_mfma_kernel<%d>", rp == 64 ? 2 : 1);
   return hipGetLastError();
 }
+#endif
 
+#if LQSGD_HAS(0)
 hipError_t launch_reduce_q(int phase, const DevArgs& a, const RTile* tiles, int ntiles, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   reduce_q_kernel<<<dim3(ntiles), dim3(256), 0, s>>>(a, tiles, phase);
   note_kernel("reduce_q_kernel");
   return hipGetLastError();
 }
+#endif
 
+#if LQSGD_HAS(1)
 hipError_t launch_residual(int rp, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   const dim3 grid(ntiles), block(256);
@@ -3205,6 +3239,7 @@ hipError_t launch_residual(int rp, int mode, const DevArgs& a, const Tile* tiles
   note_kernel("residual_kernel<%d, %d>", rp, mode);
   return hipGetLastError();
 }
+#endif
 
 // A tuning build (-DLQSGD_TUNING) can keep the 32 x 64 form at rank pad 32 for comparisons (LQSGD_MFMA_NARROW32=0).
 static bool narrow32() {
@@ -3271,15 +3306,25 @@ hipError_t launch_mfma_sweep_rp(int mode, int full_rank, const DevArgs& a, const
   return hipGetLastError();
 }
 
+// rank pads 16 and 32 in one part, 64 in another: about the same time to compile
+hipError_t launch_mfma_sweep64(int mode, int full_rank, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s);
+#if LQSGD_HAS(3)
+hipError_t launch_mfma_sweep64(int mode, int full_rank, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s) {
+  return launch_mfma_sweep_rp<64>(mode, full_rank, a, tiles, ntiles, reverse, s);
+}
+#endif
+#if LQSGD_HAS(2)
 hipError_t launch_mfma_sweep(int rp, int mode, int full_rank, const DevArgs& a, const Tile* tiles, int ntiles, int reverse,
                              hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   if (rp == 16) return launch_mfma_sweep_rp<16>(mode, full_rank, a, tiles, ntiles, reverse, s);
   if (rp == 32) return launch_mfma_sweep_rp<32>(mode, full_rank, a, tiles, ntiles, reverse, s);
-  if (rp == 64) return launch_mfma_sweep_rp<64>(mode, full_rank, a, tiles, ntiles, reverse, s);
+  if (rp == 64) return launch_mfma_sweep64(mode, full_rank, a, tiles, ntiles, reverse, s);
   return hipErrorInvalidValue;
 }
+#endif
 
+#if LQSGD_HAS(0)
 // ---------------------------------------------------------------------------
 // Scratch memory for the entry point that allocates nothing: one block per GPU,
 // part of the loaded code object, held until the process ends.  The name below
@@ -3330,5 +3375,6 @@ hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, hipStream_t s)
   pad_factor_kernel<<<dim3(64, a.L), dim3(256), 0, s>>>(a, RP, which);
   return hipGetLastError();
 }
+#endif
 
 }  // namespace lqsgd
