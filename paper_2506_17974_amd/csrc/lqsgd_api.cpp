@@ -58,7 +58,6 @@ struct lqsgd_ctx {
   const float** d_grads = nullptr; float** d_ghat = nullptr;
   std::vector<const float*> h_grads; std::vector<float*> h_ghat;
   bool grads_valid = false, ghat_valid = false;
-  bool ppad_stale = true, qpad_stale = true;   // the padded copies of P-bar / Q-bar lag behind the factors
   bool alias_checked = false;   // the bound gradient and output tables have been checked against each other
   // timing
   std::string launched[LQSGD_KERNEL_COUNT];   // device function last launched for each timing slot
@@ -206,27 +205,13 @@ int next_dir(lqsgd_ctx* c) {
   return d;
 }
 
-// Matrix-core sweeps 0 / 2 read P-bar and Q-bar from copies with padded rows when some layer has
-// fewer ranks than the register pad; whoever writes a factor marks its copy stale.
-int refresh_padded(lqsgd_ctx* c, bool need_p, bool need_q) {
-  if (!c->plan.padded) return LQSGD_OK;
-  // While the stream is being captured the flags describe the moment of the capture, not of a later
-  // replay (a host upload may come in between): every copy that is needed is then refreshed, and
-  // the flags are left as they were.
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusNone; }
-  const bool capturing = cap != hipStreamCaptureStatusNone;
-  if (need_p && (c->ppad_stale || capturing)) {
-    HIP_TRY(c, launch_pad_factor(c->plan.RP, 0, c->args, c->stream));
-    if (!capturing) c->ppad_stale = false;
-  }
-  if (need_q && (c->qpad_stale || capturing)) {
-    HIP_TRY(c, launch_pad_factor(c->plan.RP, 1, c->args, c->stream));
-    if (!capturing) c->qpad_stale = false;
-  }
+// The sweeps read P-bar and Q-bar from copies with padded rows when some layer has fewer ranks than the register
+// pad.  The exchange writes factor and copy together; every other writer of a factor calls this right after it, so a
+// copy is never older than its factor, also between the replays of captured steps.
+int refresh_padded(lqsgd_ctx* c, int which) {
+  if (c->plan.padded) HIP_TRY(c, launch_pad_factor(c->plan.RP, which, c->args, c->stream));
   return LQSGD_OK;
 }
-int full_rank(const lqsgd_ctx* c) { return (c->plan.max_rank == c->plan.RP || c->plan.padded) ? 1 : 0; }
 
 // The one-launch Gram-Schmidt's state, or null where the context must not launch cooperatively.
 CoopState* coop_state(lqsgd_ctx* c) {
@@ -234,11 +219,9 @@ CoopState* coop_state(lqsgd_ctx* c) {
 }
 
 int run_sweep0(lqsgd_ctx* c) {
-  if (c->plan.mfma_a)
-    if (int rc = refresh_padded(c, c->pending, true)) return rc;
   { Timed t(c, LQSGD_KERNEL_ADD_PROJECT);
     if (c->plan.mfma_a)
-      HIP_TRY(c, launch_mfma_sweep(c->plan.RP, c->pending ? 1 : 0, full_rank(c), c->args, c->d_tilesA, (int)c->plan.tilesA.size(),
+      HIP_TRY(c, launch_mfma_sweep(c->plan.RP, c->pending ? 1 : 0, c->args, c->d_tilesA, (int)c->plan.tilesA.size(),
                                    next_dir(c), c->stream));
     else
       HIP_TRY(c, launch_add_project(c->plan.RP, c->args, c->d_tilesA, (int)c->plan.tilesA.size(), c->pending ? 1 : 0,
@@ -264,16 +247,14 @@ int run_orth_shared(lqsgd_ctx* c) {
   a.Ppre = c->args.Porth;
   a.Porth = c->args.Pbar;
   HIP_TRY(c, launch_orth(c->plan.RP, c->plan.max_rows, c->plan.max_rank, a, coop_state(c), c->stream));
-  c->ppad_stale = true;
-  return LQSGD_OK;
+  return refresh_padded(c, 0);
 }
 int run_exchange(lqsgd_ctx* c, int mode, int phase) {
   { Timed t(c, phase ? LQSGD_KERNEL_EXCHANGE_Q : LQSGD_KERNEL_EXCHANGE_P);
     const auto& tl = phase ? c->plan.tilesXQ : c->plan.tilesXP;
     DevArgs a = c->args;
     if (c->plan.agg_first && phase == 0) a.Porth = c->args.Ppre;   // the raw factors are what gets quantised
-    HIP_TRY(c, launch_exchange(mode, phase, a, phase ? c->d_tilesXQ : c->d_tilesXP, (int)tl.size(), c->stream));
-    if (mode != kQuantOnly) (phase ? c->qpad_stale : c->ppad_stale) = true; }
+    HIP_TRY(c, launch_exchange(mode, phase, a, phase ? c->d_tilesXQ : c->d_tilesXP, (int)tl.size(), c->stream)); }
   if (c->plan.agg_first && phase == 0 && mode != kQuantOnly) return run_orth_shared(c);
   return LQSGD_OK;
 }
@@ -296,18 +277,16 @@ int run_sweep1(lqsgd_ctx* c, bool with_vectors) {
 // when asked for, is then written by a pass of its own over the layers.
 int run_sweep2(lqsgd_ctx* c, bool write_ghat) {
   const Plan& p = c->plan;
-  if (p.mfma_a && (c->eager || write_ghat))
-    if (int rc = refresh_padded(c, true, true)) return rc;
   Timed t(c, LQSGD_KERNEL_RESIDUAL);
   if (c->eager) {
     if (p.mfma_a)
-      HIP_TRY(c, launch_mfma_sweep(p.RP, write_ghat ? 3 : 2, full_rank(c), c->args, c->d_tilesA, (int)p.tilesA.size(), next_dir(c), c->stream));
+      HIP_TRY(c, launch_mfma_sweep(p.RP, write_ghat ? 3 : 2, c->args, c->d_tilesA, (int)p.tilesA.size(), next_dir(c), c->stream));
     else
       HIP_TRY(c, launch_residual(p.RP, write_ghat ? 1 : 0, c->args, c->d_tilesB, (int)p.tilesB.size(), next_dir(c), c->stream));
   } else {
     if (write_ghat) {
       if (p.mfma_a)
-        HIP_TRY(c, launch_mfma_sweep(p.RP, 4, full_rank(c), c->args, c->d_tilesAG, (int)p.tilesAG.size(), 0, c->stream));
+        HIP_TRY(c, launch_mfma_sweep(p.RP, 4, c->args, c->d_tilesAG, (int)p.tilesAG.size(), 0, c->stream));
       else
         HIP_TRY(c, launch_residual(p.RP, 2, c->args, c->d_tilesG, (int)p.tilesG.size(), 0, c->stream));
     }
@@ -319,11 +298,9 @@ int run_sweep2(lqsgd_ctx* c, bool write_ghat) {
 int materialise(lqsgd_ctx* c) {
   if (!c->pending) return LQSGD_OK;
   const Plan& p = c->plan;
-  if (p.mfma_a)
-    if (int rc = refresh_padded(c, true, true)) return rc;
   Timed t(c, LQSGD_KERNEL_RESIDUAL);
   if (p.mfma_a)
-    HIP_TRY(c, launch_mfma_sweep(p.RP, 2, full_rank(c), c->args, c->d_tilesA, (int)p.tilesA.size(), next_dir(c), c->stream));
+    HIP_TRY(c, launch_mfma_sweep(p.RP, 2, c->args, c->d_tilesA, (int)p.tilesA.size(), next_dir(c), c->stream));
   else
     HIP_TRY(c, launch_residual(p.RP, 0, c->args, c->d_tilesB, (int)p.tilesB.size(), next_dir(c), c->stream));
   c->pending = false;
@@ -411,7 +388,7 @@ int64_t lqsgd_plan_tiles(const lqsgd_config* cfg, const lqsgd_layer* layers, int
         o[4] = t.aux * d.segw;
         o[5] = std::min(d.cols, o[4] + d.segw) - o[4];
       } else {
-        const int cw = bm ? kMfmaCols : kWave * d.vec;
+        const int cw = bm ? kMfmaCols : kWave * 4;
         o[4] = t.aux * cw;
         o[5] = std::min(d.cols, o[4] + cw) - o[4];
       }
@@ -433,7 +410,7 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   HIP_TRY(c, hipGetDevice(&c->device));
   const Plan& p = c->plan;
   DevArgs& a = c->args;
-  a.W = p.W; a.L = p.L; a.n_all = p.n_all; a.bits_p = p.cfg.bits_p; a.bits_q = p.cfg.bits_q;
+  a.W = p.W; a.L = p.L; a.n_all = p.n_all; a.rank_pad = p.RP; a.bits_p = p.cfg.bits_p; a.bits_q = p.cfg.bits_q;
   a.alpha = p.cfg.alpha;
   a.agg_first = p.agg_first ? 1 : 0; a.orth_shared = 0; a.update = 0; a.eta = 0.0f;
   a.g_bf16 = (flags & LQSGD_FLAG_BF16_GRADIENTS) ? 1 : 0;
@@ -504,10 +481,11 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   TRY_(dev_alloc(c, &a.Qpart, W * p.qpart_stride + kSlack, true));
   TRY_(dev_alloc(c, &a.Qw, W * p.q_stride + kSlack, true));
   if (!ext) TRY_(dev_alloc(c, &a.Qbar, (size_t)p.q_stride + kSlack, true));
-  a.Ppad = nullptr; a.Qpad = nullptr;
+  a.padded = p.padded ? 1 : 0;
+  a.Pop = a.Pbar; a.Qop = a.Qbar;
   if (p.padded) {
-    TRY_(dev_alloc(c, &a.Ppad, (size_t)p.ppad_total + kSlack, true));
-    TRY_(dev_alloc(c, &a.Qpad, (size_t)p.qpad_total + kSlack, true));
+    TRY_(dev_alloc(c, &a.Pop, (size_t)p.ppad_total + kSlack, true));
+    TRY_(dev_alloc(c, &a.Qop, (size_t)p.qpad_total + kSlack, true));
   }
   TRY_(dev_alloc(c, &a.magP, W * p.magp_stride, true));
   TRY_(dev_alloc(c, &a.sgnP, W * p.sgnp_stride, true));
@@ -629,7 +607,7 @@ int lqsgd_set_state(lqsgd_ctx* c, int32_t layer, int32_t worker, const float* ho
                          (size_t)ld->rows * ld->cols * sizeof(float), hipMemcpyHostToDevice));
   if (host_q) {
     HIP_TRY(c, hipMemcpy(c->args.Qbar + ld->q_off, host_q, (size_t)ld->nq_el * sizeof(float), hipMemcpyHostToDevice));
-    c->qpad_stale = true;
+    return refresh_padded(c, 1);
   }
   return LQSGD_OK;
 }
@@ -853,8 +831,7 @@ int lqsgd_set_factor(lqsgd_ctx* c, int32_t which, int32_t layer, const float* ho
   if ((rc = materialise(c))) return rc;      // a deferred update is defined by the old factors
   if (int rcs = sync_stream(c)) return rcs;
   HIP_TRY(c, hipMemcpy(dst, host, n * sizeof(float), hipMemcpyHostToDevice));
-  (which == LQSGD_FACTOR_P_BAR ? c->ppad_stale : c->qpad_stale) = true;
-  return LQSGD_OK;
+  return refresh_padded(c, which == LQSGD_FACTOR_P_BAR ? 0 : 1);
 }
 
 int64_t lqsgd_wire_bytes(const lqsgd_ctx* c) { return c ? c->plan.wire_bytes : (int64_t)LQSGD_EINVAL; }
@@ -981,10 +958,11 @@ int lqsgd_step_static(const lqsgd_config* cfg, const lqsgd_layer* layers, int32_
   }
   c->args.E = residual;
   c->args.Qbar = warm_q;
+  if (!c->plan.padded) c->args.Qop = warm_q;
   c->pending = false;                        // the caller's buffer holds E, and holds E again on return
-  c->ppad_stale = c->qpad_stale = true;      // the warm-start Q is the caller's: any padded copy is out of date
   c->state = kIdle;
-  const int rc = step_impl(c, grads, ghat);
+  int rc = refresh_padded(c, 1);             // the warm-start Q is the caller's
+  if (!rc) rc = step_impl(c, grads, ghat);
   if (rc) g_create_error = c->err;
   return rc;
 }

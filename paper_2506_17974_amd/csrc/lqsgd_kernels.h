@@ -29,7 +29,7 @@ struct DevArgs {
   float* Qpart;                // sweep-1 partial products, per worker
   float* Qw;                   // Q_w
   float* Qbar;                 // aggregated Q = warm-start Q (shared)
-  float* Ppad; float* Qpad;    // copies of Pbar / Qbar with rows of RP ranks, zero beyond a layer's rank; null if unused
+  float* Pop; float* Qop;      // the factors as the sweeps read them, rows of rank_pad ranks: Pbar / Qbar, or zero-padded copies (padded)
   uint8_t* magP; uint8_t* sgnP; float* scaleP;   // packets of the P exchange
   uint8_t* magQ; uint8_t* sgnQ; float* scaleQ;   // packets of the Q exchange
   const float* thrP; const float* levP;           // quantiser tables for b_p
@@ -38,6 +38,8 @@ struct DevArgs {
   int64_t m_stride, p_stride, q_stride, ppart_stride, qpart_stride;
   int64_t magp_stride, sgnp_stride, magq_stride, sgnq_stride;
   int32_t W, L, n_all, bits_p, bits_q;
+  int32_t rank_pad;            // Plan::RP
+  int32_t padded;              // Plan::padded: Pop / Qop are copies, written by the exchange beside Pbar / Qbar
   float alpha;                 // log scale of Eq. (5)
   float qscale_p, qscale_q;    // (2^b - 1) / log2(1 + alpha) for b_p, b_q
   int32_t agg_first;           // aggregate-first order: scaleP is an atomic-max accumulator (sweep 0 zeroes it)
@@ -90,8 +92,8 @@ hipError_t launch_residual(int RP, int mode, const DevArgs& a, const Tile* tiles
 // Sweeps 0 and 2 on the matrix cores (rank pad 16, 32 or 64), over the work list of
 // sweep 0 (32-row items).  mode: 0 = M = G + E and P partials, 1 = the same with the deferred
 // residual applied on the fly, 2 = residual, 3 = residual + G-hat, 4 = G-hat only (worker 0's items).
-// full_rank: the largest effective rank of the layers equals RP (chooses between two forms of the fused add mode).
-// Refreshes a.Ppad (which = 0) or a.Qpad (which = 1) from the tightly packed factor.
+// Refreshes the copy a.Pop (which = 0) or a.Qop (which = 1) from the tightly packed factor (the exchange writes both at once;
+// this is for a factor that came another way).
 hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, hipStream_t s);
 
 // The per-GPU scratch block of the entry point that allocates nothing: device address and size of
@@ -103,7 +105,6 @@ hipError_t static_scratch(int device, void** ptr, size_t* bytes);
 // Clears `bytes` (a multiple of 16) at the 16-byte aligned device address p with a kernel.
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 
-hipError_t launch_mfma_sweep(int RP, int mode, int full_rank, const DevArgs& a, const Tile* tiles, int ntiles, int reverse,
-                             hipStream_t s);
+hipError_t launch_mfma_sweep(int RP, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s);
 
 }  // namespace lqsgd

@@ -85,8 +85,11 @@ typedef const float __attribute__((address_space(4)))* const_fp;
 #ifndef LQSGD_B_INTERLEAVE  // sweep 1: row blocks of at least this many rows are split between the wavefronts in groups of LQSGD_B_U rows
 #define LQSGD_B_INTERLEAVE 512
 #endif
-#ifndef LQSGD_A_WAVES      // occupancy target of sweep 0 (waves per SIMD)
-#define LQSGD_A_WAVES 1
+#ifndef LQSGD_A_WAVES      // most wavefronts of sweep 0 on a SIMD: more of them read slower (ResNet-18 set, r = 4: 187 / 174 / 176 / 176 us at 1 / 2 / 3 / 4)
+#define LQSGD_A_WAVES 2
+#endif
+#ifndef LQSGD_B_WAVES      // the same for sweep 1 (62.0 / 62.6 / 63.0 us at 4 / 6 / 8)
+#define LQSGD_B_WAVES 4
 #endif
 
 template <int V>
@@ -107,49 +110,46 @@ __device__ __forceinline__ T __attribute__((address_space(1)))* gptr(void* p) {
   return (T __attribute__((address_space(1)))*)p;
 }
 
-// VEC floats at (wave-uniform row base) + (per-lane byte offset).
-template <int V, bool NT>
-__device__ __forceinline__ Pk<V> ldrow(const char* rowbase, unsigned boff);
-template <>
-__device__ __forceinline__ Pk<4> ldrow<4, false>(const char* rowbase, unsigned boff) {
-  const v4f t = *gptr<v4f>(rowbase + boff);
+// x where `on`, else +0: a bit mask instead of a select, so that the compiler cannot turn the
+// unconditional load that produced x back into a branch around a conditional one
+__device__ __forceinline__ float keep_if(float x, bool on) {
+  return __uint_as_float(__float_as_uint(x) & (on ? 0xffffffffu : 0u));
+}
+
+// Four floats at (wave-uniform row base) + (per-lane byte offset).  Rows of any length: the row only has to start at a
+// multiple of the element size (global memory takes 16-byte accesses at any 4-byte address), so widths that are no
+// multiple of four stream like the others and only the last group of a row is taken apart.  Against 4-byte accesses
+// (3 x (64 x 27 .. 1000 x 2049)): sweep 1 28 -> 14 us at r = 4; sweep 0 1100 -> 59 us at r = 20, where such rows took a
+// loop of one wavefront sum per row and rank.
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+template <bool NT>
+__device__ __forceinline__ Pk<4> ldrow(const char* rowbase, unsigned boff) {
+  const auto* p = gptr<v4fu>(rowbase + boff);
+  const v4fu t = NT ? __builtin_nontemporal_load(p) : *p;
   return Pk<4>{{t.x, t.y, t.z, t.w}};
-}
-template <>
-__device__ __forceinline__ Pk<4> ldrow<4, true>(const char* rowbase, unsigned boff) {
-  const v4f t = __builtin_nontemporal_load(gptr<v4f>(rowbase + boff));
-  return Pk<4>{{t.x, t.y, t.z, t.w}};
-}
-template <>
-__device__ __forceinline__ Pk<1> ldrow<1, false>(const char* rowbase, unsigned boff) {
-  return Pk<1>{{*gptr<float>(rowbase + boff)}};
-}
-template <>
-__device__ __forceinline__ Pk<1> ldrow<1, true>(const char* rowbase, unsigned boff) {
-  return Pk<1>{{__builtin_nontemporal_load(gptr<float>(rowbase + boff))}};
 }
 // The same for a row of bfloat16 values (gradients handed over in bfloat16): boff is the byte
 // offset the fp32 loaders would use; a bfloat16 is the upper half of the float it stands for.
-typedef unsigned int v2u __attribute__((ext_vector_type(2)));
-template <int V, bool NT>
-__device__ __forceinline__ Pk<V> ldrow_bf16(const char* rowbase, unsigned boff) {
-  Pk<V> r;
-  if constexpr (V == 4) {
-    const auto* p = gptr<v2u>(rowbase + (boff >> 1));
-    const v2u t = NT ? __builtin_nontemporal_load(p) : *p;
-    r.v[0] = __uint_as_float(t.x << 16); r.v[1] = __uint_as_float(t.x & 0xffff0000u);
-    r.v[2] = __uint_as_float(t.y << 16); r.v[3] = __uint_as_float(t.y & 0xffff0000u);
-  } else {
-    const unsigned short t = *gptr<unsigned short>(rowbase + (boff >> 1));
-    r.v[0] = __uint_as_float((unsigned)t << 16);
-  }
-  return r;
+typedef unsigned int v2uu __attribute__((ext_vector_type(2), aligned(2)));
+template <bool NT>
+__device__ __forceinline__ Pk<2> ldrow_bf16_packed(const char* rowbase, unsigned boff) {
+  const auto* p = gptr<v2uu>(rowbase + (boff >> 1));
+  const v2uu t = NT ? __builtin_nontemporal_load(p) : *p;
+  return Pk<2>{{__uint_as_float(t.x), __uint_as_float(t.y)}};
+}
+__device__ __forceinline__ Pk<4> unpack_bf16(float lo, float hi) {
+  const unsigned x = __float_as_uint(lo), y = __float_as_uint(hi);
+  return Pk<4>{{__uint_as_float(x << 16), __uint_as_float(x & 0xffff0000u), __uint_as_float(y << 16), __uint_as_float(y & 0xffff0000u)}};
 }
 // Gradient row in either format.
-template <int V, bool NT, bool GB16>
-__device__ __forceinline__ Pk<V> ldgrad(const char* rowbase, unsigned boff) {
-  if constexpr (GB16) return ldrow_bf16<V, NT>(rowbase, boff);
-  else return ldrow<V, NT>(rowbase, boff);
+template <bool NT, bool GB16>
+__device__ __forceinline__ Pk<4> ldgrad(const char* rowbase, unsigned boff) {
+  if constexpr (GB16) {
+    const Pk<2> t = ldrow_bf16_packed<NT>(rowbase, boff);
+    return unpack_bf16(t.v[0], t.v[1]);
+  } else {
+    return ldrow<NT>(rowbase, boff);
+  }
 }
 // Start of gradient row `off / cols` given its element offset.
 template <bool GB16>
@@ -162,95 +162,94 @@ __device__ __forceinline__ float grad_elem(const float* G, size_t idx) {
   else return gptr<float>(G)[idx];
 }
 
-template <int V, bool NT>
-__device__ __forceinline__ void strow(char* rowbase, unsigned boff, const Pk<V>& x);
-template <>
-__device__ __forceinline__ void strow<4, false>(char* rowbase, unsigned boff, const Pk<4>& x) {
-  const v4f t = {x.v[0], x.v[1], x.v[2], x.v[3]};
-  *gptr<v4f>(rowbase + boff) = t;
-}
-template <>
-__device__ __forceinline__ void strow<4, true>(char* rowbase, unsigned boff, const Pk<4>& x) {
-  const v4f t = {x.v[0], x.v[1], x.v[2], x.v[3]};
-  __builtin_nontemporal_store(t, gptr<v4f>(rowbase + boff));
-}
-template <>
-__device__ __forceinline__ void strow<1, false>(char* rowbase, unsigned boff, const Pk<1>& x) {
-  *gptr<float>(rowbase + boff) = x.v[0];
-}
-template <>
-__device__ __forceinline__ void strow<1, true>(char* rowbase, unsigned boff, const Pk<1>& x) {
-  __builtin_nontemporal_store(x.v[0], gptr<float>(rowbase + boff));
+template <bool NT>
+__device__ __forceinline__ void strow(char* rowbase, unsigned boff, const Pk<4>& x) {
+  const v4fu t = {x.v[0], x.v[1], x.v[2], x.v[3]};
+  auto* p = gptr<v4fu>(rowbase + boff);
+  if constexpr (NT) __builtin_nontemporal_store(t, p);
+  else *p = t;
 }
 
-// Factor slice of VEC consecutive columns starting at column c of a cols x r
-// row-major factor F, as s[v*RP + k].  EXACT (r == RP) is the fast path.
+// Rows whose width is no multiple of four.  A lane's group of columns c .. c + 3 may hang over the end of its row: it is
+// then loaded from edge_col(c), the row's last four columns, like every other lane's and without a branch, and
+// edge_fix() moves the values into place, zeros behind them.  (Element loads under a branch for the last lane cost
+// sweep 0 a second memory round trip per pass: 40 us against 29 us on 3 x (64 x 27 .. 1000 x 2049).)  A store
+// writes the existing elements only.
+__device__ __forceinline__ int edge_col(int c, int cols) { return max(0, min(c, cols - 4)); }
+// Shapes of a layer's rows, a constant in every kernel's inner loops (a test inside ldedge would part the loads).
+enum RowKind { kAligned = 0, kRagged = 1, kNarrow = 2 };   // cols % 4 == 0; the rest; the rest below four columns
+template <int KIND, bool NT, bool GB16>
+__device__ __forceinline__ Pk<4> ldedge(const char* rowbase, int c, int cols) {
+  if constexpr (KIND == kNarrow) {               // element loads, the surplus ones repeat the last element
+    Pk<4> r;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) r.v[v] = grad_elem<GB16>(reinterpret_cast<const float*>(rowbase), min(v, cols - 1));
+    return r;
+  } else {
+    return ldgrad<NT, GB16>(rowbase, (unsigned)(KIND == kAligned ? c : edge_col(c, cols)) * 4u);
+  }
+}
+// N values per column, four columns loaded from edge_col(c) on -> those of columns c .. c + 3.
+template <int N>
+__device__ __forceinline__ void edge_fix(float (&x)[4 * N], int c, int cols) {
+  const int sh = c - edge_col(c, cols), n = cols - c;
+#pragma unroll
+  for (int i = 0; i < 4 * N; ++i) x[i] = (sh & 1) ? (i + N < 4 * N ? x[i + N] : 0.0f) : x[i];
+#pragma unroll
+  for (int i = 0; i < 4 * N; ++i) x[i] = (sh & 2) ? (i + 2 * N < 4 * N ? x[i + 2 * N] : 0.0f) : x[i];
+#pragma unroll
+  for (int i = 0; i < 4 * N; ++i) x[i] = i < n * N ? x[i] : 0.0f;
+}
+// Stores the first n (<= 0: none, >= 4: all) elements of a group.
+template <bool NT>
+__device__ __forceinline__ void stgroup(char* rowbase, unsigned boff, int n, const Pk<4>& x) {
+  if (n >= 4) {
+    strow<NT>(rowbase, boff, x);
+  } else {
+#pragma unroll
+    for (int v = 0; v < 3; ++v)
+      if (v < n) gptr<float>(rowbase + boff)[v] = x.v[v];
+  }
+}
+
 // Output of the reconstruction G-hat = P-bar Q-bar^T (Eq. (7)): either stored as it is, or applied
 // to the caller's parameters, w <- w - eta G-hat (Algorithm 1, "Model update"; Eq. (2)).
-template <int V>
-__device__ __forceinline__ void emit_ghat(float* __restrict__ rowbase, unsigned boff, Pk<V> gh, int update, float eta) {
+template <int KIND>
+__device__ __forceinline__ void emit_ghat(float* __restrict__ rowbase, int c, int cols, Pk<4> gh, int update, float eta) {
+  char* row = reinterpret_cast<char*>(rowbase);
   if (update) {
-    const Pk<V> w = ldrow<V, false>(reinterpret_cast<const char*>(rowbase), boff);
+    Pk<4> w = ldedge<KIND, false, false>(row, c, cols);
+    if (KIND != kAligned && c + 4 > cols) edge_fix<1>(w.v, c, cols);
 #pragma unroll
-    for (int v = 0; v < V; ++v) gh.v[v] = fmaf(-eta, gh.v[v], w.v[v]);
-    strow<V, false>(reinterpret_cast<char*>(rowbase), boff, gh);
+    for (int v = 0; v < 4; ++v) gh.v[v] = fmaf(-eta, gh.v[v], w.v[v]);
+    stgroup<false>(row, (unsigned)c * 4u, KIND == kAligned ? 4 : cols - c, gh);
   } else {
-    strow<V, true>(reinterpret_cast<char*>(rowbase), boff, gh);
+    stgroup<true>(row, (unsigned)c * 4u, KIND == kAligned ? 4 : cols - c, gh);
   }
 }
 
-// x where `on`, else +0: a bit mask instead of a select, so that the compiler cannot turn the
-// unconditional load that produced x back into a branch around a conditional one
-__device__ __forceinline__ float keep_if(float x, bool on) {
-  return __uint_as_float(__float_as_uint(x) & (on ? 0xffffffffu : 0u));
+// The factors as the sweeps read them: rows of RP ranks, zero beyond a layer's rank.  Where every layer fills the
+// register pad that is the aggregate itself, elsewhere a copy that whoever writes the aggregate writes beside it
+// (DevArgs::Pop / Qop), so that a lane's slice is whole 16-byte loads at every rank.  With tightly packed rows of
+// 7 ranks sweep 0 spent 32 four-byte loads per lane and column pass on it: ResNet-18 set, W = 8, bfloat16 gradients,
+// 405 us; 16-byte loads: 178 us.
+__device__ __forceinline__ const float* p_operand(const DevArgs& a, const LayerDesc& ld) {
+  return a.Pop + ld.pop_off;
+}
+__device__ __forceinline__ const float* q_operand(const DevArgs& a, const LayerDesc& ld) {
+  return a.Qop + ld.qop_off;
 }
 
-// Ranks that do not fill their pad (r < RP): the loaders below still fetch RP values per factor
-// row, unconditionally, running up to RP - 1 elements into what follows the row (the next row, or
-// the slack the host leaves after every factor buffer), and zero the surplus afterwards.
-template <int RP, int VEC, bool EXACT>
-__device__ __forceinline__ void load_slice(const float* __restrict__ F, int c, int r, float (&s)[VEC * RP]) {
-  if constexpr (EXACT) {
-    const float* base = F + (size_t)c * RP;
-    if constexpr ((VEC * RP) % 4 == 0) {
+// Factor slice of four consecutive columns starting at column c, as s[v*RP + k].
+template <int RP>
+__device__ __forceinline__ void load_slice(const float* __restrict__ F, int c, float (&s)[4 * RP]) {
+  const auto* base = gptr<v4fu>(F + (size_t)c * RP);
 #pragma unroll
-      for (int i = 0; i < VEC * RP / 4; ++i) {
-        const float4 t = reinterpret_cast<const float4*>(base)[i];
-        s[4 * i + 0] = t.x; s[4 * i + 1] = t.y; s[4 * i + 2] = t.z; s[4 * i + 3] = t.w;
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < VEC * RP; ++i) s[i] = base[i];
-    }
-  } else {
-#pragma unroll
-    for (int v = 0; v < VEC; ++v)
-#pragma unroll
-      for (int k = 0; k < RP; ++k) s[v * RP + k] = keep_if(F[(size_t)(c + v) * r + k], k < r);
+  for (int i = 0; i < RP; ++i) {
+    const v4fu t = base[i];
+    s[4 * i + 0] = t.x; s[4 * i + 1] = t.y; s[4 * i + 2] = t.z; s[4 * i + 3] = t.w;
   }
 }
-
-template <int RP, int VEC, bool EXACT>
-__device__ __forceinline__ void store_slice(float* __restrict__ F, int c, int r, const float (&s)[VEC * RP]) {
-  if constexpr (EXACT) {
-    float* base = F + (size_t)c * RP;
-    if constexpr ((VEC * RP) % 4 == 0) {
-#pragma unroll
-      for (int i = 0; i < VEC * RP / 4; ++i)
-        reinterpret_cast<float4*>(base)[i] = make_float4(s[4 * i], s[4 * i + 1], s[4 * i + 2], s[4 * i + 3]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < VEC * RP; ++i) base[i] = s[i];
-    }
-  } else {
-#pragma unroll
-    for (int v = 0; v < VEC; ++v)
-#pragma unroll
-      for (int k = 0; k < RP; ++k)
-        if (k < r) F[(size_t)(c + v) * r + k] = s[v * RP + k];
-  }
-}
-
 // Row of a rows x r factor into p[k] (zero beyond r), plain loads.
 template <int RP>
 __device__ __forceinline__ void load_row(const float* __restrict__ F, int row, int r, bool exact, float (&p)[RP]) {
@@ -265,21 +264,12 @@ __device__ __forceinline__ void load_row(const float* __restrict__ F, int row, i
   }
 }
 
-// Wave-uniform row of a factor written by an earlier kernel: scalar loads.
-template <int RP, bool EXACT>
-__device__ __forceinline__ void load_row_uniform(const float* F, int row, int r, float (&p)[RP]) {
-  if constexpr (EXACT) {
-    const_fp b = (const_fp)(F + (size_t)row * RP);
+// Wave-uniform row of a factor operand written by an earlier kernel: scalar loads.
+template <int RP>
+__device__ __forceinline__ void load_row_uniform(const float* F, int row, float (&p)[RP]) {
+  const_fp b = (const_fp)(F + (size_t)row * RP);
 #pragma unroll
-    for (int k = 0; k < RP; ++k) p[k] = b[k];
-  } else {
-    const_fp b = (const_fp)(F + (size_t)row * r);
-    float t[RP];
-#pragma unroll
-    for (int k = 0; k < RP; ++k) t[k] = b[k];
-#pragma unroll
-    for (int k = 0; k < RP; ++k) p[k] = keep_if(t[k], k < r);
-  }
+  for (int k = 0; k < RP; ++k) p[k] = b[k];
 }
 
 // Sum of N per-lane values over the 64 lanes of a wavefront, N a power of two.
@@ -347,30 +337,33 @@ __device__ __forceinline__ void zero_absmax_cells(const DevArgs& a, int nthreads
 // RT rows at a time; a lane accumulates RT x r partial dot products over its
 // columns, one butterfly per row group adds them over the lanes.
 // ---------------------------------------------------------------------------
-template <int RP, int VEC, int RT, bool EXACT, bool FULL, bool FUSE, bool GB16, bool NTS>
+template <int RP, int RT, bool FULL, int KIND, bool FUSE, bool GB16, bool NTS>
 __device__ __forceinline__ void add_project_cols(const char* const (&gr)[RT], char* const (&mr)[RT],
-                                                 const float* __restrict__ Q, const float (&pb)[RT * RP], int r, int nr,
-                                                 int cbeg, int cend, float (&acc)[RT * RP]) {
-  for (int c = cbeg; c < cend; c += kWave * VEC) {
-    float q[VEC * RP];
-    load_slice<RP, VEC, EXACT>(Q, c, r, q);
+                                                 const float* __restrict__ Q, const float (&pb)[RT * RP], int nr,
+                                                 int cbeg, int cend, int cols, float (&acc)[RT * RP]) {
+  for (int c = cbeg; c < cend; c += kWave * 4) {
+    float q[4 * RP];
     const unsigned boff = (unsigned)c * 4u;
-    Pk<VEC> g[RT], e[RT];
+    Pk<4> g[RT], e[RT];
+    load_slice<RP>(Q, KIND == kAligned ? c : edge_col(c, cols), q);
 #pragma unroll
-    for (int t = 0; t < RT; ++t) {
-      if (FULL || t < nr) {
-        g[t] = ldgrad<VEC, LQSGD_NT_G != 0, GB16>(gr[t], boff);
-        e[t] = ldrow<VEC, NTS>(mr[t], boff);
-      } else {
+    for (int t = 0; t < RT; ++t) {               // rows beyond nr repeat the last one: loaded, never stored
+      g[t] = ldedge<KIND, LQSGD_NT_G != 0, GB16>(gr[t], c, cols);
+      e[t] = ldedge<KIND, NTS, false>(mr[t], c, cols);
+    }
+    // All requests stay ahead of the arithmetic (left to itself the compiler trades loads in flight for
+    // registers: fc 256 x 128 6.8 us against 5.9 us).
+    __builtin_amdgcn_sched_barrier(0);
+    if (KIND != kAligned && c + 4 > cols) {
+      edge_fix<RP>(q, c, cols);
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) { g[t].v[v] = 0.0f; e[t].v[v] = 0.0f; }
-      }
+      for (int t = 0; t < RT; ++t) { edge_fix<1>(g[t].v, c, cols); edge_fix<1>(e[t].v, c, cols); }
     }
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
-      Pk<VEC> m;
+      Pk<4> m;
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) {
+      for (int v = 0; v < 4; ++v) {
         float ev = e[t].v[v];
         if constexpr (FUSE) {
           // the buffer still holds last iteration's M: E = M - P-bar Q-bar^T (Eq. (8)),
@@ -382,16 +375,28 @@ __device__ __forceinline__ void add_project_cols(const char* const (&gr)[RT], ch
         }
         m.v[v] = g[t].v[v] + ev;
       }
-      if (FULL || t < nr) strow<VEC, NTS>(mr[t], boff, m);
+      if constexpr (KIND != kAligned) e[t] = m;               // stored below, all rows in one branch
+      else if (FULL || t < nr) strow<NTS>(mr[t], boff, m);
 #pragma unroll
-      for (int v = 0; v < VEC; ++v)
+      for (int v = 0; v < 4; ++v)
 #pragma unroll
         for (int k = 0; k < RP; ++k) acc[t * RP + k] = fmaf(m.v[v], q[v * RP + k], acc[t * RP + k]);
+    }
+    if constexpr (KIND != kAligned) {
+      if (c + 4 <= cols) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+          if (FULL || t < nr) strow<NTS>(mr[t], boff, e[t]);
+      } else {
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+          if (FULL || t < nr) stgroup<NTS>(mr[t], boff, cols & 3, e[t]);
+      }
     }
   }
 }
 
-template <int RP, int VEC, int RT, bool EXACT, bool FUSE, bool GB16 = false, bool NTS = false>
+template <int RP, int RT, int KIND, bool FUSE, bool GB16, bool NTS>
 __device__ __forceinline__ void add_project_tile(const float* __restrict__ G, float* __restrict__ M,
                                                  const float* __restrict__ Q, const float* Pb,
                                                  float* __restrict__ Pp, int cols, int r, int row0, int nrows,
@@ -413,7 +418,7 @@ __device__ __forceinline__ void add_project_tile(const float* __restrict__ G, fl
       mr[t] = reinterpret_cast<char*>(M + off);
       if constexpr (FUSE) {
         float p[RP];
-        load_row_uniform<RP, EXACT>(Pb, row, r, p);
+        load_row_uniform<RP>(Pb, row, p);
 #pragma unroll
         for (int k = 0; k < RP; ++k) pb[t * RP + k] = p[k];
       } else {
@@ -422,9 +427,9 @@ __device__ __forceinline__ void add_project_tile(const float* __restrict__ G, fl
       }
     }
     if (nr == RT)
-      add_project_cols<RP, VEC, RT, EXACT, true, FUSE, GB16, NTS>(gr, mr, Q, pb, r, nr, col0 + lane * VEC, col1, acc);
+      add_project_cols<RP, RT, true, KIND, FUSE, GB16, NTS>(gr, mr, Q, pb, nr, col0 + lane * 4, col1, cols, acc);
     else
-      add_project_cols<RP, VEC, RT, EXACT, false, FUSE, GB16, NTS>(gr, mr, Q, pb, r, nr, col0 + lane * VEC, col1, acc);
+      add_project_cols<RP, RT, false, KIND, FUSE, GB16, NTS>(gr, mr, Q, pb, nr, col0 + lane * 4, col1, cols, acc);
     transpose_reduce<N, N, 32>(acc, lane);
     constexpr int NPL = (N >= kWave) ? N / kWave : 1;
 #pragma unroll
@@ -450,8 +455,8 @@ __device__ __forceinline__ void add_project_tile(const float* __restrict__ G, fl
 // NTS: the residual slabs are streamed -- E (or last iteration's M) is read with the non-temporal
 // hint and M is written with non-temporal stores; chosen by the host from the size of the working set.
 template <int RP, bool FUSE, bool GB16, bool NTS>
-__global__ __launch_bounds__(256, LQSGD_A_WAVES) void add_project_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
-  constexpr int RT = (RP <= 8) ? LQSGD_RT : 4;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, LQSGD_A_WAVES))) void add_project_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
+  constexpr int RT = LQSGD_RT;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & (kWave - 1);
   if (blockIdx.x == 0) zero_absmax_cells(a, 256);
@@ -462,20 +467,17 @@ __global__ __launch_bounds__(256, LQSGD_A_WAVES) void add_project_kernel(DevArgs
   const LayerDesc& ld = a.layers[layer];
   const float* G = a.grads[(size_t)worker * a.n_all + ld.gidx];
   float* M = a.E + (size_t)worker * a.m_stride + ld.m_off;
-  const float* Q = a.Qbar + ld.q_off;
-  const float* Pb = a.Pbar + ld.p_off;
+  const float* Q = q_operand(a, ld);
+  const float* Pb = p_operand(a, ld);
   float* Pp = a.Ppart + (size_t)worker * a.ppart_stride + ld.ppart_off + (size_t)tl.aux * ld.np_pad;
   const int col0 = tl.aux * ld.segw;
   const int col1 = min(ld.cols, col0 + ld.segw);
-  if (ld.vec == 4) {
-    if (ld.r == RP)
-      add_project_tile<RP, 4, RT, true, FUSE, GB16, NTS>(G, M, Q, Pb, Pp, ld.cols, ld.r, tl.row0, tl.nrows, col0, col1, lane);
-    else
-      add_project_tile<RP, 4, RT, false, FUSE, GB16, NTS>(G, M, Q, Pb, Pp, ld.cols, ld.r, tl.row0, tl.nrows, col0, col1, lane);
-  } else {
-    // rows that are not 16-byte aligned (cols % 4 != 0): tiny layers, one generic path
-    add_project_tile<RP, 1, RT, false, FUSE, GB16, NTS>(G, M, Q, Pb, Pp, ld.cols, ld.r, tl.row0, tl.nrows, col0, col1, lane);
-  }
+  if (ld.kind == kAligned)
+    add_project_tile<RP, RT, kAligned, FUSE, GB16, NTS>(G, M, Q, Pb, Pp, ld.cols, ld.r, tl.row0, tl.nrows, col0, col1, lane);
+  else if (ld.kind == kRagged)
+    add_project_tile<RP, RT, kRagged, FUSE, GB16, NTS>(G, M, Q, Pb, Pp, ld.cols, ld.r, tl.row0, tl.nrows, col0, col1, lane);
+  else
+    add_project_tile<RP, RT, kNarrow, FUSE, GB16, NTS>(G, M, Q, Pb, Pp, ld.cols, ld.r, tl.row0, tl.nrows, col0, col1, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1139,57 +1141,71 @@ __global__ __launch_bounds__(256) void exchange_kernel(DevArgs a, const XTile* _
   if (MODE != kQuantOnly) {
     if (gvalid && slot < nvalid) {
       float* out = (phase ? a.Qbar + ld.q_off : a.Pbar + ld.p_off) + e0;
-      out[slot] = acc / (float)a.W;
+      const float mean = acc / (float)a.W;
+      out[slot] = mean;
+      if (a.padded) {    // the sweeps' copy with rows of rank_pad ranks
+        const unsigned e = (unsigned)(e0 + slot), row = e / (unsigned)ld.r;
+        float* pad = phase ? a.Qop + ld.qop_off : a.Pop + ld.pop_off;
+        pad[(size_t)row * a.rank_pad + (e - row * (unsigned)ld.r)] = mean;
+      }
     }
   }
 }
 
 // ---------------------------------------------------------------------------
 // sweep 1: Q_w partial = M_w^T P-bar over a row block (Algorithm 1,
-// "Q <- G'^T P").  One workgroup per (row block, 64*VEC-column chunk); its four
+// "Q <- G'^T P").  One workgroup per (row block, 256-column chunk); its four
 // wavefronts split the rows and their partial sums meet in LDS, where they are
 // added in wavefront order.
 // ---------------------------------------------------------------------------
-template <int RP, int VEC, bool EXACT>
-__device__ __forceinline__ void back_project_rows(const float* __restrict__ M, const float* Pb, int cols, int r,
-                                                  int ra, int rb, unsigned boff, float (&acc)[VEC * RP]) {
+template <int RP, int KIND>
+__device__ __forceinline__ void back_project_rows(const float* __restrict__ M, const float* Pb, int cols,
+                                                  int ra, int rb, int c, float (&acc)[4 * RP]) {
   constexpr int U = LQSGD_B_U;
+  auto load = [&](int row) __attribute__((always_inline)) {
+    const char* p = reinterpret_cast<const char*>(M + (size_t)row * cols);
+    return ldedge<KIND, LQSGD_NT_M != 0, false>(p, c, cols);
+  };
   int i = ra;
   for (; i + U <= rb; i += U) {
-    Pk<VEC> m[U];
+    Pk<4> m[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      m[u] = ldrow<VEC, LQSGD_NT_M != 0>(reinterpret_cast<const char*>(M + (size_t)(i + u) * cols), boff);
+    for (int u = 0; u < U; ++u) m[u] = load(i + u);
+    if (KIND != kAligned && c + 4 > cols) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) edge_fix<1>(m[u].v, c, cols);
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       float p[RP];
-      load_row_uniform<RP, EXACT>(Pb, i + u, r, p);
+      load_row_uniform<RP>(Pb, i + u, p);
 #pragma unroll
-      for (int v = 0; v < VEC; ++v)
+      for (int v = 0; v < 4; ++v)
 #pragma unroll
         for (int k = 0; k < RP; ++k) acc[v * RP + k] = fmaf(m[u].v[v], p[k], acc[v * RP + k]);
     }
   }
   for (; i < rb; ++i) {
-    const Pk<VEC> m = ldrow<VEC, LQSGD_NT_M != 0>(reinterpret_cast<const char*>(M + (size_t)i * cols), boff);
+    Pk<4> m = load(i);
+    if (KIND != kAligned && c + 4 > cols) edge_fix<1>(m.v, c, cols);
     float p[RP];
-    load_row_uniform<RP, EXACT>(Pb, i, r, p);
+    load_row_uniform<RP>(Pb, i, p);
 #pragma unroll
-    for (int v = 0; v < VEC; ++v)
+    for (int v = 0; v < 4; ++v)
 #pragma unroll
       for (int k = 0; k < RP; ++k) acc[v * RP + k] = fmaf(m.v[v], p[k], acc[v * RP + k]);
   }
 }
 
-template <int RP, int VEC, bool EXACT>
+template <int RP, int KIND>
 __device__ __forceinline__ void back_project_tile(const DevArgs& a, const LayerDesc& ld, const Tile& tl, int layer, int worker,
                                                   float* comb, float* redmax, int wave, int lane) {
-  constexpr int NV = VEC * RP;
+  constexpr int NV = 4 * RP;
   const int cols = ld.cols, r = ld.r;
   const float* M = a.E + (size_t)worker * a.m_stride + ld.m_off;
-  const float* Pb = a.Pbar + ld.p_off;
-  const int c0 = tl.aux * (kWave * VEC);
-  const int c = c0 + lane * VEC;
+  const float* Pb = p_operand(a, ld);
+  const int c0 = tl.aux * (kWave * 4);
+  const int c = c0 + lane * 4;
   const bool active = c < cols;
   const int per = (tl.nrows + 3) >> 2;
   const int ra = min(tl.row0 + wave * per, tl.row0 + tl.nrows);
@@ -1204,9 +1220,9 @@ __device__ __forceinline__ void back_project_tile(const DevArgs& a, const LayerD
       // hundreds of rows apart read the 8192^2 set at 6.0 TB/s, interleaved at 6.6 TB/s).
       const int rend = tl.row0 + tl.nrows;
       for (int g0 = tl.row0 + wave * LQSGD_B_U; g0 < rend; g0 += 4 * LQSGD_B_U)
-        back_project_rows<RP, VEC, EXACT>(M, Pb, cols, r, g0, min(g0 + LQSGD_B_U, rend), (unsigned)c * 4u, acc);
+        back_project_rows<RP, KIND>(M, Pb, cols, g0, min(g0 + LQSGD_B_U, rend), c, acc);
     } else {
-      back_project_rows<RP, VEC, EXACT>(M, Pb, cols, r, ra, rb, (unsigned)c * 4u, acc);
+      back_project_rows<RP, KIND>(M, Pb, cols, ra, rb, c, acc);
     }
   }
   // A layer whose rows fit one row block: this item holds the whole sum, Q_w is stored directly
@@ -1216,17 +1232,19 @@ __device__ __forceinline__ void back_project_tile(const DevArgs& a, const LayerD
   float* Qp = direct ? a.Qw + (size_t)worker * a.q_stride + ld.q_off
                      : a.Qpart + (size_t)worker * a.qpart_stride + ld.qpart_off + (size_t)(tl.row0 / ld.rbb) * ld.nq_pad;
   float mx = 0.0f;
-  if constexpr (EXACT && NV % 4 == 0 && NV <= 64) {
-    // comb[wave][lane * NV + i]; afterwards every lane of the workgroup adds the four
-    // partials of NV/4 consecutive outputs (wave order) and stores them: the chunk's
-    // slice of the factor is contiguous, 64 * NV floats from column c0.
+  // comb[wave][column][rank]; afterwards the workgroup adds the four partials of every output
+  // element in wavefront order: the chunk's slice of the factor is contiguous from column c0.
+  {
+    float* mine = comb + (size_t)wave * (kWave * NV) + lane * NV;
 #pragma unroll
     for (int i = 0; i < NV / 4; ++i)
-      reinterpret_cast<float4*>(comb + (size_t)wave * (kWave * NV) + lane * NV)[i] =
-          make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
-    __syncthreads();
-    const int tid = wave * kWave + lane;
-    const int nout = min(kWave * VEC, cols - c0) * RP;     // floats this chunk owns
+      reinterpret_cast<float4*>(mine)[i] = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
+  }
+  __syncthreads();
+  const int tid = wave * kWave + lane;
+  const int ncol = min(kWave * 4, cols - c0);
+  if (KIND == kAligned && r == RP) {
+    const int nout = ncol * RP;                  // floats this chunk owns: a multiple of four
 #pragma unroll
     for (int j = 0; j < (NV + 15) / 16; ++j) {   // 64 * NV / 4 float4 outputs over 256 lanes
       const int o = (j * 256 + tid) * 4;
@@ -1242,31 +1260,15 @@ __device__ __forceinline__ void back_project_tile(const DevArgs& a, const LayerD
       }
     }
   } else {
-    // generic path: (wave 0 + wave 2) + (wave 1 + wave 3) through two LDS planes
-    if (wave >= 2) {
+    const int nout = ncol * r;
+    for (int o = tid; o < nout; o += 256) {
+      const int cc = (int)((unsigned)o / (unsigned)r);
+      const float* src = comb + cc * RP + (o - cc * r);
+      float s = src[0];
 #pragma unroll
-      for (int i = 0; i < NV; ++i) comb[(wave - 2) * (kWave * NV) + i * kWave + lane] = acc[i];
-    }
-    __syncthreads();
-    if (wave < 2) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i) acc[i] += comb[wave * (kWave * NV) + i * kWave + lane];
-    }
-    __syncthreads();
-    if (wave == 1) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i) comb[i * kWave + lane] = acc[i];
-    }
-    __syncthreads();
-    if (wave == 0 && active) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i) acc[i] += comb[i * kWave + lane];
-      store_slice<RP, VEC, EXACT>(Qp, c, r, acc);
-#pragma unroll
-      for (int v = 0; v < VEC; ++v)
-#pragma unroll
-        for (int k = 0; k < RP; ++k)
-          if (c + v < cols && k < r) mx = fmaxf(mx, fabsf(acc[v * RP + k]));
+      for (int wv = 1; wv < 4; ++wv) s += src[(size_t)wv * (kWave * NV)];
+      Qp[(size_t)c0 * r + o] = s;
+      mx = fmaxf(mx, fabsf(s));
     }
   }
   if (direct) {     // workgroup-uniform
@@ -1305,10 +1307,9 @@ __device__ __forceinline__ void vector_mean_tile(const DevArgs& a, const VTile& 
 }
 
 template <int RP>
-__global__ __launch_bounds__(256) void back_project_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, LQSGD_B_WAVES))) void back_project_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles,
                                                            const VTile* __restrict__ vtiles, int reverse) {
-  // fast path: 4 planes of 64 * 4 * RP floats (RP <= 16); generic path: 2 planes
-  __shared__ float comb[(RP <= 16 ? 4 : 2) * kWave * 4 * RP];
+  __shared__ __attribute__((aligned(16))) float comb[4 * kWave * 4 * RP];
   __shared__ float redmax[4];
   if ((int)blockIdx.x >= ntiles) {
     vector_mean_tile(a, vtiles[blockIdx.x - ntiles]);
@@ -1319,14 +1320,12 @@ __global__ __launch_bounds__(256) void back_project_kernel(DevArgs a, const Tile
   const Tile tl = tiles[reverse ? ntiles - 1 - blockIdx.x : blockIdx.x];
   const int layer = tl.lw / a.W, worker = tl.lw - layer * a.W;
   const LayerDesc& ld = a.layers[layer];
-  if (ld.vec == 4) {
-    if (ld.r == RP)
-      back_project_tile<RP, 4, true>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
-    else
-      back_project_tile<RP, 4, false>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
-  } else {
-    back_project_tile<RP, 1, false>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
-  }
+  if (ld.kind == kAligned)
+    back_project_tile<RP, kAligned>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
+  else if (ld.kind == kRagged)
+    back_project_tile<RP, kRagged>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
+  else
+    back_project_tile<RP, kNarrow>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1347,115 +1346,17 @@ __global__ __launch_bounds__(256) void back_project_kernel(DevArgs a, const Tile
 // ---------------------------------------------------------------------------
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-template <bool VEC4>
+// NB blocks of 32 ranks (rank pad 64: NB = 2): one pass over M feeds both.
+template <int NB, int KIND>
 __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const LayerDesc& ld, const Tile& tl, int worker,
-                                                       int wave, int lane) {
+                                                       int c0, int lane) {
+  constexpr int U = NB == 1 ? LQSGD_BM_U : LQSGD_BM_U2;     // pairs of rows per step
   const int cols = ld.cols, r = ld.r;
-  const int c0 = tl.aux * kMfmaCols + wave * 128;
-  if (c0 >= cols) return;
   const int li = lane & 31, h = lane >> 5;
-  const float* M = a.E + (size_t)worker * a.m_stride + ld.m_off;
-  const float* Pb = a.Pbar + ld.p_off;
-  const bool rankok = li < r;
-  const int rend = tl.row0 + tl.nrows;
   const int cl = c0 + 4 * li;                      // first of this lane's four columns
-  v16f acc[4];
-#pragma unroll
-  for (int s = 0; s < 4; ++s)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[s][i] = 0.0f;
-  constexpr int UI = LQSGD_BM_U;   // pairs of rows per step on interior strips
-  constexpr int U = 4;             // ... and on the bounds-tested path
-  int rb = tl.row0;
-  if constexpr (VEC4) {
-    // Interior strips (all 128 columns exist): whole groups of 2 UI rows with no bounds
-    // tests, and the next group's loads are issued before this group's matrix instructions, so that a
-    // wavefront overlaps its own loads with its own arithmetic (the last prefetch re-reads the last
-    // group: every load stays unconditional and in bounds).
-    if (c0 + 128 <= cols && rend - rb >= 2 * UI) {
-      const int last = rb + ((rend - rb) / (2 * UI) - 1) * (2 * UI);   // first row of the last whole group
-      Pk<4> am[UI], an[UI];
-      float bp[UI], bn[UI];
-      const int lic = min(li, r - 1);      // ranks beyond r: read a valid element, masked below
-#pragma unroll
-      for (int u = 0; u < UI; ++u) {
-        const int row = rb + 2 * u + h;
-        am[u] = ldrow<4, LQSGD_NT_M != 0>(reinterpret_cast<const char*>(M + (size_t)row * cols), (unsigned)cl * 4u);
-        bp[u] = Pb[(size_t)row * r + lic];
-      }
-      for (; rb <= last; rb += 2 * UI) {
-        const int nb = min(rb + 2 * UI, last);
-#pragma unroll
-        for (int u = 0; u < UI; ++u) {
-          const int row = nb + 2 * u + h;
-          an[u] = ldrow<4, LQSGD_NT_M != 0>(reinterpret_cast<const char*>(M + (size_t)row * cols), (unsigned)cl * 4u);
-          bn[u] = Pb[(size_t)row * r + lic];
-        }
-        // the requests above stay ahead of the arithmetic below (left to itself the compiler moves the
-        // P-bar loads down to their first use, and every group of matrix instructions then waits for
-        // its operand and, requests completing in order, for the whole prefetch in front of it)
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < UI; ++u)
-#pragma unroll
-          for (int s = 0; s < 4; ++s)
-            acc[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(am[u].v[s], keep_if(bp[u], rankok), acc[s], 0, 0, 0);
-#pragma unroll
-        for (int u = 0; u < UI; ++u) { am[u] = an[u]; bp[u] = bn[u]; }
-      }
-    }
-  }
-  for (; rb < rend; rb += 2 * U) {
-    Pk<4> am[U];
-    float bp[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int row = rb + 2 * u + h;
-      const bool ok = row < rend;
-      const float* mrow = M + (size_t)row * cols;
-      if constexpr (VEC4) {
-        if (ok && cl < cols) {
-          am[u] = ldrow<4, LQSGD_NT_M != 0>(reinterpret_cast<const char*>(mrow), (unsigned)cl * 4u);
-        } else {
-#pragma unroll
-          for (int s = 0; s < 4; ++s) am[u].v[s] = 0.0f;
-        }
-      } else {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) am[u].v[s] = (ok && cl + s < cols) ? mrow[cl + s] : 0.0f;
-      }
-      bp[u] = (ok && rankok) ? Pb[(size_t)row * r + li] : 0.0f;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) acc[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(am[u].v[s], bp[u], acc[s], 0, 0, 0);
-  }
-  float* Qp = a.Qpart + (size_t)worker * a.qpart_stride + ld.qpart_off + (size_t)(tl.row0 / ld.rbb) * ld.nq_pad;
-#pragma unroll
-  for (int s = 0; s < 4; ++s)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int col = c0 + 4 * (8 * (v >> 2) + 4 * h + (v & 3)) + s;
-      if (col < cols && rankok) Qp[(size_t)col * r + li] = acc[s][v];
-    }
-}
-
-// The same with NB blocks of 32 ranks (rank pad 64: NB = 2): one pass over M feeds both blocks.
-template <bool VEC4, int NB>
-__device__ __forceinline__ void back_project_mfma_tile_nb(const DevArgs& a, const LayerDesc& ld, const Tile& tl, int worker,
-                                                       int wave, int lane) {
-  const int cols = ld.cols, r = ld.r;
-  const int c0 = tl.aux * kMfmaCols + wave * 128;
-  if (c0 >= cols) return;
-  const int li = lane & 31, h = lane >> 5;
   const float* M = a.E + (size_t)worker * a.m_stride + ld.m_off;
-  const float* Pb = a.Pbar + ld.p_off;
-  bool rankok[NB];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) rankok[nb] = 32 * nb + li < r;
+  const float* Pb = p_operand(a, ld) + li;         // this lane's rank of each block: rows of 32 NB, zero beyond r
   const int rend = tl.row0 + tl.nrows;
-  const int cl = c0 + 4 * li;                      // first of this lane's four columns
   v16f acc[NB][4];                                  // [block of 32 ranks][column residue]
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
@@ -1463,76 +1364,21 @@ __device__ __forceinline__ void back_project_mfma_tile_nb(const DevArgs& a, cons
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[nb][s][i] = 0.0f;
-  constexpr int UI = LQSGD_BM_U2;  // pairs of rows per step on interior strips
-  constexpr int U = 4;             // ... and on the bounds-tested path
-  int rb = tl.row0;
-  if constexpr (VEC4) {
-    // interior strips: as in the one-block form, whole groups of rows without bounds tests and the
-    // next group's loads ahead of this group's matrix instructions; ranks beyond r are read from a
-    // clamped index and masked
-    if (c0 + 128 <= cols && rend - rb >= 2 * UI) {
-      const int last = rb + ((rend - rb) / (2 * UI) - 1) * (2 * UI);
-      Pk<4> am[UI], an[UI];
-      float bp[NB][UI], bn[NB][UI];
-      int rkc[NB];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) rkc[nb] = min(32 * nb + li, r - 1);
-#pragma unroll
-      for (int u = 0; u < UI; ++u) {
-        const int row = rb + 2 * u + h;
-        am[u] = ldrow<4, LQSGD_NT_M != 0>(reinterpret_cast<const char*>(M + (size_t)row * cols), (unsigned)cl * 4u);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) bp[nb][u] = Pb[(size_t)row * r + rkc[nb]];
-      }
-      for (; rb <= last; rb += 2 * UI) {
-        const int nxt = min(rb + 2 * UI, last);
-#pragma unroll
-        for (int u = 0; u < UI; ++u) {
-          const int row = nxt + 2 * u + h;
-          an[u] = ldrow<4, LQSGD_NT_M != 0>(reinterpret_cast<const char*>(M + (size_t)row * cols), (unsigned)cl * 4u);
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) bn[nb][u] = Pb[(size_t)row * r + rkc[nb]];
-        }
-        __builtin_amdgcn_sched_barrier(0);   // as in the one-block form: the requests stay ahead of the arithmetic
-#pragma unroll
-        for (int u = 0; u < UI; ++u)
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) {
-            const float bv = keep_if(bp[nb][u], rankok[nb]);
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-              acc[nb][s] = __builtin_amdgcn_mfma_f32_32x32x2f32(am[u].v[s], bv, acc[nb][s], 0, 0, 0);
-          }
-#pragma unroll
-        for (int u = 0; u < UI; ++u) {
-          am[u] = an[u];
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) bp[nb][u] = bn[nb][u];
-        }
-      }
-    }
-  }
-  for (; rb < rend; rb += 2 * U) {
-    Pk<4> am[U];
-    float bp[NB][U];
+  Pk<4> am[U], an[U];
+  float bp[NB][U], bn[NB][U];
+  auto fetch = [&](int rb, Pk<4>* m, float (*p)[U]) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int row = rb + 2 * u + h;
-      const bool ok = row < rend;
-      const float* mrow = M + (size_t)row * cols;
-      if constexpr (VEC4) {
-        if (ok && cl < cols) {
-          am[u] = ldrow<4, LQSGD_NT_M != 0>(reinterpret_cast<const char*>(mrow), (unsigned)cl * 4u);
-        } else {
+      const int row = min(rb + 2 * u + h, rend - 1);        // (clamped in the last, partial group only)
+      m[u] = ldedge<KIND, LQSGD_NT_M != 0, false>(reinterpret_cast<const char*>(M + (size_t)row * cols), cl, cols);
 #pragma unroll
-          for (int s = 0; s < 4; ++s) am[u].v[s] = 0.0f;
-        }
-      } else {
+      for (int nb = 0; nb < NB; ++nb) p[nb][u] = Pb[(size_t)row * (32 * NB) + 32 * nb];
+    }
+  };
+  auto multiply = [&](Pk<4>* m, float (*p)[U]) __attribute__((always_inline)) {
+    if constexpr (KIND != kAligned) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) am[u].v[s] = (ok && cl + s < cols) ? mrow[cl + s] : 0.0f;
-      }
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) bp[nb][u] = (ok && rankok[nb]) ? Pb[(size_t)row * r + 32 * nb + li] : 0.0f;
+      for (int u = 0; u < U; ++u) edge_fix<1>(m[u].v, cl, cols);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -1540,7 +1386,42 @@ __device__ __forceinline__ void back_project_mfma_tile_nb(const DevArgs& a, cons
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int s = 0; s < 4; ++s)
-          acc[nb][s] = __builtin_amdgcn_mfma_f32_32x32x2f32(am[u].v[s], bp[nb][u], acc[nb][s], 0, 0, 0);
+          acc[nb][s] = __builtin_amdgcn_mfma_f32_32x32x2f32(m[u].v[s], p[nb][u], acc[nb][s], 0, 0, 0);
+  };
+  // Whole groups of 2 U rows with the next group's loads issued before this group's matrix instructions, so that a
+  // wavefront overlaps its own loads with its own arithmetic (the last prefetch re-reads the last group: every load
+  // stays unconditional and in bounds), then the rows that are left.
+  int rb = tl.row0;
+  if (rend - rb >= 2 * U) {
+    const int last = rb + (tl.nrows / (2 * U) - 1) * (2 * U);   // first row of the last whole group
+    fetch(rb, am, bp);
+    for (; rb <= last; rb += 2 * U) {
+      fetch(min(rb + 2 * U, last), an, bn);
+      // the requests above stay ahead of the arithmetic below (left to itself the compiler moves the
+      // P-bar loads down to their first use, and every group of matrix instructions then waits for
+      // its operand and, requests completing in order, for the whole prefetch in front of it)
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(am, bp);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        am[u] = an[u];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) bp[nb][u] = bn[nb][u];
+      }
+    }
+  }
+  if (rb < rend) {
+    fetch(rb, am, bp);
+    // a row that does not exist counts as zeros on both sides (0 x Inf would not be zero)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool ok = rb + 2 * u + h < rend;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) am[u].v[s] = keep_if(am[u].v[s], ok);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) bp[nb][u] = keep_if(bp[nb][u], ok);
+    }
+    multiply(am, bp);
   }
   float* Qp = a.Qpart + (size_t)worker * a.qpart_stride + ld.qpart_off + (size_t)(tl.row0 / ld.rbb) * ld.nq_pad;
 #pragma unroll
@@ -1550,7 +1431,7 @@ __device__ __forceinline__ void back_project_mfma_tile_nb(const DevArgs& a, cons
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int col = c0 + 4 * (8 * (v >> 2) + 4 * h + (v & 3)) + s;
-        if (col < cols && rankok[nb]) Qp[(size_t)col * r + 32 * nb + li] = acc[nb][s][v];
+        if (col < cols && 32 * nb + li < r) Qp[(size_t)col * r + 32 * nb + li] = acc[nb][s][v];
       }
 }
 
@@ -1566,17 +1447,12 @@ __global__ __launch_bounds__(256, 2) void back_project_mfma_kernel(DevArgs a, co
   const Tile tl = tiles[reverse ? ntiles - 1 - blockIdx.x : blockIdx.x];
   const int layer = tl.lw / a.W, worker = tl.lw - layer * a.W;
   const LayerDesc& ld = a.layers[layer];
-  if constexpr (NB == 1) {
-    if (ld.vec == 4)
-      back_project_mfma_tile<true>(a, ld, tl, worker, wave, lane);
-    else
-      back_project_mfma_tile<false>(a, ld, tl, worker, wave, lane);
-  } else {
-    if (ld.vec == 4)
-      back_project_mfma_tile_nb<true, NB>(a, ld, tl, worker, wave, lane);
-    else
-      back_project_mfma_tile_nb<false, NB>(a, ld, tl, worker, wave, lane);
-  }
+  const int c0 = tl.aux * kMfmaCols + wave * 128;
+  if (c0 >= ld.cols) return;
+  // strips of which all 128 columns exist need no care at their end, whatever the alignment of the rows
+  if (c0 + 128 <= ld.cols) back_project_mfma_tile<NB, kAligned>(a, ld, tl, worker, c0, lane);
+  else if (ld.cols >= 4) back_project_mfma_tile<NB, kRagged>(a, ld, tl, worker, c0, lane);
+  else back_project_mfma_tile<NB, kNarrow>(a, ld, tl, worker, c0, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1653,44 +1529,38 @@ __global__ __launch_bounds__(256) void reduce_q_kernel(DevArgs a, const RTile* _
 // ---------------------------------------------------------------------------
 enum ResidualMode { kResidual = 0, kResidualGhat = 1, kGhatOnly = 2 };
 
-template <int RP, int VEC, bool EXACT, int MODE>
+template <int RP, int MODE, int KIND>
 __device__ __forceinline__ void residual_rows(float* __restrict__ M, const float* Pb, float* __restrict__ ghat,
-                                              int cols, int r, int ra, int rb, unsigned boff,
-                                              const float (&q)[VEC * RP], int update, float eta) {
+                                              int cols, int ra, int rb, int c,
+                                              const float (&q)[4 * RP], int update, float eta) {
   constexpr int U = 8;
+  // what this pass reads besides the factors: M, or the parameters it updates
+  const bool reads = MODE != kGhatOnly || update;
+  const float* in = MODE != kGhatOnly ? M : ghat;
+  const unsigned boff = (unsigned)c * 4u;
+  const int n = KIND == kAligned ? 4 : cols - c;
   for (int i = ra; i < rb; i += U) {
     const int nu = min(U, rb - i);
-    Pk<VEC> m[U];
-    if constexpr (MODE != kGhatOnly) {
+    Pk<4> m[U];
+    if (reads) {      // fetched for all U rows before the arithmetic starts (rows beyond nu repeat the last one)
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        if (u < nu) {
-          m[u] = ldrow<VEC, LQSGD_NT_M != 0>(reinterpret_cast<const char*>(M + (size_t)(i + u) * cols), boff);
-        } else {
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) m[u].v[v] = 0.0f;
-        }
+        const char* p = reinterpret_cast<const char*>(in + (size_t)(i + min(u, nu - 1)) * cols);
+        m[u] = ldedge<KIND, LQSGD_NT_M != 0, false>(p, c, cols);
       }
-    } else if (update) {
-      // the parameters this pass updates, fetched for all U rows before the arithmetic starts
+      if (n < 4) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (u < nu) {
-          m[u] = ldrow<VEC, true>(reinterpret_cast<const char*>(ghat + (size_t)(i + u) * cols), boff);
-        } else {
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) m[u].v[v] = 0.0f;
-        }
+        for (int u = 0; u < U; ++u) edge_fix<1>(m[u].v, c, cols);
       }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (u < nu) {
         float p[RP];
-        load_row_uniform<RP, EXACT>(Pb, i + u, r, p);
-        Pk<VEC> gh, e;
+        load_row_uniform<RP>(Pb, i + u, p);
+        Pk<4> gh, e;
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) {
+        for (int v = 0; v < 4; ++v) {
           float s = 0.0f;
 #pragma unroll
           for (int k = 0; k < RP; ++k) s = fmaf(p[k], q[v * RP + k], s);
@@ -1698,36 +1568,36 @@ __device__ __forceinline__ void residual_rows(float* __restrict__ M, const float
           if constexpr (MODE != kGhatOnly) e.v[v] = m[u].v[v] - s;
         }
         if constexpr (MODE != kGhatOnly)
-          strow<VEC, false>(reinterpret_cast<char*>(M + (size_t)(i + u) * cols), boff, e);
+          stgroup<false>(reinterpret_cast<char*>(M + (size_t)(i + u) * cols), boff, n, e);
         if constexpr (MODE == kGhatOnly) {
           if (update) {
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) gh.v[v] = fmaf(-eta, gh.v[v], m[u].v[v]);
+            for (int v = 0; v < 4; ++v) gh.v[v] = fmaf(-eta, gh.v[v], m[u].v[v]);
           }
-          strow<VEC, true>(reinterpret_cast<char*>(ghat + (size_t)(i + u) * cols), boff, gh);
+          stgroup<true>(reinterpret_cast<char*>(ghat + (size_t)(i + u) * cols), boff, n, gh);
         } else if (MODE == kResidualGhat && ghat) {
-          emit_ghat<VEC>(ghat + (size_t)(i + u) * cols, boff, gh, update, eta);
+          emit_ghat<KIND>(ghat + (size_t)(i + u) * cols, c, cols, gh, update, eta);
         }
       }
     }
   }
 }
 
-template <int RP, int VEC, bool EXACT, int MODE>
+template <int RP, int MODE, int KIND>
 __device__ __forceinline__ void residual_tile(const DevArgs& a, const LayerDesc& ld, const Tile& tl, int worker,
                                               float* __restrict__ ghat, int wave, int lane) {
-  constexpr int NV = VEC * RP;
-  const int cols = ld.cols, r = ld.r;
+  const int cols = ld.cols;
   float* M = a.E + (size_t)worker * a.m_stride + ld.m_off;
-  const float* Pb = a.Pbar + ld.p_off;
-  const int c = tl.aux * (kWave * VEC) + lane * VEC;
+  const float* Pb = p_operand(a, ld);
+  const int c = tl.aux * (kWave * 4) + lane * 4;
   if (c >= cols) return;
   const int per = (tl.nrows + 3) >> 2;
   const int ra = min(tl.row0 + wave * per, tl.row0 + tl.nrows);
   const int rb = min(ra + per, tl.row0 + tl.nrows);
-  float q[NV];
-  load_slice<RP, VEC, EXACT>(a.Qbar + ld.q_off, c, r, q);
-  residual_rows<RP, VEC, EXACT, MODE>(M, Pb, ghat, cols, r, ra, rb, (unsigned)c * 4u, q, a.update, a.eta);
+  float q[4 * RP];
+  load_slice<RP>(q_operand(a, ld), KIND == kAligned ? c : edge_col(c, cols), q);
+  if (KIND != kAligned && c + 4 > cols) edge_fix<RP>(q, c, cols);
+  residual_rows<RP, MODE, KIND>(M, Pb, ghat, cols, ra, rb, c, q, a.update, a.eta);
 }
 
 template <int RP, int MODE>
@@ -1740,14 +1610,12 @@ __global__ __launch_bounds__(256) void residual_kernel(DevArgs a, const Tile* __
   float* ghat = nullptr;
   if (MODE != kResidual && worker == 0 && a.ghat) ghat = a.ghat[ld.gidx];
   if (MODE == kGhatOnly && !ghat) return;
-  if (ld.vec == 4) {
-    if (ld.r == RP)
-      residual_tile<RP, 4, true, MODE>(a, ld, tl, worker, ghat, wave, lane);
-    else
-      residual_tile<RP, 4, false, MODE>(a, ld, tl, worker, ghat, wave, lane);
-  } else {
-    residual_tile<RP, 1, false, MODE>(a, ld, tl, worker, ghat, wave, lane);
-  }
+  if (ld.kind == kAligned)
+    residual_tile<RP, MODE, kAligned>(a, ld, tl, worker, ghat, wave, lane);
+  else if (ld.kind == kRagged)
+    residual_tile<RP, MODE, kRagged>(a, ld, tl, worker, ghat, wave, lane);
+  else
+    residual_tile<RP, MODE, kNarrow>(a, ld, tl, worker, ghat, wave, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1788,7 +1656,7 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
-template <int RP, int MODE, bool EXACT, bool GB16, bool NTS>
+template <int RP, int MODE, bool GB16, bool NTS>
 __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __restrict__ M,
                                           const float* Q, const float* Pb, float* __restrict__ Pp,
                                           float* __restrict__ ghat_out, int cols, int r, int row0, int nrows,
@@ -1800,29 +1668,22 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
   constexpr bool HASM = (MODE != kMGhatOnly);
   constexpr int KH = RP / 2;                       // ranks per half-wavefront
   constexpr int NB = (RP + 31) / 32;               // blocks of 32 ranks in the P product (2 at rank pad 64)
-  // EXACT: the rows of Q and Pb hold RP ranks (the layer's rank is RP, or the operands are the copies
-  // padded with zeros); r is then only the row length of the P partials this item writes.
-  const int rs = EXACT ? RP : r;
+  // (the rows of Q and Pb hold RP ranks; r is only the row length of the P partials this item writes)
   const int li = lane & 31, h = lane >> 5;
   const int sr = lane >> 4, c4 = (lane & 15) * 4;  // row layout: rows 4 i + sr, columns c4 .. c4 + 3
   float pa[KH];
   if constexpr (NEEDG) {
     const int row = row0 + li;
-    if constexpr (EXACT) {
-      if (li < nrows) {
-        const float4* src = reinterpret_cast<const float4*>(Pb + (size_t)row * RP + KH * h);
+    if (li < nrows) {
+      const float4* src = reinterpret_cast<const float4*>(Pb + (size_t)row * RP + KH * h);
 #pragma unroll
-        for (int t = 0; t < KH / 4; ++t) {
-          const float4 x = src[t];
-          pa[4 * t] = x.x; pa[4 * t + 1] = x.y; pa[4 * t + 2] = x.z; pa[4 * t + 3] = x.w;
-        }
-      } else {
-#pragma unroll
-        for (int k = 0; k < KH; ++k) pa[k] = 0.0f;
+      for (int t = 0; t < KH / 4; ++t) {
+        const float4 x = src[t];
+        pa[4 * t] = x.x; pa[4 * t + 1] = x.y; pa[4 * t + 2] = x.z; pa[4 * t + 3] = x.w;
       }
     } else {
 #pragma unroll
-      for (int k = 0; k < KH; ++k) pa[k] = (li < nrows && KH * h + k < r) ? Pb[(size_t)row * r + KH * h + k] : 0.0f;
+      for (int k = 0; k < KH; ++k) pa[k] = 0.0f;
     }
   }
   v16f accP[NB], accP2[NB];
@@ -1835,10 +1696,11 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
   // touch 1 KiB of each row at about the same time (a wavefront on its own reads 256-byte runs)
   // One 64-column block.  FULL: all 32 rows and all 64 columns of the block exist (every block of a
   // large layer except on its edges): no bounds tests, so nothing branches around a load.
-  auto block = [&](auto full_tag, const int c) {
+  auto block = [&](auto full_tag, auto kind_tag, const int c) {
     constexpr bool FULL = decltype(full_tag)::value;
+    constexpr int KIND = decltype(kind_tag)::value;      // of edge blocks: kRagged (which takes aligned rows too) or kNarrow
     const int cl = c + c4;
-    const bool colok = FULL || cl < col1;
+    const int ncol = FULL ? 4 : cols - cl;       // columns of this lane's group that exist
     Pk<4> g[8], e[8];
     // FULL blocks address memory as a wave-uniform base (scalar registers) plus one byte offset per
     // lane that is the same for every row group and block: lo = this lane's place in 4 rows.
@@ -1846,14 +1708,23 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int rr = 4 * i + sr;
-      const bool ok = FULL || (colok && rr < nrows);
-      const size_t off = FULL ? (size_t)(row0 + 4 * i) * cols + c : (size_t)(row0 + rr) * cols;
-      const unsigned bo = FULL ? lo : (unsigned)cl * 4u;
+      // (edge blocks: rows beyond nrows repeat the last one, and are never stored)
+      const size_t off = FULL ? (size_t)(row0 + 4 * i) * cols + c : (size_t)(row0 + min(rr, nrows - 1)) * cols;
+      if constexpr (FULL) {
+        if constexpr (ADD) g[i] = ldgrad<LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), lo);
+        if constexpr (HASM) e[i] = ldrow<(ADD ? NTS : LQSGD_NT_E != 0)>(reinterpret_cast<const char*>(M + off), lo);
+      } else {
+        if constexpr (ADD) g[i] = ldedge<KIND, LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), cl, cols);
+        if constexpr (HASM) e[i] = ldedge<KIND, (ADD ? NTS : LQSGD_NT_E != 0), false>(reinterpret_cast<const char*>(M + off), cl, cols);
+      }
+    }
+    if constexpr (!FULL) {
+      if (ncol < 4) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) { g[i].v[v] = 0.0f; e[i].v[v] = 0.0f; }
-      if (ok) {
-        if constexpr (ADD) g[i] = ldgrad<4, LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), bo);
-        if constexpr (HASM) e[i] = ldrow<4, (ADD ? NTS : LQSGD_NT_E != 0)>(reinterpret_cast<const char*>(M + off), bo);
+        for (int i = 0; i < 8; ++i) {
+          if constexpr (ADD) edge_fix<1>(g[i].v, cl, cols);
+          if constexpr (HASM) edge_fix<1>(e[i].v, cl, cols);
+        }
       }
     }
     float bq[NB][32];
@@ -1864,11 +1735,11 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
         for (int kk = 0; kk < 32; ++kk) {
           const int col = c + 32 * h + kk;
           const int rk = 32 * nb + li;
-          if constexpr (FULL && EXACT)
-            bq[nb][kk] = ldrow<1, false>(reinterpret_cast<const char*>(Q + (size_t)c * RP) + (kk * RP + 32 * nb) * 4,
-                                         (unsigned)(32 * h * RP + li) * 4u).v[0];
+          if constexpr (FULL)
+            bq[nb][kk] = *gptr<float>(reinterpret_cast<const char*>(Q + (size_t)c * RP) + (kk * RP + 32 * nb) * 4 +
+                                      (unsigned)(32 * h * RP + li) * 4u);
           else
-            bq[nb][kk] = (col < col1 && rk < rs) ? Q[(size_t)col * rs + rk] : 0.0f;
+            bq[nb][kk] = (col < col1 && rk < RP) ? Q[(size_t)col * RP + rk] : 0.0f;
         }
     };
     // In the fused mode the Q slice of the P product is fetched only after the G-hat part, when
@@ -1880,29 +1751,23 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
         const int col = c + 32 * b + li;
-        if constexpr (EXACT) {
-          if constexpr (FULL) {
-            const char* base = reinterpret_cast<const char*>(Q + (size_t)(c + 32 * b) * RP);
+        if constexpr (FULL) {
+          const char* base = reinterpret_cast<const char*>(Q + (size_t)(c + 32 * b) * RP);
 #pragma unroll
-            for (int t = 0; t < KH / 4; ++t) {
-              const Pk<4> x = ldrow<4, false>(base + 16 * t, (unsigned)(li * RP + KH * h) * 4u);
-              qb[b][4 * t] = x.v[0]; qb[b][4 * t + 1] = x.v[1]; qb[b][4 * t + 2] = x.v[2]; qb[b][4 * t + 3] = x.v[3];
-            }
-          } else if (col < col1) {
-            const float4* src = reinterpret_cast<const float4*>(Q + (size_t)col * RP + KH * h);
+          for (int t = 0; t < KH / 4; ++t) {
+            const Pk<4> x = ldrow<false>(base + 16 * t, (unsigned)(li * RP + KH * h) * 4u);
+            qb[b][4 * t] = x.v[0]; qb[b][4 * t + 1] = x.v[1]; qb[b][4 * t + 2] = x.v[2]; qb[b][4 * t + 3] = x.v[3];
+          }
+        } else if (col < col1) {
+          const float4* src = reinterpret_cast<const float4*>(Q + (size_t)col * RP + KH * h);
 #pragma unroll
-            for (int t = 0; t < KH / 4; ++t) {
-              const float4 x = src[t];
-              qb[b][4 * t] = x.x; qb[b][4 * t + 1] = x.y; qb[b][4 * t + 2] = x.z; qb[b][4 * t + 3] = x.w;
-            }
-          } else {
-#pragma unroll
-            for (int k = 0; k < KH; ++k) qb[b][k] = 0.0f;
+          for (int t = 0; t < KH / 4; ++t) {
+            const float4 x = src[t];
+            qb[b][4 * t] = x.x; qb[b][4 * t + 1] = x.y; qb[b][4 * t + 2] = x.z; qb[b][4 * t + 3] = x.w;
           }
         } else {
 #pragma unroll
-          for (int k = 0; k < KH; ++k)
-            qb[b][k] = ((FULL || col < col1) && KH * h + k < r) ? Q[(size_t)col * r + KH * h + k] : 0.0f;
+          for (int k = 0; k < KH; ++k) qb[b][k] = 0.0f;
         }
       }
       // the two 32-column blocks accumulate in turn: two independent chains on the matrix pipe
@@ -1930,10 +1795,10 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
         if (MODE == kMGhatOnly || (MODE == kMResidualGhat && ghat_out)) {
           if constexpr (FULL) {
             const Pk<4> o{{t.x, t.y, t.z, t.w}};
-            emit_ghat<4>(ghat_out + (size_t)(row0 + 4 * i) * cols + c, lo, o, update, eta);
-          } else if (colok && rr < nrows) {
+            emit_ghat<kAligned>(ghat_out + (size_t)(row0 + 4 * i) * cols + c, (int)(lo >> 2), 0, o, update, eta);
+          } else if (rr < nrows) {
             const Pk<4> o{{t.x, t.y, t.z, t.w}};
-            emit_ghat<4>(ghat_out + (size_t)(row0 + rr) * cols, (unsigned)cl * 4u, o, update, eta);
+            if (ncol > 0) emit_ghat<KIND>(ghat_out + (size_t)(row0 + rr) * cols, cl, cols, o, update, eta);
           }
         }
       }
@@ -1947,9 +1812,9 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
 #pragma unroll
         for (int v = 0; v < 4; ++v) m.v[v] = ADD ? g[i].v[v] + e[i].v[v] : e[i].v[v];
         if constexpr (FULL)
-          strow<4, NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + 4 * i) * cols + c), lo, m);
-        else if (colok && rr < nrows)
-          strow<4, NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + rr) * cols), (unsigned)cl * 4u, m);
+          strow<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + 4 * i) * cols + c), lo, m);
+        else if (rr < nrows)
+          stgroup<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + rr) * cols), (unsigned)cl * 4u, ncol, m);
         if constexpr (ADD)
           *reinterpret_cast<float4*>(lds + rr * kLP + c4) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
       }
@@ -1983,9 +1848,11 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
   const bool small_offsets = cols < (1 << 26);   // byte offsets within 4 rows fit 32 bits
   for (int c = col0 + 64 * wave; c < col1; c += 256) {
     if (nrows == 32 && c + 64 <= col1 && small_offsets)
-      block(std::true_type{}, c);
+      block(std::true_type{}, std::integral_constant<int, kAligned>{}, c);
+    else if (cols >= 4)
+      block(std::false_type{}, std::integral_constant<int, kRagged>{}, c);
     else
-      block(std::false_type{}, c);
+      block(std::false_type{}, std::integral_constant<int, kNarrow>{}, c);
   }
   if constexpr (ADD) {
     // P partial of the item = sum over the four wavefronts, added in wavefront order
@@ -2021,7 +1888,7 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
 // ---------------------------------------------------------------------------
 constexpr int kLP32 = 36;   // LDS pitch (floats) of a 32 x 32 tile: 16-byte aligned rows
 
-template <int RP, int MODE, bool EXACT, bool GB16, bool NTS>
+template <int RP, int MODE, bool GB16, bool NTS>
 __device__ __forceinline__ void mfma_tile32(const float* __restrict__ G, float* __restrict__ M,
                                             const float* Q, const float* Pb, float* __restrict__ Pp,
                                             int cols, int r, int row0, int nrows, int col0, int col1,
@@ -2030,74 +1897,57 @@ __device__ __forceinline__ void mfma_tile32(const float* __restrict__ G, float* 
   float* lds = lds_all[wave];
   constexpr bool NEEDG = (MODE != kMAdd);
   constexpr int KH = RP / 2;
-  const int rs = EXACT ? RP : r;   // row length of the operands Q and Pb (r: that of the P partials written)
   const int li = lane & 31, h = lane >> 5;
   const int sr = lane >> 3, c4 = (lane & 7) * 4;   // row layout: rows 8 i + sr, columns c4 .. c4 + 3
   float pa[KH];
   if constexpr (NEEDG) {
     const int row = row0 + li;
-    if constexpr (EXACT) {
-      if (li < nrows) {
-        const float4* src = reinterpret_cast<const float4*>(Pb + (size_t)row * RP + KH * h);
+    if (li < nrows) {
+      const float4* src = reinterpret_cast<const float4*>(Pb + (size_t)row * RP + KH * h);
 #pragma unroll
-        for (int t = 0; t < KH / 4; ++t) {
-          const float4 x = src[t];
-          pa[4 * t] = x.x; pa[4 * t + 1] = x.y; pa[4 * t + 2] = x.z; pa[4 * t + 3] = x.w;
-        }
-      } else {
-#pragma unroll
-        for (int k = 0; k < KH; ++k) pa[k] = 0.0f;
+      for (int t = 0; t < KH / 4; ++t) {
+        const float4 x = src[t];
+        pa[4 * t] = x.x; pa[4 * t + 1] = x.y; pa[4 * t + 2] = x.z; pa[4 * t + 3] = x.w;
       }
     } else {
 #pragma unroll
-      for (int k = 0; k < KH; ++k) pa[k] = (li < nrows && KH * h + k < r) ? Pb[(size_t)row * r + KH * h + k] : 0.0f;
+      for (int k = 0; k < KH; ++k) pa[k] = 0.0f;
     }
   }
   v16f accP, accP2;
 #pragma unroll
   for (int i = 0; i < 16; ++i) { accP[i] = 0.0f; accP2[i] = 0.0f; }
 
-  // the G and E (or old M) values of one 32 x 32 block
-  auto fetch = [&](auto full_tag, const int c, Pk<4>* g, Pk<4>* e) {
-    constexpr bool FULL = decltype(full_tag)::value;
+  // the G and E (or old M) values of one 32 x 32 block at an edge of the layer
+  auto fetch = [&](auto kind_tag, const int c, Pk<4>* g, Pk<4>* e) {
+    constexpr int KIND = decltype(kind_tag)::value;
     const int cl = c + c4;
-    const bool colok = FULL || cl < col1;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int rr = 8 * i + sr;
-      const bool ok = FULL || (colok && rr < nrows);
-      const size_t off = (size_t)(row0 + rr) * cols;
+      const size_t off = (size_t)(row0 + min(8 * i + sr, nrows - 1)) * cols;   // rows beyond nrows: never stored
+      g[i] = ldedge<KIND, LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), cl, cols);
+      e[i] = ldedge<KIND, NTS, false>(reinterpret_cast<const char*>(M + off), cl, cols);
+    }
+    if (cl + 4 > cols) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) { g[i].v[v] = 0.0f; e[i].v[v] = 0.0f; }
-      if (ok) {
-        g[i] = ldgrad<4, LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), (unsigned)cl * 4u);
-        e[i] = ldrow<4, NTS>(reinterpret_cast<const char*>(M + off), (unsigned)cl * 4u);
-      }
+      for (int i = 0; i < 4; ++i) { edge_fix<1>(g[i].v, cl, cols); edge_fix<1>(e[i].v, cl, cols); }
     }
   };
-  auto block = [&](auto full_tag, const int c, Pk<4>* g, Pk<4>* e) {
-    constexpr bool FULL = decltype(full_tag)::value;
+  auto block = [&](const int c, Pk<4>* g, Pk<4>* e) {
     const int cl = c + c4;
-    const bool colok = FULL || cl < col1;
     if constexpr (NEEDG) {
       float qb[KH];
       const int col = c + li;
-      if constexpr (EXACT) {
-        if (FULL || col < col1) {
-          const float4* src = reinterpret_cast<const float4*>(Q + (size_t)col * RP + KH * h);
+      if (col < col1) {
+        const float4* src = reinterpret_cast<const float4*>(Q + (size_t)col * RP + KH * h);
 #pragma unroll
-          for (int t = 0; t < KH / 4; ++t) {
-            const float4 x = src[t];
-            qb[4 * t] = x.x; qb[4 * t + 1] = x.y; qb[4 * t + 2] = x.z; qb[4 * t + 3] = x.w;
-          }
-        } else {
-#pragma unroll
-          for (int k = 0; k < KH; ++k) qb[k] = 0.0f;
+        for (int t = 0; t < KH / 4; ++t) {
+          const float4 x = src[t];
+          qb[4 * t] = x.x; qb[4 * t + 1] = x.y; qb[4 * t + 2] = x.z; qb[4 * t + 3] = x.w;
         }
       } else {
 #pragma unroll
-        for (int k = 0; k < KH; ++k)
-          qb[k] = ((FULL || col < col1) && KH * h + k < r) ? Q[(size_t)col * r + KH * h + k] : 0.0f;
+        for (int k = 0; k < KH; ++k) qb[k] = 0.0f;
       }
       v16f gh;
 #pragma unroll
@@ -2120,8 +1970,8 @@ __device__ __forceinline__ void mfma_tile32(const float* __restrict__ G, float* 
       Pk<4> m;
 #pragma unroll
       for (int v = 0; v < 4; ++v) m.v[v] = g[i].v[v] + e[i].v[v];
-      if (FULL || (colok && rr < nrows))
-        strow<4, NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + rr) * cols), (unsigned)cl * 4u, m);
+      if (rr < nrows)
+        stgroup<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + rr) * cols), (unsigned)cl * 4u, cols - cl, m);
       *reinterpret_cast<float4*>(lds + rr * kLP32 + c4) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
     }
     // the Q slice of the P product is fetched only now: the registers of the G-hat operands are free again
@@ -2129,10 +1979,7 @@ __device__ __forceinline__ void mfma_tile32(const float* __restrict__ G, float* 
 #pragma unroll
     for (int kk = 0; kk < 16; ++kk) {
       const int col = c + 16 * h + kk;
-      if constexpr (FULL && EXACT)
-        bq[kk] = Q[(size_t)col * RP + li];
-      else
-        bq[kk] = (col < col1 && li < rs) ? Q[(size_t)col * rs + li] : 0.0f;
+      bq[kk] = col < col1 ? Q[(size_t)col * RP + li] : 0.0f;
     }
     wave_lds_fence();
     {
@@ -2167,137 +2014,120 @@ __device__ __forceinline__ void mfma_tile32(const float* __restrict__ G, float* 
   if (nrows == 32 && c + 32 <= col1 && cols < (1 << 26)) {   // (byte offsets within 8 rows fit 32 bits)
     const int last = c + ((col1 - 32 - c) / 256) * 256;   // this wavefront's last whole block
     Pk<4> g[4], e[4], gn[4], en[4];
-    if constexpr (EXACT) {
-      float qb[KH], bq[16];
-      // Addresses are a wave-uniform base (scalar registers, advanced by scalar adds) plus a byte
-      // offset per lane that does not change from block to block.
-      const unsigned goff = (unsigned)(sr * cols + c4) * 4u;      // lane's place in a slab of 8 rows
-      const unsigned qboff = (unsigned)(li * RP + KH * h) * 4u;   // ... in 32 rows of Q (G-hat operand)
-      const unsigned bqoff = (unsigned)(16 * h * RP + li) * 4u;   // ... in 32 rows of Q (P operand)
-      auto fetch_ge = [&](const int cb, Pk<4>* gg, Pk<4>* ee) {
+    float qb[KH], bq[16];
+    // Addresses are a wave-uniform base (scalar registers, advanced by scalar adds) plus a byte
+    // offset per lane that does not change from block to block.
+    const unsigned goff = (unsigned)(sr * cols + c4) * 4u;      // lane's place in a slab of 8 rows
+    const unsigned qboff = (unsigned)(li * RP + KH * h) * 4u;   // ... in 32 rows of Q (G-hat operand)
+    const unsigned bqoff = (unsigned)(16 * h * RP + li) * 4u;   // ... in 32 rows of Q (P operand)
+    auto fetch_ge = [&](const int cb, Pk<4>* gg, Pk<4>* ee) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const size_t off = (size_t)(row0 + 8 * i) * cols + cb;
+        if constexpr (GB16) {   // kept packed (two registers) until the block is worked on
+          const Pk<2> t = ldrow_bf16_packed<LQSGD_NT_G != 0>(grad_row<GB16>(G, off), goff);
+          gg[i].v[0] = t.v[0]; gg[i].v[1] = t.v[1];
+        } else {
+          gg[i] = ldgrad<LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), goff);
+        }
+        ee[i] = ldrow<NTS>(reinterpret_cast<const char*>(M + off), goff);
+      }
+    };
+    auto fetch_qb = [&](const int cb) {
+      const char* base = reinterpret_cast<const char*>(Q + (size_t)cb * RP);
+#pragma unroll
+      for (int t = 0; t < KH / 4; ++t) {
+        const Pk<4> x = ldrow<false>(base + 16 * t, qboff);
+        qb[4 * t] = x.v[0]; qb[4 * t + 1] = x.v[1]; qb[4 * t + 2] = x.v[2]; qb[4 * t + 3] = x.v[3];
+      }
+    };
+    fetch_ge(c, g, e);
+    if constexpr (NEEDG) fetch_qb(c);
+    // one block; MORE: another whole block follows (a constant, so that no branch joins two
+    // request histories and every wait counts exactly)
+    auto step = [&](auto more_tag, const int c, Pk<4>* g, Pk<4>* e, Pk<4>* gn, Pk<4>* en) {
+      constexpr bool more = decltype(more_tag)::value;
+      {
+        const char* base = reinterpret_cast<const char*>(Q + (size_t)c * RP);
+#pragma unroll
+        for (int kk = 0; kk < 16; ++kk) bq[kk] = *gptr<float>(base + kk * RP * 4 + bqoff);
+      }
+      if constexpr (more) fetch_ge(c + 256, gn, en);
+      __builtin_amdgcn_sched_barrier(0);   // the requests above stay ahead of the arithmetic below
+      if constexpr (NEEDG) {
+        v16f gh;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) gh[i] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < KH; ++k) gh = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[k], qb[k], gh, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (more) fetch_qb(c + 256);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) lds[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP32 + li] = gh[v];
+        wave_lds_fence();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const size_t off = (size_t)(row0 + 8 * i) * cols + cb;
-          if constexpr (GB16) {   // kept packed (two registers) until the block is worked on
-            const auto* p = gptr<v2u>(grad_row<GB16>(G, off) + (goff >> 1));
-            const v2u t = LQSGD_NT_G ? __builtin_nontemporal_load(p) : *p;
-            gg[i].v[0] = __uint_as_float(t.x); gg[i].v[1] = __uint_as_float(t.y);
-          } else {
-            gg[i] = ldgrad<4, LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), goff);
-          }
-          ee[i] = ldrow<4, NTS>(reinterpret_cast<const char*>(M + off), goff);
-        }
-      };
-      auto fetch_qb = [&](const int cb) {
-        const char* base = reinterpret_cast<const char*>(Q + (size_t)cb * RP);
-#pragma unroll
-        for (int t = 0; t < KH / 4; ++t) {
-          const Pk<4> x = ldrow<4, false>(base + 16 * t, qboff);
-          qb[4 * t] = x.v[0]; qb[4 * t + 1] = x.v[1]; qb[4 * t + 2] = x.v[2]; qb[4 * t + 3] = x.v[3];
-        }
-      };
-      fetch_ge(c, g, e);
-      if constexpr (NEEDG) fetch_qb(c);
-      // one block; MORE: another whole block follows (a constant, so that no branch joins two
-      // request histories and every wait counts exactly)
-      auto step = [&](auto more_tag, const int c, Pk<4>* g, Pk<4>* e, Pk<4>* gn, Pk<4>* en) {
-        constexpr bool more = decltype(more_tag)::value;
-        {
-          const char* base = reinterpret_cast<const char*>(Q + (size_t)c * RP);
-#pragma unroll
-          for (int kk = 0; kk < 16; ++kk) bq[kk] = ldrow<1, false>(base + kk * RP * 4, bqoff).v[0];
-        }
-        if constexpr (more) fetch_ge(c + 256, gn, en);
-        __builtin_amdgcn_sched_barrier(0);   // the requests above stay ahead of the arithmetic below
-        if constexpr (NEEDG) {
-          v16f gh;
-#pragma unroll
-          for (int i = 0; i < 16; ++i) gh[i] = 0.0f;
-#pragma unroll
-          for (int k = 0; k < KH; ++k) gh = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[k], qb[k], gh, 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
-          if constexpr (more) fetch_qb(c + 256);
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int v = 0; v < 16; ++v) lds[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP32 + li] = gh[v];
-          wave_lds_fence();
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float4 t = *reinterpret_cast<const float4*>(lds + (8 * i + sr) * kLP32 + c4);
-            e[i].v[0] -= t.x; e[i].v[1] -= t.y; e[i].v[2] -= t.z; e[i].v[3] -= t.w;
-          }
-          wave_lds_fence();
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int rr = 8 * i + sr;
-          Pk<4> m, gv = g[i];
-          if constexpr (GB16) {
-            const unsigned x = __float_as_uint(g[i].v[0]), y = __float_as_uint(g[i].v[1]);
-            gv.v[0] = __uint_as_float(x << 16); gv.v[1] = __uint_as_float(x & 0xffff0000u);
-            gv.v[2] = __uint_as_float(y << 16); gv.v[3] = __uint_as_float(y & 0xffff0000u);
-          }
-#pragma unroll
-          for (int v = 0; v < 4; ++v) m.v[v] = gv.v[v] + e[i].v[v];
-          strow<4, NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + 8 * i) * cols + c), goff, m);
-          *reinterpret_cast<float4*>(lds + rr * kLP32 + c4) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
+          const float4 t = *reinterpret_cast<const float4*>(lds + (8 * i + sr) * kLP32 + c4);
+          e[i].v[0] -= t.x; e[i].v[1] -= t.y; e[i].v[2] -= t.z; e[i].v[3] -= t.w;
         }
         wave_lds_fence();
-        {
-          const float4 a0 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h);
-          const float4 a1 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 4);
-          const float4 a2 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 8);
-          const float4 a3 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 12);
-          accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, bq[0], accP, 0, 0, 0);
-          accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, bq[4], accP2, 0, 0, 0);
-          accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, bq[1], accP, 0, 0, 0);
-          accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, bq[5], accP2, 0, 0, 0);
-          accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, bq[2], accP, 0, 0, 0);
-          accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, bq[6], accP2, 0, 0, 0);
-          accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, bq[3], accP, 0, 0, 0);
-          accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, bq[7], accP2, 0, 0, 0);
-          accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.x, bq[8], accP, 0, 0, 0);
-          accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.x, bq[12], accP2, 0, 0, 0);
-          accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.y, bq[9], accP, 0, 0, 0);
-          accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.y, bq[13], accP2, 0, 0, 0);
-          accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.z, bq[10], accP, 0, 0, 0);
-          accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.z, bq[14], accP2, 0, 0, 0);
-          accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.w, bq[11], accP, 0, 0, 0);
-          accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.w, bq[15], accP2, 0, 0, 0);
-        }
-        wave_lds_fence();
-      };
-      // two blocks per trip, the two register sets changing roles (no copies, so nothing waits for
-      // a prefetch before its values are needed)
-      for (; c + 256 < last; c += 512) {
-        step(std::true_type{}, c, g, e, gn, en);
-        step(std::true_type{}, c + 256, gn, en, g, e);
       }
-      if (c < last) {
-        step(std::true_type{}, c, g, e, gn, en);
-        step(std::false_type{}, c + 256, gn, en, g, e);
-        c += 512;
-      } else {
-        step(std::false_type{}, c, g, e, gn, en);
-        c += 256;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int rr = 8 * i + sr;
+        Pk<4> m, gv = g[i];
+        if constexpr (GB16) gv = unpack_bf16(g[i].v[0], g[i].v[1]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) m.v[v] = gv.v[v] + e[i].v[v];
+        strow<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + 8 * i) * cols + c), goff, m);
+        *reinterpret_cast<float4*>(lds + rr * kLP32 + c4) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
       }
+      wave_lds_fence();
+      {
+        const float4 a0 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h);
+        const float4 a1 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 4);
+        const float4 a2 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 8);
+        const float4 a3 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 12);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, bq[0], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, bq[4], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, bq[1], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, bq[5], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, bq[2], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, bq[6], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, bq[3], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, bq[7], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.x, bq[8], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.x, bq[12], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.y, bq[9], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.y, bq[13], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.z, bq[10], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.z, bq[14], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.w, bq[11], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.w, bq[15], accP2, 0, 0, 0);
+      }
+      wave_lds_fence();
+    };
+    // two blocks per trip, the two register sets changing roles (no copies, so nothing waits for
+    // a prefetch before its values are needed)
+    for (; c + 256 < last; c += 512) {
+      step(std::true_type{}, c, g, e, gn, en);
+      step(std::true_type{}, c + 256, gn, en, g, e);
+    }
+    if (c < last) {
+      step(std::true_type{}, c, g, e, gn, en);
+      step(std::false_type{}, c + 256, gn, en, g, e);
+      c += 512;
     } else {
-      fetch(std::true_type{}, c, g, e);
-      for (; c <= last; c += 256) {
-        const bool more = c < last;
-        if (more) fetch(std::true_type{}, c + 256, gn, en);
-        block(std::true_type{}, c, g, e);
-        if (more) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) { g[i] = gn[i]; e[i] = en[i]; }
-        }
-      }
+      step(std::false_type{}, c, g, e, gn, en);
+      c += 256;
     }
   }
   for (; c < col1; c += 256) {
     Pk<4> g[4], e[4];
-    fetch(std::false_type{}, c, g, e);
-    block(std::false_type{}, c, g, e);
+    if (cols >= 4) fetch(std::integral_constant<int, kRagged>{}, c, g, e);
+    else fetch(std::integral_constant<int, kNarrow>{}, c, g, e);
+    block(c, g, e);
   }
   // P partial of the item = sum over the eight wavefronts, added in wavefront order
 #pragma unroll
@@ -2312,64 +2142,6 @@ __device__ __forceinline__ void mfma_tile32(const float* __restrict__ G, float* 
     for (int wv = 1; wv < 8; ++wv) t += lds_all[wv][rr * kLP32 + k];
     if (rr < nrows && k < r) Pp[(size_t)(row0 + rr) * r + k] = t;
   }
-}
-
-// Rows that are not 16-byte aligned (tiny layers): a plain loop, one wavefront over the rows of its
-// share, lanes over columns; the r dot products of a row go through wave sums.
-template <int MODE, bool GB16>
-__device__ __forceinline__ void plain_rows_fallback(const DevArgs& a, const LayerDesc& ld, const Tile& tl,
-                                                    const float* G, float* M, float* Pp, float* ghat_out,
-                                                    int col0, int col1, int lane) {
-  constexpr bool ADD = (MODE == kMAdd || MODE == kMAddFused);
-  constexpr bool NEEDG = (MODE != kMAdd);
-  const int cols = ld.cols, r = ld.r;
-  const float* Pb = a.Pbar + ld.p_off;
-  const float* Q = a.Qbar + ld.q_off;
-  for (int row = tl.row0; row < tl.row0 + tl.nrows; ++row) {
-    for (int k0 = 0; k0 < (ADD ? r : 1); ++k0) {
-      // add modes: pass k0 forms P[row][k0]; the tile itself is updated in pass 0 only
-      float dot = 0.0f;
-      for (int c = col0 + lane; c < col1; c += kWave) {
-        float m;
-        if (k0 == 0) {
-          float gh = 0.0f;
-          if constexpr (NEEDG)
-            for (int k = 0; k < r; ++k) gh = fmaf(Pb[(size_t)row * r + k], Q[(size_t)c * r + k], gh);
-          if constexpr (MODE == kMGhatOnly) {
-            const Pk<1> o{{gh}};
-            emit_ghat<1>(ghat_out + (size_t)row * cols, (unsigned)c * 4u, o, a.update, a.eta);
-            continue;
-          } else {
-            float e = M[(size_t)row * cols + c];
-            if constexpr (NEEDG) e -= gh;
-            m = ADD ? grad_elem<GB16>(G, (size_t)row * cols + c) + e : e;
-            M[(size_t)row * cols + c] = m;
-            if (MODE == kMResidualGhat && ghat_out) {
-              const Pk<1> o{{gh}};
-              emit_ghat<1>(ghat_out + (size_t)row * cols, (unsigned)c * 4u, o, a.update, a.eta);
-            }
-          }
-        } else {
-          m = M[(size_t)row * cols + c];            // this lane wrote it in pass 0
-        }
-        if constexpr (ADD) dot = fmaf(m, Q[(size_t)c * r + k0], dot);
-      }
-      if constexpr (ADD) {
-        dot = wave_sum(dot);
-        if (lane == 0) Pp[(size_t)row * r + k0] = dot;
-      }
-    }
-  }
-}
-
-// Rows that are not 16-byte aligned (cols % 4 != 0; tiny layers) take the plain loop: the register-
-// tiled vector code would set the register count of the whole kernel (rank pad x 4 accumulators and
-// as many factor values per lane) and with it the number of wavefronts per SIMD of the main path.
-template <int RP, int MODE, bool GB16>
-__device__ __forceinline__ void mfma_mode_vector_fallback(const DevArgs& a, const LayerDesc& ld, const Tile& tl, int worker,
-                                                          const float* G, float* M, float* Pp, float* ghat_out,
-                                                          int col0, int col1, int lane) {
-  plain_rows_fallback<MODE, GB16>(a, ld, tl, G, M, Pp, ghat_out, col0, col1, lane);
 }
 
 // Wavefronts per SIMD the register allocation aims for: two at rank pad 16 (2.65 -> 2.47 ms on
@@ -2391,23 +2163,8 @@ __global__ __launch_bounds__(256, RP <= 16 ? 2 : 1) void mfma_sweep_kernel(DevAr
   if (MODE == kMGhatOnly && !ghat_out) return;
   const int col0 = tl.aux * ld.segw;
   const int col1 = min(ld.cols, col0 + ld.segw);
-  if (ld.vec != 4) {
-    // tiny layers: the vector code, eight of the item's rows per wavefront
-    Tile sub = tl;
-    sub.row0 = tl.row0 + 8 * wave;
-    sub.nrows = min(8, tl.nrows - 8 * wave);
-    if (sub.nrows > 0) mfma_mode_vector_fallback<RP, MODE, GB16>(a, ld, sub, worker, G, M, Pp, ghat_out, col0, col1, lane);
-    return;
-  }
-  if (a.Qpad)   // operands with rows of RP ranks, zero beyond the layer's rank
-    mfma_tile<RP, MODE, true, GB16, NTS>(G, M, a.Qpad + ld.qpad_off, a.Ppad + ld.ppad_off, Pp, ghat_out, ld.cols, ld.r, tl.row0,
-                              tl.nrows, col0, col1, lane, wave, lds_all, a.update, a.eta);
-  else if (ld.r == RP)
-    mfma_tile<RP, MODE, true, GB16, NTS>(G, M, a.Qbar + ld.q_off, a.Pbar + ld.p_off, Pp, ghat_out, ld.cols, ld.r, tl.row0,
-                              tl.nrows, col0, col1, lane, wave, lds_all, a.update, a.eta);
-  else
-    mfma_tile<RP, MODE, false, GB16, NTS>(G, M, a.Qbar + ld.q_off, a.Pbar + ld.p_off, Pp, ghat_out, ld.cols, ld.r, tl.row0,
-                               tl.nrows, col0, col1, lane, wave, lds_all, a.update, a.eta);
+  mfma_tile<RP, MODE, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ghat_out, ld.cols, ld.r, tl.row0,
+                                 tl.nrows, col0, col1, lane, wave, lds_all, a.update, a.eta);
 }
 
 template <int RP, int MODE, bool GB16, bool NTS>
@@ -2424,23 +2181,8 @@ __global__ __launch_bounds__(512, 2) void mfma_sweep32_kernel(DevArgs a, const T
   float* Pp = a.Ppart + (size_t)worker * a.ppart_stride + ld.ppart_off + (size_t)tl.aux * ld.np_pad;
   const int col0 = tl.aux * ld.segw;
   const int col1 = min(ld.cols, col0 + ld.segw);
-  if (ld.vec != 4) {
-    // tiny layers: the vector code, four of the item's rows per wavefront
-    Tile sub = tl;
-    sub.row0 = tl.row0 + 4 * wave;
-    sub.nrows = min(4, tl.nrows - 4 * wave);
-    if (sub.nrows > 0) mfma_mode_vector_fallback<RP, MODE, GB16>(a, ld, sub, worker, G, M, Pp, nullptr, col0, col1, lane);
-    return;
-  }
-  if (a.Qpad)
-    mfma_tile32<RP, MODE, true, GB16, NTS>(G, M, a.Qpad + ld.qpad_off, a.Ppad + ld.ppad_off, Pp, ld.cols, ld.r, tl.row0, tl.nrows,
-                                      col0, col1, lane, wave, lds_all);
-  else if (ld.r == RP)
-    mfma_tile32<RP, MODE, true, GB16, NTS>(G, M, a.Qbar + ld.q_off, a.Pbar + ld.p_off, Pp, ld.cols, ld.r, tl.row0, tl.nrows,
-                                      col0, col1, lane, wave, lds_all);
-  else
-    mfma_tile32<RP, MODE, false, GB16, NTS>(G, M, a.Qbar + ld.q_off, a.Pbar + ld.p_off, Pp, ld.cols, ld.r, tl.row0, tl.nrows,
-                                       col0, col1, lane, wave, lds_all);
+  mfma_tile32<RP, MODE, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ld.cols, ld.r, tl.row0, tl.nrows,
+                                   col0, col1, lane, wave, lds_all);
 }
 
 // Copies of the aggregated factors with rows of RP ranks (zero beyond the layer's rank) for the
@@ -2449,7 +2191,7 @@ __global__ __launch_bounds__(256) void pad_factor_kernel(DevArgs a, int RP, int 
   const LayerDesc& ld = a.layers[blockIdx.y];
   const int n = which ? ld.cols : ld.rows, r = ld.r;
   const float* src = which ? a.Qbar + ld.q_off : a.Pbar + ld.p_off;
-  float* dst = which ? a.Qpad + ld.qpad_off : a.Ppad + ld.ppad_off;
+  float* dst = which ? a.Qop + ld.qop_off : a.Pop + ld.pop_off;
   const long long total = (long long)n * RP;
   for (long long e = blockIdx.x * 256 + threadIdx.x; e < total; e += gridDim.x * 256) {
     const long long row = e / RP;
@@ -2946,6 +2688,19 @@ const char* last_launched_kernel() { return g_launched; }
 #endif
 static inline const char* tf(bool b) { return b ? "true" : "false"; }
 
+// Rank pads of the vector sweeps: up to 8 (sweep 1: up to 16); higher ones run on the matrix cores.
+#define LQSGD_RP_SWITCH8(RPV, CALL)           \
+  switch (RPV) {                              \
+    case 1: { constexpr int RP = 1; CALL; } break;   \
+    case 2: { constexpr int RP = 2; CALL; } break;   \
+    case 4: { constexpr int RP = 4; CALL; } break;   \
+    case 8: { constexpr int RP = 8; CALL; } break;   \
+    default: return hipErrorInvalidValue;     \
+  }
+#define LQSGD_RP_SWITCH16(RPV, CALL)                    \
+  if ((RPV) == 16) { constexpr int RP = 16; CALL; } else \
+    LQSGD_RP_SWITCH8(RPV, CALL)
+
 #define LQSGD_RP_SWITCH(RPV, CALL)            \
   switch (RPV) {                              \
     case 1: { constexpr int RP = 1; CALL; } break;   \
@@ -2968,8 +2723,8 @@ hipError_t launch_add_project(int rp, const DevArgs& a, const Tile* tiles, int n
   if (ntiles <= 0) return hipSuccess;
   const dim3 grid((ntiles + 3) / 4), block(256);
 #define LQSGD_LAUNCH_A(FUSE, GB) \
-  if (a.nt_store) { LQSGD_RP_SWITCH(rp, (add_project_kernel<RP, FUSE, GB, true><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); } \
-  else { LQSGD_RP_SWITCH(rp, (add_project_kernel<RP, FUSE, GB, false><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); }
+  if (a.nt_store) { LQSGD_RP_SWITCH8(rp, (add_project_kernel<RP, FUSE, GB, true><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); } \
+  else { LQSGD_RP_SWITCH8(rp, (add_project_kernel<RP, FUSE, GB, false><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); }
   if (a.g_bf16) {
     if (fuse_residual) { LQSGD_LAUNCH_A(true, true) } else { LQSGD_LAUNCH_A(false, true) }
   } else if (fuse_residual) {
@@ -3200,7 +2955,7 @@ hipError_t launch_back_project(int rp, const DevArgs& a, const Tile* tiles, int 
                                int reverse, hipStream_t s) {
   if (ntiles + nvtiles <= 0) return hipSuccess;
   const dim3 grid(ntiles + nvtiles), block(256);
-  LQSGD_RP_SWITCH(rp, (back_project_kernel<RP><<<grid, block, 0, s>>>(a, tiles, ntiles, vtiles, reverse)));
+  LQSGD_RP_SWITCH16(rp, (back_project_kernel<RP><<<grid, block, 0, s>>>(a, tiles, ntiles, vtiles, reverse)));
   note_kernel("back_project_kernel<%d>", rp);
   return hipGetLastError();
 }
@@ -3231,9 +2986,9 @@ hipError_t launch_residual(int rp, int mode, const DevArgs& a, const Tile* tiles
   if (ntiles <= 0) return hipSuccess;
   const dim3 grid(ntiles), block(256);
   switch (mode) {
-    case kResidual: LQSGD_RP_SWITCH(rp, (residual_kernel<RP, kResidual><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); break;
-    case kResidualGhat: LQSGD_RP_SWITCH(rp, (residual_kernel<RP, kResidualGhat><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); break;
-    case kGhatOnly: LQSGD_RP_SWITCH(rp, (residual_kernel<RP, kGhatOnly><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); break;
+    case kResidual: LQSGD_RP_SWITCH8(rp, (residual_kernel<RP, kResidual><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); break;
+    case kResidualGhat: LQSGD_RP_SWITCH8(rp, (residual_kernel<RP, kResidualGhat><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); break;
+    case kGhatOnly: LQSGD_RP_SWITCH8(rp, (residual_kernel<RP, kGhatOnly><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); break;
     default: return hipErrorInvalidValue;
   }
   note_kernel("residual_kernel<%d, %d>", rp, mode);
@@ -3241,85 +2996,51 @@ hipError_t launch_residual(int rp, int mode, const DevArgs& a, const Tile* tiles
 }
 #endif
 
-// A tuning build (-DLQSGD_TUNING) can keep the 32 x 64 form at rank pad 32 for comparisons (LQSGD_MFMA_NARROW32=0).
-static bool narrow32() {
-#ifdef LQSGD_TUNING
-  static const bool on = [] { const char* e = std::getenv("LQSGD_MFMA_NARROW32"); return !(e && e[0] == '0'); }();
-  return on;
-#else
-  return true;
-#endif
+template <int RP, int MODE>
+void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s) {
+  const dim3 grid(ntiles);
+  // the narrow form at rank pad 32, where the wide one runs one wavefront per SIMD (8192^2 x 16, r = 32: 2.77 -> 2.60 ms)
+#define LQSGD_LAUNCH_MA(GB, NT)                                                                                            \
+  if constexpr (RP == 32) mfma_sweep32_kernel<RP, MODE, GB, NT><<<grid, dim3(512), 0, s>>>(a, tiles, ntiles, reverse);     \
+  else mfma_sweep_kernel<RP, MODE, GB, NT><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, reverse)
+  if (a.g_bf16) {
+    if (a.nt_store) { LQSGD_LAUNCH_MA(true, true); } else { LQSGD_LAUNCH_MA(true, false); }
+  } else {
+    if (a.nt_store) { LQSGD_LAUNCH_MA(false, true); } else { LQSGD_LAUNCH_MA(false, false); }
+  }
+#undef LQSGD_LAUNCH_MA
+  note_kernel("%s<%d, %d, %s, %s>", RP == 32 ? "mfma_sweep32_kernel" : "mfma_sweep_kernel", RP, MODE, tf(a.g_bf16), tf(a.nt_store));
 }
 
 template <int RP>
-hipError_t launch_mfma_sweep_rp(int mode, int full_rank, const DevArgs& a, const Tile* tiles, int ntiles, int reverse,
-                                hipStream_t s) {
+hipError_t launch_mfma_sweep_rp(int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s) {
   const dim3 grid(ntiles), block(256);
   switch (mode) {
-    case kMAdd:
-      // same form as the fused mode below, so that P comes out of one summation order whether or
-      // not the residual update is deferred
-      if constexpr (RP == 32) {
-        if (narrow32() && full_rank) {
-          if (a.g_bf16) { if (a.nt_store) mfma_sweep32_kernel<32, kMAdd, true, true><<<grid, dim3(512), 0, s>>>(a, tiles, ntiles, reverse);
-                          else mfma_sweep32_kernel<32, kMAdd, true, false><<<grid, dim3(512), 0, s>>>(a, tiles, ntiles, reverse); }
-          else { if (a.nt_store) mfma_sweep32_kernel<32, kMAdd, false, true><<<grid, dim3(512), 0, s>>>(a, tiles, ntiles, reverse);
-                 else mfma_sweep32_kernel<32, kMAdd, false, false><<<grid, dim3(512), 0, s>>>(a, tiles, ntiles, reverse); }
-          break;
-        }
-      }
-      if (a.g_bf16) { if (a.nt_store) mfma_sweep_kernel<RP, kMAdd, true, true><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse);
-                      else mfma_sweep_kernel<RP, kMAdd, true, false><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse); }
-      else { if (a.nt_store) mfma_sweep_kernel<RP, kMAdd, false, true><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse);
-             else mfma_sweep_kernel<RP, kMAdd, false, false><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse); }
-      break;
-    case kMAddFused:
-      // the narrow form pays where the fused mode would otherwise run one wavefront per SIMD and every
-      // layer fills the rank pad (measured on 8192^2 x 16: r = 32 2.77 -> 2.60 ms; at r = 30 it costs
-      // 3.11 -> 3.22 ms, so ranks below the pad stay with the 32 x 64 form)
-      if constexpr (RP == 32) {
-        if (narrow32() && full_rank) {
-          if (a.g_bf16) { if (a.nt_store) mfma_sweep32_kernel<32, kMAddFused, true, true><<<grid, dim3(512), 0, s>>>(a, tiles, ntiles, reverse);
-                          else mfma_sweep32_kernel<32, kMAddFused, true, false><<<grid, dim3(512), 0, s>>>(a, tiles, ntiles, reverse); }
-          else { if (a.nt_store) mfma_sweep32_kernel<32, kMAddFused, false, true><<<grid, dim3(512), 0, s>>>(a, tiles, ntiles, reverse);
-                 else mfma_sweep32_kernel<32, kMAddFused, false, false><<<grid, dim3(512), 0, s>>>(a, tiles, ntiles, reverse); }
-          break;
-        }
-      }
-      if (a.g_bf16) { if (a.nt_store) mfma_sweep_kernel<RP, kMAddFused, true, true><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse);
-                      else mfma_sweep_kernel<RP, kMAddFused, true, false><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse); }
-      else { if (a.nt_store) mfma_sweep_kernel<RP, kMAddFused, false, true><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse);
-             else mfma_sweep_kernel<RP, kMAddFused, false, false><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse); }
-      break;
+    case kMAdd: launch_mfma_add<RP, kMAdd>(a, tiles, ntiles, reverse, s); return hipGetLastError();
+    case kMAddFused: launch_mfma_add<RP, kMAddFused>(a, tiles, ntiles, reverse, s); return hipGetLastError();
     case kMResidual: mfma_sweep_kernel<RP, kMResidual><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse); break;
     case kMResidualGhat: mfma_sweep_kernel<RP, kMResidualGhat><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse); break;
     case kMGhatOnly: mfma_sweep_kernel<RP, kMGhatOnly><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse); break;
     default: return hipErrorInvalidValue;
   }
-  {
-    const bool add = mode == kMAdd || mode == kMAddFused;
-    if (add && RP == 32 && narrow32() && full_rank)
-      note_kernel("mfma_sweep32_kernel<32, %d, %s, %s>", mode, tf(a.g_bf16), tf(a.nt_store));
-    else
-      note_kernel("mfma_sweep_kernel<%d, %d, %s, %s>", RP, mode, tf(add && a.g_bf16), tf(add && a.nt_store));
-  }
+  note_kernel("mfma_sweep_kernel<%d, %d, false, false>", RP, mode);
   return hipGetLastError();
 }
 
 // rank pads 16 and 32 in one part, 64 in another: about the same time to compile
-hipError_t launch_mfma_sweep64(int mode, int full_rank, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s);
+hipError_t launch_mfma_sweep64(int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s);
 #if LQSGD_HAS(3)
-hipError_t launch_mfma_sweep64(int mode, int full_rank, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s) {
-  return launch_mfma_sweep_rp<64>(mode, full_rank, a, tiles, ntiles, reverse, s);
+hipError_t launch_mfma_sweep64(int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s) {
+  return launch_mfma_sweep_rp<64>(mode, a, tiles, ntiles, reverse, s);
 }
 #endif
 #if LQSGD_HAS(2)
-hipError_t launch_mfma_sweep(int rp, int mode, int full_rank, const DevArgs& a, const Tile* tiles, int ntiles, int reverse,
+hipError_t launch_mfma_sweep(int rp, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse,
                              hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-  if (rp == 16) return launch_mfma_sweep_rp<16>(mode, full_rank, a, tiles, ntiles, reverse, s);
-  if (rp == 32) return launch_mfma_sweep_rp<32>(mode, full_rank, a, tiles, ntiles, reverse, s);
-  if (rp == 64) return launch_mfma_sweep64(mode, full_rank, a, tiles, ntiles, reverse, s);
+  if (rp == 16) return launch_mfma_sweep_rp<16>(mode, a, tiles, ntiles, reverse, s);
+  if (rp == 32) return launch_mfma_sweep_rp<32>(mode, a, tiles, ntiles, reverse, s);
+  if (rp == 64) return launch_mfma_sweep64(mode, a, tiles, ntiles, reverse, s);
   return hipErrorInvalidValue;
 }
 #endif
@@ -3371,7 +3092,7 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
 }
 
 hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, hipStream_t s) {
-  if (a.L <= 0 || !a.Ppad || !a.Qpad) return hipSuccess;
+  if (a.L <= 0 || !a.padded) return hipSuccess;
   pad_factor_kernel<<<dim3(64, a.L), dim3(256), 0, s>>>(a, RP, which);
   return hipGetLastError();
 }

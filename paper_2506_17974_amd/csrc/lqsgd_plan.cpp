@@ -108,7 +108,7 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
       d.rows = l.rows;
       d.cols = l.cols;
       d.r = std::min(c->rank, std::min(l.rows, l.cols));
-      d.vec = (l.cols % 4 == 0) ? 4 : 1;
+      d.kind = l.cols % 4 == 0 ? 0 : l.cols > 4 ? 1 : 2;
       d.gidx = i;
       d.np_el = d.rows * d.r;
       d.nq_el = d.cols * d.r;
@@ -125,8 +125,8 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
   V = (int32_t)vecs.size();
   RP = pad_rank(max_r);
   max_rank = max_r;
-  mfma_a = RP >= env_i64("LQSGD_MFMA_A_MIN_RP", 16);
-  mfma = RP >= env_i64("LQSGD_MFMA_MIN_RP", 32);   // measured: at rank pad 16 the vector kernel is still faster
+  mfma_a = RP >= 16;
+  mfma = RP >= 32;                  // measured: at rank pad 16 the vector kernel is still faster
 
   // ---- tile sizes --------------------------------------------------------
   // A launch wants several times 256 CUs x 16 wavefronts of work items, each
@@ -156,8 +156,8 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
   const int32_t rq_chunk = reduce_chunk(true), rp_chunk = reduce_chunk(false);
   for (int li = 0; li < L; ++li) {
     LayerDesc& d = layers[li];
-    const int cw = kWave * d.vec;
-    const int64_t segmax = std::max<int64_t>(cw, d.vec == 4 ? round_up(segmax4, cw) : 256);
+    constexpr int cw = kWave * 4;                        // columns of a wavefront's pass over a row
+    const int64_t segmax = round_up(segmax4, cw);
     int nseg = (int)((d.cols + segmax - 1) / segmax);
     d.segw = (int32_t)round_up((d.cols + nseg - 1) / nseg, cw);
     d.nseg = (d.cols + d.segw - 1) / d.segw;
@@ -198,9 +198,9 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
     d.q_off = q_acc;   q_acc += round_up(d.nq_el, 64);
     d.ppart_off = pp_acc; pp_acc += (int64_t)d.nseg * d.np_pad;
     d.qpart_off = qp_acc; qp_acc += d.direct_q ? 0 : (int64_t)d.nrb * d.nq_pad;   // no partial planes where sweep 1 stores Q_w itself
-    d.ppad_off = ppd_acc; ppd_acc += round_up((int64_t)d.rows * RP, 64);
-    d.qpad_off = qpd_acc; qpd_acc += round_up((int64_t)d.cols * RP, 64);
-    if (mfma_a && d.vec == 4 && d.r < RP && env_i64("LQSGD_NO_PAD_OPERANDS", 0) == 0) padded = true;
+    d.pop_off = ppd_acc; ppd_acc += round_up((int64_t)d.rows * RP, 64);
+    d.qop_off = qpd_acc; qpd_acc += round_up((int64_t)d.cols * RP, 64);
+    if (d.r < RP) padded = true;
     const int64_t gp = (d.np_el + kXGroup - 1) / kXGroup, gq = (d.nq_el + kXGroup - 1) / kXGroup;
     d.magp_off = mp_acc; mp_acc += round_up(gp * std::max(1, cfg.bits_p), 16);
     d.sgnp_off = sp_acc; sp_acc += round_up(gp, 16);
@@ -247,6 +247,8 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
   sgnp_stride = round_up(sp_acc, 64);
   magq_stride = round_up(mq_acc, 64);
   sgnq_stride = round_up(sq_acc, 64);
+  if (!padded)
+    for (LayerDesc& d : layers) { d.pop_off = d.p_off; d.qop_off = d.q_off; }
   ppad_total = padded ? ppd_acc : 0;
   qpad_total = padded ? qpd_acc : 0;
 

@@ -21,13 +21,14 @@ constexpr int kFactorSlack = 64;   // readable floats after the last row of ever
 // One matrix layer as the kernels see it.  Offsets are in elements (floats)
 // from the start of a per-worker slab unless they say bytes.
 struct LayerDesc {
-  int32_t rows, cols, r, vec;   // vec = 4 when rows are 16-byte aligned (cols % 4 == 0), else 1
-  int32_t segw, nseg;           // sweep 0: column segment width (multiple of 64*vec) and count
+  int32_t rows, cols, r, kind;  // kind of rows: 0 = cols % 4 == 0 (16-byte aligned), 1 = not, 2 = not and below four columns
+  int32_t segw, nseg;           // sweep 0: column segment width (multiple of 256) and count
   int32_t rbb, nrb;             // sweeps 1, 2: rows per row block and count
   int32_t gidx;                 // position in the caller's tensor list
   int32_t np_el, nq_el;         // rows*r, cols*r
   int32_t np_pad, nq_pad;       // the same rounded up to 16 elements (stride of the partial planes)
   int32_t direct_q;             // sweep 1 covers all rows in one block and writes Q_w (and its absmax) itself: no partial planes, no reduce
+  int64_t pop_off, qop_off;     // into the factors the sweeps read: copies with rows padded to RP ranks (Plan::padded), or p_off / q_off
   int64_t m_off;                // into E / M          (worker stride m_stride)
   int64_t p_off;                // into rows x r slabs (worker stride p_stride)
   int64_t q_off;                // into cols x r slabs (worker stride q_stride)
@@ -35,7 +36,6 @@ struct LayerDesc {
   int64_t qpart_off;            // nrb planes of nq_pad  (worker stride qpart_stride)
   int64_t magp_off, sgnp_off;   // bytes (worker strides magp_stride, sgnp_stride)
   int64_t magq_off, sgnq_off;   // bytes
-  int64_t ppad_off, qpad_off;   // into the copies of P-bar / Q-bar with rows padded to RP ranks (Plan::padded)
 };
 
 struct VecDesc {
@@ -45,7 +45,7 @@ struct VecDesc {
 
 // Work item of a streaming sweep.  lw = layer * W + worker.
 // sweep 0: one wavefront; rows [row0, row0+nrows), column segment `aux`.
-// sweeps 1, 2: one workgroup; rows [row0, row0+nrows), column chunk `aux` (64*vec wide).
+// sweeps 1, 2: one workgroup; rows [row0, row0+nrows), column chunk `aux` (256 wide).
 struct Tile {
   int32_t lw, row0, nrows, aux;
 };
@@ -79,9 +79,9 @@ struct Plan {
   std::vector<RTile> tilesRQ;
   std::vector<RTile> tilesRP;      // aggregate-first order: reduce of the P partials (1024 elements each)
   bool agg_first = false;          // LQSGD_FLAG_AGGREGATE_FIRST
-  // Some layer that the matrix-core sweeps 0 / 2 handle has fewer ranks than the register pad: these
-  // sweeps then read P-bar and Q-bar from copies whose rows are padded with zeros to RP ranks
-  // (16-byte aligned rows, no rank tests in the loops); ppad_total / qpad_total floats.
+  // Some layer has fewer ranks than the register pad: the sweeps then read P-bar and Q-bar from copies
+  // whose rows are padded with zeros to RP ranks (aligned rows, no rank tests in the loops);
+  // ppad_total / qpad_total floats.
   bool padded = false;
   int64_t ppad_total = 0, qpad_total = 0;
   std::vector<VTile> tilesV;

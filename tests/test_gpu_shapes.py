@@ -1,0 +1,101 @@
+"""GPU parity at the edges of the kernels' tiles: row widths around multiples of four, 64 and 256, widths below four
+columns, heights around multiples of 8 and 32, ranks below their register pad, and the G-hat / parameter outputs'
+neighbours in memory.  Needs a real MI355X."""
+import zlib
+
+import numpy as np
+import pytest
+
+from paper_2506_17974_amd import binding as B
+from tests import parity_utils as pu
+
+pytestmark = pytest.mark.gpu
+f32 = np.float32
+
+
+def _say(*a):
+    print(*a, flush=True)
+
+
+# (factors at least twice as tall as wide, or one column: Gram-Schmidt in 32 bits is off by about 6e-8 times the condition
+# number of its input, which for a square normal matrix can be hundreds; the staged check's bar is for well-conditioned ones)
+WIDTHS = [
+    [(9, 1), (8, 2), (7, 3), (33, 4), (16, 5), (31, 7)],
+    [(101, 255), (103, 257), (130, 259), (1, 6), (128, 254)],
+    [(105, 1025), (103, 1283), (135, 1026)],
+    [(129, 63), (130, 65), (161, 129), (136, 513), (1, 515)],
+]
+
+
+@pytest.mark.parametrize("rank,bits,W", [(1, 8, 2), (3, 8, 3), (4, 4, 2), (7, 8, 2), (8, 0, 2), (12, 8, 2), (20, 8, 3), (32, 8, 1), (50, 8, 2)])
+@pytest.mark.parametrize("layers", WIDTHS, ids=lambda ls: "+".join("%dx%d" % s for s in ls))
+def test_ragged_shapes(layers, rank, bits, W):
+    """Two staged iterations against the oracle, then deferred and eager schedules bit for bit, with sentinels behind
+    every output (rows of any width are written up to their last element and not one further)."""
+    import torch
+    _say("case: ragged", layers, rank, bits, W)
+    rng = np.random.default_rng(zlib.crc32(str((layers, rank, bits, W)).encode()) % 1000)
+    ll = B.layer_list(layers, ())
+    ml = list(range(len(layers)))
+    Q0 = [rng.standard_normal((c, min(rank, r, c))).astype(f32) for r, c in layers]
+    Gs = [[[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)] for _ in range(3)]
+    comp = B.Compressor(ll, rank, bits, bits, W)
+    for l in ml:
+        comp.set_q(l, Q0[l])
+    E = [[np.zeros(s, f32) for s in layers] for _ in range(W)]
+    Q = [q.copy() for q in Q0]
+    rep = pu.StageReport()
+    for t in range(2):
+        E, Q = pu.staged_iteration(comp, Gs[t], pu.to_device(Gs[t]), E, Q, ml, rep)
+    comp.close()
+    _say("  ", rep)
+
+    outs = []
+    for flags in (0, B.FLAG_EAGER_RESIDUAL):
+        comp = B.Compressor(ll, rank, bits, bits, W, 255.0, flags)
+        for l in ml:
+            comp.set_q(l, Q0[l])
+        bufs = [torch.full((r * c + 8,), 7.0, device="cuda") for r, c in layers]
+        views = [b[:r * c].view(r, c) for b, (r, c) in zip(bufs, layers)]
+        got = []
+        for t in range(3):
+            comp.step(pu.to_device(Gs[t]), views)
+            torch.cuda.synchronize()
+            got += [v.cpu().numpy().copy() for v in views]
+            assert all(bool((b[-8:] == 7.0).all()) for b in bufs)
+        got += [comp.get_state(l, w)[0] for l in ml for w in range(W)]
+        before = [v.clone() for v in views]
+        comp.step_update(pu.to_device(Gs[0]), views, 0.5)
+        torch.cuda.synchronize()
+        assert all(bool((b[-8:] == 7.0).all()) for b in bufs)
+        got += [(v - w).cpu().numpy() for v, w in zip(views, before)]
+        outs.append(got)
+        comp.close()
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("rank", [3, 7, 20])
+def test_ragged_bf16_gradients(rank):
+    """Rows of bfloat16 gradients that start at any even address give what the same values in float32 give."""
+    import torch
+    _say("case: ragged bfloat16", rank)
+    layers, W = WIDTHS[1] + WIDTHS[3], 2
+    rng = np.random.default_rng(rank)
+    ll = B.layer_list(layers, (33,))
+    shapes = layers + [(33,)]
+    g16 = [[torch.from_numpy((rng.standard_normal(s) * 1e-3).astype(f32)).cuda().bfloat16() for s in shapes] for _ in range(W)]
+    res = []
+    for flags, g in ((B.FLAG_BF16_GRADIENTS, g16), (0, [[t.float() for t in gw] for gw in g16])):
+        comp = B.Compressor(ll, rank, 8, 8, W, 255.0, flags)
+        q = np.random.default_rng(1)
+        for l, (r, c) in enumerate(layers):
+            comp.set_q(l, q.standard_normal((c, min(rank, r, c))).astype(f32))
+        out = [torch.zeros(s, device="cuda") for s in shapes]
+        for _ in range(2):
+            comp.step(g, out)
+        torch.cuda.synchronize()
+        res.append([t.cpu().numpy() for t in out])
+        comp.close()
+    for a, b in zip(*res):
+        assert np.array_equal(a, b)
