@@ -462,7 +462,9 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
     // gives the same bits.
     const size_t nslice = (size_t)(p.max_rows + 255) / 256, pairs = W * (size_t)std::max(p.L, 1);
     const size_t ne = (size_t)chol_entries(p.RP);
-    if (ne && nslice >= 8 && pairs * (nslice + 1) * ne * 12 <= ((size_t)1 << 30)) {
+    // (rank pad 64 leaves the one-workgroup form at 1024 rows; a caller-provided block stays as small as it was)
+    const bool tall = nslice >= 8 || (!ext && p.RP == 64 && p.max_rows > 1024);
+    if (ne && tall && pairs * (nslice + 1) * ne * 12 <= ((size_t)1 << 30)) {
       if (!ext && nslice <= 64) TRY_(dev_alloc(c, &a.chol_table, pairs * (nslice + 1) * ne, true));   // the one-launch form's limit
       TRY_(dev_alloc(c, &a.chol_part, pairs * nslice * ne, true));
       TRY_(dev_alloc(c, &a.chol_redo, pairs, true));

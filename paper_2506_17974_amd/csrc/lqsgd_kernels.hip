@@ -537,96 +537,15 @@ __device__ __forceinline__ void quantise_group(const float (&x)[kXGroup], float 
 // orth: P_w = sum of the column-segment partials; modified Gram-Schmidt
 // (Algorithm 1, "Orthonormalize"), right-looking: column j is normalised, then
 // removed from every later column, which applies the projections to a column
-// in the same order as the left-looking form.  One workgroup per (layer,
-// worker); a lane owns rows tid, tid+256, ... through all passes, so the only
-// communication is the block-wide sums.  Ends with absmax(P_w) -> scaleP.
+// in the same order as the left-looking form.  Ends with absmax(P_w) -> scaleP.
 // In the aggregate-first order (orth_shared) the same kernels run once per layer
 // on the aggregated factor: input = one plane at P-bar, output in place, the
 // un-orthonormalised aggregate kept where `Ppre` points, no absmax.
-// ---------------------------------------------------------------------------
-template <int RP>
-__global__ __launch_bounds__(256) void orth_kernel(DevArgs a) {
-  __shared__ float red[2][4][RP];
-  __shared__ float redmax[4];
-  const int lw = blockIdx.x;
-  const int layer = lw / a.W, worker = lw - layer * a.W;
-  const LayerDesc& ld = a.layers[layer];
-  const int rows = ld.rows, r = ld.r, nseg = a.orth_shared ? 1 : ld.nseg;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
-  const float* Pp = a.Ppart + (size_t)worker * a.ppart_stride + (a.orth_shared ? ld.p_off : ld.ppart_off);
-  float* pre = a.Ppre + (size_t)worker * a.p_stride + ld.p_off;
-  float* orth = a.Porth + (size_t)worker * a.p_stride + ld.p_off;
-
-  for (int row = tid; row < rows; row += 256) {
-    float v[RP];
-#pragma unroll
-    for (int k = 0; k < RP; ++k) v[k] = 0.0f;
-    for (int s = 0; s < nseg; ++s) {
-      const float* src = Pp + (size_t)s * ld.np_pad + (size_t)row * r;
-#pragma unroll
-      for (int k = 0; k < RP; ++k)
-        if (k < r) v[k] += src[k];
-    }
-#pragma unroll
-    for (int k = 0; k < RP; ++k)
-      if (k < r) {
-        pre[(size_t)row * r + k] = v[k];
-        orth[(size_t)row * r + k] = v[k];
-      }
-  }
-
-  for (int j = 0; j < r; ++j) {
-    // s[k] = <column j, column k> for every k (entries k < j are not used)
-    float s[RP];
-#pragma unroll
-    for (int k = 0; k < RP; ++k) s[k] = 0.0f;
-    for (int row = tid; row < rows; row += 256) {
-      const float* src = orth + (size_t)row * r;
-      const float vj = src[j];
-#pragma unroll
-      for (int k = 0; k < RP; ++k)
-        if (k < r) s[k] = fmaf(vj, src[k], s[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < RP; ++k) s[k] = wave_sum(s[k]);
-    const int b = j & 1;
-    if (lane == 0) {
-#pragma unroll
-      for (int k = 0; k < RP; ++k) red[b][wave][k] = s[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < RP; ++k) s[k] = (red[b][0][k] + red[b][1][k]) + (red[b][2][k] + red[b][3][k]);
-    const float nrm2 = (red[b][0][j] + red[b][1][j]) + (red[b][2][j] + red[b][3][j]);
-    const float inv = (nrm2 > FLT_MIN) ? 1.0f / sqrtf(nrm2) : 0.0f;
-    for (int row = tid; row < rows; row += 256) {
-      float* dst = orth + (size_t)row * r;
-      const float qv = dst[j] * inv;
-      dst[j] = qv;
-#pragma unroll
-      for (int k = 0; k < RP; ++k)
-        if (k > j && k < r) dst[k] = fmaf(-(s[k] * inv), qv, dst[k]);
-    }
-  }
-
-  float mx = 0.0f;
-  for (int row = tid; row < rows; row += 256) {
-    const float* src = orth + (size_t)row * r;
-#pragma unroll
-    for (int k = 0; k < RP; ++k)
-      if (k < r) mx = fmaxf(mx, fabsf(src[k]));
-  }
-  mx = wave_max(mx);
-  if (lane == 0) redmax[wave] = mx;
-  __syncthreads();
-  if (tid == 0 && !a.orth_shared)
-    a.scaleP[(size_t)worker * a.L + layer] = fmaxf(fmaxf(redmax[0], redmax[1]), fmaxf(redmax[2], redmax[3]));
-}
-
-// ---------------------------------------------------------------------------
-// orth, register-resident: the same computation for layers of at most
+//
+// orth, rows on lanes: one workgroup per (layer, worker) for layers of at most
 // BS * RPT rows; a lane keeps its RPT rows in registers through all passes and
-// only the block-wide sums go through LDS (one barrier per column).
+// only the block-wide sums go through LDS (one barrier per column).  Rank pads 1
+// and 2: two columns leave nothing to gain from columns on lanes.
 // ---------------------------------------------------------------------------
 template <int RP, int RPT, int BS>
 __global__ __launch_bounds__(BS) void orth_reg_kernel(DevArgs a) {
@@ -663,76 +582,35 @@ __global__ __launch_bounds__(BS) void orth_reg_kernel(DevArgs a) {
     }
   }
 
-  // The column index must reach every use as a constant, so that the rows stay in registers (a
-  // run-time index would move v to scratch memory).  Up to rank pad 16 unrolling does that; at rank
-  // pad 32 the loop is too large to be unrolled on request, and each column is an instantiation.
-  if constexpr (RP >= 32) {
-    static_for<RP>([&](auto jc) __attribute__((always_inline)) {
-      constexpr int j = decltype(jc)::value;
-      // only the products with columns j .. RP - 1 are needed: they lie in the last N columns,
-      // N the next power of two (the width the butterfly below needs)
-      constexpr int N = pow2ceil(RP - j), K0 = RP - N, LGN = log2c(N);
-      if (j < r) {
-        float s[N];
 #pragma unroll
-        for (int k = 0; k < N; ++k) s[k] = 0.0f;
+  for (int j = 0; j < RP; ++j) {
+    if (j < r) {
+      float s[RP];
 #pragma unroll
-        for (int i = 0; i < RPT; ++i)
+      for (int k = 0; k < RP; ++k) s[k] = 0.0f;
 #pragma unroll
-          for (int k = 0; k < N; ++k) s[k] = fmaf(v[i][j], v[i][K0 + k], s[k]);
-        transpose_reduce<N, N, 32>(s, lane);
-        const int b = j & 1;
-        if ((lane & (kWave / N - 1)) == 0) red[b][wave][K0 + (lane >> (6 - LGN))] = s[0];
-        __syncthreads();
+      for (int i = 0; i < RPT; ++i)
 #pragma unroll
-        for (int k = 0; k < N; ++k) {
-          float t = 0.0f;
+        for (int k = 0; k < RP; ++k) s[k] = fmaf(v[i][j], v[i][k], s[k]);
+      transpose_reduce<RP, RP, 32>(s, lane);
+      const int b = j & 1;
+      if ((lane & (kWave / RP - 1)) == 0) red[b][wave][lane >> (6 - LG)] = s[0];
+      __syncthreads();
 #pragma unroll
-          for (int wv = 0; wv < NW; ++wv) t += red[b][wv][K0 + k];
-          s[k] = t;
-        }
-        const float nrm2 = s[j - K0];
-        const float inv = (nrm2 > FLT_MIN) ? 1.0f / sqrtf(nrm2) : 0.0f;
+      for (int k = 0; k < RP; ++k) {
+        float t = 0.0f;
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-          const float qv = v[i][j] * inv;
-          v[i][j] = qv;
-#pragma unroll
-          for (int k = j + 1; k < RP; ++k) v[i][k] = fmaf(-(s[k - K0] * inv), qv, v[i][k]);
-        }
+        for (int wv = 0; wv < NW; ++wv) t += red[b][wv][k];
+        s[k] = t;
       }
-    });
-  } else {
+      const float nrm2 = s[j];
+      const float inv = (nrm2 > FLT_MIN) ? 1.0f / sqrtf(nrm2) : 0.0f;
 #pragma unroll
-    for (int j = 0; j < RP; ++j) {
-      if (j < r) {
-        float s[RP];
-  #pragma unroll
-        for (int k = 0; k < RP; ++k) s[k] = 0.0f;
-  #pragma unroll
-        for (int i = 0; i < RPT; ++i)
-  #pragma unroll
-          for (int k = 0; k < RP; ++k) s[k] = fmaf(v[i][j], v[i][k], s[k]);
-        transpose_reduce<RP, RP, 32>(s, lane);
-        const int b = j & 1;
-        if ((lane & (kWave / RP - 1)) == 0) red[b][wave][lane >> (6 - LG)] = s[0];
-        __syncthreads();
-  #pragma unroll
-        for (int k = 0; k < RP; ++k) {
-          float t = 0.0f;
-  #pragma unroll
-          for (int wv = 0; wv < NW; ++wv) t += red[b][wv][k];
-          s[k] = t;
-        }
-        const float nrm2 = s[j];
-        const float inv = (nrm2 > FLT_MIN) ? 1.0f / sqrtf(nrm2) : 0.0f;
-  #pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-          const float qv = v[i][j] * inv;
-          v[i][j] = qv;
-  #pragma unroll
-          for (int k = j + 1; k < RP; ++k) v[i][k] = fmaf(-(s[k] * inv), qv, v[i][k]);
-        }
+      for (int i = 0; i < RPT; ++i) {
+        const float qv = v[i][j] * inv;
+        v[i][j] = qv;
+#pragma unroll
+        for (int k = j + 1; k < RP; ++k) v[i][k] = fmaf(-(s[k] * inv), qv, v[i][k]);
       }
     }
   }
@@ -757,6 +635,153 @@ __global__ __launch_bounds__(BS) void orth_reg_kernel(DevArgs a) {
     float m = redmax[0];
 #pragma unroll
     for (int wv = 1; wv < NW; ++wv) m = fmaxf(m, redmax[wv]);
+    a.scaleP[(size_t)worker * a.L + layer] = m;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// orth, one workgroup per (layer, worker), columns on lanes: lane (g, k) of a
+// wavefront holds RPT rows of column k (C columns, 64 / C groups of rows), so a
+// column's products with all later ones are RPT multiply-adds per lane and no
+// sum over lanes at all: the column goes round its wavefront through LDS (its
+// lane writes, all read the same words), the groups and wavefronts add up one
+// value per column.  What bounds a column is this chain of LDS round trips and
+// the one barrier; with rows on lanes (orth_reg_kernel) it is a butterfly over
+// up to 64 values.  The loop over the columns is rolled: no register index
+// depends on it, and the code stays a few KB at any rank (a workgroup runs it
+// once).
+// Before and after (rows on lanes, or in memory where the rows did not fit the
+// registers): ResNet-18 set 8.6 -> 7.4 us at r = 4, 12.4 -> 10.1 at r = 7, 35 ->
+// 19 at r = 16, 61 -> 39 at r = 32, 164 -> 85 at r = 50; 1000 rows at r = 20 424
+// -> 37 us, at r = 64 5.2 -> 0.22 ms.  More wavefronts with fewer rows each do
+// better up to 16 (r = 32: 38.6 us with 16 x 16 rows, 40.6 with 8 x 32); lane
+// reads instead of LDS for the column cost more (r = 50: 106 against 96 us).
+// ---------------------------------------------------------------------------
+template <int C, int RPT, int NW>
+__global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
+  constexpr int G = kWave / C;
+  constexpr int PS = NW + 4;                     // pitch of a column's partials: 16-byte reads of 16 lanes hit all banks once
+  __shared__ __attribute__((aligned(16))) float bc[NW][G][RPT];
+  __shared__ __attribute__((aligned(16))) float part[2][C][PS];
+  __shared__ float redmax[NW];
+  const int lw = blockIdx.x;
+  const int layer = lw / a.W, worker = lw - layer * a.W;
+  const LayerDesc& ld = a.layers[layer];
+  const int rows = ld.rows, r = ld.r, nseg = a.orth_shared ? 1 : ld.nseg;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int k = lane & (C - 1), g = lane / C;
+  const float* Pp = a.Ppart + (size_t)worker * a.ppart_stride + (a.orth_shared ? ld.p_off : ld.ppart_off);
+  float* pre = a.Ppre + (size_t)worker * a.p_stride + ld.p_off;
+  float* orth = a.Porth + (size_t)worker * a.p_stride + ld.p_off;
+  const int row0 = wave * G + g;                 // this lane's rows: row0, row0 + NW G, ...
+  const bool col = k < r;
+
+  float v[RPT];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) v[i] = 0.0f;
+  // elements beyond the factor re-read its first one; they count as zeros from here on
+  for (int s = 0; s < nseg; ++s) {
+    const float* src = Pp + (size_t)s * ld.np_pad;
+    constexpr int CH = RPT < 16 ? RPT : 16;      // loads in flight
+#pragma unroll
+    for (int i0 = 0; i0 < RPT; i0 += CH) {
+      float t[CH];
+#pragma unroll
+      for (int i = 0; i < CH; ++i) {
+        const int row = row0 + (i0 + i) * (NW * G);
+        t[i] = src[(col && row < rows) ? row * r + k : 0];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < CH; ++i) v[i0 + i] += t[i];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int row = row0 + i * (NW * G);
+    if (col && row < rows) pre[row * r + k] = v[i];
+    else v[i] = 0.0f;
+  }
+
+  for (int j = 0; j < r; ++j) {
+    constexpr bool KEEP = NW <= 8 || RPT <= 32;  // the column stays in registers between its two uses, or is read twice
+    float4* mine = reinterpret_cast<float4*>(bc[wave][g]);
+    if (k == j) {
+#pragma unroll
+      for (int i = 0; i < RPT / 4; ++i) mine[i] = make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // DS operations of a wavefront stay in order
+    __builtin_amdgcn_wave_barrier();
+    auto fetch = [&](int i, float (&t)[4]) __attribute__((always_inline)) {
+      const float4 x = mine[i];
+      t[0] = x.x; t[1] = x.y; t[2] = x.z; t[3] = x.w;
+    };
+    float b[KEEP ? RPT / 4 : 1][4];
+    float s4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < RPT / 4; ++i) {
+      float t[4];
+      fetch(i, t);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s4[e] = fmaf(t[e], v[4 * i + e], s4[e]);
+        if constexpr (KEEP) b[i][e] = t[e];
+      }
+    }
+    float s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+#pragma unroll
+    for (int off = C; off < kWave; off <<= 1) s += __shfl_xor(s, off, kWave);
+    float* mypart = part[j & 1][k];
+    if (g == 0) mypart[wave] = s;
+    __syncthreads();
+    s = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; w += 4) {
+      const float4 t = *reinterpret_cast<const float4*>(mypart + w);
+      s += (t.x + t.y) + (t.z + t.w);
+    }
+    const float nrm2 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(s), j));
+    // 1 / sqrt: the hardware's, one Newton step (every wavefront does this: the correctly rounded root and
+    // quotient are forty instructions)
+    float inv = __builtin_amdgcn_rsqf(nrm2);
+    inv = fmaf(0.5f * inv, fmaf(-(nrm2 * inv), inv, 1.0f), inv);
+    if (!(nrm2 > FLT_MIN)) inv = 0.0f;
+    const float f = -(s * inv) * inv;
+    if (k > j) {
+#pragma unroll
+      for (int i = 0; i < RPT / 4; ++i) {
+        float t[4];
+        if constexpr (KEEP) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) t[e] = b[i][e];
+        } else {
+          fetch(i, t);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * i + e] = fmaf(f, t[e], v[4 * i + e]);
+      }
+    } else if (k == j) {
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) v[i] *= inv;
+    }
+  }
+
+  float mx = 0.0f;
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int row = row0 + i * (NW * G);
+    if (col && row < rows) {
+      orth[row * r + k] = v[i];
+      mx = fmaxf(mx, fabsf(v[i]));
+    }
+  }
+  mx = wave_max(mx);
+  if (lane == 0) redmax[wave] = mx;
+  __syncthreads();
+  if (tid == 0 && !a.orth_shared) {
+    float m = redmax[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m = fmaxf(m, redmax[w]);
     a.scaleP[(size_t)worker * a.L + layer] = m;
   }
 }
@@ -2739,17 +2764,41 @@ hipError_t launch_add_project(int rp, const DevArgs& a, const Tile* tiles, int n
 #endif
 
 #if LQSGD_HAS(4)
-// Register-resident Gram-Schmidt where rows-per-lane x rank fits the register
-// file comfortably; the in-memory kernel otherwise.
-template <int RP, int RPT, int BS>
-void launch_orth_reg(const DevArgs& a, dim3 grid, hipStream_t s) {
-  if constexpr (RP * RPT <= (BS == 256 ? (RPT == 2 ? 128 : 64) : 48)) {
-    orth_reg_kernel<RP, RPT, BS><<<grid, dim3(BS), 0, s>>>(a);
-    note_kernel("orth_reg_kernel<%d, %d, %d>", RP, RPT, BS);
-  } else {
-    orth_kernel<RP><<<grid, dim3(256), 0, s>>>(a);
-    note_kernel("orth_kernel<%d>", RP);
+// Rows on lanes, rank pads 1 and 2.
+template <int RP>
+bool launch_orth_reg(const DevArgs& a, int max_rows, dim3 grid, hipStream_t s) {
+#define LQSGD_LAUNCH_OR(RPT, BS)                                  \
+  if (max_rows <= (RPT) * (BS)) {                                 \
+    orth_reg_kernel<RP, RPT, BS><<<grid, dim3(BS), 0, s>>>(a);    \
+    note_kernel("orth_reg_kernel<%d, %d, %d>", RP, RPT, BS);      \
+    return true;                                                  \
   }
+  LQSGD_LAUNCH_OR(2, 256)
+  LQSGD_LAUNCH_OR(8, 256)
+  LQSGD_LAUNCH_OR(4, 1024)
+  LQSGD_LAUNCH_OR(11, 1024)
+#undef LQSGD_LAUNCH_OR
+  return false;
+}
+
+// Columns on lanes: workgroups of up to 16 wavefronts with up to 64 rows per lane.
+template <int C>
+bool launch_orth_col(const DevArgs& a, int max_rows, dim3 grid, hipStream_t s) {
+  constexpr int G = kWave / C;
+#define LQSGD_LAUNCH_OC(RPT, NW)                                       \
+  if (max_rows <= (RPT) * (NW) * G) {                                  \
+    orth_col_kernel<C, RPT, NW><<<grid, dim3(64 * (NW)), 0, s>>>(a);   \
+    note_kernel("orth_col_kernel<%d, %d, %d>", C, RPT, NW);            \
+    return true;                                                       \
+  }
+  LQSGD_LAUNCH_OC(8, 4)
+  LQSGD_LAUNCH_OC(8, 8)
+  LQSGD_LAUNCH_OC(16, 8)
+  LQSGD_LAUNCH_OC(16, 16)
+  LQSGD_LAUNCH_OC(32, 16)
+  LQSGD_LAUNCH_OC(64, 16)
+#undef LQSGD_LAUNCH_OC
+  return false;
 }
 
 // One cooperative launch if every workgroup of the grid can be resident at once; returns false
@@ -2900,10 +2949,9 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, Coo
   const dim3 grid(a.L * a.W);
   const int nslice = (max_rows + 255) / 256;
   // Tall factors and too few (layer, worker) pairs to fill 256 CUs with one workgroup
-  // each, or no register-resident variant for this rank: one launch per column.
-  const bool reg_fits = (max_rows <= 512 && rp * 2 <= 128) || (max_rows <= 2048 && rp * 8 <= 64) ||
-                        (max_rows <= 4096 && rp * 4 <= 48) || (max_rows <= 11264 && rp * 11 <= 48);
-  if (a.orth_part && nslice >= 8 && ((int)grid.x < 128 || !reg_fits)) {
+  // each, or more rows than one workgroup holds: many workgroups per factor.
+  const bool fits = max_rows <= (rp <= 2 ? 11264 : 65536 / rp);
+  if (a.orth_part && (!fits || (nslice >= 8 && (int)grid.x < 128))) {
 #ifdef LQSGD_TUNING
     static const bool chol = [] { const char* e = std::getenv("LQSGD_ORTH_CHOL"); return !(e && e[0] == '0'); }();
 #else
@@ -2912,6 +2960,7 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, Coo
     if (chol && rp >= 8 && a.chol_part && a.chol_redo) {
       return launch_orth_chol(rp, nslice, max_rank, a, (int)grid.x * nslice, coop, s);
     }
+    // (no Cholesky-QR buffers, or a pad below 8)
     if (launch_orth_coop(rp, nslice, max_rank, a, (int)grid.x * nslice, coop, s)) return hipSuccess;
     for (int j = 0; j <= max_rank; ++j) {
       LQSGD_RP_SWITCH_ORTH(rp, (orth_wide_kernel<RP><<<dim3(grid.x * nslice), dim3(256), 0, s>>>(a, j, nslice, nullptr)));
@@ -2919,18 +2968,18 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, Coo
     note_kernel("orth_wide_kernel<%d> x %d launches", rp, max_rank + 1);
     return hipGetLastError();
   }
-  if (max_rows <= 512) {
-    LQSGD_RP_SWITCH_ORTH(rp, (launch_orth_reg<RP, 2, 256>(a, grid, s)));
-  } else if (max_rows <= 2048) {
-    LQSGD_RP_SWITCH_ORTH(rp, (launch_orth_reg<RP, 8, 256>(a, grid, s)));
-  } else if (max_rows <= 4096) {
-    LQSGD_RP_SWITCH_ORTH(rp, (launch_orth_reg<RP, 4, 1024>(a, grid, s)));
-  } else if (max_rows <= 11264) {
-    LQSGD_RP_SWITCH_ORTH(rp, (launch_orth_reg<RP, 11, 1024>(a, grid, s)));
-  } else {
-    LQSGD_RP_SWITCH_ORTH(rp, (orth_kernel<RP><<<grid, dim3(256), 0, s>>>(a)));
-    note_kernel("orth_kernel<%d>", rp);
+  bool done = false;
+  switch (rp) {
+    case 1: done = launch_orth_reg<1>(a, max_rows, grid, s); break;
+    case 2: done = launch_orth_reg<2>(a, max_rows, grid, s); break;
+    case 4: done = launch_orth_col<4>(a, max_rows, grid, s); break;
+    case 8: done = launch_orth_col<8>(a, max_rows, grid, s); break;
+    case 16: done = launch_orth_col<16>(a, max_rows, grid, s); break;
+    case 32: done = launch_orth_col<32>(a, max_rows, grid, s); break;
+    case 64: done = launch_orth_col<64>(a, max_rows, grid, s); break;
+    default: return hipErrorInvalidValue;
   }
+  if (!done) return hipErrorInvalidValue;        // (without slices' buffers: a caller this library does not have)
   return hipGetLastError();
 }
 #endif

@@ -99,3 +99,27 @@ def test_ragged_bf16_gradients(rank):
         comp.close()
     for a, b in zip(*res):
         assert np.array_equal(a, b)
+
+
+# heights at the edges of the one-workgroup Gram-Schmidt's forms (rows per lane x wavefronts x groups of rows), and the
+# first heights beyond them
+ORTH = [(3, (33, 512, 513, 1025)), (8, (257, 512, 1024)), (12, (128, 129, 513)), (16, (256, 1025)),
+        (20, (64, 65, 1024)), (32, (129, 512, 513, 1500)), (50, (128, 257)), (64, (256, 513, 1024, 1025, 1500))]
+
+
+@pytest.mark.parametrize("rank,rows", [(r, n) for r, heights in ORTH for n in heights])
+def test_gram_schmidt_heights(rank, rows):
+    _say("case: Gram-Schmidt", rank, rows)
+    rng = np.random.default_rng(rank * 7919 + rows)
+    layers, W = [(rows, 140), (2 * rank + 1, 160)], 2
+    comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, W)
+    Q = [rng.standard_normal((c, min(rank, r, c))).astype(f32) for r, c in layers]
+    for l, q in enumerate(Q):
+        comp.set_q(l, q)
+    E = [[np.zeros(s, f32) for s in layers] for _ in range(W)]
+    rep = pu.StageReport()
+    G = [[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)]
+    pu.staged_iteration(comp, G, pu.to_device(G), E, Q, [0, 1], rep)
+    _say("  ", comp.launched_kernel(B.KERNEL_ORTH), rep)
+    assert comp.launched_kernel(B.KERNEL_ORTH).startswith("orth_chol" if rank > 32 and rows > 1024 else "orth_col")
+    comp.close()
