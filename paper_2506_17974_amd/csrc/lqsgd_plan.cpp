@@ -162,7 +162,9 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
     d.segw = (int32_t)round_up((d.cols + nseg - 1) / nseg, cw);
     d.nseg = (d.cols + d.segw - 1) / d.segw;
     const int rowgrp = mfma_a ? 32 : kRowsPerGroup;      // a matrix-core item is one 32-row tile
-    const int64_t seg_elems = (int64_t)rowgrp * std::min(d.segw, d.cols);
+    // (counted in whole passes of 256 columns: a row of 21 costs a pass like one of 256, and a wavefront that takes a dozen
+    // groups of such rows one after the other is what a small set waits for: 1210 x 21 at r = 7, 60 -> 14 us)
+    const int64_t seg_elems = (int64_t)rowgrp * std::min<int64_t>(d.segw, round_up(d.cols, cw));
     int64_t ng = mfma_a ? 1 : std::max<int64_t>(1, (tgtA + seg_elems / 2) / seg_elems);
     const int32_t trows = (int32_t)std::min<int64_t>(round_up(d.rows, rowgrp), ng * rowgrp);
 
