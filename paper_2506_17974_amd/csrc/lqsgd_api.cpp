@@ -431,6 +431,10 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
     if (const char* f = std::getenv("LQSGD_FLIP")) c->flip = (f[0] != '0');
 #endif
   }
+  // The estimate of a code is off by the rounding of 1 + alpha u and of log2 (about 2e-7 together, near 1) times qscale:
+  // below 0.01 levels from alpha = 1/16 up.  Up to 2^40 the first threshold lies above 2^-47, far from where the
+  // quotient's remainder could underflow.  Outside, the quantiser divides and walks.
+  a.quant_fast = p.cfg.alpha >= 0.0625f && p.cfg.alpha <= 0x1p40f ? 1 : 0;
   a.qscale_p = (float)(((1 << p.cfg.bits_p) - 1) / std::log2(1.0 + (double)p.cfg.alpha));
   a.qscale_q = (float)(((1 << p.cfg.bits_q) - 1) / std::log2(1.0 + (double)p.cfg.alpha));
   a.m_stride = p.m_stride; a.p_stride = p.p_stride; a.q_stride = p.q_stride;

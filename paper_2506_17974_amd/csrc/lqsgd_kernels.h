@@ -41,6 +41,7 @@ struct DevArgs {
   int32_t rank_pad;            // Plan::RP
   int32_t padded;              // Plan::padded: Pop / Qop are copies, written by the exchange beside Pbar / Qbar
   float alpha;                 // log scale of Eq. (5)
+  int32_t quant_fast;          // alpha is such that the hardware log2 finds a code to within one level
   float qscale_p, qscale_q;    // (2^b - 1) / log2(1 + alpha) for b_p, b_q
   int32_t agg_first;           // aggregate-first order: scaleP is an atomic-max accumulator (sweep 0 zeroes it)
   int32_t orth_shared;         // the Gram-Schmidt kernels run once per layer, in place on the plane at Ppart + p_off

@@ -486,51 +486,65 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, LQSGD_A_
 // output, and by the sweeps that dequantise packets themselves).
 // The code of u = |x|/s is the number of decision thresholds <= u, i.e.
 // nearest-level rounding in the q-domain of Eq. (5): a hardware log2 gives the
-// level to within one, the two loops move it to the exact count.
+// level, and the thresholds on its two sides move it to the exact count.
 // ---------------------------------------------------------------------------
+// s_thr points at threshold 0; s_thr[-1] and s_thr[lv] are NaN, which no comparison holds for.
+// ONESTEP: the estimate is known to be within one level (DevArgs::quant_fast), else it is walked all the way.
+template <bool ONESTEP>
 __device__ __forceinline__ int quantise_one(float u, float alpha, float qscale, int lv, const float* s_thr) {
   const float t = __log2f(fmaf(alpha, u, 1.0f)) * qscale;
   int k = (int)(t + 0.5f);
   k = max(0, min(lv, k));
-  while (k < lv && s_thr[k] <= u) ++k;
-  while (k > 0 && s_thr[k - 1] > u) --k;
+  if constexpr (ONESTEP) {
+    const float below = s_thr[k - 1], above = s_thr[k];
+    k += (above <= u ? 1 : 0) - (below > u ? 1 : 0);
+  } else {
+    while (k < lv && s_thr[k] <= u) ++k;
+    while (k > 0 && s_thr[k - 1] > u) --k;
+  }
   return k;
 }
 
 // One group of kXGroup consecutive factor elements of one worker: LogQuantize against the worker's
 // absmax s (codes: number of thresholds <= |x| / s; sign bit only on a non-zero code), the packed
-// group (`bits` magnitude bytes, one sign byte) stored if STORE, and the dequantised values
-// (Eq. (6): +-s level_k) in val.
-template <bool STORE>
+// group (`bits` magnitude bytes, one sign byte) stored, and the dequantised values (Eq. (6): +-s level_k) in val.
+// FAST: the estimate of a code is within one level (ONESTEP above), and the quotient comes from the reciprocal of s, taken once,
+// and a remainder step (Markstein, "Computation of elementary functions on the IBM RISC System/6000", 1990: correctly
+// rounded like the division it replaces, given a correctly rounded reciprocal and no under- or overflow: s_fast).
+template <bool FAST>
 __device__ __forceinline__ void quantise_group(const float (&x)[kXGroup], float s, int bits, int lv, float alpha, float qscale,
                                                const float* s_thr, const float* s_lev, uint8_t* mp, uint8_t* sp,
                                                float (&val)[kXGroup]) {
   unsigned long long magbits = 0;
   unsigned sgnbits = 0;
+  const float rs = 1.0f / s;
 #pragma unroll
   for (int i = 0; i < kXGroup; ++i) {
-    const int k = (s > 0.0f) ? quantise_one(fabsf(x[i]) / s, alpha, qscale, lv, s_thr) : 0;
-    magbits |= (unsigned long long)k << (i * bits);
-    if (x[i] < 0.0f && k > 0) sgnbits |= 1u << i;
-  }
-  if constexpr (STORE) {
-    if (bits == 8) {
-      *reinterpret_cast<unsigned long long*>(mp) = magbits;
-    } else if (bits == 4) {
-      *reinterpret_cast<unsigned*>(mp) = (unsigned)magbits;
-    } else if (bits == 2) {
-      *reinterpret_cast<unsigned short*>(mp) = (unsigned short)magbits;
+    const float ax = fabsf(x[i]);
+    float u;
+    if constexpr (FAST) {
+      const float q = ax * rs;
+      u = fmaf(fmaf(-q, s, ax), rs, q);
     } else {
-      for (int bb = 0; bb < bits; ++bb) mp[bb] = (uint8_t)(magbits >> (8 * bb));
+      u = ax / s;
     }
-    *sp = (uint8_t)sgnbits;
-  }
-#pragma unroll
-  for (int i = 0; i < kXGroup; ++i) {
-    const int k = (int)((magbits >> (i * bits)) & (unsigned long long)lv);
+    const int k = (s > 0.0f) ? quantise_one<FAST>(u, alpha, qscale, lv, s_thr) : 0;
+    magbits |= (unsigned long long)k << (i * bits);
+    const bool neg = x[i] < 0.0f && k > 0;
+    if (neg) sgnbits |= 1u << i;
     const float v = s * s_lev[k];
-    val[i] = ((sgnbits >> i) & 1u) ? -v : v;
+    val[i] = neg ? -v : v;
   }
+  if (bits == 8) {
+    *reinterpret_cast<unsigned long long*>(mp) = magbits;
+  } else if (bits == 4) {
+    *reinterpret_cast<unsigned*>(mp) = (unsigned)magbits;
+  } else if (bits == 2) {
+    *reinterpret_cast<unsigned short*>(mp) = (unsigned short)magbits;
+  } else {
+    for (int bb = 0; bb < bits; ++bb) mp[bb] = (uint8_t)(magbits >> (8 * bb));
+  }
+  *sp = (uint8_t)sgnbits;
 }
 
 // ---------------------------------------------------------------------------
@@ -1076,32 +1090,31 @@ __global__ __launch_bounds__(256) void orth_coop_kernel(DevArgs a, int nslice_ma
 //   kFused:     factors -> packets and mean in one pass
 // A workgroup takes kXBlockGroups groups of 8 consecutive factor elements; a
 // lane handles one (group, worker) pair -- b magnitude bytes + 1 sign byte --
-// eight workers at a time; the dequantised values meet in LDS, where lane
-// (group, j) adds up element j over the workers in worker order.
-// The code of u = |x|/s is the number of decision thresholds <= u, i.e.
-// nearest-level rounding in the q-domain of Eq. (5): a hardware log2 gives the
-// level to within one, the two loops move it to the exact count.
+// eight workers at a time; the dequantised values meet in LDS, where thread e
+// adds up element e of the workgroup's 256 over the workers in worker order.
+// What bounds it at high ranks is the quantiser's arithmetic (see quantise_group).
 // ---------------------------------------------------------------------------
 template <int MODE>
 __global__ __launch_bounds__(256) void exchange_kernel(DevArgs a, const XTile* __restrict__ tiles, int phase) {
-  __shared__ float s_thr[256];
+  __shared__ float s_tab[258];                         // thresholds, NaN before and after them
   __shared__ float s_lev[256];
-  __shared__ float s_val[8][kXGroup][kXBlockGroups];   // [worker slot][element][group]
+  __shared__ __attribute__((aligned(16))) float s_val[8][kXGroup * kXBlockGroups];   // [worker slot][element]
   const int bits = phase ? a.bits_q : a.bits_p;
   const int lv = (1 << bits) - 1;
   const int tid = threadIdx.x;
   if (bits > 0) {
     const float* thr = phase ? a.thrQ : a.thrP;
     const float* lev = phase ? a.levQ : a.levP;
-    if (tid < lv) s_thr[tid] = thr[tid];
+    if (tid < lv) s_tab[1 + tid] = thr[tid];
     if (tid <= lv) s_lev[tid] = lev[tid];
+    if (tid < 2) s_tab[tid * (lv + 1)] = __uint_as_float(0x7fc00000u);
   }
   __syncthreads();
   const XTile tl = tiles[blockIdx.x];
   const LayerDesc& ld = a.layers[tl.layer];
   const int n_el = phase ? ld.nq_el : ld.np_el;
   const int gl = tid & (kXBlockGroups - 1);
-  const int slot = tid / kXBlockGroups;            // worker slot, and the element this lane sums
+  const int slot = tid / kXBlockGroups;            // worker slot
   const int g = tl.grp0 + gl;
   const int e0 = g * kXGroup;
   const bool gvalid = e0 < n_el;
@@ -1138,8 +1151,13 @@ __global__ __launch_bounds__(256) void exchange_kernel(DevArgs a, const XTile* _
       } else {
         const float s = scale[(size_t)w * a.L + tl.layer];
         if (MODE != kMeanOnly) {
-          quantise_group<true>(x, s, bits, lv, a.alpha, qscale, s_thr, s_lev, mag + (size_t)w * mstride,
-                               sgn + (size_t)w * sstride, val);
+          uint8_t* mp = mag + (size_t)w * mstride;
+          uint8_t* sp = sgn + (size_t)w * sstride;
+          // (s between 2^-60 and 2^60: neither the reciprocal nor a remainder that matters leaves the normal range)
+          if (a.quant_fast && s > 0x1p-60f && s < 0x1p60f)
+            quantise_group<true>(x, s, bits, lv, a.alpha, qscale, s_tab + 1, s_lev, mp, sp, val);
+          else
+            quantise_group<false>(x, s, bits, lv, a.alpha, qscale, s_tab + 1, s_lev, mp, sp, val);
         } else {
           unsigned long long magbits = 0;
           const uint8_t* mp = mag + (size_t)w * mstride;
@@ -1155,23 +1173,24 @@ __global__ __launch_bounds__(256) void exchange_kernel(DevArgs a, const XTile* _
       }
     }
     if (MODE != kQuantOnly) {
-#pragma unroll
-      for (int i = 0; i < kXGroup; ++i) s_val[slot][i][gl] = val[i];
+      float4* mine = reinterpret_cast<float4*>(s_val[slot] + gl * kXGroup);
+      mine[0] = make_float4(val[0], val[1], val[2], val[3]);
+      mine[1] = make_float4(val[4], val[5], val[6], val[7]);
       __syncthreads();
       const int nw = min(8, a.W - wbase);
-      for (int sidx = 0; sidx < nw; ++sidx) acc += s_val[sidx][slot][gl];
+      for (int sidx = 0; sidx < nw; ++sidx) acc += s_val[sidx][tid];
       __syncthreads();
     }
   }
   if (MODE != kQuantOnly) {
-    if (gvalid && slot < nvalid) {
-      float* out = (phase ? a.Qbar + ld.q_off : a.Pbar + ld.p_off) + e0;
+    const int e = tl.grp0 * kXGroup + tid;       // a workgroup's elements are consecutive, one per thread
+    if (e < n_el) {
       const float mean = acc / (float)a.W;
-      out[slot] = mean;
+      (phase ? a.Qbar + ld.q_off : a.Pbar + ld.p_off)[e] = mean;
       if (a.padded) {    // the sweeps' copy with rows of rank_pad ranks
-        const unsigned e = (unsigned)(e0 + slot), row = e / (unsigned)ld.r;
+        const unsigned row = (unsigned)e / (unsigned)ld.r;
         float* pad = phase ? a.Qop + ld.qop_off : a.Pop + ld.pop_off;
-        pad[(size_t)row * a.rank_pad + (e - row * (unsigned)ld.r)] = mean;
+        pad[(size_t)row * a.rank_pad + ((unsigned)e - row * (unsigned)ld.r)] = mean;
       }
     }
   }

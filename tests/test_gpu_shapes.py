@@ -123,3 +123,35 @@ def test_gram_schmidt_heights(rank, rows):
     _say("  ", comp.launched_kernel(B.KERNEL_ORTH), rep)
     assert comp.launched_kernel(B.KERNEL_ORTH).startswith("orth_chol" if rank > 32 and rows > 1024 else "orth_col")
     comp.close()
+
+
+@pytest.mark.parametrize("alpha", [1e-3, 0.0625, 1.0, 255.0, 1e6])
+@pytest.mark.parametrize("scale", [1e-3, 3e-20, 1e17])      # (squares of factor columns stay in the range of floats: 1e-35 .. 1e38)
+def test_quantiser_ranges(alpha, scale):
+    """Codes on both sides of the quantiser's fast form: estimates further than a level away (small alpha) and factors
+    whose absmax is far from one, where a reciprocal or a remainder could leave the normal range (Q_w carries the
+    gradients' scale; P_w is orthonormal)."""
+    _say("case: quantiser", alpha, scale)
+    rng = np.random.default_rng(17)
+    layers, W, rank = [(96, 130), (64, 27)], 3, 5
+    for bits in (8, 3):
+        comp = B.Compressor(B.layer_list(layers, ()), rank, bits, bits, W, alpha)
+        Q = [rng.standard_normal((c, rank)).astype(f32) for r, c in layers]
+        for l, q in enumerate(Q):
+            comp.set_q(l, q)
+        G = [[(rng.standard_normal(s) * scale).astype(f32) for s in layers] for _ in range(W)]
+        comp.step(pu.to_device(G))
+        comp.synchronize()
+        for phase, factor in ((B.PHASE_P, B.FACTOR_P_ORTH), (B.PHASE_Q, B.FACTOR_Q_W)):
+            for l in range(len(layers)):
+                for w in range(W):
+                    x = comp.get_factor(factor, l, w)
+                    k, s, sc = comp.get_packet(phase, l, w)
+                    assert sc == np.abs(x).max() and sc > 0
+                    u = (np.abs(x) / sc).astype(f32)                     # correctly rounded, as the device's
+                    lv = (1 << bits) - 1
+                    thr = (np.expm1((np.arange(lv) + 0.5) / lv * np.log1p(float(f32(alpha)))) / float(f32(alpha))).astype(f32)
+                    want = np.searchsorted(thr, u, side="right")         # thresholds <= u
+                    assert np.array_equal(k, want), np.abs(k.astype(int) - want).max()
+                    assert np.array_equal(s.astype(bool), (x < 0) & (want > 0))
+        comp.close()
