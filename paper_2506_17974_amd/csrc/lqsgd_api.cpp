@@ -51,7 +51,7 @@ struct lqsgd_ctx {
   size_t arena_cap = 0, arena_used = 0;
   DevArgs args{};
   // device copies of the work lists
-  Tile* d_tilesA = nullptr; Tile* d_tilesB = nullptr; Tile* d_tilesG = nullptr; Tile* d_tilesBM = nullptr; Tile* d_tilesAG = nullptr;
+  Tile* d_tilesA = nullptr; Tile* d_tilesB = nullptr; Tile* d_tilesG = nullptr; Tile* d_tilesBM = nullptr; Tile* d_tilesAG = nullptr; Tile* d_tilesR = nullptr;
   XTile* d_tilesXP = nullptr; XTile* d_tilesXQ = nullptr;
   RTile* d_tilesRQ = nullptr; RTile* d_tilesRP = nullptr; VTile* d_tilesV = nullptr;
   // pointer tables
@@ -277,12 +277,14 @@ int run_sweep1(lqsgd_ctx* c, bool with_vectors) {
 // when asked for, is then written by a pass of its own over the layers.
 int run_sweep2(lqsgd_ctx* c, bool write_ghat) {
   const Plan& p = c->plan;
+  const Tile* res = c->d_tilesR ? c->d_tilesR : c->d_tilesB;
+  const int n_res = (int)(c->d_tilesR ? p.tilesR.size() : p.tilesB.size());
   Timed t(c, LQSGD_KERNEL_RESIDUAL);
   if (c->eager) {
     if (p.mfma_a)
       HIP_TRY(c, launch_mfma_sweep(p.RP, write_ghat ? 3 : 2, c->args, c->d_tilesA, (int)p.tilesA.size(), next_dir(c), c->stream));
     else
-      HIP_TRY(c, launch_residual(p.RP, write_ghat ? 1 : 0, c->args, c->d_tilesB, (int)p.tilesB.size(), next_dir(c), c->stream));
+      HIP_TRY(c, launch_residual(p.RP, write_ghat ? 1 : 0, c->args, res, n_res, next_dir(c), c->stream));
   } else {
     if (write_ghat) {
       if (p.mfma_a)
@@ -298,11 +300,13 @@ int run_sweep2(lqsgd_ctx* c, bool write_ghat) {
 int materialise(lqsgd_ctx* c) {
   if (!c->pending) return LQSGD_OK;
   const Plan& p = c->plan;
+  const Tile* res = c->d_tilesR ? c->d_tilesR : c->d_tilesB;
+  const int n_res = (int)(c->d_tilesR ? p.tilesR.size() : p.tilesB.size());
   Timed t(c, LQSGD_KERNEL_RESIDUAL);
   if (p.mfma_a)
     HIP_TRY(c, launch_mfma_sweep(p.RP, 2, c->args, c->d_tilesA, (int)p.tilesA.size(), next_dir(c), c->stream));
   else
-    HIP_TRY(c, launch_residual(p.RP, 0, c->args, c->d_tilesB, (int)p.tilesB.size(), next_dir(c), c->stream));
+    HIP_TRY(c, launch_residual(p.RP, 0, c->args, res, n_res, next_dir(c), c->stream));
   c->pending = false;
   return LQSGD_OK;
 }
@@ -357,7 +361,7 @@ int lqsgd_plan_query(const lqsgd_config* cfg, const lqsgd_layer* layers, int32_t
   out->rank_pad = p.RP;
   out->tiles[0] = (int32_t)p.tilesA.size();
   out->tiles[1] = (int32_t)(p.mfma ? p.tilesBM.size() : p.tilesB.size());
-  out->tiles[2] = (int32_t)(p.mfma_a ? p.tilesA.size() : p.tilesB.size());
+  out->tiles[2] = (int32_t)(p.mfma_a ? p.tilesA.size() : p.tilesR.size());
   out->residual_stride = p.m_stride;
   out->warm_q_floats = p.q_stride + kFactorSlack;
   return LQSGD_OK;
@@ -372,7 +376,7 @@ int64_t lqsgd_plan_tiles(const lqsgd_config* cfg, const lqsgd_layer* layers, int
   const bool bm = sweep == 1 && p.mfma;
   const bool as0 = sweep == 0 || (sweep >= 2 && p.mfma_a);     // items of sweep 0's kind
   const std::vector<Tile>& tl = sweep == 3 ? (p.mfma_a ? p.tilesAG : p.tilesG)
-                                           : as0 ? p.tilesA : (bm ? p.tilesBM : p.tilesB);
+                                           : as0 ? p.tilesA : (bm ? p.tilesBM : sweep == 2 ? p.tilesR : p.tilesB);
   if (out) {
     const int64_t n = std::min<int64_t>(cap, (int64_t)tl.size());
     for (int64_t i = 0; i < n; ++i) {
@@ -520,6 +524,8 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   TRY_(dev_upload(c, &c->d_tilesRQ, p.tilesRQ));
   TRY_(dev_upload(c, &c->d_tilesRP, p.tilesRP));
   TRY_(dev_upload(c, &c->d_tilesV, p.tilesV));
+  // (last: in a caller-provided block without room for it the residual sweep takes sweep 1's items, as good in everything but time)
+  if (!p.mfma_a && (!ext || p.tilesR.size() * sizeof(Tile) + 256 <= c->arena_cap - c->arena_used)) TRY_(dev_upload(c, &c->d_tilesR, p.tilesR));
 #undef TRY_
   a.layers = d_layers; a.vecs = d_vecs;
   a.thrP = thrP; a.levP = levP; a.thrQ = thrQ; a.levQ = levQ;

@@ -79,6 +79,9 @@ typedef const float __attribute__((address_space(4)))* const_fp;
 #ifndef LQSGD_BQ_LATE      // matrix-core sweep 0, fused mode: fetch the P product's Q slice after the G-hat part
 #define LQSGD_BQ_LATE 1
 #endif
+#ifndef LQSGD_R_WAVES      // the same for the residual sweep (ResNet-18 set: 141 / 136 / 143 / 142 us at 2 / 3 / 4 / 8; with non-temporal stores 176, with plain loads 147)
+#define LQSGD_R_WAVES 3
+#endif
 #ifndef LQSGD_B_U          // rows a wavefront of sweep 1 has in flight
 #define LQSGD_B_U 8
 #endif
@@ -215,17 +218,23 @@ __device__ __forceinline__ void stgroup(char* rowbase, unsigned boff, int n, con
 // Output of the reconstruction G-hat = P-bar Q-bar^T (Eq. (7)): either stored as it is, or applied
 // to the caller's parameters, w <- w - eta G-hat (Algorithm 1, "Model update"; Eq. (2)).
 template <int KIND>
-__device__ __forceinline__ void emit_ghat(float* __restrict__ rowbase, int c, int cols, Pk<4> gh, int update, float eta) {
+__device__ __forceinline__ void emit_ghat(float* __restrict__ rowbase, int c, int cols, Pk<4> gh, int update, float eta, const Pk<4>& w) {
   char* row = reinterpret_cast<char*>(rowbase);
+  const int n = KIND == kAligned ? 4 : cols - c;
   if (update) {
-    Pk<4> w = ldedge<KIND, false, false>(row, c, cols);
-    if (KIND != kAligned && c + 4 > cols) edge_fix<1>(w.v, c, cols);
 #pragma unroll
     for (int v = 0; v < 4; ++v) gh.v[v] = fmaf(-eta, gh.v[v], w.v[v]);
-    stgroup<false>(row, (unsigned)c * 4u, KIND == kAligned ? 4 : cols - c, gh);
+    stgroup<false>(row, (unsigned)c * 4u, n, gh);
   } else {
-    stgroup<true>(row, (unsigned)c * 4u, KIND == kAligned ? 4 : cols - c, gh);
+    stgroup<true>(row, (unsigned)c * 4u, n, gh);
   }
+}
+// The parameters that emit_ghat updates: fetched well ahead of it, or a row waits for them alone.
+template <int KIND>
+__device__ __forceinline__ Pk<4> load_params(const float* rowbase, int c, int cols) {
+  Pk<4> w = ldedge<KIND, false, false>(reinterpret_cast<const char*>(rowbase), c, cols);
+  if (KIND != kAligned && c + 4 > cols) edge_fix<1>(w.v, c, cols);
+  return w;
 }
 
 // The factors as the sweeps read them: rows of RP ranks, zero beyond a layer's rank.  Where every layer fills the
@@ -352,8 +361,8 @@ __device__ __forceinline__ void add_project_cols(const char* const (&gr)[RT], ch
       e[t] = ldedge<KIND, NTS, false>(mr[t], c, cols);
     }
     // All requests stay ahead of the arithmetic (left to itself the compiler trades loads in flight for
-    // registers: fc 256 x 128 6.8 us against 5.9 us).
-    __builtin_amdgcn_sched_barrier(0);
+    // registers; at ranks 1 and 2 it has them and does better alone).
+    if constexpr (RP >= 4) __builtin_amdgcn_sched_barrier(0);
     if (KIND != kAligned && c + 4 > cols) {
       edge_fix<RP>(q, c, cols);
 #pragma unroll
@@ -1592,10 +1601,16 @@ __device__ __forceinline__ void residual_rows(float* __restrict__ M, const float
         const char* p = reinterpret_cast<const char*>(in + (size_t)(i + min(u, nu - 1)) * cols);
         m[u] = ldedge<KIND, LQSGD_NT_M != 0, false>(p, c, cols);
       }
+      __builtin_amdgcn_sched_barrier(0);
       if (n < 4) {
 #pragma unroll
         for (int u = 0; u < U; ++u) edge_fix<1>(m[u].v, c, cols);
       }
+    }
+    Pk<4> wp[MODE == kResidualGhat ? U : 1];
+    if (MODE == kResidualGhat && ghat && update) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) wp[MODE == kResidualGhat ? u : 0] = load_params<KIND>(ghat + (size_t)(i + min(u, nu - 1)) * cols, c, cols);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -1620,7 +1635,7 @@ __device__ __forceinline__ void residual_rows(float* __restrict__ M, const float
           }
           stgroup<true>(reinterpret_cast<char*>(ghat + (size_t)(i + u) * cols), boff, n, gh);
         } else if (MODE == kResidualGhat && ghat) {
-          emit_ghat<KIND>(ghat + (size_t)(i + u) * cols, c, cols, gh, update, eta);
+          emit_ghat<KIND>(ghat + (size_t)(i + u) * cols, c, cols, gh, update, eta, wp[MODE == kResidualGhat ? u : 0]);
         }
       }
     }
@@ -1645,7 +1660,7 @@ __device__ __forceinline__ void residual_tile(const DevArgs& a, const LayerDesc&
 }
 
 template <int RP, int MODE>
-__global__ __launch_bounds__(256) void residual_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MODE == kGhatOnly ? 8 : LQSGD_R_WAVES))) void residual_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & (kWave - 1);
   const Tile tl = tiles[reverse ? ntiles - 1 - blockIdx.x : blockIdx.x];
@@ -1771,6 +1786,16 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
         }
       }
     }
+    Pk<4> wp[8];                                 // the parameters to update
+    if constexpr (MODE == kMResidualGhat || MODE == kMGhatOnly) {
+      if (update && ghat_out) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          if constexpr (FULL) wp[i] = load_params<kAligned>(ghat_out + (size_t)(row0 + 4 * i) * cols + c, (int)(lo >> 2), 0);
+          else wp[i] = load_params<KIND>(ghat_out + (size_t)(row0 + min(4 * i + sr, nrows - 1)) * cols, cl, cols);
+        }
+      }
+    }
     float bq[NB][32];
     auto load_bq = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -1839,10 +1864,10 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
         if (MODE == kMGhatOnly || (MODE == kMResidualGhat && ghat_out)) {
           if constexpr (FULL) {
             const Pk<4> o{{t.x, t.y, t.z, t.w}};
-            emit_ghat<kAligned>(ghat_out + (size_t)(row0 + 4 * i) * cols + c, (int)(lo >> 2), 0, o, update, eta);
+            emit_ghat<kAligned>(ghat_out + (size_t)(row0 + 4 * i) * cols + c, (int)(lo >> 2), 0, o, update, eta, wp[i]);
           } else if (rr < nrows) {
             const Pk<4> o{{t.x, t.y, t.z, t.w}};
-            if (ncol > 0) emit_ghat<KIND>(ghat_out + (size_t)(row0 + rr) * cols, cl, cols, o, update, eta);
+            if (ncol > 0) emit_ghat<KIND>(ghat_out + (size_t)(row0 + rr) * cols, cl, cols, o, update, eta, wp[i]);
           }
         }
       }

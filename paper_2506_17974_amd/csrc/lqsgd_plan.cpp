@@ -70,7 +70,7 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
   W = c->workers;
   n_all = n_layers;
   layers.clear(); vecs.clear(); kind_of.clear();
-  tilesA.clear(); tilesAG.clear(); tilesB.clear(); tilesBM.clear(); tilesG.clear(); tilesXP.clear(); tilesXQ.clear(); tilesRQ.clear(); tilesRP.clear(); tilesV.clear();
+  tilesA.clear(); tilesAG.clear(); tilesB.clear(); tilesBM.clear(); tilesG.clear(); tilesR.clear(); tilesXP.clear(); tilesXQ.clear(); tilesRQ.clear(); tilesRP.clear(); tilesV.clear();
 
   int max_r = 1;
   max_rows = 0;
@@ -135,6 +135,11 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
   const int64_t total = matrix_elements * W;
   const int64_t tgtA = env_i64("LQSGD_TILE_A", std::min<int64_t>(131072, std::max<int64_t>(2048, total / 49152)));
   const int64_t tgtB = env_i64("LQSGD_TILE_B", std::min<int64_t>(524288, std::max<int64_t>(16384, total / 2730)));   // (floor: small CNN set, sweep 1 17.1 -> 14.7 us against 8192)
+  // The residual sweep has no sums to carry down its columns, so its items are lower than sweep 1's (which take a layer's
+  // whole height where they can): 8 rows per wavefront, more only where the list would pass 131072 items.  With sweep 1's
+  // items a wavefront goes through up to 128 rows in rounds of 8: 240 x 309 .. 1628 x 28, W = 7 44 -> 9 us, ResNet-18 set,
+  // W = 8 136 -> 113 us (115 / 120 / 128 with 16384 / 32768 / 65536 elements).
+  const int64_t tgtR = env_i64("LQSGD_TILE_R", std::min<int64_t>(tgtB, std::max<int64_t>(8192, total / 131072)));
   // the G-hat-only pass covers one worker's worth of elements: smaller items keep its grid wide
   const int64_t tgtG = env_i64("LQSGD_TILE_G", std::min<int64_t>(tgtB, std::max<int64_t>(4096, matrix_elements / 2730)));
   // column segments: at most 1024 columns (2048 at rank pad 32, where fewer, longer segments save
@@ -222,6 +227,12 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
       for (int32_t rb = 0; rb < nrb_v; ++rb)
         for (int32_t ch = 0; ch < nchunk; ++ch)
           tilesB.push_back(Tile{lw, rb * rbb_v, std::min(rbb_v, d.rows - rb * rbb_v), ch});
+      if (!mfma_a) {
+        const int32_t rbr = (int32_t)std::min<int64_t>(round_up(std::max<int64_t>(1, tgtR / cw), 4), round_up(d.rows, 4));
+        for (int32_t row0 = 0; row0 < d.rows; row0 += rbr)
+          for (int32_t ch = 0; ch < nchunk; ++ch)
+            tilesR.push_back(Tile{lw, row0, std::min(rbr, d.rows - row0), ch});
+      }
       if (w == 0) {
         const int32_t rbg = (int32_t)std::min<int64_t>(round_up(std::max<int64_t>(1, tgtG / cw), 4), round_up(d.rows, 4));
         for (int32_t row0 = 0; row0 < d.rows; row0 += rbg)
@@ -262,7 +273,7 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
   }
   v_total = v_acc;
 
-  const int64_t tile_bytes = (int64_t)(tilesA.size() + tilesAG.size() + tilesB.size() + tilesBM.size() + tilesG.size()) * sizeof(Tile) +
+  const int64_t tile_bytes = (int64_t)(tilesA.size() + tilesAG.size() + tilesR.size() + tilesB.size() + tilesBM.size() + tilesG.size()) * sizeof(Tile) +
                              (int64_t)(tilesXP.size() + tilesXQ.size()) * sizeof(XTile) +
                              (int64_t)(tilesRQ.size() + tilesRP.size()) * sizeof(RTile) + (int64_t)tilesV.size() * sizeof(VTile);
   device_bytes = 4 * ((int64_t)W * (m_stride + 2 * p_stride + q_stride + ppart_stride + qpart_stride) +

@@ -72,6 +72,7 @@ struct Plan {
   std::vector<VecDesc> vecs;
   std::vector<int32_t> kind_of;    // per caller index: >= 0 matrix index, < 0 -(vector index) - 1
   std::vector<Tile> tilesA, tilesB;
+  std::vector<Tile> tilesR;        // residual sweep of the vector path: row block x 256 columns, all workers
   std::vector<Tile> tilesAG;       // worker 0's items of tilesA (G-hat pass of the matrix-core path)
   std::vector<Tile> tilesBM;       // sweep 1 on the matrix cores (rank pad >= 16): row block x 128-column group
   std::vector<Tile> tilesG;        // worker 0's items of tilesB: one pass over every layer (G-hat only)
