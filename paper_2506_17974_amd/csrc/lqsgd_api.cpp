@@ -165,6 +165,22 @@ int check_worker(lqsgd_ctx* c, int32_t worker) {
   return LQSGD_OK;
 }
 
+// Copies a pointer list to its device table, which launches already enqueued may still be reading.  Short lists go
+// there in stream order (ResNet-18 set, W = 8, other buffers every step: the wait and the two copies cost 60 us a step);
+// long ones, and any list that changes while the stream is being captured, after a wait, as a captured copy would
+// bring this call's pointers back at every replay.
+int upload_pointers(lqsgd_ctx* c, const void** dst, const void* const* src, size_t n) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusActive; }
+  if (cap == hipStreamCaptureStatusNone && n <= 4 * (size_t)kPointerBatch) {
+    HIP_TRY(c, launch_write_pointers(dst, src, n, c->stream));
+    return LQSGD_OK;
+  }
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  HIP_TRY(c, hipMemcpy(dst, src, n * sizeof(void*), hipMemcpyHostToDevice));
+  return LQSGD_OK;
+}
+
 // Copies the caller's pointer list to the device table when it changed.
 int bind_grads(lqsgd_ctx* c, const float* const* grads) {
   const size_t n = (size_t)c->plan.W * c->plan.n_all;
@@ -173,9 +189,9 @@ int bind_grads(lqsgd_ctx* c, const float* const* grads) {
     if (reinterpret_cast<uintptr_t>(grads[i]) & 15u) return fail(c, LQSGD_EINVAL, "gradient pointer not 16-byte aligned");
   }
   if (c->grads_valid && std::memcmp(c->h_grads.data(), grads, n * sizeof(float*)) == 0) return LQSGD_OK;
-  HIP_TRY(c, hipStreamSynchronize(c->stream));   // the old table may still be in use
+  c->grads_valid = false;
+  if (int rc = upload_pointers(c, reinterpret_cast<const void**>(c->d_grads), reinterpret_cast<const void* const*>(grads), n)) return rc;
   c->h_grads.assign(grads, grads + n);
-  HIP_TRY(c, hipMemcpy(c->d_grads, c->h_grads.data(), n * sizeof(float*), hipMemcpyHostToDevice));
   c->grads_valid = true;
   c->alias_checked = false;
   return LQSGD_OK;
@@ -188,9 +204,9 @@ int bind_ghat(lqsgd_ctx* c, float* const* ghat) {
     if (ghat[i] && (reinterpret_cast<uintptr_t>(ghat[i]) & 15u))
       return fail(c, LQSGD_EINVAL, "G-hat pointer not 16-byte aligned");
   if (!(c->ghat_valid && std::memcmp(c->h_ghat.data(), ghat, n * sizeof(float*)) == 0)) {
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    c->ghat_valid = false;
+    if (int rc = upload_pointers(c, const_cast<const void**>(reinterpret_cast<void**>(c->d_ghat)), reinterpret_cast<const void* const*>(ghat), n)) return rc;
     c->h_ghat.assign(ghat, ghat + n);
-    HIP_TRY(c, hipMemcpy(c->d_ghat, c->h_ghat.data(), n * sizeof(float*), hipMemcpyHostToDevice));
     c->ghat_valid = true;
     c->alias_checked = false;
   }

@@ -106,6 +106,10 @@ hipError_t static_scratch(int device, void** ptr, size_t* bytes);
 // Clears `bytes` (a multiple of 16) at the 16-byte aligned device address p with a kernel.
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 
+// Writes n device pointers to the device table dst, in the order of the stream (kPointerBatch of them per launch).
+constexpr int kPointerBatch = 448;       // 3.5 KB of kernel arguments
+hipError_t launch_write_pointers(const void** dst, const void* const* src, size_t n, hipStream_t s);
+
 hipError_t launch_mfma_sweep(int RP, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s);
 
 }  // namespace lqsgd

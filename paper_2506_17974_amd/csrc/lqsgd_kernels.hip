@@ -3184,6 +3184,25 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Pointers carried in the kernel's arguments, written to the device table in stream order: the table of the launches
+// already enqueued needs no wait, and the copy no staging memory.
+struct PointerBatch { const void* p[kPointerBatch]; };
+__global__ __launch_bounds__(256) void write_pointers_kernel(PointerBatch b, const void** dst, int n) {
+  for (int i = threadIdx.x; i < n; i += 256) dst[i] = b.p[i];
+}
+hipError_t launch_write_pointers(const void** dst, const void* const* src, size_t n, hipStream_t s) {
+  for (size_t i = 0; i < n; i += kPointerBatch) {
+    PointerBatch b;
+    const int m = (int)std::min<size_t>(kPointerBatch, n - i);
+    for (int k = 0; k < m; ++k) b.p[k] = src[i + k];
+    for (int k = m; k < kPointerBatch; ++k) b.p[k] = nullptr;
+    write_pointers_kernel<<<dim3(1), dim3(256), 0, s>>>(b, dst + i, m);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, hipStream_t s) {
   if (a.L <= 0 || !a.padded) return hipSuccess;
   pad_factor_kernel<<<dim3(64, a.L), dim3(256), 0, s>>>(a, RP, which);
