@@ -1759,6 +1759,11 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
     constexpr bool FULL = decltype(full_tag)::value;
     constexpr int KIND = decltype(kind_tag)::value;      // of edge blocks: kRagged (which takes aligned rows too) or kNarrow
     const int cl = c + c4;
+    // Edge blocks: this lane's row number is hidden from the optimiser, which otherwise computes the addresses of all
+    // rows once, ahead of the loop over the blocks, and keeps them in registers that the whole blocks need (rank pad
+    // 16: 92 values spilled, 8192^2 x 8 workers sweep 0 1098 -> 1220 us).
+    int sr_ = sr;
+    if constexpr (!FULL) asm volatile("" : "+v"(sr_));
     const int ncol = FULL ? 4 : cols - cl;       // columns of this lane's group that exist
     Pk<4> g[8], e[8];
     // FULL blocks address memory as a wave-uniform base (scalar registers) plus one byte offset per
@@ -1766,7 +1771,7 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
     const unsigned lo = (unsigned)(sr * cols + c4) * 4u;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int rr = 4 * i + sr;
+      const int rr = 4 * i + sr_;
       // (edge blocks: rows beyond nrows repeat the last one, and are never stored)
       const size_t off = FULL ? (size_t)(row0 + 4 * i) * cols + c : (size_t)(row0 + min(rr, nrows - 1)) * cols;
       if constexpr (FULL) {
@@ -1792,7 +1797,7 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           if constexpr (FULL) wp[i] = load_params<kAligned>(ghat_out + (size_t)(row0 + 4 * i) * cols + c, (int)(lo >> 2), 0);
-          else wp[i] = load_params<KIND>(ghat_out + (size_t)(row0 + min(4 * i + sr, nrows - 1)) * cols, cl, cols);
+          else wp[i] = load_params<KIND>(ghat_out + (size_t)(row0 + min(4 * i + sr_, nrows - 1)) * cols, cl, cols);
         }
       }
     }
@@ -1856,7 +1861,7 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
       wave_lds_fence();
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int rr = 4 * i + sr;
+        const int rr = 4 * i + sr_;
         const float4 t = *reinterpret_cast<const float4*>(lds + rr * kLP + c4);
         if constexpr (HASM) {
           e[i].v[0] -= t.x; e[i].v[1] -= t.y; e[i].v[2] -= t.z; e[i].v[3] -= t.w;
@@ -1876,7 +1881,7 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
     if constexpr (HASM) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int rr = 4 * i + sr;
+        const int rr = 4 * i + sr_;
         Pk<4> m;
 #pragma unroll
         for (int v = 0; v < 4; ++v) m.v[v] = ADD ? g[i].v[v] + e[i].v[v] : e[i].v[v];
@@ -1884,6 +1889,7 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
           strow<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + 4 * i) * cols + c), lo, m);
         else if (rr < nrows)
           stgroup<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + rr) * cols), (unsigned)cl * 4u, ncol, m);
+
         if constexpr (ADD)
           *reinterpret_cast<float4*>(lds + rr * kLP + c4) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
       }

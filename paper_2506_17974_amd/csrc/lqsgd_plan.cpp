@@ -144,7 +144,17 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
   const int64_t tgtG = env_i64("LQSGD_TILE_G", std::min<int64_t>(tgtB, std::max<int64_t>(4096, matrix_elements / 2730)));
   // column segments: at most 1024 columns (2048 at rank pad 32, where fewer, longer segments save
   // more in partial planes and Gram-Schmidt input than they cost in sweep 0)
-  const int64_t segmax4 = env_i64("LQSGD_SEGMAX", RP >= 32 ? 2048 : 1024);
+  // ... and where a small set would have fewer than four items of 32 rows per CU that way: ragged set at r = 20, sweep 0
+  // 59 -> 52 us, G-hat pass 14 -> 10).
+  auto mfma_items = [&](int64_t rows, int64_t cols) {
+    int64_t n = 0;
+    for (const LayerDesc& d : layers) n += W * ((d.rows + rows - 1) / rows) * ((d.cols + cols - 1) / cols);
+    return n;
+  };
+  const int64_t segmax4 = env_i64("LQSGD_SEGMAX", RP >= 32 && mfma_items(32, 2048) >= 1024 ? 2048 : 1024);
+  // row blocks of the matrix-core sweep 1: at least 256 rows, less where that leaves CUs without two items (ragged set at
+  // r = 20: 256 / 128 rows 35 / 23 us; on the ResNet-18 set at r = 32, 1794 items of 256, 85 / 90)
+  const int64_t rbm_min = mfma_items(256, kMfmaCols) >= 512 ? 256 : mfma_items(128, kMfmaCols) >= 512 ? 128 : 64;
 
   int64_t m_acc = 0, p_acc = 0, q_acc = 0, pp_acc = 0, qp_acc = 0;
   int64_t mp_acc = 0, sp_acc = 0, mq_acc = 0, sq_acc = 0;
@@ -191,7 +201,7 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
     }
     // the partial planes of Q belong to whichever kernel runs sweep 1
     if (mfma) {
-      const int64_t rbm = env_i64("LQSGD_TILE_BM", std::min<int64_t>(2048, std::max<int64_t>(256, total / (49152 * 16))));
+      const int64_t rbm = env_i64("LQSGD_TILE_BM", std::min<int64_t>(2048, std::max<int64_t>(rbm_min, total / (49152 * 16))));
       d.rbb = (int32_t)std::min<int64_t>(round_up(rbm, 2), round_up(d.rows, 2));
     } else {
       d.rbb = rbb_v;
