@@ -143,9 +143,8 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
   // the G-hat-only pass covers one worker's worth of elements: smaller items keep its grid wide
   const int64_t tgtG = env_i64("LQSGD_TILE_G", std::min<int64_t>(tgtB, std::max<int64_t>(4096, matrix_elements / 2730)));
   // column segments: at most 1024 columns (2048 at rank pad 32, where fewer, longer segments save
-  // more in partial planes and Gram-Schmidt input than they cost in sweep 0)
-  // ... and where a small set would have fewer than four items of 32 rows per CU that way: ragged set at r = 20, sweep 0
-  // 59 -> 52 us, G-hat pass 14 -> 10).
+  // more in partial planes and Gram-Schmidt input than they cost in sweep 0; 1024 there too where a small set would have
+  // fewer than four items of 32 rows per CU: ragged set at r = 20, sweep 0 59 -> 52 us, G-hat pass 14 -> 10)
   auto mfma_items = [&](int64_t rows, int64_t cols) {
     int64_t n = 0;
     for (const LayerDesc& d : layers) n += W * ((d.rows + rows - 1) / rows) * ((d.cols + cols - 1) / cols);
