@@ -673,16 +673,42 @@ __global__ __launch_bounds__(BS) void orth_reg_kernel(DevArgs a) {
 // up to 64 values.  The loop over the columns is rolled: no register index
 // depends on it, and the code stays a few KB at any rank (a workgroup runs it
 // once).
-// Before and after (rows on lanes, or in memory where the rows did not fit the
-// registers): ResNet-18 set 8.6 -> 7.4 us at r = 4, 12.4 -> 10.1 at r = 7, 35 ->
-// 19 at r = 16, 61 -> 39 at r = 32, 164 -> 85 at r = 50; 1000 rows at r = 20 424
-// -> 37 us, at r = 64 5.2 -> 0.22 ms.  More wavefronts with fewer rows each do
+//
+// Every sum is the one that rows on lanes gives, to the last bit: products of
+// rows t, t + 256, ... in a chain for each thread t < 256, a butterfly (32, 16,
+// .. 1) over each 64 of these threads, then their wavefronts in order
+// (t, t + 1024, ... and 16 wavefronts where WV = 16).  Where a factor is close
+// to singular -- ranks clipped to a layer's width, later iterations of a high
+// rank -- Gram-Schmidt magnifies the rounding of its sums by the factor's
+// condition number, a thousand times and more: with the same products added in
+// another order single values of G-hat move by 1e-4 of its root mean square, in
+// one of eight runs of the ResNet-18 set at r = 50 by 3e-3.  So which rows a lane
+// holds, and the order in which it goes through them, follow that tree: a lane
+// holds the LL threads of one of its subtrees, in bit-reversed order, so that
+// neighbouring partial sums always meet first.
+// PAIRS: wavefronts added as (0 + 1) + (2 + 3) instead of one after the other.
+// Before and after, microseconds (rows on lanes in the registers, or in memory
+// where they did not fit; columns on lanes): ResNet-18 set 10.2 -> 9.2 at r = 4,
+// 13.5 -> 12.1 at r = 7, 33 -> 20.6 at r = 16, 61 -> 43 at r = 32, 165 -> 95 at
+// r = 50; 1000 rows 421 -> 43 at r = 20, 1400 -> 62 at r = 32, 5200 -> 227 at
+// r = 64; 130 factors of 10000 rows at r = 4 36 -> 27.  (Sums in any order, with
+// 1 / sqrt from the hardware's estimate and the scaled column folded into the
+// factor f, are 3 to 10 % faster.)  More wavefronts with fewer rows each do
 // better up to 16 (r = 32: 38.6 us with 16 x 16 rows, 40.6 with 8 x 32); lane
 // reads instead of LDS for the column cost more (r = 50: 106 against 96 us).
 // ---------------------------------------------------------------------------
-template <int C, int RPT, int NW>
+constexpr int bit_reverse(int x, int bits) { return bits == 0 ? 0 : ((x & 1) << (bits - 1)) | bit_reverse(x >> 1, bits - 1); }
+constexpr int trailing_zeros(int x) { return (x & 1) ? 0 : 1 + trailing_zeros(x >> 1); }
+
+template <int C, int WV, int NI, int NW, bool PAIRS>
 __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
   constexpr int G = kWave / C;
+  constexpr int SUB = NW / WV;                   // wavefronts here per 64 threads of the tree
+  constexpr int SP = SUB * G;                    // subtrees of 64 threads
+  constexpr int LL = kWave / SP;                 // threads of a lane's subtree
+  constexpr int RPT = LL * NI;                   // NI rows each
+  constexpr int STEP = WV > 4 ? kWave * WV : 256;
+  static_assert(NW % WV == 0 && SP <= kWave && RPT % 4 == 0 && (WV >= 4 || NI == 1) && (!PAIRS || WV == 4), "");
   constexpr int PS = NW + 4;                     // pitch of a column's partials: 16-byte reads of 16 lanes hit all banks once
   __shared__ __attribute__((aligned(16))) float bc[NW][G][RPT];
   __shared__ __attribute__((aligned(16))) float part[2][C][PS];
@@ -696,7 +722,12 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
   const float* Pp = a.Ppart + (size_t)worker * a.ppart_stride + (a.orth_shared ? ld.p_off : ld.ppart_off);
   float* pre = a.Ppre + (size_t)worker * a.p_stride + ld.p_off;
   float* orth = a.Porth + (size_t)worker * a.p_stride + ld.p_off;
-  const int row0 = wave * G + g;                 // this lane's rows: row0, row0 + NW G, ...
+  int row0 = (wave / SUB) * kWave + g * SUB + wave % SUB;
+  // Many rows per lane: the optimiser would keep all their addresses in registers from one use to the next, and spill
+  // (1000 rows at r = 64 255 -> 227 us, 1700 at r = 32 142 -> 106); few rows: it may (r = 7 14.0 -> 12.1 us).
+  auto hide_row = [&]() __attribute__((always_inline)) { if constexpr (RPT > 32) asm volatile("" : "+v"(row0)); };
+  // row of the lane's value i, from row0
+  auto row_of = [](int i) __attribute__((always_inline)) { return bit_reverse(i / NI, log2c(LL)) * SP + (i % NI) * STEP; };
   const bool col = k < r;
 
   float v[RPT];
@@ -705,13 +736,15 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
   // elements beyond the factor re-read its first one; they count as zeros from here on
   for (int s = 0; s < nseg; ++s) {
     const float* src = Pp + (size_t)s * ld.np_pad;
-    constexpr int CH = RPT < 16 ? RPT : 16;      // loads in flight
+    hide_row();
+    constexpr int CH = RPT % 16 == 0 ? 16 : RPT % 14 == 0 ? 14 : RPT % 11 == 0 ? 11 : RPT;      // loads in flight
+    static_assert(RPT % CH == 0, "");
 #pragma unroll
     for (int i0 = 0; i0 < RPT; i0 += CH) {
       float t[CH];
 #pragma unroll
       for (int i = 0; i < CH; ++i) {
-        const int row = row0 + (i0 + i) * (NW * G);
+        const int row = row0 + row_of(i0 + i);
         t[i] = src[(col && row < rows) ? row * r + k : 0];
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -719,9 +752,10 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
       for (int i = 0; i < CH; ++i) v[i0 + i] += t[i];
     }
   }
+  hide_row();
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
-    const int row = row0 + i * (NW * G);
+    const int row = row0 + row_of(i);
     if (col && row < rows) pre[row * r + k] = v[i];
     else v[i] = 0.0f;
   }
@@ -740,36 +774,55 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
       t[0] = x.x; t[1] = x.y; t[2] = x.z; t[3] = x.w;
     };
     float b[KEEP ? RPT / 4 : 1][4];
-    float s4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    float level[log2c(LL) + 1];                  // one open partial sum per level of the subtree
+    float chain = 0.0f;
 #pragma unroll
     for (int i = 0; i < RPT / 4; ++i) {
       float t[4];
       fetch(i, t);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        s4[e] = fmaf(t[e], v[4 * i + e], s4[e]);
+        const int n = 4 * i + e, p = n / NI;     // value, thread of the subtree
+        chain = fmaf(t[e], v[n], n % NI == 0 ? 0.0f : chain);
+        if (n % NI == NI - 1) {                  // thread p is complete: close what ends with it
+          const int top = trailing_zeros(p + 1);
+          float sum = chain;
+#pragma unroll
+          for (int l = 0; l < log2c(LL); ++l)
+            if (l < top) sum = level[l] + sum;
+          level[top] = sum;
+        }
         if constexpr (KEEP) b[i][e] = t[e];
       }
     }
-    float s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+    float s = level[log2c(LL)];
 #pragma unroll
-    for (int off = C; off < kWave; off <<= 1) s += __shfl_xor(s, off, kWave);
+    for (int off = kWave / 2; off >= C; off >>= 1) s += __shfl_xor(s, off, kWave);
     float* mypart = part[j & 1][k];
     if (g == 0) mypart[wave] = s;
     __syncthreads();
-    s = 0.0f;
+    float pw[NW];
 #pragma unroll
     for (int w = 0; w < NW; w += 4) {
       const float4 t = *reinterpret_cast<const float4*>(mypart + w);
-      s += (t.x + t.y) + (t.z + t.w);
+      pw[w] = t.x; pw[w + 1] = t.y; pw[w + 2] = t.z; pw[w + 3] = t.w;
+    }
+#pragma unroll
+    for (int wv = 0; wv < WV; ++wv)
+#pragma unroll
+      for (int h = SUB / 2; h >= 1; h /= 2)
+#pragma unroll
+        for (int i = 0; i < h; ++i) pw[wv * SUB + i] += pw[wv * SUB + i + h];
+    if constexpr (PAIRS) {
+      s = (pw[0] + pw[SUB]) + (pw[2 * SUB] + pw[3 * SUB]);
+    } else {
+      s = pw[0];
+#pragma unroll
+      for (int wv = 1; wv < WV; ++wv) s += pw[wv * SUB];
     }
     const float nrm2 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(s), j));
-    // 1 / sqrt: the hardware's, one Newton step (every wavefront does this: the correctly rounded root and
-    // quotient are forty instructions)
-    float inv = __builtin_amdgcn_rsqf(nrm2);
-    inv = fmaf(0.5f * inv, fmaf(-(nrm2 * inv), inv, 1.0f), inv);
-    if (!(nrm2 > FLT_MIN)) inv = 0.0f;
-    const float f = -(s * inv) * inv;
+    const float inv = (nrm2 > FLT_MIN) ? 1.0f / sqrtf(nrm2) : 0.0f;
+    const float f = -(s * inv);
     if (k > j) {
 #pragma unroll
       for (int i = 0; i < RPT / 4; ++i) {
@@ -781,7 +834,10 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
           fetch(i, t);
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[4 * i + e] = fmaf(f, t[e], v[4 * i + e]);
+        for (int e = 0; e < 4; ++e) {
+          const float qv = t[e] * inv;
+          v[4 * i + e] = fmaf(f, qv, v[4 * i + e]);
+        }
       }
     } else if (k == j) {
 #pragma unroll
@@ -790,9 +846,10 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
   }
 
   float mx = 0.0f;
+  hide_row();
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
-    const int row = row0 + i * (NW * G);
+    const int row = row0 + row_of(i);
     if (col && row < rows) {
       orth[row * r + k] = v[i];
       mx = fmaxf(mx, fabsf(v[i]));
@@ -2831,22 +2888,50 @@ bool launch_orth_reg(const DevArgs& a, int max_rows, dim3 grid, hipStream_t s) {
   return false;
 }
 
-// Columns on lanes: workgroups of up to 16 wavefronts with up to 64 rows per lane.
+// Columns on lanes: workgroups of up to 16 wavefronts, up to 64 rows per lane; the sums are those of 256 threads with
+// rows on lanes (1024 threads beyond 2048 rows), their wavefronts added in pairs from rank pad 16 and 513 rows on.
 template <int C>
 bool launch_orth_col(const DevArgs& a, int max_rows, dim3 grid, hipStream_t s) {
-  constexpr int G = kWave / C;
-#define LQSGD_LAUNCH_OC(RPT, NW)                                       \
-  if (max_rows <= (RPT) * (NW) * G) {                                  \
-    orth_col_kernel<C, RPT, NW><<<grid, dim3(64 * (NW)), 0, s>>>(a);   \
-    note_kernel("orth_col_kernel<%d, %d, %d>", C, RPT, NW);            \
-    return true;                                                       \
+#define LQSGD_LAUNCH_OC(ROWS, WV, NI, NW, PAIRS)                                                     \
+  if (max_rows <= (ROWS)) {                                                                          \
+    static_assert((ROWS) <= ((WV) > 4 ? 64 * (WV) : (NI) > 1 ? 256 : 64 * (WV)) * (NI), "");         \
+    orth_col_kernel<C, WV, NI, NW, PAIRS><<<grid, dim3(64 * (NW)), 0, s>>>(a);                       \
+    note_kernel("orth_col_kernel<%d, %d, %d, %d, %s>", C, WV, NI, NW, tf(PAIRS));                    \
+    return true;                                                                                     \
   }
-  LQSGD_LAUNCH_OC(8, 4)
-  LQSGD_LAUNCH_OC(8, 8)
-  LQSGD_LAUNCH_OC(16, 8)
-  LQSGD_LAUNCH_OC(16, 16)
-  LQSGD_LAUNCH_OC(32, 16)
-  LQSGD_LAUNCH_OC(64, 16)
+  if constexpr (C == 4) {
+    LQSGD_LAUNCH_OC(512, 4, 2, 4, false)
+    LQSGD_LAUNCH_OC(1024, 4, 4, 8, false)
+    LQSGD_LAUNCH_OC(2048, 4, 8, 8, false)
+    LQSGD_LAUNCH_OC(4096, 16, 4, 16, false)
+    LQSGD_LAUNCH_OC(8192, 16, 8, 16, false)
+    LQSGD_LAUNCH_OC(11264, 16, 11, 16, false)
+  } else if constexpr (C == 8) {
+    LQSGD_LAUNCH_OC(256, 4, 1, 4, false)
+    LQSGD_LAUNCH_OC(512, 4, 2, 8, false)
+    LQSGD_LAUNCH_OC(1024, 4, 4, 8, false)
+    LQSGD_LAUNCH_OC(2048, 4, 8, 16, false)
+    LQSGD_LAUNCH_OC(4096, 16, 4, 16, false)
+  } else if constexpr (C == 16) {
+    LQSGD_LAUNCH_OC(128, 2, 1, 4, false)
+    LQSGD_LAUNCH_OC(256, 4, 1, 8, false)
+    LQSGD_LAUNCH_OC(512, 4, 2, 8, false)
+    LQSGD_LAUNCH_OC(1024, 4, 4, 16, true)
+    LQSGD_LAUNCH_OC(1792, 4, 7, 16, true)
+  } else if constexpr (C == 32) {
+    LQSGD_LAUNCH_OC(64, 1, 1, 4, false)
+    LQSGD_LAUNCH_OC(128, 2, 1, 8, false)
+    LQSGD_LAUNCH_OC(256, 4, 1, 8, false)
+    LQSGD_LAUNCH_OC(512, 4, 2, 16, false)
+    LQSGD_LAUNCH_OC(1024, 4, 4, 16, true)
+    LQSGD_LAUNCH_OC(1792, 4, 7, 16, true)
+  } else {
+    LQSGD_LAUNCH_OC(64, 1, 1, 8, false)
+    LQSGD_LAUNCH_OC(128, 2, 1, 8, false)
+    LQSGD_LAUNCH_OC(256, 4, 1, 16, false)
+    LQSGD_LAUNCH_OC(512, 4, 2, 16, false)
+    LQSGD_LAUNCH_OC(1024, 4, 4, 16, true)
+  }
 #undef LQSGD_LAUNCH_OC
   return false;
 }
@@ -2999,8 +3084,11 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, Coo
   const dim3 grid(a.L * a.W);
   const int nslice = (max_rows + 255) / 256;
   // Tall factors and too few (layer, worker) pairs to fill 256 CUs with one workgroup
-  // each, or more rows than one workgroup holds: many workgroups per factor.
-  const bool fits = max_rows <= (rp <= 2 ? 11264 : 65536 / rp);
+  // each, or more rows than one workgroup holds: many workgroups per factor.  The limits of
+  // pads 8 to 32 keep each factor with the form, and so the sums, that it has had: one workgroup of columns on lanes would
+  // hold up to 8192 rows at pad 8 (130 factors of 8000 rows: 121 us, Cholesky-QR 186) and 4096 at pad 16 (3000 rows:
+  // 119 and 125), with results that differ by their rounding times the factor's condition number.
+  const bool fits = max_rows <= (rp <= 4 ? 11264 : rp == 8 ? 4096 : rp <= 32 ? 1792 : 1024);
   if (a.orth_part && (!fits || (nslice >= 8 && (int)grid.x < 128))) {
 #ifdef LQSGD_TUNING
     static const bool chol = [] { const char* e = std::getenv("LQSGD_ORTH_CHOL"); return !(e && e[0] == '0'); }();
