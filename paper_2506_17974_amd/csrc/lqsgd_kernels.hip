@@ -181,6 +181,7 @@ __device__ __forceinline__ void strow(char* rowbase, unsigned boff, const Pk<4>&
 __device__ __forceinline__ int edge_col(int c, int cols) { return max(0, min(c, cols - 4)); }
 // Shapes of a layer's rows, a constant in every kernel's inner loops (a test inside ldedge would part the loads).
 enum RowKind { kAligned = 0, kRagged = 1, kNarrow = 2 };   // cols % 4 == 0; the rest; the rest below four columns
+constexpr int kOneColumnPerLane = 2;                       // LayerDesc::kind, see narrow_rows
 template <int KIND, bool NT, bool GB16>
 __device__ __forceinline__ Pk<4> ldedge(const char* rowbase, int c, int cols) {
   if constexpr (KIND == kNarrow) {               // element loads, the surplus ones repeat the last element
@@ -458,6 +459,77 @@ __device__ __forceinline__ void add_project_tile(const float* __restrict__ G, fl
   }
 }
 
+// Sweeps 0 and 2 over rows of at most 64 columns that are no multiple of four (input layers, class counts): a lane has
+// one column, so that a pass of 4-byte loads covers a row, and the P products of a row are added by one butterfly over the
+// lanes.  Four columns on a lane, as in wider rows, would leave most lanes idle, and on the matrix cores most of a
+// 32-column block; and the order of these sums is part of the results: ranks are often clipped to the width of such a
+// layer, its factor is then close to singular, and Gram-Schmidt magnifies what another order changes (64 x 27 at r = 27:
+// single values of G-hat 2e-4 of its root mean square).  It is not slower:
+// sweep 0 of the ResNet-18 set at r = 50 366 us (four columns on the matrix cores 368), of 4 x (100000 x 21), W = 8, r = 4
+// 692 us (965).
+// `nrows` rows from row0 on, at most R; ADD: M = G + E and the P partials; FUSE: E is still last iteration's M;
+// EMIT: G-hat goes out.  ADD is false in the sweeps that only finish E (HASM) or only write G-hat.
+template <int RP, int R, bool ADD, bool FUSE, bool HASM, bool EMIT, bool GB16, bool NTS>
+__device__ __forceinline__ void narrow_rows(const float* __restrict__ G, float* __restrict__ M, const float* Q, const float* Pb,
+                                            float* __restrict__ Pp, float* __restrict__ ghat, int cols, int r, int row0, int nrows,
+                                            int lane, int update, float eta) {
+  constexpr int RT = RP >= kWave ? 1 : R * RP <= kWave ? R : kWave / RP;   // rows of a butterfly
+  const bool on = lane < cols;
+  const int c = min(lane, cols - 1);             // the other lanes repeat the last column, and count as zeros
+  float q[RP], g[R], e[R], w[R];
+  if constexpr (RP >= 4) {
+#pragma unroll
+    for (int i = 0; i < RP / 4; ++i) {
+      const Pk<4> t = ldrow<false>(reinterpret_cast<const char*>(Q), (unsigned)(c * RP + 4 * i) * 4u);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) q[4 * i + v] = t.v[v];
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < RP; ++k) q[k] = gptr<float>(Q)[c * RP + k];
+  }
+#pragma unroll
+  for (int t = 0; t < R; ++t) {                  // rows beyond nrows repeat the last one: loaded, never stored
+    const size_t at = (size_t)(row0 + min(t, nrows - 1)) * cols + c;
+    if constexpr (ADD) g[t] = grad_elem<GB16>(G, at);
+    if constexpr (HASM) e[t] = gptr<float>(M)[at];
+    if constexpr (EMIT) w[t] = update && ghat ? gptr<float>(ghat)[at] : 0.0f;
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < RP; ++k) q[k] = keep_if(q[k], on);
+#pragma unroll
+  for (int t0 = 0; t0 < R; t0 += RT) {
+    float acc[RT * RP];
+#pragma unroll
+    for (int t1 = 0; t1 < RT; ++t1) {
+      const int t = t0 + t1;
+      float m = HASM ? e[t] : 0.0f;
+      const size_t at = (size_t)(row0 + t) * cols + c;
+      const bool mine = on && t < nrows;
+      if constexpr (FUSE || !ADD) {              // the same operation order as everywhere: G-hat in rank order, then E
+        float p[RP], gh = 0.0f;
+        load_row_uniform<RP>(Pb, row0 + min(t, nrows - 1), p);
+#pragma unroll
+        for (int k = 0; k < RP; ++k) gh = fmaf(p[k], q[k], gh);
+        m = m - gh;
+        if (EMIT && ghat && mine) gptr<float>(ghat)[at] = update ? fmaf(-eta, gh, w[t]) : gh;
+      }
+      if constexpr (ADD) m = g[t] + m;
+      if (HASM && mine) gptr<float>(M)[at] = m;
+      m = keep_if(m, on);
+#pragma unroll
+      for (int k = 0; k < RP; ++k) acc[t1 * RP + k] = fmaf(m, q[k], 0.0f);
+    }
+    if constexpr (ADD) {
+      constexpr int N = RT * RP;
+      transpose_reduce<N, N, 32>(acc, lane);     // N <= 64: lane l has value l / (64 / N)
+      const int idx = lane >> (6 - log2c(N)), t = t0 + idx / RP, k = idx & (RP - 1);
+      if ((lane & (kWave / N - 1)) == 0 && t < nrows && k < r) Pp[(size_t)(row0 + t) * r + k] = acc[0];
+    }
+  }
+}
+
 // FUSE: the residual update of the previous iteration has been deferred; the
 // buffer holds M_{t-1} and this sweep forms E_{t-1} = M_{t-1} - P-bar Q-bar^T on
 // the fly (Q-bar is the warm-start Q this sweep multiplies by anyway).
@@ -485,8 +557,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, LQSGD_A_
     add_project_tile<RP, RT, kAligned, FUSE, GB16, NTS>(G, M, Q, Pb, Pp, ld.cols, ld.r, tl.row0, tl.nrows, col0, col1, lane);
   else if (ld.kind == kRagged)
     add_project_tile<RP, RT, kRagged, FUSE, GB16, NTS>(G, M, Q, Pb, Pp, ld.cols, ld.r, tl.row0, tl.nrows, col0, col1, lane);
-  else
-    add_project_tile<RP, RT, kNarrow, FUSE, GB16, NTS>(G, M, Q, Pb, Pp, ld.cols, ld.r, tl.row0, tl.nrows, col0, col1, lane);
+  else                                           // one segment
+    for (int i = 0; i < tl.nrows; i += 8)
+      narrow_rows<RP, 8, true, FUSE, true, false, GB16, NTS>(G, M, Q, Pb, Pp, nullptr, ld.cols, ld.r, tl.row0 + i,
+                                                             min(8, tl.nrows - i), lane, 0, 0.0f);
 }
 
 // ---------------------------------------------------------------------------
@@ -1374,9 +1448,8 @@ __device__ __forceinline__ void back_project_tile(const DevArgs& a, const LayerD
     for (int o = tid; o < nout; o += 256) {
       const int cc = (int)((unsigned)o / (unsigned)r);
       const float* src = comb + cc * RP + (o - cc * r);
-      float s = src[0];
-#pragma unroll
-      for (int wv = 1; wv < 4; ++wv) s += src[(size_t)wv * (kWave * NV)];
+      constexpr size_t P = (size_t)kWave * NV;
+      const float s = (src[0] + src[2 * P]) + (src[P] + src[3 * P]);
       Qp[(size_t)c0 * r + o] = s;
       mx = fmaxf(mx, fabsf(s));
     }
@@ -1432,7 +1505,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, LQSGD_B_
   const LayerDesc& ld = a.layers[layer];
   if (ld.kind == kAligned)
     back_project_tile<RP, kAligned>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
-  else if (ld.kind == kRagged)
+  else if (ld.cols >= 4)
     back_project_tile<RP, kRagged>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
   else
     back_project_tile<RP, kNarrow>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
@@ -1728,7 +1801,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MODE == 
   if (MODE == kGhatOnly && !ghat) return;
   if (ld.kind == kAligned)
     residual_tile<RP, MODE, kAligned>(a, ld, tl, worker, ghat, wave, lane);
-  else if (ld.kind == kRagged)
+  else if (ld.cols >= 4)
     residual_tile<RP, MODE, kRagged>(a, ld, tl, worker, ghat, wave, lane);
   else
     residual_tile<RP, MODE, kNarrow>(a, ld, tl, worker, ghat, wave, lane);
@@ -1812,9 +1885,9 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
   // touch 1 KiB of each row at about the same time (a wavefront on its own reads 256-byte runs)
   // One 64-column block.  FULL: all 32 rows and all 64 columns of the block exist (every block of a
   // large layer except on its edges): no bounds tests, so nothing branches around a load.
-  auto block = [&](auto full_tag, auto kind_tag, const int c) {
+  auto block = [&](auto full_tag, const int c) {
     constexpr bool FULL = decltype(full_tag)::value;
-    constexpr int KIND = decltype(kind_tag)::value;      // of edge blocks: kRagged (which takes aligned rows too) or kNarrow
+    constexpr int KIND = kRagged;                // of edge blocks (takes aligned rows too)
     const int cl = c + c4;
     // Edge blocks: this lane's row number is hidden from the optimiser, which otherwise computes the addresses of all
     // rows once, ahead of the loop over the blocks, and keeps them in registers that the whole blocks need (rank pad
@@ -1980,11 +2053,9 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
   const bool small_offsets = cols < (1 << 26);   // byte offsets within 4 rows fit 32 bits
   for (int c = col0 + 64 * wave; c < col1; c += 256) {
     if (nrows == 32 && c + 64 <= col1 && small_offsets)
-      block(std::true_type{}, std::integral_constant<int, kAligned>{}, c);
-    else if (cols >= 4)
-      block(std::false_type{}, std::integral_constant<int, kRagged>{}, c);
+      block(std::true_type{}, c);
     else
-      block(std::false_type{}, std::integral_constant<int, kNarrow>{}, c);
+      block(std::false_type{}, c);
   }
   if constexpr (ADD) {
     // P partial of the item = sum over the four wavefronts, added in wavefront order
@@ -2051,14 +2122,13 @@ __device__ __forceinline__ void mfma_tile32(const float* __restrict__ G, float* 
   for (int i = 0; i < 16; ++i) { accP[i] = 0.0f; accP2[i] = 0.0f; }
 
   // the G and E (or old M) values of one 32 x 32 block at an edge of the layer
-  auto fetch = [&](auto kind_tag, const int c, Pk<4>* g, Pk<4>* e) {
-    constexpr int KIND = decltype(kind_tag)::value;
+  auto fetch = [&](const int c, Pk<4>* g, Pk<4>* e) {
     const int cl = c + c4;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const size_t off = (size_t)(row0 + min(8 * i + sr, nrows - 1)) * cols;   // rows beyond nrows: never stored
-      g[i] = ldedge<KIND, LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), cl, cols);
-      e[i] = ldedge<KIND, NTS, false>(reinterpret_cast<const char*>(M + off), cl, cols);
+      g[i] = ldedge<kRagged, LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), cl, cols);
+      e[i] = ldedge<kRagged, NTS, false>(reinterpret_cast<const char*>(M + off), cl, cols);
     }
     if (cl + 4 > cols) {
 #pragma unroll
@@ -2257,8 +2327,7 @@ __device__ __forceinline__ void mfma_tile32(const float* __restrict__ G, float* 
   }
   for (; c < col1; c += 256) {
     Pk<4> g[4], e[4];
-    if (cols >= 4) fetch(std::integral_constant<int, kRagged>{}, c, g, e);
-    else fetch(std::integral_constant<int, kNarrow>{}, c, g, e);
+    fetch(c, g, e);
     block(c, g, e);
   }
   // P partial of the item = sum over the eight wavefronts, added in wavefront order
@@ -2295,6 +2364,14 @@ __global__ __launch_bounds__(256, RP <= 16 ? 2 : 1) void mfma_sweep_kernel(DevAr
   if (MODE == kMGhatOnly && !ghat_out) return;
   const int col0 = tl.aux * ld.segw;
   const int col1 = min(ld.cols, col0 + ld.segw);
+  if (ld.kind == kOneColumnPerLane) {            // eight of the item's rows per wavefront
+    constexpr bool ADD = MODE == kMAdd || MODE == kMAddFused;
+    const int nr = min(8, tl.nrows - 8 * wave);
+    if (nr > 0)
+      narrow_rows<RP, 8, ADD, MODE == kMAddFused, MODE != kMGhatOnly, MODE == kMResidualGhat || MODE == kMGhatOnly, GB16, NTS>(
+          G, M, q_operand(a, ld), p_operand(a, ld), Pp, ghat_out, ld.cols, ld.r, tl.row0 + 8 * wave, nr, lane, a.update, a.eta);
+    return;
+  }
   mfma_tile<RP, MODE, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ghat_out, ld.cols, ld.r, tl.row0,
                                  tl.nrows, col0, col1, lane, wave, lds_all, a.update, a.eta);
 }
@@ -2313,6 +2390,13 @@ __global__ __launch_bounds__(512, 2) void mfma_sweep32_kernel(DevArgs a, const T
   float* Pp = a.Ppart + (size_t)worker * a.ppart_stride + ld.ppart_off + (size_t)tl.aux * ld.np_pad;
   const int col0 = tl.aux * ld.segw;
   const int col1 = min(ld.cols, col0 + ld.segw);
+  if (ld.kind == kOneColumnPerLane) {            // four of the item's rows per wavefront
+    const int nr = min(4, tl.nrows - 4 * wave);
+    if (nr > 0)
+      narrow_rows<RP, 4, true, MODE == kMAddFused, true, false, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, nullptr,
+                                                                           ld.cols, ld.r, tl.row0 + 4 * wave, nr, lane, 0, 0.0f);
+    return;
+  }
   mfma_tile32<RP, MODE, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ld.cols, ld.r, tl.row0, tl.nrows,
                                    col0, col1, lane, wave, lds_all);
 }

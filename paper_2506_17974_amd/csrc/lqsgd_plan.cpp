@@ -108,7 +108,7 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
       d.rows = l.rows;
       d.cols = l.cols;
       d.r = std::min(c->rank, std::min(l.rows, l.cols));
-      d.kind = l.cols % 4 == 0 ? 0 : l.cols > 4 ? 1 : 2;
+      d.kind = l.cols % 4 == 0 ? 0 : l.cols > kWave ? 1 : 2;
       d.gidx = i;
       d.np_el = d.rows * d.r;
       d.nq_el = d.cols * d.r;

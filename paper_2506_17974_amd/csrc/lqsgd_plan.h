@@ -21,7 +21,7 @@ constexpr int kFactorSlack = 64;   // readable floats after the last row of ever
 // One matrix layer as the kernels see it.  Offsets are in elements (floats)
 // from the start of a per-worker slab unless they say bytes.
 struct LayerDesc {
-  int32_t rows, cols, r, kind;  // kind of rows: 0 = cols % 4 == 0 (16-byte aligned), 1 = not, 2 = not and below four columns
+  int32_t rows, cols, r, kind;  // kind of rows: 0 = cols % 4 == 0 (16-byte aligned), 1 = not, 2 = not and at most 64 columns
   int32_t segw, nseg;           // sweep 0: column segment width (multiple of 256) and count
   int32_t rbb, nrb;             // sweeps 1, 2: rows per row block and count
   int32_t gidx;                 // position in the caller's tensor list

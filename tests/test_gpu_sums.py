@@ -91,3 +91,72 @@ def test_gram_schmidt_sums_of_many_tall_factors(rank, rows):
         want = _gram_schmidt(comp.get_factor(B.FACTOR_P_PRE, l, w), 256 if rows <= 2048 else 1024, False)
         assert np.array_equal(comp.get_factor(B.FACTOR_P_ORTH, l, w), want), (l, w)
     comp.close()
+
+
+@pytest.mark.parametrize("rank", [2, 4, 7, 20, 50])
+def test_gram_schmidt_of_a_column_whose_squared_norm_overflows(rank):
+    """Finite values whose squares leave the range of floats: the column becomes zero and the others, whose products with it
+    are finite, stay what they are without it.  Nothing of it reaches G-hat or the residual."""
+    import torch
+    _say("case: overflowing column", rank)
+    rng = np.random.default_rng(rank)
+    layers, W = [(300, 210)], 2
+    comp = B.Compressor(B.layer_list(layers, ()), rank, 0, 0, W)
+    q = rng.standard_normal((210, rank)).astype(f32)
+    q[:, rank // 2] *= f32(1e22)
+    comp.set_q(0, q)
+    G = [[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)]
+    out = [torch.zeros(s, device="cuda") for s in layers]
+    comp.step(pu.to_device(G), out)
+    for w in range(W):
+        pre, got = comp.get_factor(B.FACTOR_P_PRE, 0, w), comp.get_factor(B.FACTOR_P_ORTH, 0, w)
+        assert np.isfinite(pre).all() and np.abs(pre).max() > 1e19
+        assert not got[:, rank // 2].any() and np.isfinite(got).all()
+        with np.errstate(over="ignore"):
+            want = _gram_schmidt(pre, 256, False)
+        assert pu.rel_fro(got, want) < pu.FP_TOL if rank <= 2 else np.array_equal(got, want)
+        assert np.isfinite(comp.get_state(0, w)[0]).all()
+    assert bool(torch.isfinite(out[0]).all())
+    comp.close()
+
+
+@pytest.mark.parametrize("rank", [1, 2, 3, 7, 8, 12, 20, 32, 50])
+@pytest.mark.parametrize("eager", [False, True])
+def test_narrow_rows_sums_and_reconstructions(rank, eager):
+    """Rows of at most 64 columns, no multiple of four of them: products added by a butterfly over the columns, the
+    reconstruction in the order of the ranks, in a first and in a second iteration (whose residual is the deferred or the
+    finished one)."""
+    import torch
+    _say("case: narrow rows", rank, eager)
+    rng = np.random.default_rng(rank)
+    layers, W = [(70, 27), (64, 63), (33, 1), (41, 2), (9, 3), (65, 5), (100, 33), (300, 64), (64, 200)], 2
+    comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, W, 255.0, B.FLAG_EAGER_RESIDUAL if eager else 0)
+    Q = [rng.standard_normal((c, min(rank, n, c))).astype(f32) for n, c in layers]
+    for l, q in enumerate(Q):
+        comp.set_q(l, q)
+    out = [torch.zeros(s, device="cuda") for s in layers]
+    E = [[np.zeros(s, f32) for s in layers] for _ in range(W)]
+    for _ in range(2):
+        G = [[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)]
+        comp.step(pu.to_device(G), out)
+        for l, (n, c) in enumerate(layers):
+            if c % 4 == 0 or c > 64:
+                continue
+            k = Q[l].shape[1]
+            P, Qn = comp.get_factor(B.FACTOR_P_BAR, l), comp.get_factor(B.FACTOR_Q_BAR, l)
+            hat = np.zeros((n, c), f32)
+            for j in range(k):
+                hat = _fma(P[:, j:j + 1], Qn[:, j], hat)
+            assert np.array_equal(out[l].cpu().numpy(), hat), (l, "G-hat")
+            for w in range(W):
+                M = G[w][l] + E[w][l]
+                lanes = np.zeros((n, 64, k), f32)
+                lanes[:, :c] = M[:, :, None] * Q[l][None]
+                assert np.array_equal(comp.get_factor(B.FACTOR_P_PRE, l, w), _butterfly(lanes)), (l, w)
+                E[w][l] = M - hat
+            Q[l] = Qn
+    for l, (n, c) in enumerate(layers):
+        if c % 4 and c <= 64:
+            for w in range(W):
+                assert np.array_equal(comp.get_state(l, w)[0], E[w][l]), (l, w)
+    comp.close()
