@@ -479,20 +479,15 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   TRY_(dev_alloc(c, &a.Ppre, W * p.p_stride + kSlack, true));
   TRY_(dev_alloc(c, &a.Porth, W * p.p_stride + kSlack, true));
   TRY_(dev_alloc(c, &a.orth_part, orth_cells, true));
-  {
-    // Tall factors at rank pads >= 16 exchange whole Gram matrices instead of single columns
-    // (launch_orth decides per call; the same lower height limit as there).  A caller-provided block
-    // and factors of more than 64 slices get the buffers of the form of three launches only, which
-    // gives the same bits.
-    const size_t nslice = (size_t)(p.max_rows + 255) / 256, pairs = W * (size_t)std::max(p.L, 1);
-    const size_t ne = (size_t)chol_entries(p.RP);
-    // (rank pad 64 leaves the one-workgroup form at 1024 rows; a caller-provided block stays as small as it was)
-    const bool tall = nslice >= 8 || (!ext && p.RP == 64 && p.max_rows > 1024);
-    if (ne && tall && pairs * (nslice + 1) * ne * 12 <= ((size_t)1 << 30)) {
-      if (!ext && nslice <= 64) TRY_(dev_alloc(c, &a.chol_table, pairs * (nslice + 1) * ne, true));   // the one-launch form's limit
-      TRY_(dev_alloc(c, &a.chol_part, pairs * nslice * ne, true));
-      TRY_(dev_alloc(c, &a.chol_redo, pairs, true));
-    }
+  // Tall factors at rank pads >= 8 exchange whole Gram matrices instead of single columns (launch_orth decides per call).
+  // A caller-provided block and factors of more than 64 slices get the buffers of the form of three launches only, which
+  // gives the same bits.
+  const size_t nslice = (size_t)(p.max_rows + 255) / 256, pairs = W * (size_t)std::max(p.L, 1);
+  const size_t ne = (size_t)chol_entries(p.RP);
+  const bool chol_size = ne && pairs * (nslice + 1) * ne * 12 <= ((size_t)1 << 30);
+  if (chol_size && nslice >= 8) {
+    TRY_(dev_alloc(c, &a.chol_part, pairs * nslice * ne, true));
+    TRY_(dev_alloc(c, &a.chol_redo, pairs, true));
   }
   if (!ext) {
     TRY_(dev_alloc(c, &a.orth_table, orth_cells, true));
@@ -505,6 +500,15 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   }
   TRY_(dev_alloc(c, &a.Pbar, (size_t)p.p_stride + kSlack, true));
   TRY_(dev_alloc(c, &a.Qpart, W * p.qpart_stride + kSlack, true));
+  // Rank pad 64 leaves the one-workgroup form at 1024 rows already.  From there to 8 slices the Gram matrices lie where
+  // sweep 1 will put its partial planes, which are dead while Gram-Schmidt runs, or, in a set whose planes are too small
+  // for them, the columns are exchanged one by one: the same choice with and without a caller-provided block, whose sizes
+  // this leaves alone (it is another method with other rounding: 2 x (1700 x 640), W = 4, 160 us against 8.6 ms in memory).
+  if (chol_size && p.RP == 64 && p.max_rows > 1024 && nslice < 8 && pairs * (nslice * ne + 1) <= W * (size_t)p.qpart_stride) {
+    a.chol_part = a.Qpart;
+    a.chol_redo = reinterpret_cast<int*>(a.Qpart + pairs * nslice * ne);
+  }
+  if (!ext && a.chol_part && nslice <= 64) TRY_(dev_alloc(c, &a.chol_table, pairs * (nslice + 1) * ne, true));   // the one-launch form's limit
   TRY_(dev_alloc(c, &a.Qw, W * p.q_stride + kSlack, true));
   if (!ext) TRY_(dev_alloc(c, &a.Qbar, (size_t)p.q_stride + kSlack, true));
   a.padded = p.padded ? 1 : 0;

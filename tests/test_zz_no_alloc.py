@@ -130,3 +130,20 @@ def test_step_static_rejects_what_does_not_fit():
     rng = np.random.default_rng(1)
     E, Q = _fresh_state([(64, 27)], 4, 2, rng)
     _one_call([(64, 27)], [], 4, 8, 2, 0, rng, E, Q, "after a rejected call")
+
+
+# rank pad 64, tallest layer of 1025 .. 1792 rows: Gram-Schmidt forms of several workgroups, with room for their Gram
+# matrices among sweep 1's partial planes and without (many small layers beside a tall one)
+@pytest.mark.parametrize("matrices,chol", [([(1500, 300), (129, 160)], True), ([(1792, 140)], True),
+                                           ([(1025, 40)] + [(64, 35)] * 20, False)])
+def test_step_static_matches_step_at_rank_pad_64(matrices, chol):
+    rng = np.random.default_rng(64)
+    layers = B.layer_list(matrices, ())
+    ref = B.Compressor(layers, 50, 8, 8, 2)
+    import torch
+    ref.step([[torch.zeros(s, device="cuda") for s in matrices] for _ in range(2)])
+    assert ref.launched_kernel(B.KERNEL_ORTH).startswith("orth_chol" if chol else "orth_coop")
+    ref.close()
+    E, Q = _fresh_state(matrices, 50, 2, rng)
+    E, Q = _one_call(matrices, [], 50, 8, 2, 0, rng, E, Q, "rank pad 64")
+    _one_call(matrices, [], 50, 0, 2, B.FLAG_AGGREGATE_FIRST, rng, E, Q, "rank pad 64, aggregate-first, no quantisation")
