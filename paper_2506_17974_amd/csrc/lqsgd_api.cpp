@@ -241,7 +241,7 @@ int run_sweep0(lqsgd_ctx* c) {
                                    next_dir(c), c->stream));
     else
       HIP_TRY(c, launch_add_project(c->plan.RP, c->args, c->d_tilesA, (int)c->plan.tilesA.size(), c->pending ? 1 : 0,
-                                    next_dir(c), c->stream)); }
+                                    c->plan.narrow_rows ? 1 : 0, next_dir(c), c->stream)); }
   c->pending = false;
   if (c->plan.agg_first) {   // the exchange comes first: only add up the partial planes (and take the absmax)
     Timed t(c, LQSGD_KERNEL_REDUCE_P);
@@ -300,13 +300,13 @@ int run_sweep2(lqsgd_ctx* c, bool write_ghat) {
     if (p.mfma_a)
       HIP_TRY(c, launch_mfma_sweep(p.RP, write_ghat ? 3 : 2, c->args, c->d_tilesA, (int)p.tilesA.size(), next_dir(c), c->stream));
     else
-      HIP_TRY(c, launch_residual(p.RP, write_ghat ? 1 : 0, c->args, res, n_res, next_dir(c), c->stream));
+      HIP_TRY(c, launch_residual(p.RP, write_ghat ? 1 : 0, c->args, res, n_res, p.narrow_rows ? 1 : 0, next_dir(c), c->stream));
   } else {
     if (write_ghat) {
       if (p.mfma_a)
         HIP_TRY(c, launch_mfma_sweep(p.RP, 4, c->args, c->d_tilesAG, (int)p.tilesAG.size(), 0, c->stream));
       else
-        HIP_TRY(c, launch_residual(p.RP, 2, c->args, c->d_tilesG, (int)p.tilesG.size(), 0, c->stream));
+        HIP_TRY(c, launch_residual(p.RP, 2, c->args, c->d_tilesG, (int)p.tilesG.size(), 0, 0, c->stream));
     }
     c->pending = true;
   }
@@ -322,7 +322,7 @@ int materialise(lqsgd_ctx* c) {
   if (p.mfma_a)
     HIP_TRY(c, launch_mfma_sweep(p.RP, 2, c->args, c->d_tilesA, (int)p.tilesA.size(), next_dir(c), c->stream));
   else
-    HIP_TRY(c, launch_residual(p.RP, 0, c->args, res, n_res, next_dir(c), c->stream));
+    HIP_TRY(c, launch_residual(p.RP, 0, c->args, res, n_res, p.narrow_rows ? 1 : 0, next_dir(c), c->stream));
   c->pending = false;
   return LQSGD_OK;
 }

@@ -62,7 +62,7 @@ const char* last_launched_kernel();
 // each one starts on the data the previous one touched last (still in the memory-side cache).
 // fuse_residual: the buffer E holds last iteration's M and the residual update
 // E = M - P-bar Q-bar^T is applied on the fly (see add_project_kernel).
-hipError_t launch_add_project(int RP, const DevArgs& a, const Tile* tiles, int ntiles, int fuse_residual, int reverse,
+hipError_t launch_add_project(int RP, const DevArgs& a, const Tile* tiles, int ntiles, int fuse_residual, int narrow_rows, int reverse,
                               hipStream_t s);
 // What a context keeps for the one-launch (cooperative) Gram-Schmidt of tall factors.
 struct CoopState {
@@ -88,7 +88,7 @@ hipError_t launch_back_project_mfma(int RP, const DevArgs& a, const Tile* tiles,
 // planes (aggregate-first order, where the exchange comes before Gram-Schmidt).
 hipError_t launch_reduce_q(int phase, const DevArgs& a, const RTile* tiles, int ntiles, hipStream_t s);
 // mode: 0 = residual for all workers, 1 = residual + G-hat, 2 = G-hat only (tiles of worker 0).
-hipError_t launch_residual(int RP, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s);
+hipError_t launch_residual(int RP, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int narrow_rows, int reverse, hipStream_t s);
 
 // Sweeps 0 and 2 on the matrix cores (rank pad 16, 32 or 64), over the work list of
 // sweep 0 (32-row items).  mode: 0 = M = G + E and P partials, 1 = the same with the deferred

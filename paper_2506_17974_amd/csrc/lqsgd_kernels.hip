@@ -79,21 +79,22 @@ typedef const float __attribute__((address_space(4)))* const_fp;
 #ifndef LQSGD_BQ_LATE      // matrix-core sweep 0, fused mode: fetch the P product's Q slice after the G-hat part
 #define LQSGD_BQ_LATE 1
 #endif
-#ifndef LQSGD_R_WAVES      // the same for the residual sweep (ResNet-18 set: 141 / 136 / 143 / 142 us at 2 / 3 / 4 / 8; with non-temporal stores 176, with plain loads 147)
-#define LQSGD_R_WAVES 3
-#endif
 #ifndef LQSGD_B_U          // rows a wavefront of sweep 1 has in flight
 #define LQSGD_B_U 8
 #endif
 #ifndef LQSGD_B_INTERLEAVE  // sweep 1: row blocks of at least this many rows are split between the wavefronts in groups of LQSGD_B_U rows
 #define LQSGD_B_INTERLEAVE 512
 #endif
-#ifndef LQSGD_A_WAVES      // most wavefronts of sweep 0 on a SIMD: more of them read slower (ResNet-18 set, r = 4: 187 / 174 / 176 / 176 us at 1 / 2 / 3 / 4)
-#define LQSGD_A_WAVES 2
-#endif
-#ifndef LQSGD_B_WAVES      // the same for sweep 1 (62.0 / 62.6 / 63.0 us at 4 / 6 / 8)
-#define LQSGD_B_WAVES 4
-#endif
+// Dynamic LDS that sweep 0 asks for, and does not use, to keep it at two workgroups a CU, two wavefronts a SIMD: where rows
+// fill a wavefront's pass more of them read slower (ResNet-18 set, r = 4: 187 / 174.7 / 177 / 177 us at 1 / 2 / 3 / 4).  Rows
+// much narrower than a pass wait for memory instead, and take what the registers allow (1000000 x 16, r = 4, W = 8: 1980 us
+// at two, 1560 without the limit, one group of rows an item).  (Three is also what the registers are shared out for: at four,
+// rank pad 2 gets 117 instead of 142 of them and 8192^2 x 16 takes 2190 instead of 2085 us.)  Sweep 1 takes what they allow
+// everywhere (those narrow rows 434 us at four, 344 without a limit; the ResNet-18 set 64.5 and 64.9).
+[[maybe_unused]] constexpr unsigned kTwoPerCu = 56 * 1024;
+// The same for the residual sweep: three (ResNet-18 set 141 / 136 / 143 / 142 us at 2 / 3 / 4 / 8; with non-temporal stores 176,
+// with plain loads 147; narrow rows see Plan::build).
+[[maybe_unused]] constexpr unsigned kThreePerCu = 48 * 1024;
 
 template <int V>
 struct Pk {
@@ -461,22 +462,32 @@ __device__ __forceinline__ void add_project_tile(const float* __restrict__ G, fl
 
 // Sweeps 0 and 2 over rows of at most 64 columns that are no multiple of four (input layers, class counts): a lane has
 // one column, so that a pass of 4-byte loads covers a row, and the P products of a row are added by one butterfly over the
-// lanes.  Four columns on a lane, as in wider rows, would leave most lanes idle, and on the matrix cores most of a
-// 32-column block; and the order of these sums is part of the results: ranks are often clipped to the width of such a
+// lanes (and sweep 1, back_project_tile, holds one column per lane too).  Four columns on a lane, as in wider rows, would
+// leave most lanes idle, and on the matrix cores most of a 32-column block; and the order of these sums is part of the results: ranks are often clipped to the width of such a
 // layer, its factor is then close to singular, and Gram-Schmidt magnifies what another order changes (64 x 27 at r = 27:
 // single values of G-hat 2e-4 of its root mean square).  It is not slower:
-// sweep 0 of the ResNet-18 set at r = 50 366 us (four columns on the matrix cores 368), of 4 x (100000 x 21), W = 8, r = 4
-// 692 us (965).
+// sweep 0 of the ResNet-18 set at r = 50 366 us (four columns on the matrix cores 368); 4 x (100000 x 21), W = 8, r = 4, four
+// columns per lane and one: sweep 0 407 and 299 us, sweep 1 169 and 73, finished residual 593 and 184.
 // `nrows` rows from row0 on, at most R; ADD: M = G + E and the P partials; FUSE: E is still last iteration's M;
 // EMIT: G-hat goes out.  ADD is false in the sweeps that only finish E (HASM) or only write G-hat.
 template <int RP, int R, bool ADD, bool FUSE, bool HASM, bool EMIT, bool GB16, bool NTS>
 __device__ __forceinline__ void narrow_rows(const float* __restrict__ G, float* __restrict__ M, const float* Q, const float* Pb,
                                             float* __restrict__ Pp, float* __restrict__ ghat, int cols, int r, int row0, int nrows,
                                             int lane, int update, float eta) {
-  constexpr int RT = RP >= kWave ? 1 : R * RP <= kWave ? R : kWave / RP;   // rows of a butterfly
+  constexpr int RT = R * RP <= kWave ? R : kWave / RP;                     // rows of a butterfly
   const bool on = lane < cols;
   const int c = min(lane, cols - 1);             // the other lanes repeat the last column, and count as zeros
-  float q[RP], g[R], e[R], w[R];
+  float q[RP], g[R], e[R], w[R], p[RT * RP];
+  auto fetch_p = [&](int t0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t1 = 0; t1 < RT; ++t1) {
+      float x[RP];
+      load_row_uniform<RP>(Pb, row0 + min(t0 + t1, nrows - 1), x);
+#pragma unroll
+      for (int k = 0; k < RP; ++k) p[t1 * RP + k] = x[k];
+    }
+  };
+  if constexpr (FUSE || !ADD) fetch_p(0);
   if constexpr (RP >= 4) {
 #pragma unroll
     for (int i = 0; i < RP / 4; ++i) {
@@ -501,6 +512,8 @@ __device__ __forceinline__ void narrow_rows(const float* __restrict__ G, float* 
 #pragma unroll
   for (int t0 = 0; t0 < R; t0 += RT) {
     float acc[RT * RP];
+    if constexpr (FUSE || !ADD)
+      if (t0 > 0) fetch_p(t0);
 #pragma unroll
     for (int t1 = 0; t1 < RT; ++t1) {
       const int t = t0 + t1;
@@ -508,10 +521,9 @@ __device__ __forceinline__ void narrow_rows(const float* __restrict__ G, float* 
       const size_t at = (size_t)(row0 + t) * cols + c;
       const bool mine = on && t < nrows;
       if constexpr (FUSE || !ADD) {              // the same operation order as everywhere: G-hat in rank order, then E
-        float p[RP], gh = 0.0f;
-        load_row_uniform<RP>(Pb, row0 + min(t, nrows - 1), p);
+        float gh = 0.0f;
 #pragma unroll
-        for (int k = 0; k < RP; ++k) gh = fmaf(p[k], q[k], gh);
+        for (int k = 0; k < RP; ++k) gh = fmaf(p[t1 * RP + k], q[k], gh);
         m = m - gh;
         if (EMIT && ghat && mine) gptr<float>(ghat)[at] = update ? fmaf(-eta, gh, w[t]) : gh;
       }
@@ -530,13 +542,24 @@ __device__ __forceinline__ void narrow_rows(const float* __restrict__ G, float* 
   }
 }
 
+// Rows row0 .. rend of a wavefront; in sweep 0, whose loads are what it waits for, 16 at a time as long as there are as many.
+template <int RP, bool ADD, bool FUSE, bool HASM, bool EMIT, bool GB16, bool NTS>
+__device__ __forceinline__ void narrow_item(const float* __restrict__ G, float* __restrict__ M, const float* Q, const float* Pb,
+                                            float* __restrict__ Pp, float* __restrict__ ghat, int cols, int r, int row0, int rend,
+                                            int lane, int update, float eta) {
+  for (; ADD && row0 + 16 <= rend; row0 += 16)
+    narrow_rows<RP, 16, ADD, FUSE, HASM, EMIT, GB16, NTS>(G, M, Q, Pb, Pp, ghat, cols, r, row0, 16, lane, update, eta);
+  for (; row0 < rend; row0 += 8)
+    narrow_rows<RP, 8, ADD, FUSE, HASM, EMIT, GB16, NTS>(G, M, Q, Pb, Pp, ghat, cols, r, row0, min(8, rend - row0), lane, update, eta);
+}
+
 // FUSE: the residual update of the previous iteration has been deferred; the
 // buffer holds M_{t-1} and this sweep forms E_{t-1} = M_{t-1} - P-bar Q-bar^T on
 // the fly (Q-bar is the warm-start Q this sweep multiplies by anyway).
 // NTS: the residual slabs are streamed -- E (or last iteration's M) is read with the non-temporal
 // hint and M is written with non-temporal stores; chosen by the host from the size of the working set.
 template <int RP, bool FUSE, bool GB16, bool NTS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, LQSGD_A_WAVES))) void add_project_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) void add_project_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
   constexpr int RT = LQSGD_RT;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & (kWave - 1);
@@ -558,9 +581,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, LQSGD_A_
   else if (ld.kind == kRagged)
     add_project_tile<RP, RT, kRagged, FUSE, GB16, NTS>(G, M, Q, Pb, Pp, ld.cols, ld.r, tl.row0, tl.nrows, col0, col1, lane);
   else                                           // one segment
-    for (int i = 0; i < tl.nrows; i += 8)
-      narrow_rows<RP, 8, true, FUSE, true, false, GB16, NTS>(G, M, Q, Pb, Pp, nullptr, ld.cols, ld.r, tl.row0 + i,
-                                                             min(8, tl.nrows - i), lane, 0, 0.0f);
+    narrow_item<RP, true, FUSE, true, false, GB16, NTS>(G, M, Q, Pb, Pp, nullptr, ld.cols, ld.r, tl.row0, tl.row0 + tl.nrows, lane, 0, 0.0f);
 }
 
 // ---------------------------------------------------------------------------
@@ -1342,40 +1363,47 @@ __global__ __launch_bounds__(256) void exchange_kernel(DevArgs a, const XTile* _
 // wavefronts split the rows and their partial sums meet in LDS, where they are
 // added in wavefront order.
 // ---------------------------------------------------------------------------
+// Columns a lane of sweep 1 holds.
+template <int KIND>
+constexpr int lane_cols() { return KIND == kNarrow ? 1 : 4; }
 template <int RP, int KIND>
 __device__ __forceinline__ void back_project_rows(const float* __restrict__ M, const float* Pb, int cols,
-                                                  int ra, int rb, int c, float (&acc)[4 * RP]) {
-  constexpr int U = LQSGD_B_U;
+                                                  int ra, int rb, int c, float (&acc)[lane_cols<KIND>() * RP]) {
+  constexpr int U = LQSGD_B_U, V = lane_cols<KIND>();
   auto load = [&](int row) __attribute__((always_inline)) {
-    const char* p = reinterpret_cast<const char*>(M + (size_t)row * cols);
-    return ldedge<KIND, LQSGD_NT_M != 0, false>(p, c, cols);
+    const float* p = M + (size_t)row * cols;
+    if constexpr (V == 1) return Pk<1>{{gptr<float>(p)[c]}};
+    else return ldedge<KIND, LQSGD_NT_M != 0, false>(reinterpret_cast<const char*>(p), c, cols);
   };
   int i = ra;
   for (; i + U <= rb; i += U) {
-    Pk<4> m[U];
+    Pk<V> m[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) m[u] = load(i + u);
-    if (KIND != kAligned && c + 4 > cols) {
+    if constexpr (KIND == kRagged) {
+      if (c + 4 > cols) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) edge_fix<1>(m[u].v, c, cols);
+        for (int u = 0; u < U; ++u) edge_fix<1>(m[u].v, c, cols);
+      }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       float p[RP];
       load_row_uniform<RP>(Pb, i + u, p);
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
+      for (int v = 0; v < V; ++v)
 #pragma unroll
         for (int k = 0; k < RP; ++k) acc[v * RP + k] = fmaf(m[u].v[v], p[k], acc[v * RP + k]);
     }
   }
   for (; i < rb; ++i) {
-    Pk<4> m = load(i);
-    if (KIND != kAligned && c + 4 > cols) edge_fix<1>(m.v, c, cols);
+    Pk<V> m = load(i);
+    if constexpr (KIND == kRagged)
+      if (c + 4 > cols) edge_fix<1>(m.v, c, cols);
     float p[RP];
     load_row_uniform<RP>(Pb, i, p);
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
+    for (int v = 0; v < V; ++v)
 #pragma unroll
       for (int k = 0; k < RP; ++k) acc[v * RP + k] = fmaf(m.v[v], p[k], acc[v * RP + k]);
   }
@@ -1384,12 +1412,12 @@ __device__ __forceinline__ void back_project_rows(const float* __restrict__ M, c
 template <int RP, int KIND>
 __device__ __forceinline__ void back_project_tile(const DevArgs& a, const LayerDesc& ld, const Tile& tl, int layer, int worker,
                                                   float* comb, float* redmax, int wave, int lane) {
-  constexpr int NV = 4 * RP;
+  constexpr int V = lane_cols<KIND>(), NV = V * RP;
   const int cols = ld.cols, r = ld.r;
   const float* M = a.E + (size_t)worker * a.m_stride + ld.m_off;
   const float* Pb = p_operand(a, ld);
-  const int c0 = tl.aux * (kWave * 4);
-  const int c = c0 + lane * 4;
+  const int c0 = tl.aux * (kWave * 4);           // (one column per lane: one chunk)
+  const int c = c0 + lane * V;
   const bool active = c < cols;
   const int per = (tl.nrows + 3) >> 2;
   const int ra = min(tl.row0 + wave * per, tl.row0 + tl.nrows);
@@ -1420,9 +1448,14 @@ __device__ __forceinline__ void back_project_tile(const DevArgs& a, const LayerD
   // element in wavefront order: the chunk's slice of the factor is contiguous from column c0.
   {
     float* mine = comb + (size_t)wave * (kWave * NV) + lane * NV;
+    if constexpr (NV % 4 == 0) {
 #pragma unroll
-    for (int i = 0; i < NV / 4; ++i)
-      reinterpret_cast<float4*>(mine)[i] = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
+      for (int i = 0; i < NV / 4; ++i)
+        reinterpret_cast<float4*>(mine)[i] = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) mine[i] = acc[i];
+    }
   }
   __syncthreads();
   const int tid = wave * kWave + lane;
@@ -1490,7 +1523,7 @@ __device__ __forceinline__ void vector_mean_tile(const DevArgs& a, const VTile& 
 }
 
 template <int RP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, LQSGD_B_WAVES))) void back_project_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) void back_project_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles,
                                                            const VTile* __restrict__ vtiles, int reverse) {
   __shared__ __attribute__((aligned(16))) float comb[4 * kWave * 4 * RP];
   __shared__ float redmax[4];
@@ -1505,7 +1538,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, LQSGD_B_
   const LayerDesc& ld = a.layers[layer];
   if (ld.kind == kAligned)
     back_project_tile<RP, kAligned>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
-  else if (ld.cols >= 4)
+  else if (ld.kind != kOneColumnPerLane)
     back_project_tile<RP, kRagged>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
   else
     back_project_tile<RP, kNarrow>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
@@ -1779,10 +1812,15 @@ __device__ __forceinline__ void residual_tile(const DevArgs& a, const LayerDesc&
   float* M = a.E + (size_t)worker * a.m_stride + ld.m_off;
   const float* Pb = p_operand(a, ld);
   const int c = tl.aux * (kWave * 4) + lane * 4;
-  if (c >= cols) return;
   const int per = (tl.nrows + 3) >> 2;
   const int ra = min(tl.row0 + wave * per, tl.row0 + tl.nrows);
   const int rb = min(ra + per, tl.row0 + tl.nrows);
+  if constexpr (KIND == kNarrow) {
+    narrow_item<RP, false, false, MODE != kGhatOnly, MODE != kResidual, false, false>(nullptr, M, q_operand(a, ld), Pb, nullptr, ghat, cols,
+                                                                                      ld.r, ra, rb, lane, a.update, a.eta);
+    return;
+  }
+  if (c >= cols) return;
   float q[4 * RP];
   load_slice<RP>(q_operand(a, ld), KIND == kAligned ? c : edge_col(c, cols), q);
   if (KIND != kAligned && c + 4 > cols) edge_fix<RP>(q, c, cols);
@@ -1790,7 +1828,7 @@ __device__ __forceinline__ void residual_tile(const DevArgs& a, const LayerDesc&
 }
 
 template <int RP, int MODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MODE == kGhatOnly ? 8 : LQSGD_R_WAVES))) void residual_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) void residual_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & (kWave - 1);
   const Tile tl = tiles[reverse ? ntiles - 1 - blockIdx.x : blockIdx.x];
@@ -1801,7 +1839,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MODE == 
   if (MODE == kGhatOnly && !ghat) return;
   if (ld.kind == kAligned)
     residual_tile<RP, MODE, kAligned>(a, ld, tl, worker, ghat, wave, lane);
-  else if (ld.cols >= 4)
+  else if (ld.kind != kOneColumnPerLane)
     residual_tile<RP, MODE, kRagged>(a, ld, tl, worker, ghat, wave, lane);
   else
     residual_tile<RP, MODE, kNarrow>(a, ld, tl, worker, ghat, wave, lane);
@@ -2934,13 +2972,14 @@ static inline const char* tf(bool b) { return b ? "true" : "false"; }
     LQSGD_RP_SWITCH(RPV, CALL)
 
 #if LQSGD_HAS(1)
-hipError_t launch_add_project(int rp, const DevArgs& a, const Tile* tiles, int ntiles, int fuse_residual, int reverse,
-                              hipStream_t s) {
+hipError_t launch_add_project(int rp, const DevArgs& a, const Tile* tiles, int ntiles, int fuse_residual, int narrow_rows,
+                              int reverse, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   const dim3 grid((ntiles + 3) / 4), block(256);
+  const unsigned lds = narrow_rows ? 0 : kTwoPerCu;
 #define LQSGD_LAUNCH_A(FUSE, GB) \
-  if (a.nt_store) { LQSGD_RP_SWITCH8(rp, (add_project_kernel<RP, FUSE, GB, true><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); } \
-  else { LQSGD_RP_SWITCH8(rp, (add_project_kernel<RP, FUSE, GB, false><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); }
+  if (a.nt_store) { LQSGD_RP_SWITCH8(rp, (add_project_kernel<RP, FUSE, GB, true><<<grid, block, lds, s>>>(a, tiles, ntiles, reverse))); } \
+  else { LQSGD_RP_SWITCH8(rp, (add_project_kernel<RP, FUSE, GB, false><<<grid, block, lds, s>>>(a, tiles, ntiles, reverse))); }
   if (a.g_bf16) {
     if (fuse_residual) { LQSGD_LAUNCH_A(true, true) } else { LQSGD_LAUNCH_A(false, true) }
   } else if (fuse_residual) {
@@ -3253,12 +3292,14 @@ hipError_t launch_reduce_q(int phase, const DevArgs& a, const RTile* tiles, int 
 #endif
 
 #if LQSGD_HAS(1)
-hipError_t launch_residual(int rp, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s) {
+hipError_t launch_residual(int rp, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int narrow_rows, int reverse,
+                           hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   const dim3 grid(ntiles), block(256);
+  const unsigned lds = narrow_rows ? 0 : kThreePerCu;
   switch (mode) {
-    case kResidual: LQSGD_RP_SWITCH8(rp, (residual_kernel<RP, kResidual><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); break;
-    case kResidualGhat: LQSGD_RP_SWITCH8(rp, (residual_kernel<RP, kResidualGhat><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); break;
+    case kResidual: LQSGD_RP_SWITCH8(rp, (residual_kernel<RP, kResidual><<<grid, block, lds, s>>>(a, tiles, ntiles, reverse))); break;
+    case kResidualGhat: LQSGD_RP_SWITCH8(rp, (residual_kernel<RP, kResidualGhat><<<grid, block, lds, s>>>(a, tiles, ntiles, reverse))); break;
     case kGhatOnly: LQSGD_RP_SWITCH8(rp, (residual_kernel<RP, kGhatOnly><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse))); break;
     default: return hipErrorInvalidValue;
   }

@@ -155,6 +155,25 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
   // r = 20: 256 / 128 rows 35 / 23 us; on the ResNet-18 set at r = 32, 1794 items of 256, 85 / 90)
   const int64_t rbm_min = mfma_items(256, kMfmaCols) >= 512 ? 256 : mfma_items(128, kMfmaCols) >= 512 ? 128 : 64;
 
+  // sweep 0's column segments, and the items it would have with one group of rows in each
+  constexpr int cw = kWave * 4;                          // columns of a wavefront's pass over a row
+  const int rowgrp = mfma_a ? 32 : kRowsPerGroup;        // a matrix-core item is one 32-row tile
+  int64_t items0 = 0, narrow = 0;
+  for (LayerDesc& d : layers) {
+    const int64_t segmax = round_up(segmax4, cw);
+    const int nseg = (int)((d.cols + segmax - 1) / segmax);
+    d.segw = (int32_t)round_up((d.cols + nseg - 1) / nseg, cw);
+    d.nseg = (d.cols + d.segw - 1) / d.segw;
+    items0 += (int64_t)W * ((d.rows + rowgrp - 1) / rowgrp) * d.nseg;
+    if (d.cols < cw) narrow += (int64_t)d.rows * d.cols;
+  }
+  narrow_rows = 2 * narrow > matrix_elements;
+  // the residual sweep's items likewise, 32 rows each; layers of at most 64 columns take up to four times as many rows where
+  // the list is long (1000000 x 16 at r = 4, W = 8 1097 us with 32 rows and three wavefronts a SIMD, 680 with 128 and what the
+  // registers allow)
+  int64_t itemsR = 0;
+  for (const LayerDesc& d : layers) itemsR += (int64_t)W * ((d.rows + 31) / 32) * ((d.cols + cw - 1) / cw);
+
   int64_t m_acc = 0, p_acc = 0, q_acc = 0, pp_acc = 0, qp_acc = 0;
   int64_t mp_acc = 0, sp_acc = 0, mq_acc = 0, sq_acc = 0;
   int64_t ppd_acc = 0, qpd_acc = 0;
@@ -170,20 +189,26 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
   const int32_t rq_chunk = reduce_chunk(true), rp_chunk = reduce_chunk(false);
   for (int li = 0; li < L; ++li) {
     LayerDesc& d = layers[li];
-    constexpr int cw = kWave * 4;                        // columns of a wavefront's pass over a row
-    const int64_t segmax = round_up(segmax4, cw);
-    int nseg = (int)((d.cols + segmax - 1) / segmax);
-    d.segw = (int32_t)round_up((d.cols + nseg - 1) / nseg, cw);
-    d.nseg = (d.cols + d.segw - 1) / d.segw;
-    const int rowgrp = mfma_a ? 32 : kRowsPerGroup;      // a matrix-core item is one 32-row tile
-    // (counted in whole passes of 256 columns: a row of 21 costs a pass like one of 256, and a wavefront that takes a dozen
-    // groups of such rows one after the other is what a small set waits for: 1210 x 21 at r = 7, 60 -> 14 us)
-    const int64_t seg_elems = (int64_t)rowgrp * std::min<int64_t>(d.segw, round_up(d.cols, cw));
-    int64_t ng = mfma_a ? 1 : std::max<int64_t>(1, (tgtA + seg_elems / 2) / seg_elems);
+    // Groups of rows per item.  Counted in whole passes of 256 columns, a row of 21 costs a pass like one of 256, and a
+    // wavefront that takes a dozen groups of such rows one after the other is what a small set waits for (1210 x 21 at
+    // r = 7 45 -> 14 us).  With many times as many items as the chip holds wavefronts it is the set-up of an item that
+    // counts, and the elements decide (1000000 x 16 at r = 4, W = 8: one group 1560 us, 4 groups 1110, 20 groups 1030;
+    // 4 x (100000 x 16) 630 / 450 / 430): one group per 16384 items in between.
+    auto groups = [&](int64_t width) {
+      const int64_t e = (int64_t)rowgrp * width;
+      return std::max<int64_t>(1, (tgtA + e / 2) / e);
+    };
+    int64_t ng = 1;
+    if (!mfma_a) {
+      const int64_t lo = groups(std::min<int64_t>(d.segw, round_up(d.cols, cw))), hi = groups(std::min(d.segw, d.cols));
+      ng = std::min(hi, std::max(lo, items0 / 16384));
+    }
     const int32_t trows = (int32_t)std::min<int64_t>(round_up(d.rows, rowgrp), ng * rowgrp);
 
-    // sweeps 1 / 2 on the vector units: row blocks of rbb_v rows
-    int64_t rbb = std::max<int64_t>(4, round_up(std::max<int64_t>(1, tgtB / cw), 4));
+    // sweeps 1 / 2 on the vector units: row blocks of rbb_v rows (rows of one column per lane count 64 columns: 4 x (100000 x
+    // 21) at r = 4, W = 8, sweep 1 91 us and reduce 17 with 384 rows, 184 and 50 with 96)
+    const int64_t rowcols = d.kind == 2 ? kWave : cw;
+    int64_t rbb = std::max<int64_t>(4, round_up(std::max<int64_t>(1, tgtB / rowcols), 4));
     int32_t rbb_v = (int32_t)std::min<int64_t>(rbb, round_up(d.rows, 4));
     int32_t nrb_v = (d.rows + rbb_v - 1) / rbb_v;
     // equal blocks: 8192 rows in blocks of 1536 would end in a block of 512
@@ -194,7 +219,7 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
     // it streams as fast with 512-row items as with 128-row ones (63 us either way).
     // Not where that would leave the launch with too few items: at most four times the size the
     // work list aims for (a 1024-row layer of a small set keeps its row blocks).
-    if (!mfma && (int64_t)d.rows * cw <= env_i64("LQSGD_DIRECT_Q_MAX", 262144) && d.rows <= 4 * rbb) {
+    if (!mfma && (int64_t)d.rows * rowcols <= env_i64("LQSGD_DIRECT_Q_MAX", 262144) && d.rows <= 4 * rbb) {
       rbb_v = (int32_t)round_up(d.rows, 4);
       nrb_v = 1;
     }
@@ -237,13 +262,14 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
         for (int32_t ch = 0; ch < nchunk; ++ch)
           tilesB.push_back(Tile{lw, rb * rbb_v, std::min(rbb_v, d.rows - rb * rbb_v), ch});
       if (!mfma_a) {
-        const int32_t rbr = (int32_t)std::min<int64_t>(round_up(std::max<int64_t>(1, tgtR / cw), 4), round_up(d.rows, 4));
+        const int64_t rr = std::max<int64_t>(1, tgtR / cw) * (d.cols > kWave ? 1 : std::min<int64_t>(4, std::max<int64_t>(1, itemsR / 16384)));
+        const int32_t rbr = (int32_t)std::min<int64_t>(round_up(rr, 4), round_up(d.rows, 4));
         for (int32_t row0 = 0; row0 < d.rows; row0 += rbr)
           for (int32_t ch = 0; ch < nchunk; ++ch)
             tilesR.push_back(Tile{lw, row0, std::min(rbr, d.rows - row0), ch});
       }
       if (w == 0) {
-        const int32_t rbg = (int32_t)std::min<int64_t>(round_up(std::max<int64_t>(1, tgtG / cw), 4), round_up(d.rows, 4));
+        const int32_t rbg = (int32_t)std::min<int64_t>(round_up(std::max<int64_t>(1, tgtG / rowcols), 4), round_up(d.rows, 4));
         for (int32_t row0 = 0; row0 < d.rows; row0 += rbg)
           for (int32_t ch = 0; ch < nchunk; ++ch)
             tilesG.push_back(Tile{lw, row0, std::min(rbg, d.rows - row0), ch});

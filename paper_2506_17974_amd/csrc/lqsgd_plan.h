@@ -80,6 +80,7 @@ struct Plan {
   std::vector<RTile> tilesRQ;
   std::vector<RTile> tilesRP;      // aggregate-first order: reduce of the P partials (1024 elements each)
   bool agg_first = false;          // LQSGD_FLAG_AGGREGATE_FIRST
+  bool narrow_rows = false;        // most elements are in layers of fewer than 256 columns
   // Some layer has fewer ranks than the register pad: the sweeps then read P-bar and Q-bar from copies
   // whose rows are padded with zeros to RP ranks (aligned rows, no rank tests in the loops);
   // ppad_total / qpad_total floats.

@@ -160,3 +160,37 @@ def test_narrow_rows_sums_and_reconstructions(rank, eager):
             for w in range(W):
                 assert np.array_equal(comp.get_state(l, w)[0], E[w][l]), (l, w)
     comp.close()
+
+
+@pytest.mark.parametrize("rank", [1, 2, 7, 12])
+def test_tall_layers_of_few_columns(rank):
+    """Several row blocks and several groups of rows per item, one column per lane and four: two staged iterations against
+    the oracle, deferred and finished residuals bit for bit."""
+    import torch
+    _say("case: tall layers of few columns", rank)
+    rng = np.random.default_rng(rank)
+    layers, W = [(5003, 21), (2600, 7), (3001, 16), (40000, 3), (9000, 9), (1100, 61)], 2
+    ll, ml = B.layer_list(layers, ()), list(range(len(layers)))
+    Q0 = [rng.standard_normal((c, min(rank, n, c))).astype(f32) for n, c in layers]
+    Gs = [[[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)] for _ in range(3)]
+    comp = B.Compressor(ll, rank, 8, 8, W)
+    for l in ml:
+        comp.set_q(l, Q0[l])
+    E, Q, rep = [[np.zeros(s, f32) for s in layers] for _ in range(W)], [q.copy() for q in Q0], pu.StageReport()
+    for t in range(2):
+        E, Q = pu.staged_iteration(comp, Gs[t], pu.to_device(Gs[t]), E, Q, ml, rep)
+    comp.close()
+    _say("  ", rep)
+    outs = []
+    for flags in (0, B.FLAG_EAGER_RESIDUAL):
+        comp = B.Compressor(ll, rank, 8, 8, W, 255.0, flags)
+        for l in ml:
+            comp.set_q(l, Q0[l])
+        got, out = [], [torch.zeros(s, device="cuda") for s in layers]
+        for t in range(3):
+            comp.step(pu.to_device(Gs[t]), out)
+            got += [v.cpu().numpy() for v in out]
+        outs.append(got + [comp.get_state(l, w)[0] for l in ml for w in range(W)])
+        comp.close()
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)

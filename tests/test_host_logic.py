@@ -182,3 +182,18 @@ def test_header_is_plain_c(tmp_path):
                     "-L", libdir, "-l:" + os.path.basename(B.LIB_PATH), "-Wl,-rpath," + libdir], check=True)
     out = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split()
     assert out == ["0", "1", "1", str(64 * 576)]
+
+
+def test_sweep_0_items_of_narrow_layers():
+    """A small set of narrow layers has one group of 8 rows per item; a large one has as many groups as keep the list near
+    16384 items, and no more than a wider layer of as many elements would."""
+    small = B.layer_list([(240, 309), (1210, 21), (1628, 28)], ())
+    assert B.plan_tiles(small, 7, 8, 8, 7, 0)[:, 3].max() == 8
+    for layers, rank, W, most in (([(1000000, 16)], 4, 8, 60000), ([(100000, 16)] * 4, 4, 8, 40000), ([(100000, 21)] * 4, 4, 8, 40000),
+                                  ([(20000, 8)] * 4, 2, 4, 25000)):
+        tiles = B.plan_tiles(B.layer_list(layers, ()), rank, 8, 8, W, 0)
+        assert 8192 <= len(tiles) <= most, (layers, len(tiles))
+        cover = {}
+        for gidx, w, row0, nrows, col0, ncols in tiles.tolist():
+            cover[gidx, w] = cover.get((gidx, w), 0) + nrows * ncols
+        assert all(cover[l, w] == layers[l][0] * layers[l][1] for l in range(len(layers)) for w in range(W))
