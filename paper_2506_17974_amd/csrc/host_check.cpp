@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "lqsgd.h"
+#include "lqsgd_plan.h"
 
 static int failures = 0;
 #define EXPECT(cond)                                                         \
@@ -83,6 +84,22 @@ int main() {
     const lqsgd_config c = cfg(1 + (int)(rng() % 64), (int)(rng() % 9), (int)(rng() % 9), 1 + (int)(rng() % 64), 0.5f + (float)(rng() % 1000));
     EXPECT(lqsgd_plan_query(&c, ls.data(), n, &info) == LQSGD_OK);
     check_tiles(c, ls);
+  }
+  // ---- sets that fit the block of the entry point that allocates nothing, and must go on fitting ------
+  {
+    struct { int rank, bits, W; std::vector<lqsgd_layer> ls; } const fit[] = {
+        {32, 8, 4, {{2048, 2048, 0}}}, {50, 8, 4, {{2048, 2048, 0}}}, {32, 8, 1, {{4096, 4096, 0}}}, {32, 8, 8, {{1024, 2048, 0}}},
+        {32, 8, 4, std::vector<lqsgd_layer>(4, {1024, 1024, 0})}, {32, 8, 1, std::vector<lqsgd_layer>(4, {2048, 2048, 0})},
+        {64, 8, 1, std::vector<lqsgd_layer>(2, {2048, 2048, 0})}, {45, 8, 6, {{2634, 1596, 0}}}, {44, 8, 2, {{4278, 3388, 0}}},
+        {14, 8, 6, {{485, 60, 0}, {981, 11145, 0}}}, {15, 4, 9, {{459, 5749, 0}, {1153, 302, 0}, {2775, 707, 0}}},
+        {24, 4, 14, {{3783, 384, 0}}}, {8, 8, 8, resnet}};
+    for (const auto& f : fit) {
+      const lqsgd_config c = cfg(f.rank, f.bits, f.bits, f.W);
+      lqsgd::Plan p;
+      EXPECT(p.build(&c, f.ls.data(), (int32_t)f.ls.size()) == LQSGD_OK);
+      EXPECT(p.block_bytes() <= LQSGD_STATIC_SCRATCH_BYTES);
+      check_tiles(c, f.ls);
+    }
   }
   // ---- rejected configurations ---------------------------------------------------------------
   {

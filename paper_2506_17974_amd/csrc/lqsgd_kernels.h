@@ -99,9 +99,6 @@ hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, hipStream_t s)
 
 // The per-GPU scratch block of the entry point that allocates nothing: device address and size of
 // the block of `device`, which must be the current device on the first call for it.
-#ifndef LQSGD_STATIC_SCRATCH_BYTES
-#define LQSGD_STATIC_SCRATCH_BYTES (32u << 20)
-#endif
 hipError_t static_scratch(int device, void** ptr, size_t* bytes);
 // Clears `bytes` (a multiple of 16) at the 16-byte aligned device address p with a kernel.
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);

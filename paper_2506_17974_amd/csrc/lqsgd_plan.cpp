@@ -45,7 +45,33 @@ void quantiser_tables(int bits, double alpha, std::vector<float>& thr, std::vect
   lev[lv] = 1.0f;   // (1+alpha)^1 - 1 = alpha exactly: the top level is the scale itself
 }
 
+int64_t Plan::block_bytes() const {
+  auto granules = [](int64_t bytes) { return round_up(std::max<int64_t>(1, bytes), 256); };
+  const int64_t w = W, l = std::max(L, 1), slack = kFactorSlack, slices = (max_rows + 255) / 256;
+  int64_t n = 0;
+  n += granules(4 * (w * ppart_stride + slack)) + granules(4 * (w * qpart_stride + slack));
+  n += 2 * granules(4 * (w * p_stride + slack)) + granules(4 * (p_stride + slack)) + granules(4 * (w * q_stride + slack));
+  n += granules(4 * 2 * w * l * slices * RP);
+  if (slices >= 8 && RP >= 8) n += granules(4 * w * l * slices * RP * RP) + granules(4 * w * l);
+  n += granules(w * magp_stride) + granules(w * sgnp_stride) + granules(w * magq_stride) + granules(w * sgnq_stride);
+  n += 2 * granules(4 * w * l) + granules(4 * v_total) + granules(8 * w * n_all) + granules(8 * (int64_t)n_all);
+  n += granules(sizeof(LayerDesc) * L) + granules(sizeof(VecDesc) * V) + 4 * granules(4 * 256);
+  n += granules(sizeof(Tile) * tilesA.size()) + granules(sizeof(Tile) * tilesB.size()) + granules(sizeof(Tile) * tilesBM.size());
+  n += granules(sizeof(XTile) * tilesXP.size()) + granules(sizeof(XTile) * tilesXQ.size());
+  n += granules(sizeof(RTile) * tilesRQ.size()) + granules(sizeof(RTile) * tilesRP.size()) + granules(sizeof(VTile) * tilesV.size());
+  return n;
+}
+
+// The finer splits (small sets at rank pads 32 and 64; rows of more than 64 columns that are no multiple of four) have up to
+// four times the partial planes.  They are taken where the set still fits the block of the entry point that allocates nothing,
+// whose results are the context's to the last bit: the split decides their order of sums, so both take the same one.
 int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) {
+  const int rc = build_split(c, ls, n_layers, true);
+  if (rc || !fine_split || block_bytes() <= LQSGD_STATIC_SCRATCH_BYTES) return rc;
+  return build_split(c, ls, n_layers, false);
+}
+
+int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers, bool fine) {
   char buf[256];
   if (!c || !ls) { err = "NULL config or layer list"; return LQSGD_EINVAL; }
   if (n_layers < 1) { err = "n_layers must be >= 1"; return LQSGD_EINVAL; }
@@ -144,16 +170,23 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
   const int64_t tgtG = env_i64("LQSGD_TILE_G", std::min<int64_t>(tgtB, std::max<int64_t>(4096, matrix_elements / 2730)));
   // column segments: at most 1024 columns (2048 at rank pad 32, where fewer, longer segments save
   // more in partial planes and Gram-Schmidt input than they cost in sweep 0; 1024 there too where a small set would have
-  // fewer than four items of 32 rows per CU: ragged set at r = 20, sweep 0 59 -> 52 us, G-hat pass 14 -> 10)
+  // fewer than four items of 32 rows per CU.  Sweep 0, Gram-Schmidt and G-hat pass together, microseconds at 2048 / 1024: ragged
+  // set at r = 20 120 / 110, 1024 x 2048, W = 4, r = 32 121 / 104, 2 x 2048^2, W = 1, r = 64 265 / 236, 4096^2, W = 1, r = 32
+  // 155 / 157)
   auto mfma_items = [&](int64_t rows, int64_t cols) {
     int64_t n = 0;
     for (const LayerDesc& d : layers) n += W * ((d.rows + rows - 1) / rows) * ((d.cols + cols - 1) / cols);
     return n;
   };
-  const int64_t segmax4 = env_i64("LQSGD_SEGMAX", RP >= 32 && mfma_items(32, 2048) >= 1024 ? 2048 : 1024);
-  // row blocks of the matrix-core sweep 1: at least 256 rows, less where that leaves CUs without two items (ragged set at
-  // r = 20: 256 / 128 rows 35 / 23 us; on the ResNet-18 set at r = 32, 1794 items of 256, 85 / 90)
-  const int64_t rbm_min = mfma_items(256, kMfmaCols) >= 512 ? 256 : mfma_items(128, kMfmaCols) >= 512 ? 128 : 64;
+  const bool seg_fine = mfma && fine && mfma_items(32, 2048) < 1024;
+  const int64_t segmax4 = env_i64("LQSGD_SEGMAX", mfma && !seg_fine ? 2048 : 1024);
+  // Row blocks of the matrix-core sweep 1: 256 rows at least, 128 where that leaves CUs without two items, 64 where 128 leaves
+  // CUs without any.  Sweep 1 and its reduce, microseconds at 256 / 128 / 64 rows: 4 x 512^2, W = 2, r = 32 (16 items of 256 rows)
+  // 37 / 26 / 21; 2 x 2048^2, W = 1, r = 64 (64) 59 / 42 / 37; 1024 x 2048, W = 4, r = 32 (64) 39 / 30 / 27; 4096^2, W = 1, r = 32
+  // (128) 41 / 34 / 40; 4 x 1024^2, W = 4, r = 32 (128) 43 / 35 / 39; 2048^2, W = 4, r = 50 (128) 62 / 48 / 56; ragged set at
+  // r = 20 (132 items of 256, 248 of 128) 44 / 33 / 32; the ResNet-18 set at r = 32 (1794) sweep 1 85 / 90 at 256 / 128.
+  const int64_t rbm_min = !mfma || !fine || mfma_items(256, kMfmaCols) >= 512 ? 256 : mfma_items(128, kMfmaCols) >= 256 ? 128 : 64;
+  fine_split = seg_fine || rbm_min < 256;
 
   // sweep 0's column segments, and the items it would have with one group of rows in each
   constexpr int cw = kWave * 4;                          // columns of a wavefront's pass over a row
@@ -207,7 +240,8 @@ int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) 
 
     // sweeps 1 / 2 on the vector units: row blocks of rbb_v rows (rows of one column per lane count 64 columns: 4 x (100000 x
     // 21) at r = 4, W = 8, sweep 1 91 us and reduce 17 with 384 rows, 184 and 50 with 96)
-    const int64_t rowcols = d.kind == 2 ? kWave : cw;
+    const int64_t rowcols = d.kind == 2 || (d.kind == 1 && !fine) ? kWave : cw;
+    fine_split |= !mfma && d.kind == 1;
     int64_t rbb = std::max<int64_t>(4, round_up(std::max<int64_t>(1, tgtB / rowcols), 4));
     int32_t rbb_v = (int32_t)std::min<int64_t>(rbb, round_up(d.rows, 4));
     int32_t nrb_v = (d.rows + rbb_v - 1) / rbb_v;

@@ -18,6 +18,11 @@ constexpr int kXGroup = 8;         // elements one lane quantises / packs (b byt
 constexpr int kXBlockGroups = 32;  // groups of 8 elements one exchange workgroup covers
 constexpr int kFactorSlack = 64;   // readable floats after the last row of every factor buffer (loaders of ranks below their pad overrun)
 
+// Device memory of the entry point that allocates nothing (lqsgd_step_static), per GPU.
+#ifndef LQSGD_STATIC_SCRATCH_BYTES
+#define LQSGD_STATIC_SCRATCH_BYTES (32u << 20)
+#endif
+
 // One matrix layer as the kernels see it.  Offsets are in elements (floats)
 // from the start of a per-worker slab unless they say bytes.
 struct LayerDesc {
@@ -94,6 +99,13 @@ struct Plan {
 
   // Returns LQSGD_OK or a negative status with `err` set.
   int build(const lqsgd_config* cfg, const lqsgd_layer* layers, int32_t n_layers);
+
+  // Bytes of a caller-provided block that hold everything but the padded operand copies (an upper bound).
+  int64_t block_bytes() const;
+
+ private:
+  int build_split(const lqsgd_config* cfg, const lqsgd_layer* layers, int32_t n_layers, bool fine);
+  bool fine_split = false;         // sweeps 0 / 1 at rank pads 32 and 64: shorter segments or lower row blocks than usual
 };
 
 // Quantiser tables of Section 4.1 for one bit width, computed in double and

@@ -147,3 +147,11 @@ def test_step_static_matches_step_at_rank_pad_64(matrices, chol):
     E, Q = _fresh_state(matrices, 50, 2, rng)
     E, Q = _one_call(matrices, [], 50, 8, 2, 0, rng, E, Q, "rank pad 64")
     _one_call(matrices, [], 50, 0, 2, B.FLAG_AGGREGATE_FIRST, rng, E, Q, "rank pad 64, aggregate-first, no quantisation")
+
+
+@pytest.mark.parametrize("rank,W,matrices", [(32, 4, [(2048, 2048)]), (50, 4, [(2048, 2048)]), (32, 1, [(4096, 4096)]),
+                                             (32, 8, [(1024, 2048)]), (14, 6, [(485, 60), (981, 11145)])])
+def test_step_static_takes_sets_whose_finer_split_would_not_fit(rank, W, matrices):
+    rng = np.random.default_rng(rank + W)
+    E, Q = _fresh_state(matrices, rank, W, rng)
+    _one_call(matrices, [], rank, 8, W, 0, rng, E, Q, "partial planes near the size of the block")
