@@ -101,6 +101,15 @@ int main() {
       check_tiles(c, f.ls);
     }
   }
+  // (neither the operand copies nor the residual sweep's own items find room beside these, see tests/test_zz_no_alloc.py)
+  {
+    const std::vector<lqsgd_layer> tall(8, {2424, 24, 0});
+    const lqsgd_config c = cfg(7, 8, 8, 16);
+    lqsgd::Plan p;
+    EXPECT(p.build(&c, tall.data(), 8) == LQSGD_OK);
+    const int64_t left = LQSGD_STATIC_SCRATCH_BYTES - p.block_bytes();
+    EXPECT(p.padded && left >= 0 && 4 * (p.ppad_total + p.qpad_total) > left && (int64_t)(p.tilesR.size() * sizeof(lqsgd::Tile)) > left);
+  }
   // ---- rejected configurations ---------------------------------------------------------------
   {
     lqsgd_layer one = {256, 128, 0};

@@ -49,6 +49,8 @@ struct lqsgd_ctx {
   // (the context then owns no device memory at all).
   unsigned char* arena = nullptr;
   size_t arena_cap = 0, arena_used = 0;
+  unsigned char* operands = nullptr;   // ... and another for the padded operand copies that it has no room for
+  size_t operands_cap = 0;
   DevArgs args{};
   // device copies of the work lists
   Tile* d_tilesA = nullptr; Tile* d_tilesB = nullptr; Tile* d_tilesG = nullptr; Tile* d_tilesBM = nullptr; Tile* d_tilesAG = nullptr; Tile* d_tilesR = nullptr;
@@ -513,7 +515,7 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   if (!ext) TRY_(dev_alloc(c, &a.Qbar, (size_t)p.q_stride + kSlack, true));
   a.padded = p.padded ? 1 : 0;
   a.Pop = a.Pbar; a.Qop = a.Qbar;
-  if (p.padded) {
+  if (p.padded && !ext) {
     TRY_(dev_alloc(c, &a.Pop, (size_t)p.ppad_total + kSlack, true));
     TRY_(dev_alloc(c, &a.Qop, (size_t)p.qpad_total + kSlack, true));
   }
@@ -536,14 +538,32 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   TRY_(dev_upload(c, &thrQ, tQ)); TRY_(dev_upload(c, &levQ, lQ));
   TRY_(dev_upload(c, &c->d_tilesA, p.tilesA));
   TRY_(dev_upload(c, &c->d_tilesB, p.tilesB));
-  TRY_(dev_upload(c, &c->d_tilesG, p.tilesG));
   TRY_(dev_upload(c, &c->d_tilesBM, p.tilesBM));
-  TRY_(dev_upload(c, &c->d_tilesAG, p.tilesAG));
+  if (!ext) {                                    // (G-hat passes of deferred residuals)
+    TRY_(dev_upload(c, &c->d_tilesG, p.tilesG));
+    TRY_(dev_upload(c, &c->d_tilesAG, p.tilesAG));
+  }
   TRY_(dev_upload(c, &c->d_tilesXP, p.tilesXP));
   TRY_(dev_upload(c, &c->d_tilesXQ, p.tilesXQ));
   TRY_(dev_upload(c, &c->d_tilesRQ, p.tilesRQ));
   TRY_(dev_upload(c, &c->d_tilesRP, p.tilesRP));
   TRY_(dev_upload(c, &c->d_tilesV, p.tilesV));
+  if (p.padded && ext) {
+    auto copy_bytes = [](int64_t floats) { return (size_t)round_up(4 * (floats + kFactorSlack), 256); };
+    const size_t pb = copy_bytes(p.ppad_total), bytes = pb + copy_bytes(p.qpad_total);
+    unsigned char* at = c->operands;
+    if (bytes <= c->arena_cap - c->arena_used) {
+      at = c->arena + c->arena_used;
+      c->arena_used += bytes;
+    } else if (bytes > c->operands_cap) {
+      char buf[200];
+      std::snprintf(buf, sizeof buf, "this configuration needs more scratch memory than the static buffers hold (%zu bytes of operand copies)", bytes);
+      return fail(c, LQSGD_EUNSUPPORTED, buf);
+    }
+    a.Pop = reinterpret_cast<float*>(at);
+    a.Qop = reinterpret_cast<float*>(at + pb);
+    HIP_TRY(c, launch_fill_zero(at, bytes, c->stream));
+  }
   // (last: in a caller-provided block without room for it the residual sweep takes sweep 1's items, as good in everything but time)
   if (!p.mfma_a && (!ext || p.tilesR.size() * sizeof(Tile) + 256 <= c->arena_cap - c->arena_used)) TRY_(dev_upload(c, &c->d_tilesR, p.tilesR));
 #undef TRY_
@@ -945,10 +965,9 @@ int lqsgd_step_static(const lqsgd_config* cfg, const lqsgd_layer* layers, int32_
     if (e != hipSuccess) return fail_hip(nullptr, e, "hipGetDevice");
   }
   if (dev < 0 || dev >= kMaxDevices) return fail(nullptr, LQSGD_EUNSUPPORTED, "device index beyond the table of static scratch blocks");
-  void* block = nullptr;
-  size_t block_bytes = 0;
+  void *block = nullptr, *operands = nullptr;
   {
-    hipError_t e = static_scratch(dev, &block, &block_bytes);
+    hipError_t e = static_scratch(dev, &block, &operands);
     if (e != hipSuccess) return fail_hip(nullptr, e, "hipGetSymbolAddress(scratch)");
   }
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
@@ -971,7 +990,9 @@ int lqsgd_step_static(const lqsgd_config* cfg, const lqsgd_layer* layers, int32_
     }
     c->stream = stream;
     c->arena = static_cast<unsigned char*>(block);
-    c->arena_cap = block_bytes;
+    c->arena_cap = LQSGD_STATIC_SCRATCH_BYTES;
+    c->operands = static_cast<unsigned char*>(operands);
+    c->operands_cap = LQSGD_STATIC_OPERAND_BYTES;
     if ((rc = setup_device(c, cfg->flags))) {
       g_create_error = c->err;
       delete c;

@@ -97,9 +97,9 @@ hipError_t launch_residual(int RP, int mode, const DevArgs& a, const Tile* tiles
 // this is for a factor that came another way).
 hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, hipStream_t s);
 
-// The per-GPU scratch block of the entry point that allocates nothing: device address and size of
-// the block of `device`, which must be the current device on the first call for it.
-hipError_t static_scratch(int device, void** ptr, size_t* bytes);
+// The per-GPU blocks of the entry point that allocates nothing, scratch and operand copies: device addresses of
+// those of `device`, which must be the current device on the first call for it.
+hipError_t static_scratch(int device, void** scratch, void** operands);
 // Clears `bytes` (a multiple of 16) at the 16-byte aligned device address p with a kernel.
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 

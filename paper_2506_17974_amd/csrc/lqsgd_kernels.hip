@@ -37,10 +37,11 @@
 #endif
 
 #if LQSGD_HAS(0)
-// Scratch block of lqsgd_step_static (see static_scratch() below): device memory that is part of
-// the code object, one copy per GPU.  In host code this name is a handle for hipGetSymbolAddress,
-// never an address.
+// Blocks of lqsgd_step_static (see static_scratch() below): device memory that is part of
+// the code object, one copy per GPU.  In host code these names are handles for hipGetSymbolAddress,
+// never addresses.
 static __device__ __align__(256) unsigned char scratch[LQSGD_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char operands[LQSGD_STATIC_OPERAND_BYTES];
 #endif
 
 namespace lqsgd {
@@ -3365,25 +3366,25 @@ hipError_t launch_mfma_sweep(int rp, int mode, const DevArgs& a, const Tile* til
 // device and that address is what kernels and copies use.  (The array itself
 // is defined at file scope, at the top of this file.)
 // ---------------------------------------------------------------------------
-constexpr size_t kStaticScratchBytes = (size_t)LQSGD_STATIC_SCRATCH_BYTES;
 
-hipError_t static_scratch(int device, void** ptr, size_t* bytes) {
+hipError_t static_scratch(int device, void** scratch_ptr, void** operands_ptr) {
   constexpr int kMaxDev = 64;
-  static void* addr[kMaxDev] = {};              // per device; the caller serialises calls
+  static void* addr[kMaxDev][2] = {};           // per device; the caller serialises calls
   if (device < 0 || device >= kMaxDev) return hipErrorInvalidDevice;
-  if (!addr[device]) {
+  if (!addr[device][1]) {
     int cur = -1;
     hipError_t e = hipGetDevice(&cur);
     if (e != hipSuccess) return e;
     if (cur != device) return hipErrorInvalidDevice;     // the address belongs to the device that is current
-    void* p = nullptr;
-    e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (e != hipSuccess) return e;
-    if (!p) return hipErrorInvalidSymbol;
-    addr[device] = p;
+    void *p = nullptr, *q = nullptr;
+    if ((e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch))) != hipSuccess) return e;
+    if ((e = hipGetSymbolAddress(&q, HIP_SYMBOL(operands))) != hipSuccess) return e;
+    if (!p || !q) return hipErrorInvalidSymbol;
+    addr[device][0] = p;
+    addr[device][1] = q;
   }
-  *ptr = addr[device];
-  *bytes = kStaticScratchBytes;
+  *scratch_ptr = addr[device][0];
+  *operands_ptr = addr[device][1];
   return hipSuccess;
 }
 

@@ -22,6 +22,11 @@ constexpr int kFactorSlack = 64;   // readable floats after the last row of ever
 #ifndef LQSGD_STATIC_SCRATCH_BYTES
 #define LQSGD_STATIC_SCRATCH_BYTES (32u << 20)
 #endif
+// ... and of the padded operand copies (Plan::padded) where that block has no room left for them.  Where the layers' ranks
+// are more than half their register pad, the copies are at most twice what the block already holds of the same factors.
+#ifndef LQSGD_STATIC_OPERAND_BYTES
+#define LQSGD_STATIC_OPERAND_BYTES (64u << 20)
+#endif
 
 // One matrix layer as the kernels see it.  Offsets are in elements (floats)
 // from the start of a per-worker slab unless they say bytes.

@@ -155,3 +155,16 @@ def test_step_static_takes_sets_whose_finer_split_would_not_fit(rank, W, matrice
     rng = np.random.default_rng(rank + W)
     E, Q = _fresh_state(matrices, rank, W, rng)
     _one_call(matrices, [], rank, 8, W, 0, rng, E, Q, "partial planes near the size of the block")
+
+
+def test_step_static_in_a_block_without_room_for_copies_and_residual_items():
+    """Operand copies go to the second block and the residual sweep runs over sweep 1's items (csrc/host_check.cpp pins that
+    this set leaves no room for either); a smaller set in between lays both blocks out anew."""
+    rng = np.random.default_rng(24)
+    full = [(2424, 24)] * 8
+    E, Q = _fresh_state(full, 7, 16, rng)
+    E, Q = _one_call(full, [], 7, 8, 16, 0, rng, E, Q, "full block")
+    small = [(200, 100), (64, 27)]
+    Es, Qs = _fresh_state(small, 3, 2, rng)
+    _one_call(small, [], 3, 8, 2, 0, rng, Es, Qs, "copies in the first block")
+    _one_call(full, [], 7, 8, 16, 0, rng, E, Q, "full block again")
