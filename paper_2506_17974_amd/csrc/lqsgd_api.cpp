@@ -226,8 +226,8 @@ int next_dir(lqsgd_ctx* c) {
 // The sweeps read P-bar and Q-bar from copies with padded rows when some layer has fewer ranks than the register
 // pad.  The exchange writes factor and copy together; every other writer of a factor calls this right after it, so a
 // copy is never older than its factor, also between the replays of captured steps.
-int refresh_padded(lqsgd_ctx* c, int which) {
-  if (c->plan.padded) HIP_TRY(c, launch_pad_factor(c->plan.RP, which, c->args, c->stream));
+int refresh_padded(lqsgd_ctx* c, int which, int layer, int n) {
+  if (c->plan.padded) HIP_TRY(c, launch_pad_factor(c->plan.RP, which, c->args, layer, n, c->stream));
   return LQSGD_OK;
 }
 
@@ -265,7 +265,7 @@ int run_orth_shared(lqsgd_ctx* c) {
   a.Ppre = c->args.Porth;
   a.Porth = c->args.Pbar;
   HIP_TRY(c, launch_orth(c->plan.RP, c->plan.max_rows, c->plan.max_rank, a, coop_state(c), c->stream));
-  return refresh_padded(c, 0);
+  return refresh_padded(c, 0, 0, c->plan.L);
 }
 int run_exchange(lqsgd_ctx* c, int mode, int phase) {
   { Timed t(c, phase ? LQSGD_KERNEL_EXCHANGE_Q : LQSGD_KERNEL_EXCHANGE_P);
@@ -659,7 +659,7 @@ int lqsgd_set_state(lqsgd_ctx* c, int32_t layer, int32_t worker, const float* ho
                          (size_t)ld->rows * ld->cols * sizeof(float), hipMemcpyHostToDevice));
   if (host_q) {
     HIP_TRY(c, hipMemcpy(c->args.Qbar + ld->q_off, host_q, (size_t)ld->nq_el * sizeof(float), hipMemcpyHostToDevice));
-    return refresh_padded(c, 1);
+    return refresh_padded(c, 1, c->plan.kind_of[layer], 1);
   }
   return LQSGD_OK;
 }
@@ -883,7 +883,7 @@ int lqsgd_set_factor(lqsgd_ctx* c, int32_t which, int32_t layer, const float* ho
   if ((rc = materialise(c))) return rc;      // a deferred update is defined by the old factors
   if (int rcs = sync_stream(c)) return rcs;
   HIP_TRY(c, hipMemcpy(dst, host, n * sizeof(float), hipMemcpyHostToDevice));
-  return refresh_padded(c, which == LQSGD_FACTOR_P_BAR ? 0 : 1);
+  return refresh_padded(c, which == LQSGD_FACTOR_P_BAR ? 0 : 1, c->plan.kind_of[layer], 1);
 }
 
 int64_t lqsgd_wire_bytes(const lqsgd_ctx* c) { return c ? c->plan.wire_bytes : (int64_t)LQSGD_EINVAL; }
@@ -1014,7 +1014,7 @@ int lqsgd_step_static(const lqsgd_config* cfg, const lqsgd_layer* layers, int32_
   if (!c->plan.padded) c->args.Qop = warm_q;
   c->pending = false;                        // the caller's buffer holds E, and holds E again on return
   c->state = kIdle;
-  int rc = refresh_padded(c, 1);             // the warm-start Q is the caller's
+  int rc = refresh_padded(c, 1, 0, c->plan.L);   // the warm-start Q is the caller's
   if (!rc) rc = step_impl(c, grads, ghat);
   if (rc) g_create_error = c->err;
   return rc;

@@ -93,9 +93,9 @@ hipError_t launch_residual(int RP, int mode, const DevArgs& a, const Tile* tiles
 // Sweeps 0 and 2 on the matrix cores (rank pad 16, 32 or 64), over the work list of
 // sweep 0 (32-row items).  mode: 0 = M = G + E and P partials, 1 = the same with the deferred
 // residual applied on the fly, 2 = residual, 3 = residual + G-hat, 4 = G-hat only (worker 0's items).
-// Refreshes the copy a.Pop (which = 0) or a.Qop (which = 1) from the tightly packed factor (the exchange writes both at once;
-// this is for a factor that came another way).
-hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, hipStream_t s);
+// Refreshes the copy a.Pop (which = 0) or a.Qop (which = 1) of n layers from `layer` on from the tightly packed factor (the
+// exchange writes both at once; this is for a factor that came another way).
+hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, int layer, int n, hipStream_t s);
 
 // The per-GPU blocks of the entry point that allocates nothing, scratch and operand copies: device addresses of
 // those of `device`, which must be the current device on the first call for it.

@@ -194,3 +194,35 @@ def test_tall_layers_of_few_columns(rank):
         comp.close()
     for a, b in zip(*outs):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("rank", [3, 20])
+def test_factors_set_layer_by_layer(rank):
+    """Q and P-bar set for single layers, in any order, in a list whose 1-D tensors shift the matrix layers: the sweeps read
+    what was set (ranks below their pad: from copies)."""
+    import torch
+    _say("case: factors set layer by layer", rank)
+    rng = np.random.default_rng(rank)
+    layers, W = [(7, 1, B.LAYER_VECTOR), (200, 100, 0), (33, 1, B.LAYER_VECTOR), (64, 27, 0), (300, 130, 0)], 2
+    ml = [1, 3, 4]
+    comp = B.Compressor(layers, rank, 0, 0, W)
+    G = [[(rng.standard_normal((n, c)[:1 if f else 2]) * 1e-3).astype(f32) for n, c, f in layers] for _ in range(W)]
+    for rep in range(2):
+        Q = {l: rng.standard_normal((layers[l][1], min(rank, *layers[l][:2]))).astype(f32) for l in ml}
+        for l in (4, 1, 3):
+            comp.set_q(l, Q[l])
+        E = {(l, w): comp.get_state(l, w)[0] for l in ml for w in range(W)}
+        comp.compress(B.PHASE_P, pu.to_device(G))
+        for l in ml:
+            for w in range(W):
+                assert pu.rel_fro(comp.get_factor(B.FACTOR_P_PRE, l, w), (G[w][l] + E[l, w]) @ Q[l]) < pu.FP_TOL
+        comp.decompress(B.PHASE_P)
+        P = {l: rng.standard_normal((layers[l][0], Q[l].shape[1])).astype(f32) for l in ml}
+        for l in (3, 4, 1):
+            comp.set_factor(B.FACTOR_P_BAR, l, P[l])
+        comp.compress(B.PHASE_Q)
+        for l in ml:
+            for w in range(W):
+                assert pu.rel_fro(comp.get_factor(B.FACTOR_Q_W, l, w), (G[w][l] + E[l, w]).T @ P[l]) < pu.FP_TOL
+        comp.decompress(B.PHASE_Q)
+    comp.close()
