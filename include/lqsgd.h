@@ -184,9 +184,11 @@ int lqsgd_set_state(lqsgd_ctx* ctx, int32_t layer, int32_t worker, const float* 
  * grads[w * n_layers + l] -> fp32 tensor of layer l on worker w, 16-byte
  * aligned, read-only.  The pointer values are copied; the array itself need
  * not outlive the call.  The context keeps a device copy of the list: a call
- * whose list (or G-hat / parameter list) differs from the previous call's waits
- * for the context's stream, then copies the new list to the device
- * (synchronously); a call that repeats the previous lists only enqueues kernels.
+ * whose list (or G-hat / parameter list) differs from the previous call's has
+ * the new one written there in stream order, by a kernel that carries it in its
+ * arguments; beyond 1792 pointers it waits for the context's stream and copies
+ * the list synchronously.  While the stream is being captured a list cannot
+ * change: the call returns EHIP and records nothing.
  *
  * lqsgd_compress(PHASE_P, grads): for every matrix layer and worker
  *     M_w = G_w + E_w (kept in the context, Eq. (9)); P_w = M_w Q;
@@ -268,8 +270,8 @@ int lqsgd_step_update(lqsgd_ctx* ctx, const float* const* grads, float* const* p
  * The first call with a configuration (or stream) other than the previous
  * call's on that GPU waits for the previous call's stream, lays the block out
  * anew and copies its tables in with synchronous copies; calls that repeat the
- * previous configuration only enqueue kernels (plus one small copy when the
- * pointer lists change).  All calls on a GPU share that GPU's block: two calls
+ * previous configuration only enqueue kernels (pointer lists that change are
+ * handled as in lqsgd_compress).  All calls on a GPU share that GPU's block: two calls
  * whose work overlaps in time -- different streams, or different threads --
  * race; a caller that uses more than one stream orders them itself.  The
  * Gram-Schmidt of tall factors takes its form of several ordinary launches here.

@@ -168,13 +168,18 @@ int check_worker(lqsgd_ctx* c, int32_t worker) {
 }
 
 // Copies a pointer list to its device table, which launches already enqueued may still be reading.  Short lists go
-// there in stream order (ResNet-18 set, W = 8, other buffers every step: the wait and the two copies cost 60 us a step);
-// long ones, and any list that changes while the stream is being captured, after a wait, as a captured copy would
-// bring this call's pointers back at every replay.
-int upload_pointers(lqsgd_ctx* c, const void** dst, const void* const* src, size_t n) {
+// there in stream order (ResNet-18 set, W = 8, other buffers every step: the wait and the two copies cost 60 us a step),
+// long ones after a wait.  A list cannot change while the stream is being captured: a captured copy would bring this
+// call's pointers back at every replay, and a wait would end the capture.  Such a call is refused before it touches
+// the stream, and the list that is bound stays bound.  *valid: whether the table holds the host's copy of the list.
+int upload_pointers(lqsgd_ctx* c, const void** dst, const void* const* src, size_t n, bool* valid) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusActive; }
-  if (cap == hipStreamCaptureStatusNone && n <= 4 * (size_t)kPointerBatch) {
+  const bool known = hipStreamIsCapturing(c->stream, &cap) == hipSuccess;
+  if (!known) (void)hipGetLastError();
+  if (known && cap != hipStreamCaptureStatusNone)
+    return fail(c, LQSGD_EHIP, "the pointer lists of a call that is being captured must have been used in an ordinary call before");
+  *valid = false;
+  if (known && n <= 4 * (size_t)kPointerBatch) {
     HIP_TRY(c, launch_write_pointers(dst, src, n, c->stream));
     return LQSGD_OK;
   }
@@ -191,8 +196,7 @@ int bind_grads(lqsgd_ctx* c, const float* const* grads) {
     if (reinterpret_cast<uintptr_t>(grads[i]) & 15u) return fail(c, LQSGD_EINVAL, "gradient pointer not 16-byte aligned");
   }
   if (c->grads_valid && std::memcmp(c->h_grads.data(), grads, n * sizeof(float*)) == 0) return LQSGD_OK;
-  c->grads_valid = false;
-  if (int rc = upload_pointers(c, reinterpret_cast<const void**>(c->d_grads), reinterpret_cast<const void* const*>(grads), n)) return rc;
+  if (int rc = upload_pointers(c, reinterpret_cast<const void**>(c->d_grads), reinterpret_cast<const void* const*>(grads), n, &c->grads_valid)) return rc;
   c->h_grads.assign(grads, grads + n);
   c->grads_valid = true;
   c->alias_checked = false;
@@ -206,8 +210,7 @@ int bind_ghat(lqsgd_ctx* c, float* const* ghat) {
     if (ghat[i] && (reinterpret_cast<uintptr_t>(ghat[i]) & 15u))
       return fail(c, LQSGD_EINVAL, "G-hat pointer not 16-byte aligned");
   if (!(c->ghat_valid && std::memcmp(c->h_ghat.data(), ghat, n * sizeof(float*)) == 0)) {
-    c->ghat_valid = false;
-    if (int rc = upload_pointers(c, const_cast<const void**>(reinterpret_cast<void**>(c->d_ghat)), reinterpret_cast<const void* const*>(ghat), n)) return rc;
+    if (int rc = upload_pointers(c, const_cast<const void**>(reinterpret_cast<void**>(c->d_ghat)), reinterpret_cast<const void* const*>(ghat), n, &c->ghat_valid)) return rc;
     c->h_ghat.assign(ghat, ghat + n);
     c->ghat_valid = true;
     c->alias_checked = false;

@@ -226,3 +226,87 @@ def test_factors_set_layer_by_layer(rank):
                 assert pu.rel_fro(comp.get_factor(B.FACTOR_Q_W, l, w), (G[w][l] + E[l, w]).T @ P[l]) < pu.FP_TOL
         comp.decompress(B.PHASE_Q)
     comp.close()
+
+
+@pytest.mark.parametrize("tensors,W", [(130, 2), (300, 7)])
+def test_pointer_lists_that_change_from_step_to_step(tensors, W):
+    """Other buffers in every step, in lists that go to the device in stream order and in lists (of 2100 pointers) that are
+    copied after a wait, give what the same values in the same buffers give."""
+    import torch
+    _say("case: pointer lists", tensors, W)
+    rng = np.random.default_rng(tensors)
+    layers = [(16 + i % 5, 12 + i % 7) for i in range(tensors)]
+    Q = [rng.standard_normal((c, 3)).astype(f32) for _, c in layers]
+    G = [[[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)] for _ in range(3)]
+    outs = []
+    for change in (False, True):
+        comp = B.Compressor(B.layer_list(layers, ()), 3, 8, 8, W)
+        for l, q in enumerate(Q):
+            comp.set_q(l, q)
+        bufs, out = pu.to_device(G[0]), [torch.zeros(s, device="cuda") for s in layers]
+        keep, got = [bufs, out], []
+        for t in range(3):
+            if change:
+                bufs, out = pu.to_device(G[t]), [torch.zeros(s, device="cuda") for s in layers]
+                keep += [bufs, out]
+            else:
+                for w in range(W):
+                    for b, g in zip(bufs[w], G[t][w]):
+                        b.copy_(torch.from_numpy(g))
+            comp.step(bufs, out)
+            got.append(torch.cat([o.reshape(-1) for o in out]))
+        outs.append([g.cpu().numpy() for g in got])
+        comp.close()
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("rank,layers", [(3, [(200, 100), (64, 27)]), (7, [(300, 130), (97, 515)]), (2, [(40, 60), (1, 9)])])
+def test_capture_below_the_rank_pad_and_with_other_pointers(rank, layers):
+    """A step of the vector sweeps with padded operand copies, recorded and replayed with eager work in between; a recording
+    call with other pointers is refused, and neither the capture nor the bound list suffers."""
+    import torch
+    _say("case: capture", rank, layers)
+    rng, W = np.random.default_rng(rank), 2
+    ll = B.layer_list(layers, ())
+    s = torch.cuda.Stream()
+    rec, ref = B.Compressor(ll, rank, 8, 8, W, 255.0, 0, stream=s.cuda_stream), B.Compressor(ll, rank, 8, 8, W)
+    for l, (n, c) in enumerate(layers):
+        q = rng.standard_normal((c, min(rank, n, c))).astype(f32)
+        rec.set_q(l, q)
+        ref.set_q(l, q)
+
+    def values():
+        return [[(rng.standard_normal(sh) * 1e-3).astype(f32) for sh in layers] for _ in range(W)]
+
+    buf, out, out_ref = pu.to_device(values()), [torch.zeros(sh, device="cuda") for sh in layers], [torch.zeros(sh, device="cuda") for sh in layers]
+    other = pu.to_device(values())
+    torch.cuda.synchronize()
+    for _ in range(2):
+        rec.step(buf, out)
+        ref.step(buf, out_ref)
+        rec.synchronize()
+        ref.synchronize()
+    import ctypes as C
+    tab, tab_other, gt = rec.pointer_table(buf), rec.pointer_table(other), (C.c_void_p * len(layers))(*[t.data_ptr() for t in out])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        with pytest.raises(B.LqsgdError) as ei:
+            rec.step_raw(tab_other, gt)
+        assert ei.value.code == B.EHIP
+        rec.step_raw(tab, gt)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for b, g in zip(buf, values()):
+            for x, y in zip(b, g):
+                x.copy_(torch.from_numpy(y))
+        torch.randn(1 << 16, device="cuda").sum()          # unrelated eager work between replays
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        ref.step(buf, out_ref)
+        ref.synchronize()
+        for a, b in zip(out, out_ref):
+            assert torch.equal(a, b)
+    rec.close()
+    ref.close()
