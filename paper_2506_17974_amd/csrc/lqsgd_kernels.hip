@@ -50,7 +50,6 @@ namespace {
 // ---------------------------------------------------------------------------
 // small helpers
 // ---------------------------------------------------------------------------
-typedef float v4f __attribute__((ext_vector_type(4)));
 // Loads through a pointer in the constant address space are assumed not to
 // change while the kernel runs; with a wave-uniform address they become
 // scalar loads (one fetch per wavefront, no vector register traffic).  Used
@@ -309,11 +308,6 @@ __device__ __forceinline__ void transpose_reduce(float (&v)[NT], int lane) {
   }
 }
 
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, kWave);
-  return x;
-}
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) x = fmaxf(x, __shfl_xor(x, off, kWave));
@@ -321,7 +315,6 @@ __device__ __forceinline__ float wave_max(float x) {
 }
 
 constexpr int log2c(int n) { return n <= 1 ? 0 : 1 + log2c(n / 2); }
-constexpr int pow2ceil(int n) { return n <= 1 ? 1 : 2 * pow2ceil((n + 1) / 2); }
 
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order.
 template <int N, int I = 0, typename F>
@@ -471,7 +464,7 @@ __device__ __forceinline__ void add_project_tile(const float* __restrict__ G, fl
 // columns per lane and one: sweep 0 407 and 299 us, sweep 1 169 and 73, finished residual 593 and 184.
 // `nrows` rows from row0 on, at most R; ADD: M = G + E and the P partials; FUSE: E is still last iteration's M;
 // EMIT: G-hat goes out.  ADD is false in the sweeps that only finish E (HASM) or only write G-hat.
-template <int RP, int R, bool ADD, bool FUSE, bool HASM, bool EMIT, bool GB16, bool NTS>
+template <int RP, int R, bool ADD, bool FUSE, bool HASM, bool EMIT, bool GB16>
 __device__ __forceinline__ void narrow_rows(const float* __restrict__ G, float* __restrict__ M, const float* Q, const float* Pb,
                                             float* __restrict__ Pp, float* __restrict__ ghat, int cols, int r, int row0, int nrows,
                                             int lane, int update, float eta) {
@@ -544,14 +537,14 @@ __device__ __forceinline__ void narrow_rows(const float* __restrict__ G, float* 
 }
 
 // Rows row0 .. rend of a wavefront; in sweep 0, whose loads are what it waits for, 16 at a time as long as there are as many.
-template <int RP, bool ADD, bool FUSE, bool HASM, bool EMIT, bool GB16, bool NTS>
+template <int RP, bool ADD, bool FUSE, bool HASM, bool EMIT, bool GB16>
 __device__ __forceinline__ void narrow_item(const float* __restrict__ G, float* __restrict__ M, const float* Q, const float* Pb,
                                             float* __restrict__ Pp, float* __restrict__ ghat, int cols, int r, int row0, int rend,
                                             int lane, int update, float eta) {
   for (; ADD && row0 + 16 <= rend; row0 += 16)
-    narrow_rows<RP, 16, ADD, FUSE, HASM, EMIT, GB16, NTS>(G, M, Q, Pb, Pp, ghat, cols, r, row0, 16, lane, update, eta);
+    narrow_rows<RP, 16, ADD, FUSE, HASM, EMIT, GB16>(G, M, Q, Pb, Pp, ghat, cols, r, row0, 16, lane, update, eta);
   for (; row0 < rend; row0 += 8)
-    narrow_rows<RP, 8, ADD, FUSE, HASM, EMIT, GB16, NTS>(G, M, Q, Pb, Pp, ghat, cols, r, row0, min(8, rend - row0), lane, update, eta);
+    narrow_rows<RP, 8, ADD, FUSE, HASM, EMIT, GB16>(G, M, Q, Pb, Pp, ghat, cols, r, row0, min(8, rend - row0), lane, update, eta);
 }
 
 // FUSE: the residual update of the previous iteration has been deferred; the
@@ -582,7 +575,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) voi
   else if (ld.kind == kRagged)
     add_project_tile<RP, RT, kRagged, FUSE, GB16, NTS>(G, M, Q, Pb, Pp, ld.cols, ld.r, tl.row0, tl.nrows, col0, col1, lane);
   else                                           // one segment
-    narrow_item<RP, true, FUSE, true, false, GB16, NTS>(G, M, Q, Pb, Pp, nullptr, ld.cols, ld.r, tl.row0, tl.row0 + tl.nrows, lane, 0, 0.0f);
+    narrow_item<RP, true, FUSE, true, false, GB16>(G, M, Q, Pb, Pp, nullptr, ld.cols, ld.r, tl.row0, tl.row0 + tl.nrows, lane, 0, 0.0f);
 }
 
 // ---------------------------------------------------------------------------
@@ -1817,8 +1810,8 @@ __device__ __forceinline__ void residual_tile(const DevArgs& a, const LayerDesc&
   const int ra = min(tl.row0 + wave * per, tl.row0 + tl.nrows);
   const int rb = min(ra + per, tl.row0 + tl.nrows);
   if constexpr (KIND == kNarrow) {
-    narrow_item<RP, false, false, MODE != kGhatOnly, MODE != kResidual, false, false>(nullptr, M, q_operand(a, ld), Pb, nullptr, ghat, cols,
-                                                                                      ld.r, ra, rb, lane, a.update, a.eta);
+    narrow_item<RP, false, false, MODE != kGhatOnly, MODE != kResidual, false>(nullptr, M, q_operand(a, ld), Pb, nullptr, ghat, cols,
+                                                                               ld.r, ra, rb, lane, a.update, a.eta);
     return;
   }
   if (c >= cols) return;
@@ -2407,7 +2400,7 @@ __global__ __launch_bounds__(256, RP <= 16 ? 2 : 1) void mfma_sweep_kernel(DevAr
     constexpr bool ADD = MODE == kMAdd || MODE == kMAddFused;
     const int nr = min(8, tl.nrows - 8 * wave);
     if (nr > 0)
-      narrow_rows<RP, 8, ADD, MODE == kMAddFused, MODE != kMGhatOnly, MODE == kMResidualGhat || MODE == kMGhatOnly, GB16, NTS>(
+      narrow_rows<RP, 8, ADD, MODE == kMAddFused, MODE != kMGhatOnly, MODE == kMResidualGhat || MODE == kMGhatOnly, GB16>(
           G, M, q_operand(a, ld), p_operand(a, ld), Pp, ghat_out, ld.cols, ld.r, tl.row0 + 8 * wave, nr, lane, a.update, a.eta);
     return;
   }
@@ -2432,8 +2425,8 @@ __global__ __launch_bounds__(512, 2) void mfma_sweep32_kernel(DevArgs a, const T
   if (ld.kind == kOneColumnPerLane) {            // four of the item's rows per wavefront
     const int nr = min(4, tl.nrows - 4 * wave);
     if (nr > 0)
-      narrow_rows<RP, 4, true, MODE == kMAddFused, true, false, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, nullptr,
-                                                                           ld.cols, ld.r, tl.row0 + 4 * wave, nr, lane, 0, 0.0f);
+      narrow_rows<RP, 4, true, MODE == kMAddFused, true, false, GB16>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, nullptr,
+                                                                      ld.cols, ld.r, tl.row0 + 4 * wave, nr, lane, 0, 0.0f);
     return;
   }
   mfma_tile32<RP, MODE, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ld.cols, ld.r, tl.row0, tl.nrows,
@@ -3112,9 +3105,7 @@ bool launch_orth_coop(int rp, int nslice, int max_rank, const DevArgs& a, int nb
     case 1: return try_orth_coop<1>(nslice, max_rank, a, nblocks, cs, s);
     case 2: return try_orth_coop<2>(nslice, max_rank, a, nblocks, cs, s);
     case 4: return try_orth_coop<4>(nslice, max_rank, a, nblocks, cs, s);
-    case 8: return try_orth_coop<8>(nslice, max_rank, a, nblocks, cs, s);
-    case 16: return try_orth_coop<16>(nslice, max_rank, a, nblocks, cs, s);
-    case 32: return try_orth_coop<32>(nslice, max_rank, a, nblocks, cs, s);
+    // (rank pads 8 to 32 come here only from sets far too large for one cooperative launch, see setup_device)
     case 64: return try_orth_coop<64>(nslice, max_rank, a, nblocks, cs, s);
     default: return false;
   }
