@@ -88,8 +88,9 @@ typedef const float __attribute__((address_space(4)))* const_fp;
 // Dynamic LDS that sweep 0 asks for, and does not use, to keep it at two workgroups a CU, two wavefronts a SIMD: where rows
 // fill a wavefront's pass more of them read slower (ResNet-18 set, r = 4: 187 / 174.7 / 177 / 177 us at 1 / 2 / 3 / 4).  Rows
 // much narrower than a pass wait for memory instead, and take what the registers allow (1000000 x 16, r = 4, W = 8: 1980 us
-// at two, 1560 without the limit, one group of rows an item).  (Three is also what the registers are shared out for: at four,
-// rank pad 2 gets 117 instead of 142 of them and 8192^2 x 16 takes 2190 instead of 2085 us.)  Sweep 1 takes what they allow
+// at two, 1560 without the limit, one group of rows an item).  (The registers are shared out for three, and rank pad 8 needs
+// those of two: for four, rank pad 2 gets 117 instead of 142 of them and 8192^2 x 16 takes 2190 instead of 2085 us.)
+// Sweep 1 takes what they allow
 // everywhere (those narrow rows 434 us at four, 344 without a limit; the ResNet-18 set 64.5 and 64.9).
 [[maybe_unused]] constexpr unsigned kTwoPerCu = 56 * 1024;
 // The same for the residual sweep: three (ResNet-18 set 141 / 136 / 143 / 142 us at 2 / 3 / 4 / 8; with non-temporal stores 176,
@@ -537,11 +538,12 @@ __device__ __forceinline__ void narrow_rows(const float* __restrict__ G, float* 
 }
 
 // Rows row0 .. rend of a wavefront; in sweep 0, whose loads are what it waits for, 16 at a time as long as there are as many.
+// (Not at rank pad 8: 16 rows there cost the aligned rows in the same kernel, bfloat16 gradients, ResNet-18 set 184 against 172 us.)
 template <int RP, bool ADD, bool FUSE, bool HASM, bool EMIT, bool GB16>
 __device__ __forceinline__ void narrow_item(const float* __restrict__ G, float* __restrict__ M, const float* Q, const float* Pb,
                                             float* __restrict__ Pp, float* __restrict__ ghat, int cols, int r, int row0, int rend,
                                             int lane, int update, float eta) {
-  for (; ADD && row0 + 16 <= rend; row0 += 16)
+  for (; ADD && RP <= 4 && row0 + 16 <= rend; row0 += 16)
     narrow_rows<RP, 16, ADD, FUSE, HASM, EMIT, GB16>(G, M, Q, Pb, Pp, ghat, cols, r, row0, 16, lane, update, eta);
   for (; row0 < rend; row0 += 8)
     narrow_rows<RP, 8, ADD, FUSE, HASM, EMIT, GB16>(G, M, Q, Pb, Pp, ghat, cols, r, row0, min(8, rend - row0), lane, update, eta);
@@ -553,7 +555,7 @@ __device__ __forceinline__ void narrow_item(const float* __restrict__ G, float* 
 // NTS: the residual slabs are streamed -- E (or last iteration's M) is read with the non-temporal
 // hint and M is written with non-temporal stores; chosen by the host from the size of the working set.
 template <int RP, bool FUSE, bool GB16, bool NTS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3))) void add_project_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, RP >= 8 ? 2 : 3))) void add_project_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
   constexpr int RT = LQSGD_RT;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & (kWave - 1);
