@@ -49,8 +49,8 @@ struct lqsgd_ctx {
   // (the context then owns no device memory at all).
   unsigned char* arena = nullptr;
   size_t arena_cap = 0, arena_used = 0;
-  unsigned char* operands = nullptr;   // ... and another for the padded operand copies that it has no room for
-  size_t operands_cap = 0;
+  unsigned char* operands = nullptr;   // ... and another for padded operand copies and items that it has no room for
+  size_t operands_cap = 0, operands_used = 0;
   DevArgs args{};
   // device copies of the work lists
   Tile* d_tilesA = nullptr; Tile* d_tilesB = nullptr; Tile* d_tilesG = nullptr; Tile* d_tilesBM = nullptr; Tile* d_tilesAG = nullptr; Tile* d_tilesR = nullptr;
@@ -298,14 +298,12 @@ int run_sweep1(lqsgd_ctx* c, bool with_vectors) {
 // when asked for, is then written by a pass of its own over the layers.
 int run_sweep2(lqsgd_ctx* c, bool write_ghat) {
   const Plan& p = c->plan;
-  const Tile* res = c->d_tilesR ? c->d_tilesR : c->d_tilesB;
-  const int n_res = (int)(c->d_tilesR ? p.tilesR.size() : p.tilesB.size());
   Timed t(c, LQSGD_KERNEL_RESIDUAL);
   if (c->eager) {
     if (p.mfma_a)
       HIP_TRY(c, launch_mfma_sweep(p.RP, write_ghat ? 3 : 2, c->args, c->d_tilesA, (int)p.tilesA.size(), next_dir(c), c->stream));
     else
-      HIP_TRY(c, launch_residual(p.RP, write_ghat ? 1 : 0, c->args, res, n_res, p.narrow_rows ? 1 : 0, next_dir(c), c->stream));
+      HIP_TRY(c, launch_residual(p.RP, write_ghat ? 1 : 0, c->args, c->d_tilesR, (int)p.tilesR.size(), p.narrow_rows ? 1 : 0, next_dir(c), c->stream));
   } else {
     if (write_ghat) {
       if (p.mfma_a)
@@ -321,13 +319,11 @@ int run_sweep2(lqsgd_ctx* c, bool write_ghat) {
 int materialise(lqsgd_ctx* c) {
   if (!c->pending) return LQSGD_OK;
   const Plan& p = c->plan;
-  const Tile* res = c->d_tilesR ? c->d_tilesR : c->d_tilesB;
-  const int n_res = (int)(c->d_tilesR ? p.tilesR.size() : p.tilesB.size());
   Timed t(c, LQSGD_KERNEL_RESIDUAL);
   if (p.mfma_a)
     HIP_TRY(c, launch_mfma_sweep(p.RP, 2, c->args, c->d_tilesA, (int)p.tilesA.size(), next_dir(c), c->stream));
   else
-    HIP_TRY(c, launch_residual(p.RP, 0, c->args, res, n_res, p.narrow_rows ? 1 : 0, next_dir(c), c->stream));
+    HIP_TRY(c, launch_residual(p.RP, 0, c->args, c->d_tilesR, (int)p.tilesR.size(), p.narrow_rows ? 1 : 0, next_dir(c), c->stream));
   c->pending = false;
   return LQSGD_OK;
 }
@@ -413,7 +409,7 @@ int64_t lqsgd_plan_tiles(const lqsgd_config* cfg, const lqsgd_layer* layers, int
         o[4] = t.aux * d.segw;
         o[5] = std::min(d.cols, o[4] + d.segw) - o[4];
       } else {
-        const int cw = bm ? kMfmaCols : kWave * 4;
+        const int cw = bm ? kMfmaCols : sweep == 1 ? d.bcw : kWave * 4;
         o[4] = t.aux * cw;
         o[5] = std::min(d.cols, o[4] + cw) - o[4];
       }
@@ -551,24 +547,38 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   TRY_(dev_upload(c, &c->d_tilesRQ, p.tilesRQ));
   TRY_(dev_upload(c, &c->d_tilesRP, p.tilesRP));
   TRY_(dev_upload(c, &c->d_tilesV, p.tilesV));
-  if (p.padded && ext) {
-    auto copy_bytes = [](int64_t floats) { return (size_t)round_up(4 * (floats + kFactorSlack), 256); };
-    const size_t pb = copy_bytes(p.ppad_total), bytes = pb + copy_bytes(p.qpad_total);
-    unsigned char* at = c->operands;
+  // The padded copies of a caller-held state and the residual sweep's own items, which came after the block's size, go to the
+  // second block where the first has no room left.
+  auto late = [&](void** out, size_t bytes) {
+    bytes = (size_t)round_up((int64_t)bytes, 256);
     if (bytes <= c->arena_cap - c->arena_used) {
-      at = c->arena + c->arena_used;
+      *out = c->arena + c->arena_used;
       c->arena_used += bytes;
-    } else if (bytes > c->operands_cap) {
+    } else if (bytes <= c->operands_cap - c->operands_used) {
+      *out = c->operands + c->operands_used;
+      c->operands_used += bytes;
+    } else {
       char buf[200];
-      std::snprintf(buf, sizeof buf, "this configuration needs more scratch memory than the static buffers hold (%zu bytes of operand copies)", bytes);
+      std::snprintf(buf, sizeof buf, "this configuration needs more scratch memory than the static buffers hold (%zu bytes of operand copies or items)", bytes);
       return fail(c, LQSGD_EUNSUPPORTED, buf);
     }
-    a.Pop = reinterpret_cast<float*>(at);
-    a.Qop = reinterpret_cast<float*>(at + pb);
-    HIP_TRY(c, launch_fill_zero(at, bytes, c->stream));
+    return (int)LQSGD_OK;
+  };
+  if (p.padded && ext) {
+    const size_t pb = (size_t)round_up(4 * (p.ppad_total + kFactorSlack), 256), qb = (size_t)round_up(4 * (p.qpad_total + kFactorSlack), 256);
+    void* at = nullptr;
+    TRY_(late(&at, pb + qb));
+    a.Pop = static_cast<float*>(at);
+    a.Qop = a.Pop + pb / 4;
+    HIP_TRY(c, launch_fill_zero(at, pb + qb, c->stream));
   }
-  // (last: in a caller-provided block without room for it the residual sweep takes sweep 1's items, as good in everything but time)
-  if (!p.mfma_a && (!ext || p.tilesR.size() * sizeof(Tile) + 256 <= c->arena_cap - c->arena_used)) TRY_(dev_upload(c, &c->d_tilesR, p.tilesR));
+  if (!p.mfma_a && !ext) TRY_(dev_upload(c, &c->d_tilesR, p.tilesR));
+  if (!p.mfma_a && ext && !p.tilesR.empty()) {
+    void* at = nullptr;
+    TRY_(late(&at, p.tilesR.size() * sizeof(Tile)));
+    c->d_tilesR = static_cast<Tile*>(at);
+    HIP_TRY(c, hipMemcpy(at, p.tilesR.data(), p.tilesR.size() * sizeof(Tile), hipMemcpyHostToDevice));
+  }
 #undef TRY_
   a.layers = d_layers; a.vecs = d_vecs;
   a.thrP = thrP; a.levP = levP; a.thrQ = thrQ; a.levQ = levQ;

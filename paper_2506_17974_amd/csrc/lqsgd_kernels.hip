@@ -1412,7 +1412,7 @@ __device__ __forceinline__ void back_project_tile(const DevArgs& a, const LayerD
   const int cols = ld.cols, r = ld.r;
   const float* M = a.E + (size_t)worker * a.m_stride + ld.m_off;
   const float* Pb = p_operand(a, ld);
-  const int c0 = tl.aux * (kWave * 4);           // (one column per lane: one chunk)
+  const int c0 = tl.aux * (kWave * V);
   const int c = c0 + lane * V;
   const bool active = c < cols;
   const int per = (tl.nrows + 3) >> 2;
@@ -1455,7 +1455,7 @@ __device__ __forceinline__ void back_project_tile(const DevArgs& a, const LayerD
   }
   __syncthreads();
   const int tid = wave * kWave + lane;
-  const int ncol = min(kWave * 4, cols - c0);
+  const int ncol = min(kWave * V, cols - c0);
   if (KIND == kAligned && r == RP) {
     const int nout = ncol * RP;                  // floats this chunk owns: a multiple of four
 #pragma unroll
@@ -1534,7 +1534,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) voi
   const LayerDesc& ld = a.layers[layer];
   if (ld.kind == kAligned)
     back_project_tile<RP, kAligned>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
-  else if (ld.kind != kOneColumnPerLane)
+  else if (ld.bcw != kWave)
     back_project_tile<RP, kRagged>(a, ld, tl, layer, worker, comb, redmax, wave, lane);
   else
     back_project_tile<RP, kNarrow>(a, ld, tl, layer, worker, comb, redmax, wave, lane);

@@ -63,12 +63,15 @@ int64_t Plan::block_bytes() const {
 }
 
 // The finer splits (small sets at rank pads 32 and 64; rows of more than 64 columns that are no multiple of four) have up to
-// four times the partial planes.  They are taken where the set still fits the block of the entry point that allocates nothing,
-// whose results are the context's to the last bit: the split decides their order of sums, so both take the same one.
+// four times the partial planes.  A set that fits the block of the entry point that allocates nothing only without them goes
+// without: that entry point's results are the context's to the last bit, the split decides their order of sums, and so both
+// take the same one.
 int Plan::build(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers) {
   const int rc = build_split(c, ls, n_layers, true);
   if (rc || !fine_split || block_bytes() <= LQSGD_STATIC_SCRATCH_BYTES) return rc;
-  return build_split(c, ls, n_layers, false);
+  const int rc2 = build_split(c, ls, n_layers, false);
+  if (rc2 || block_bytes() <= LQSGD_STATIC_SCRATCH_BYTES) return rc2;
+  return build_split(c, ls, n_layers, true);     // it does not fit either way
 }
 
 int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_layers, bool fine) {
@@ -240,7 +243,8 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
 
     // sweeps 1 / 2 on the vector units: row blocks of rbb_v rows (rows of one column per lane count 64 columns: 4 x (100000 x
     // 21) at r = 4, W = 8, sweep 1 91 us and reduce 17 with 384 rows, 184 and 50 with 96)
-    const int64_t rowcols = d.kind == 2 || (d.kind == 1 && !fine) ? kWave : cw;
+    d.bcw = d.kind == 2 || (d.kind == 1 && !fine) ? kWave : cw;
+    const int64_t rowcols = d.bcw;
     fine_split |= !mfma && d.kind == 1;
     int64_t rbb = std::max<int64_t>(4, round_up(std::max<int64_t>(1, tgtB / rowcols), 4));
     int32_t rbb_v = (int32_t)std::min<int64_t>(rbb, round_up(d.rows, 4));
@@ -266,7 +270,7 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
     }
     d.nrb = (d.rows + d.rbb - 1) / d.rbb;
     d.direct_q = (!mfma && d.nrb == 1) ? 1 : 0;
-    const int nchunk = (d.cols + cw - 1) / cw;
+    const int nchunk = (d.cols + cw - 1) / cw, nchunk_b = (d.cols + d.bcw - 1) / d.bcw;
 
     d.m_off = m_acc;   m_acc += round_up((int64_t)d.rows * d.cols, 64);
     d.p_off = p_acc;   p_acc += round_up(d.np_el, 64);
@@ -293,7 +297,7 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
           if (w == 0) tilesAG.push_back(tilesA.back());
         }
       for (int32_t rb = 0; rb < nrb_v; ++rb)
-        for (int32_t ch = 0; ch < nchunk; ++ch)
+        for (int32_t ch = 0; ch < nchunk_b; ++ch)
           tilesB.push_back(Tile{lw, rb * rbb_v, std::min(rbb_v, d.rows - rb * rbb_v), ch});
       if (!mfma_a) {
         const int64_t rr = std::max<int64_t>(1, tgtR / cw) * (d.cols > kWave ? 1 : std::min<int64_t>(4, std::max<int64_t>(1, itemsR / 16384)));

@@ -22,7 +22,7 @@ constexpr int kFactorSlack = 64;   // readable floats after the last row of ever
 #ifndef LQSGD_STATIC_SCRATCH_BYTES
 #define LQSGD_STATIC_SCRATCH_BYTES (32u << 20)
 #endif
-// ... and of the padded operand copies (Plan::padded) where that block has no room left for them.  Where the layers' ranks
+// ... and of the padded operand copies (Plan::padded) and the residual sweep's items where that block has no room left.  Where the layers' ranks
 // are more than half their register pad, the copies are at most twice what the block already holds of the same factors.
 #ifndef LQSGD_STATIC_OPERAND_BYTES
 #define LQSGD_STATIC_OPERAND_BYTES (64u << 20)
@@ -33,7 +33,8 @@ constexpr int kFactorSlack = 64;   // readable floats after the last row of ever
 struct LayerDesc {
   int32_t rows, cols, r, kind;  // kind of rows: 0 = cols % 4 == 0 (16-byte aligned), 1 = not, 2 = not and at most 64 columns
   int32_t segw, nseg;           // sweep 0: column segment width (multiple of 256) and count
-  int32_t rbb, nrb;             // sweeps 1, 2: rows per row block and count
+  int32_t rbb, nrb;             // sweep 1: rows per row block and count
+  int32_t bcw;                  // sweep 1 on the vector units: columns of a chunk, 256 or (one per lane) 64
   int32_t gidx;                 // position in the caller's tensor list
   int32_t np_el, nq_el;         // rows*r, cols*r
   int32_t np_pad, nq_pad;       // the same rounded up to 16 elements (stride of the partial planes)
@@ -105,7 +106,8 @@ struct Plan {
   // Returns LQSGD_OK or a negative status with `err` set.
   int build(const lqsgd_config* cfg, const lqsgd_layer* layers, int32_t n_layers);
 
-  // Bytes of a caller-provided block that hold everything but the padded operand copies (an upper bound).
+  // Bytes of a caller-provided block that hold everything but the padded operand copies and the residual sweep's items (an
+  // upper bound).
   int64_t block_bytes() const;
 
  private:

@@ -158,8 +158,8 @@ def test_step_static_takes_sets_whose_finer_split_would_not_fit(rank, W, matrice
 
 
 def test_step_static_in_a_block_without_room_for_copies_and_residual_items():
-    """Operand copies go to the second block and the residual sweep runs over sweep 1's items (csrc/host_check.cpp pins that
-    this set leaves no room for either); a smaller set in between lays both blocks out anew."""
+    """Operand copies and the residual sweep's items go to the second block (csrc/host_check.cpp pins that this set leaves no
+    room for either in the first); a smaller set in between lays both blocks out anew."""
     rng = np.random.default_rng(24)
     full = [(2424, 24)] * 8
     E, Q = _fresh_state(full, 7, 16, rng)
