@@ -469,8 +469,8 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   quantiser_tables(p.cfg.bits_p, (double)p.cfg.alpha, tP, lP);
   quantiser_tables(p.cfg.bits_q, (double)p.cfg.alpha, tQ, lQ);
 #define TRY_(x) do { if ((rc = (x))) return rc; } while (0)
-  // Loaders for ranks below their register pad fetch whole padded rows and may run up to 31 floats
-  // past the last row of a factor: every factor buffer ends with this much readable slack.
+  // Loaders fetch whole padded rows, and four of them at a time, and may run up to 63 floats past the last
+  // row of a factor: every factor buffer ends with this much readable slack.
   constexpr size_t kSlack = kFactorSlack;
   const size_t orth_cells = 2 * W * (size_t)std::max(p.L, 1) * ((p.max_rows + 255) / 256) * p.RP;
   a.E = nullptr; a.Qbar = nullptr; a.orth_table = nullptr; a.status = nullptr;

@@ -20,7 +20,8 @@ struct DevArgs {
   float* Porth;                // P_w after Gram-Schmidt
   float* orth_part;            // [2][L*W][ceil(max_rows/256)][RP] slice partials of the many-workgroup Gram-Schmidt
   unsigned long long* orth_table;      // [2][L*W][ceil(max_rows/256)][RP] tagged partials of its one-launch form
-  // Cholesky-QR form of the tall Gram-Schmidt (rank pads >= 16; all three null if the context has none):
+  // Cholesky-QR form of the tall Gram-Schmidt (rank pads >= 8; null if the context has none; at rank pad 64 and fewer than 8
+  // slices the last two lie in Qpart, whose planes are dead while Gram-Schmidt runs):
   unsigned long long* chol_table;      // [L*W][ceil(max_rows/256) + 1][NE] tagged Gram matrices of the slices, their total last
   float* chol_part;            // [L*W][ceil(max_rows/256)][NE] the same matrices in plain memory, for the form of three launches
   int* chol_redo;              // [L*W] raised for a pair that has to be done column by column
@@ -62,6 +63,7 @@ const char* last_launched_kernel();
 // each one starts on the data the previous one touched last (still in the memory-side cache).
 // fuse_residual: the buffer E holds last iteration's M and the residual update
 // E = M - P-bar Q-bar^T is applied on the fly (see add_project_kernel).
+// narrow_rows (Plan::narrow_rows): as many wavefronts as the registers allow, see kTwoPerCu.
 hipError_t launch_add_project(int RP, const DevArgs& a, const Tile* tiles, int ntiles, int fuse_residual, int narrow_rows, int reverse,
                               hipStream_t s);
 // What a context keeps for the one-launch (cooperative) Gram-Schmidt of tall factors.
@@ -90,9 +92,6 @@ hipError_t launch_reduce_q(int phase, const DevArgs& a, const RTile* tiles, int 
 // mode: 0 = residual for all workers, 1 = residual + G-hat, 2 = G-hat only (tiles of worker 0).
 hipError_t launch_residual(int RP, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int narrow_rows, int reverse, hipStream_t s);
 
-// Sweeps 0 and 2 on the matrix cores (rank pad 16, 32 or 64), over the work list of
-// sweep 0 (32-row items).  mode: 0 = M = G + E and P partials, 1 = the same with the deferred
-// residual applied on the fly, 2 = residual, 3 = residual + G-hat, 4 = G-hat only (worker 0's items).
 // Refreshes the copy a.Pop (which = 0) or a.Qop (which = 1) of n layers from `layer` on from the tightly packed factor (the
 // exchange writes both at once; this is for a factor that came another way).
 hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, int layer, int n, hipStream_t s);
@@ -107,6 +106,9 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 constexpr int kPointerBatch = 448;       // 3.5 KB of kernel arguments
 hipError_t launch_write_pointers(const void** dst, const void* const* src, size_t n, hipStream_t s);
 
+// Sweeps 0 and 2 on the matrix cores (rank pad 16, 32 or 64), over the work list of
+// sweep 0 (32-row items).  mode: 0 = M = G + E and P partials, 1 = the same with the deferred
+// residual applied on the fly, 2 = residual, 3 = residual + G-hat, 4 = G-hat only (worker 0's items).
 hipError_t launch_mfma_sweep(int RP, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s);
 
 }  // namespace lqsgd

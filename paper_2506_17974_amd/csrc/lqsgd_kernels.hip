@@ -13,7 +13,8 @@
 //   residual      E = M - P-bar Q-bar^T (and G-hat once per layer)    8 B / element
 //
 // Lanes own columns in every sweep (one float4 per lane per row: a wavefront
-// reads 1 KiB of a row per instruction); the r-wide factor slice of a lane's
+// reads 1 KiB of a row per instruction; one column per lane where rows are at
+// most 64 columns, no multiple of four of them); the r-wide factor slice of a lane's
 // columns lives in registers; rows of the other factor are wave-uniform.
 // All reductions have a fixed order, so results are bit-identical run to run.
 #include "lqsgd_kernels.h"
@@ -89,9 +90,8 @@ typedef const float __attribute__((address_space(4)))* const_fp;
 // fill a wavefront's pass more of them read slower (ResNet-18 set, r = 4: 187 / 174.7 / 177 / 177 us at 1 / 2 / 3 / 4).  Rows
 // much narrower than a pass wait for memory instead, and take what the registers allow (1000000 x 16, r = 4, W = 8: 1980 us
 // at two, 1560 without the limit, one group of rows an item).  (The registers are shared out for three, and rank pad 8 needs
-// those of two: for four, rank pad 2 gets 117 instead of 142 of them and 8192^2 x 16 takes 2190 instead of 2085 us.)
-// Sweep 1 takes what they allow
-// everywhere (those narrow rows 434 us at four, 344 without a limit; the ResNet-18 set 64.5 and 64.9).
+// those of two: for four, rank pad 2 gets 117 instead of 142 of them and 8192^2 x 16 takes 2190 instead of 2085 us.)  Sweep 1
+// takes what they allow everywhere (those narrow rows 434 us at four, 344 without a limit; the ResNet-18 set 64.5 and 64.9).
 [[maybe_unused]] constexpr unsigned kTwoPerCu = 56 * 1024;
 // The same for the residual sweep: three (ResNet-18 set 141 / 136 / 143 / 142 us at 2 / 3 / 4 / 8; with non-temporal stores 176,
 // with plain loads 147; narrow rows see Plan::build).
@@ -581,9 +581,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, RP >= 8 
 }
 
 // ---------------------------------------------------------------------------
-// LogQuantize of Section 4.1 for one value and for a packed group of 8 (used by
-// the exchange kernels, by the Gram-Schmidt kernels that quantise their own
-// output, and by the sweeps that dequantise packets themselves).
+// LogQuantize of Section 4.1 for one value and for a packed group of 8, as the
+// exchange kernel uses them.
 // The code of u = |x|/s is the number of decision thresholds <= u, i.e.
 // nearest-level rounding in the q-domain of Eq. (5): a hardware log2 gives the
 // level, and the thresholds on its two sides move it to the exact count.
@@ -1355,9 +1354,10 @@ __global__ __launch_bounds__(256) void exchange_kernel(DevArgs a, const XTile* _
 
 // ---------------------------------------------------------------------------
 // sweep 1: Q_w partial = M_w^T P-bar over a row block (Algorithm 1,
-// "Q <- G'^T P").  One workgroup per (row block, 256-column chunk); its four
-// wavefronts split the rows and their partial sums meet in LDS, where they are
-// added in wavefront order.
+// "Q <- G'^T P").  One workgroup per (row block, chunk of 256 columns, or of 64
+// with one column per lane); its four wavefronts split the rows and their partial
+// sums meet in LDS, where they are added in wavefront order (aligned rows whose
+// rank fills its pad) or as (0 + 2) + (1 + 3).
 // ---------------------------------------------------------------------------
 // Columns a lane of sweep 1 holds.
 template <int KIND>
@@ -1441,7 +1441,7 @@ __device__ __forceinline__ void back_project_tile(const DevArgs& a, const LayerD
                      : a.Qpart + (size_t)worker * a.qpart_stride + ld.qpart_off + (size_t)(tl.row0 / ld.rbb) * ld.nq_pad;
   float mx = 0.0f;
   // comb[wave][column][rank]; afterwards the workgroup adds the four partials of every output
-  // element in wavefront order: the chunk's slice of the factor is contiguous from column c0.
+  // element: the chunk's slice of the factor is contiguous from column c0.
   {
     float* mine = comb + (size_t)wave * (kWave * NV) + lane * NV;
     if constexpr (NV % 4 == 0) {
@@ -2777,8 +2777,8 @@ __device__ __forceinline__ void chol_sum_planes(const float* planes, int nseg, s
   }
 }
 
-// Row `row` of a rows x r factor (zero beyond r and for a thread without a row): whole-row loads that may
-// run into what follows the row, as in load_slice.
+// Row `row` of a rows x r factor (zero beyond r and for a thread without a row): loads of RP values that may
+// run into what follows the row (kFactorSlack).
 template <int RP>
 __device__ __forceinline__ void chol_load_row(const float* F, int row, int rows, int r, float (&v)[RP]) {
   load_row<RP>(F, min(row, rows - 1), r, r == RP, v);

@@ -56,7 +56,7 @@ struct VecDesc {
 
 // Work item of a streaming sweep.  lw = layer * W + worker.
 // sweep 0: one wavefront; rows [row0, row0+nrows), column segment `aux`.
-// sweeps 1, 2: one workgroup; rows [row0, row0+nrows), column chunk `aux` (256 wide).
+// sweep 1: one workgroup; rows [row0, row0+nrows), column chunk `aux` (LayerDesc::bcw wide).  Sweep 2: the same, 256 wide.
 struct Tile {
   int32_t lw, row0, nrows, aux;
 };
@@ -74,10 +74,10 @@ struct Plan {
   lqsgd_config cfg{};
   int32_t n_all = 0;            // tensors in the caller's list
   int32_t W = 0, L = 0, V = 0;  // workers, matrix layers, vector layers
-  int32_t RP = 0;               // register rank: smallest of 1,2,4,8,16,32 >= max layer rank
+  int32_t RP = 0;               // register rank: smallest of 1, 2, 4, .. 64 >= max layer rank
   int32_t max_rows = 0;         // largest row count of a matrix layer
   int32_t max_rank = 0;         // largest effective rank of a matrix layer
-  bool mfma = false;            // sweep 1 runs on the matrix cores (rank pad 32)
+  bool mfma = false;            // sweep 1 runs on the matrix cores (rank pads 32 and 64)
   bool mfma_a = false;          // sweeps 0 and 2 run on the matrix cores (rank pad >= 16): 32-row work items
   std::vector<LayerDesc> layers;
   std::vector<VecDesc> vecs;
@@ -85,8 +85,8 @@ struct Plan {
   std::vector<Tile> tilesA, tilesB;
   std::vector<Tile> tilesR;        // residual sweep of the vector path: row block x 256 columns, all workers
   std::vector<Tile> tilesAG;       // worker 0's items of tilesA (G-hat pass of the matrix-core path)
-  std::vector<Tile> tilesBM;       // sweep 1 on the matrix cores (rank pad >= 16): row block x 128-column group
-  std::vector<Tile> tilesG;        // worker 0's items of tilesB: one pass over every layer (G-hat only)
+  std::vector<Tile> tilesBM;       // sweep 1 on the matrix cores (rank pads 32 and 64): row block x 512-column group
+  std::vector<Tile> tilesG;        // one pass over every layer of worker 0 (G-hat only): row block x 256 columns
   std::vector<XTile> tilesXP, tilesXQ;
   std::vector<RTile> tilesRQ;
   std::vector<RTile> tilesRP;      // aggregate-first order: reduce of the P partials (1024 elements each)

@@ -1,5 +1,5 @@
 """GPU parity for the code paths and API calls that the other files do not reach:
-the in-memory Gram-Schmidt kernel (factors of 513..2048 rows at rank pads >= 16),
+Gram-Schmidt of factors of 513..1792 rows at rank pads >= 16,
 factor injection through lqsgd_set_factor, the checkpoint round trip through
 lqsgd_get_state / lqsgd_set_state, and what lqsgd_get_state returns in the middle of
 a staged iteration.  Everything here needs a real MI355X."""
@@ -17,8 +17,9 @@ f32, f64 = np.float32, np.float64
 
 
 # ---------------------------------------------------------------------------
-# Gram-Schmidt in memory: one workgroup per (layer, worker), rows beyond what the
-# register-resident form holds at that rank
+# Gram-Schmidt of one workgroup per (layer, worker) beyond 512 rows, where its sums
+# follow those of a form that kept the factor in memory (rank pad 64 from 1025 rows on:
+# Cholesky-QR)
 # ---------------------------------------------------------------------------
 @pytest.mark.parametrize("layers,rank,W", [
     ([(1024, 260)], 16, 2),                       # 1024 rows at rank pad 16
@@ -28,7 +29,7 @@ f32, f64 = np.float32, np.float64
     ([(1024, 132)], 20, 3),                       # rank below its pad
 ])
 def test_in_memory_gram_schmidt(layers, rank, W):
-    _say("case: in-memory Gram-Schmidt", layers, rank, W)
+    _say("case: Gram-Schmidt beyond 512 rows", layers, rank, W)
     rep = _run_staged(layers, rank, 8, 8, W, steps=2, seed=rank + W, e0_scale=3e-4)
     _say("  ", rep)
 
