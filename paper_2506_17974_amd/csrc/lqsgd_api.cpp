@@ -60,6 +60,7 @@ struct lqsgd_ctx {
   const float** d_grads = nullptr; float** d_ghat = nullptr;
   std::vector<const float*> h_grads; std::vector<float*> h_ghat;
   bool grads_valid = false, ghat_valid = false;
+  bool stale[2] = {false, false};   // the padded copies of P-bar / Q-bar lag behind a factor that the host has set
   bool alias_checked = false;   // the bound gradient and output tables have been checked against each other
   // timing
   std::string launched[LQSGD_KERNEL_COUNT];   // device function last launched for each timing slot
@@ -227,10 +228,21 @@ int next_dir(lqsgd_ctx* c) {
 }
 
 // The sweeps read P-bar and Q-bar from copies with padded rows when some layer has fewer ranks than the register
-// pad.  The exchange writes factor and copy together; every other writer of a factor calls this right after it, so a
-// copy is never older than its factor, also between the replays of captured steps.
-int refresh_padded(lqsgd_ctx* c, int which, int layer, int n) {
-  if (c->plan.padded) HIP_TRY(c, launch_pad_factor(c->plan.RP, which, c->args, layer, n, c->stream));
+// pad.  The exchange writes factor and copy together; other kernels that write a factor are followed by this.
+int refresh_padded(lqsgd_ctx* c, int which) {
+  if (c->plan.padded) HIP_TRY(c, launch_pad_factor(c->plan.RP, which, c->args, c->stream));
+  return LQSGD_OK;
+}
+// A factor that the host has set is copied by the next sweep that reads copies: one launch for all layers set by then.
+// While the stream is being captured the launch only becomes part of the graph, and the factor stays to be copied.
+int refresh_stale(lqsgd_ctx* c) {
+  for (int which = 0; which < 2; ++which) {
+    if (!c->stale[which]) continue;
+    if (int rc = refresh_padded(c, which)) return rc;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusNone; }
+    c->stale[which] = cap != hipStreamCaptureStatusNone;
+  }
   return LQSGD_OK;
 }
 
@@ -240,6 +252,7 @@ CoopState* coop_state(lqsgd_ctx* c) {
 }
 
 int run_sweep0(lqsgd_ctx* c) {
+  if (int rc = refresh_stale(c)) return rc;
   { Timed t(c, LQSGD_KERNEL_ADD_PROJECT);
     if (c->plan.mfma_a)
       HIP_TRY(c, launch_mfma_sweep(c->plan.RP, c->pending ? 1 : 0, c->args, c->d_tilesA, (int)c->plan.tilesA.size(),
@@ -268,7 +281,7 @@ int run_orth_shared(lqsgd_ctx* c) {
   a.Ppre = c->args.Porth;
   a.Porth = c->args.Pbar;
   HIP_TRY(c, launch_orth(c->plan.RP, c->plan.max_rows, c->plan.max_rank, a, coop_state(c), c->stream));
-  return refresh_padded(c, 0, 0, c->plan.L);
+  return refresh_padded(c, 0);
 }
 int run_exchange(lqsgd_ctx* c, int mode, int phase) {
   { Timed t(c, phase ? LQSGD_KERNEL_EXCHANGE_Q : LQSGD_KERNEL_EXCHANGE_P);
@@ -280,6 +293,7 @@ int run_exchange(lqsgd_ctx* c, int mode, int phase) {
   return LQSGD_OK;
 }
 int run_sweep1(lqsgd_ctx* c, bool with_vectors) {
+  if (int rc = refresh_stale(c)) return rc;
   { Timed t(c, LQSGD_KERNEL_BACK_PROJECT);
     const int nv = with_vectors ? (int)c->plan.tilesV.size() : 0;
     if (c->plan.mfma)
@@ -298,6 +312,7 @@ int run_sweep1(lqsgd_ctx* c, bool with_vectors) {
 // when asked for, is then written by a pass of its own over the layers.
 int run_sweep2(lqsgd_ctx* c, bool write_ghat) {
   const Plan& p = c->plan;
+  if (int rc = refresh_stale(c)) return rc;
   Timed t(c, LQSGD_KERNEL_RESIDUAL);
   if (c->eager) {
     if (p.mfma_a)
@@ -319,6 +334,7 @@ int run_sweep2(lqsgd_ctx* c, bool write_ghat) {
 int materialise(lqsgd_ctx* c) {
   if (!c->pending) return LQSGD_OK;
   const Plan& p = c->plan;
+  if (int rc = refresh_stale(c)) return rc;
   Timed t(c, LQSGD_KERNEL_RESIDUAL);
   if (p.mfma_a)
     HIP_TRY(c, launch_mfma_sweep(p.RP, 2, c->args, c->d_tilesA, (int)p.tilesA.size(), next_dir(c), c->stream));
@@ -672,7 +688,7 @@ int lqsgd_set_state(lqsgd_ctx* c, int32_t layer, int32_t worker, const float* ho
                          (size_t)ld->rows * ld->cols * sizeof(float), hipMemcpyHostToDevice));
   if (host_q) {
     HIP_TRY(c, hipMemcpy(c->args.Qbar + ld->q_off, host_q, (size_t)ld->nq_el * sizeof(float), hipMemcpyHostToDevice));
-    return refresh_padded(c, 1, c->plan.kind_of[layer], 1);
+    c->stale[1] = c->plan.padded;
   }
   return LQSGD_OK;
 }
@@ -896,7 +912,8 @@ int lqsgd_set_factor(lqsgd_ctx* c, int32_t which, int32_t layer, const float* ho
   if ((rc = materialise(c))) return rc;      // a deferred update is defined by the old factors
   if (int rcs = sync_stream(c)) return rcs;
   HIP_TRY(c, hipMemcpy(dst, host, n * sizeof(float), hipMemcpyHostToDevice));
-  return refresh_padded(c, which == LQSGD_FACTOR_P_BAR ? 0 : 1, c->plan.kind_of[layer], 1);
+  c->stale[which == LQSGD_FACTOR_P_BAR ? 0 : 1] = c->plan.padded;
+  return LQSGD_OK;
 }
 
 int64_t lqsgd_wire_bytes(const lqsgd_ctx* c) { return c ? c->plan.wire_bytes : (int64_t)LQSGD_EINVAL; }
@@ -1027,7 +1044,7 @@ int lqsgd_step_static(const lqsgd_config* cfg, const lqsgd_layer* layers, int32_
   if (!c->plan.padded) c->args.Qop = warm_q;
   c->pending = false;                        // the caller's buffer holds E, and holds E again on return
   c->state = kIdle;
-  int rc = refresh_padded(c, 1, 0, c->plan.L);   // the warm-start Q is the caller's
+  int rc = refresh_padded(c, 1);             // the warm-start Q is the caller's
   if (!rc) rc = step_impl(c, grads, ghat);
   if (rc) g_create_error = c->err;
   return rc;

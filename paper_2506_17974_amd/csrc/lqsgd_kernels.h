@@ -92,9 +92,9 @@ hipError_t launch_reduce_q(int phase, const DevArgs& a, const RTile* tiles, int 
 // mode: 0 = residual for all workers, 1 = residual + G-hat, 2 = G-hat only (tiles of worker 0).
 hipError_t launch_residual(int RP, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int narrow_rows, int reverse, hipStream_t s);
 
-// Refreshes the copy a.Pop (which = 0) or a.Qop (which = 1) of n layers from `layer` on from the tightly packed factor (the
-// exchange writes both at once; this is for a factor that came another way).
-hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, int layer, int n, hipStream_t s);
+// Refreshes the copy a.Pop (which = 0) or a.Qop (which = 1) from the tightly packed factor (the exchange writes both at once;
+// this is for a factor that came another way).
+hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, hipStream_t s);
 
 // The per-GPU blocks of the entry point that allocates nothing, scratch and operand copies: device addresses of
 // those of `device`, which must be the current device on the first call for it.

@@ -2436,9 +2436,9 @@ __global__ __launch_bounds__(512, 2) void mfma_sweep32_kernel(DevArgs a, const T
 }
 
 // Copies of the aggregated factors with rows of RP ranks (zero beyond the layer's rank), as the sweeps
-// read them.  blockIdx.y = layer, from `layer` on; which: 0 = P-bar, 1 = Q-bar.
-__global__ __launch_bounds__(256) void pad_factor_kernel(DevArgs a, int RP, int which, int layer) {
-  const LayerDesc& ld = a.layers[layer + blockIdx.y];
+// read them.  blockIdx.y = layer; which: 0 = P-bar, 1 = Q-bar.
+__global__ __launch_bounds__(256) void pad_factor_kernel(DevArgs a, int RP, int which) {
+  const LayerDesc& ld = a.layers[blockIdx.y];
   const int n = which ? ld.cols : ld.rows, r = ld.r;
   const float* src = which ? a.Qbar + ld.q_off : a.Pbar + ld.p_off;
   float* dst = which ? a.Qop + ld.qop_off : a.Pop + ld.pop_off;
@@ -3416,9 +3416,9 @@ hipError_t launch_write_pointers(const void** dst, const void* const* src, size_
   return hipSuccess;
 }
 
-hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, int layer, int n, hipStream_t s) {
-  if (n <= 0 || !a.padded) return hipSuccess;
-  pad_factor_kernel<<<dim3(64, n), dim3(256), 0, s>>>(a, RP, which, layer);
+hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, hipStream_t s) {
+  if (a.L <= 0 || !a.padded) return hipSuccess;
+  pad_factor_kernel<<<dim3(64, a.L), dim3(256), 0, s>>>(a, RP, which);
   return hipGetLastError();
 }
 #endif
