@@ -228,7 +228,8 @@ int next_dir(lqsgd_ctx* c) {
 }
 
 // The sweeps read P-bar and Q-bar from copies with padded rows when some layer has fewer ranks than the register
-// pad.  The exchange writes factor and copy together; other kernels that write a factor are followed by this.
+// pad.  The exchange and the Gram-Schmidt of an aggregate by one workgroup write factor and copy together; other kernels
+// that write a factor are followed by this.
 int refresh_padded(lqsgd_ctx* c, int which) {
   if (c->plan.padded) HIP_TRY(c, launch_pad_factor(c->plan.RP, which, c->args, c->stream));
   return LQSGD_OK;
@@ -266,7 +267,8 @@ int run_sweep0(lqsgd_ctx* c) {
     HIP_TRY(c, launch_reduce_q(0, c->args, c->d_tilesRP, (int)c->plan.tilesRP.size(), c->stream));
   } else {
     Timed t(c, LQSGD_KERNEL_ORTH);
-    HIP_TRY(c, launch_orth(c->plan.RP, c->plan.max_rows, c->plan.max_rank, c->args, coop_state(c), c->stream));
+    bool copied = false;
+    HIP_TRY(c, launch_orth(c->plan.RP, c->plan.max_rows, c->plan.max_rank, c->args, coop_state(c), &copied, c->stream));
   }
   return LQSGD_OK;
 }
@@ -280,14 +282,18 @@ int run_orth_shared(lqsgd_ctx* c) {
   a.Ppart = c->args.Pbar; a.ppart_stride = 0;
   a.Ppre = c->args.Porth;
   a.Porth = c->args.Pbar;
-  HIP_TRY(c, launch_orth(c->plan.RP, c->plan.max_rows, c->plan.max_rank, a, coop_state(c), c->stream));
-  return refresh_padded(c, 0);
+  bool copied = false;
+  HIP_TRY(c, launch_orth(c->plan.RP, c->plan.max_rows, c->plan.max_rank, a, coop_state(c), &copied, c->stream));
+  return copied ? LQSGD_OK : refresh_padded(c, 0);
 }
 int run_exchange(lqsgd_ctx* c, int mode, int phase) {
   { Timed t(c, phase ? LQSGD_KERNEL_EXCHANGE_Q : LQSGD_KERNEL_EXCHANGE_P);
     const auto& tl = phase ? c->plan.tilesXQ : c->plan.tilesXP;
     DevArgs a = c->args;
-    if (c->plan.agg_first && phase == 0) a.Porth = c->args.Ppre;   // the raw factors are what gets quantised
+    if (c->plan.agg_first && phase == 0) {
+      a.Porth = c->args.Ppre;                    // the raw factors are what gets quantised
+      a.padded = 0;                              // Gram-Schmidt is still to come
+    }
     HIP_TRY(c, launch_exchange(mode, phase, a, phase ? c->d_tilesXQ : c->d_tilesXP, (int)tl.size(), c->stream)); }
   if (c->plan.agg_first && phase == 0 && mode != kQuantOnly) return run_orth_shared(c);
   return LQSGD_OK;

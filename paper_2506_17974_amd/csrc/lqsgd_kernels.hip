@@ -729,6 +729,7 @@ __global__ __launch_bounds__(BS) void orth_reg_kernel(DevArgs a) {
   }
 
   float mx = 0.0f;
+  float* copy = a.orth_shared && a.padded ? a.Pop + ld.pop_off : nullptr;
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
     const int row = tid + i * BS;
@@ -737,6 +738,7 @@ __global__ __launch_bounds__(BS) void orth_reg_kernel(DevArgs a) {
       for (int k = 0; k < RP; ++k)
         if (k < r) {
           orth[(size_t)row * r + k] = v[i][k];
+          if (copy) copy[(size_t)row * RP + k] = v[i][k];
           mx = fmaxf(mx, fabsf(v[i][k]));
         }
     }
@@ -936,12 +938,14 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
   }
 
   float mx = 0.0f;
+  float* copy = a.orth_shared && a.padded ? a.Pop + ld.pop_off : nullptr;   // the sweeps' copy of an orthonormalised aggregate
   hide_row();
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
     const int row = row0 + row_of(i);
     if (col && row < rows) {
       orth[row * r + k] = v[i];
+      if (copy) copy[row * C + k] = v[i];
       mx = fmaxf(mx, fabsf(v[i]));
     }
   }
@@ -3196,7 +3200,8 @@ hipError_t launch_orth_chol(int rp, int nslice, int max_rank, const DevArgs& a, 
 hipError_t launch_orth_chol(int rp, int nslice, int max_rank, const DevArgs& a, int nblocks, CoopState* coop, hipStream_t s);
 
 #if LQSGD_HAS(4)
-hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, CoopState* coop, hipStream_t s) {
+hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, CoopState* coop, bool* copied, hipStream_t s) {
+  *copied = a.L <= 0;
   if (a.L <= 0) return hipSuccess;
   const dim3 grid(a.L * a.W);
   const int nslice = (max_rows + 255) / 256;
@@ -3235,6 +3240,7 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, Coo
     default: return hipErrorInvalidValue;
   }
   if (!done) return hipErrorInvalidValue;        // (without slices' buffers: a caller this library does not have)
+  *copied = true;
   return hipGetLastError();
 }
 #endif

@@ -310,3 +310,34 @@ def test_capture_below_the_rank_pad_and_with_other_pointers(rank, layers):
             assert torch.equal(a, b)
     rec.close()
     ref.close()
+
+
+@pytest.mark.parametrize("rank,layers", [(2, [(300, 260), (40, 1)]), (3, [(1232, 160), (64, 224)]), (7, [(600, 130), (64, 5)]),
+                                         (20, [(1000, 140), (64, 27)]), (50, [(700, 160), (64, 35)]), (50, [(1500, 60), (64, 40)]), (7, [(2600, 30)])])
+@pytest.mark.parametrize("eager", [False, True])
+def test_aggregate_first_below_the_rank_pad(rank, layers, eager):
+    """The sweeps read the orthonormalised aggregate, from the copy that Gram-Schmidt or a launch after it has written: G-hat,
+    the Q products and the residuals are those of the P-bar that the factor tap shows."""
+    import torch
+    _say("case: aggregate-first", rank, layers, eager)
+    rng, W = np.random.default_rng(rank), 3
+    comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 0, W, 255.0, B.FLAG_AGGREGATE_FIRST | (B.FLAG_EAGER_RESIDUAL if eager else 0))
+    for l, (n, c) in enumerate(layers):
+        comp.set_q(l, rng.standard_normal((c, min(rank, n, c))).astype(f32))
+    out = [torch.zeros(s, device="cuda") for s in layers]
+    E = [[np.zeros(s, f32) for s in layers] for _ in range(W)]
+    for _ in range(3):
+        G = [[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)]
+        comp.step(pu.to_device(G), out)
+        for l in range(len(layers)):
+            P, Q = comp.get_factor(B.FACTOR_P_BAR, l).astype(np.float64), comp.get_factor(B.FACTOR_Q_BAR, l).astype(np.float64)
+            hat = P @ Q.T
+            assert pu.rel_fro(out[l].cpu().numpy(), hat) < 1e-5
+            for w in range(W):
+                M = G[w][l] + E[w][l]
+                assert pu.rel_fro(comp.get_factor(B.FACTOR_Q_W, l, w), M.T @ P) < pu.FP_TOL
+                E[w][l] = (M - hat).astype(f32)
+    for l in range(len(layers)):
+        for w in range(W):
+            assert np.abs(comp.get_state(l, w)[0] - E[w][l]).max() <= 1e-5 * np.abs(G[w][l]).max()
+    comp.close()
