@@ -195,20 +195,49 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
   constexpr int cw = kWave * 4;                          // columns of a wavefront's pass over a row
   const int rowgrp = mfma_a ? 32 : kRowsPerGroup;        // a matrix-core item is one 32-row tile
   int64_t items0 = 0, narrow = 0;
-  for (LayerDesc& d : layers) {
-    const int64_t segmax = round_up(segmax4, cw);
+  auto cut = [&](LayerDesc& d, int64_t segmax) {
     const int nseg = (int)((d.cols + segmax - 1) / segmax);
     d.segw = (int32_t)round_up((d.cols + nseg - 1) / nseg, cw);
     d.nseg = (d.cols + d.segw - 1) / d.segw;
+  };
+  for (LayerDesc& d : layers) {
+    cut(d, round_up(segmax4, cw));
     items0 += (int64_t)W * ((d.rows + rowgrp - 1) / rowgrp) * d.nseg;
     if (d.cols < cw) narrow += (int64_t)d.rows * d.cols;
   }
   narrow_rows = 2 * narrow > matrix_elements;
+  // Sets with less than one item per SIMD wait for a single wavefront's passes: rows that are no multiple of four, whose last
+  // group takes the longest, then have one pass per segment (240 x 309, r = 7, W = 7, sweep 0 13.3 -> 10.4 us; 128 x 1001, r = 8,
+  // W = 4 16.2 -> 10.4).
+  if (!mfma_a && items0 < 1024)
+    for (LayerDesc& d : layers)
+      if (d.kind == 1) cut(d, cw);
   // the residual sweep's items likewise, 32 rows each; layers of at most 64 columns take up to four times as many rows where
   // the list is long (1000000 x 16 at r = 4, W = 8 1097 us with 32 rows and three wavefronts a SIMD, 680 with 128 and what the
   // registers allow)
   int64_t itemsR = 0;
   for (const LayerDesc& d : layers) itemsR += (int64_t)W * ((d.rows + 31) / 32) * ((d.cols + cw - 1) / cw);
+
+  // Sweep 1 on the vector units: rows of a row block (rows of one column per lane count 64 columns: 4 x (100000 x 21) at r = 4,
+  // W = 8, sweep 1 91 us and reduce 17 with 384 rows, 184 and 50 with 96).
+  auto row_block = [&](const LayerDesc& d) {
+    const int64_t rowcols = d.kind == 2 || (d.kind == 1 && !fine) ? kWave : cw;
+    const int64_t rbb = std::max<int64_t>(4, round_up(std::max<int64_t>(1, tgtB / rowcols), 4));
+    // Layers of moderate height take one row block per column chunk: sweep 1 then writes Q_w itself
+    // (no partial planes, no reduce pass for this layer), and measured on the ResNet-18-shaped set
+    // it streams as fast with 512-row items as with 128-row ones (63 us either way).
+    // Not where that would leave the launch with too few items: at most four times the size the
+    // work list aims for (a 1024-row layer of a small set keeps its row blocks).
+    if (!mfma && (int64_t)d.rows * rowcols <= env_i64("LQSGD_DIRECT_Q_MAX", 262144) && d.rows <= 4 * rbb) return (int32_t)round_up(d.rows, 4);
+    const int64_t r = std::min<int64_t>(rbb, round_up(d.rows, 4)), n = (d.rows + r - 1) / r;
+    // equal blocks: 8192 rows in blocks of 1536 would end in a block of 512
+    return (int32_t)std::min<int64_t>(r, round_up((d.rows + n - 1) / n, 4));
+  };
+  // Its items in chunks of 256 columns.  Sets with fewer than CUs take rows that are no multiple of four in chunks of 64, one
+  // column per lane: the same sums on four times the workgroups (240 x 309, r = 7, W = 7 26.0 -> 11.0 us; 300 x 515, r = 3, W = 1
+  // 10.8 -> 7.5; 1000 x 1002, r = 12, W = 2 14.5 -> 8.9).
+  int64_t items1 = 0;
+  for (const LayerDesc& d : layers) items1 += (int64_t)W * ((d.rows + row_block(d) - 1) / row_block(d)) * ((d.cols + cw - 1) / cw);
 
   int64_t m_acc = 0, p_acc = 0, q_acc = 0, pp_acc = 0, qp_acc = 0;
   int64_t mp_acc = 0, sp_acc = 0, mq_acc = 0, sq_acc = 0;
@@ -241,26 +270,9 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
     }
     const int32_t trows = (int32_t)std::min<int64_t>(round_up(d.rows, rowgrp), ng * rowgrp);
 
-    // sweeps 1 / 2 on the vector units: row blocks of rbb_v rows (rows of one column per lane count 64 columns: 4 x (100000 x
-    // 21) at r = 4, W = 8, sweep 1 91 us and reduce 17 with 384 rows, 184 and 50 with 96)
-    d.bcw = d.kind == 2 || (d.kind == 1 && !fine) ? kWave : cw;
-    const int64_t rowcols = d.bcw;
+    const int32_t rbb_v = row_block(d), nrb_v = (d.rows + rbb_v - 1) / rbb_v;
+    d.bcw = d.kind == 2 || (d.kind == 1 && (!fine || items1 < 256)) ? kWave : cw;
     fine_split |= !mfma && d.kind == 1;
-    int64_t rbb = std::max<int64_t>(4, round_up(std::max<int64_t>(1, tgtB / rowcols), 4));
-    int32_t rbb_v = (int32_t)std::min<int64_t>(rbb, round_up(d.rows, 4));
-    int32_t nrb_v = (d.rows + rbb_v - 1) / rbb_v;
-    // equal blocks: 8192 rows in blocks of 1536 would end in a block of 512
-    rbb_v = (int32_t)std::min<int64_t>(rbb_v, round_up((d.rows + nrb_v - 1) / nrb_v, 4));
-    nrb_v = (d.rows + rbb_v - 1) / rbb_v;
-    // Layers of moderate height take one row block per column chunk: sweep 1 then writes Q_w itself
-    // (no partial planes, no reduce pass for this layer), and measured on the ResNet-18-shaped set
-    // it streams as fast with 512-row items as with 128-row ones (63 us either way).
-    // Not where that would leave the launch with too few items: at most four times the size the
-    // work list aims for (a 1024-row layer of a small set keeps its row blocks).
-    if (!mfma && (int64_t)d.rows * rowcols <= env_i64("LQSGD_DIRECT_Q_MAX", 262144) && d.rows <= 4 * rbb) {
-      rbb_v = (int32_t)round_up(d.rows, 4);
-      nrb_v = 1;
-    }
     // the partial planes of Q belong to whichever kernel runs sweep 1
     if (mfma) {
       const int64_t rbm = env_i64("LQSGD_TILE_BM", std::min<int64_t>(2048, std::max<int64_t>(rbm_min, total / (49152 * 16))));
@@ -307,7 +319,7 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
             tilesR.push_back(Tile{lw, row0, std::min(rbr, d.rows - row0), ch});
       }
       if (w == 0) {
-        const int32_t rbg = (int32_t)std::min<int64_t>(round_up(std::max<int64_t>(1, tgtG / rowcols), 4), round_up(d.rows, 4));
+        const int32_t rbg = (int32_t)std::min<int64_t>(round_up(std::max<int64_t>(1, tgtG / (d.kind == 2 ? kWave : cw)), 4), round_up(d.rows, 4));
         for (int32_t row0 = 0; row0 < d.rows; row0 += rbg)
           for (int32_t ch = 0; ch < nchunk; ++ch)
             tilesG.push_back(Tile{lw, row0, std::min(rbg, d.rows - row0), ch});

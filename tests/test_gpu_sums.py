@@ -341,3 +341,39 @@ def test_aggregate_first_below_the_rank_pad(rank, layers, eager):
         for w in range(W):
             assert np.abs(comp.get_state(l, w)[0] - E[w][l]).max() <= 1e-5 * np.abs(G[w][l]).max()
     comp.close()
+
+
+@pytest.mark.parametrize("rank", [1, 3, 8, 12])
+def test_rows_of_any_width_in_sets_of_many_items(rank):
+    """Enough work items that rows which are no multiple of four take the wide segments and chunks (small sets, as in the
+    other tests, take narrower ones): a staged iteration against the oracle, deferred and finished residuals bit for bit."""
+    import torch
+    _say("case: many ragged layers", rank)
+    rng = np.random.default_rng(rank)
+    layers, W = [(72, 1283)] * 12 + [(130, 257)] * 40 + [(9, 65)] * 8, 2
+    tiles = B.plan_tiles(B.layer_list(layers, ()), rank, 8, 8, W, 1)
+    assert tiles[:, 5].max() == 256 and B.plan_tiles(B.layer_list(layers, ()), rank, 8, 8, W, 0)[:, 5].max() > 256
+    ll, ml = B.layer_list(layers, ()), list(range(len(layers)))
+    Q0 = [rng.standard_normal((c, min(rank, n, c))).astype(f32) for n, c in layers]
+    Gs = [[[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)] for _ in range(2)]
+    comp = B.Compressor(ll, rank, 8, 8, W)
+    for l in ml:
+        comp.set_q(l, Q0[l])
+    E, Q, rep = [[np.zeros(s, f32) for s in layers] for _ in range(W)], [q.copy() for q in Q0], pu.StageReport()
+    for t in range(2):
+        E, Q = pu.staged_iteration(comp, Gs[t], pu.to_device(Gs[t]), E, Q, ml, rep)
+    comp.close()
+    _say("  ", rep)
+    outs = []
+    for flags in (0, B.FLAG_EAGER_RESIDUAL):
+        comp = B.Compressor(ll, rank, 8, 8, W, 255.0, flags)
+        for l in ml:
+            comp.set_q(l, Q0[l])
+        got, out = [], [torch.zeros(s, device="cuda") for s in layers]
+        for t in range(2):
+            comp.step(pu.to_device(Gs[t]), out)
+            got.append(torch.cat([v.reshape(-1) for v in out]).cpu().numpy())
+        outs.append(got + [comp.get_state(l, 1)[0] for l in ml])
+        comp.close()
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)

@@ -197,3 +197,21 @@ def test_sweep_0_items_of_narrow_layers():
         for gidx, w, row0, nrows, col0, ncols in tiles.tolist():
             cover[gidx, w] = cover.get((gidx, w), 0) + nrows * ncols
         assert all(cover[l, w] == layers[l][0] * layers[l][1] for l in range(len(layers)) for w in range(W))
+
+
+@pytest.mark.parametrize("rank", [4, 7, 12])
+@pytest.mark.parametrize("sweep", [0, 1, 2, 3])
+@pytest.mark.parametrize("shapes", [[(240, 309)], [(128, 1001), (9, 63)], [(300, 515), (1000, 257)], [(72, 1283)] * 12 + [(130, 257)] * 40])
+def test_work_lists_of_ragged_sets_cover_each_element_once(sweep, rank, shapes):
+    """Rows that are no multiple of four, in sets of few items (one pass per segment, chunks of 64 columns) and of many."""
+    layers, W = B.layer_list(shapes, ()), 2
+    cover = _coverage(layers, rank, W, sweep)
+    assert sorted(cover) == [(i, w) for i in range(len(shapes)) for w in range(1 if sweep == 3 else W)]
+    for key, m in cover.items():
+        assert m.min() == 1 and m.max() == 1, key
+    few = len(shapes) < 10
+    widest = B.plan_tiles(layers, rank, 8, 8, W, sweep)[:, 5].max()
+    if sweep == 1:
+        assert widest == (64 if few else 256)
+    if sweep == 0 and rank < 9:
+        assert widest <= 256 if few else widest > 256
