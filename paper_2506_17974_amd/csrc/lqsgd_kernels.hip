@@ -2383,6 +2383,296 @@ __device__ __forceinline__ void mfma_tile32(const float* __restrict__ G, float* 
   }
 }
 
+// ---------------------------------------------------------------------------
+// The add modes at rank pad 64 with the factor operand shared through LDS.
+//
+// The 32 x 64 form above fetches 16 KB of Q per wavefront and block from L2 -- once as the G-hat operand, 16 bytes
+// of 64 different rows per instruction, once as the P operand, 4 bytes a lane: 80 memory instructions beside the 24 of
+// the streams -- and has registers for one wavefront per SIMD: that is what bounded it, not the matrix rate.  Here a
+// workgroup of eight wavefronts takes 64 rows: wavefront w works on the 32 rows w / 4 and on the 64 columns w % 4 of a
+// round of 256, so that every row of Q in a round serves two wavefronts and comes once, coalesced, through LDS.
+// Both matrix operands are read from there: 16-byte chunk x of row c lies at x ^ (c % 16), so that a read of 64 rows'
+// chunks and a read of one row's ranks both hit all banks.  The next round's rows of Q, G and E are requested
+// when this round's M is formed and arrive behind its P product and the next G-hat; one register set of each is
+// enough, which leaves room for two wavefronts per SIMD.  Sums are those of the form above, to the bit.
+// Microseconds, before and now: 8192^2, W = 16, r = 64 3720 / 3020; ResNet-18 set, W = 8, r = 50 373 / 277; 16 x (512 x 4096),
+// W = 8 970 / 676; ragged set (64 x 27 .. 1000 x 2049), W = 4, r = 50 88 / 67.  At 8192^2 the matrix pipes are busy 67 % of
+// the time, at a clock that falls from 2.4 to 2.1 GHz under them.
+// ---------------------------------------------------------------------------
+template <int MODE, bool GB16, bool NTS>
+__device__ __forceinline__ void mfma_pair_tile(const float* __restrict__ G, float* __restrict__ M, const float* Q, const float* Pb,
+                                               float* __restrict__ Pp, int cols, int r, int item_row0, int item_rows,
+                                               int col0, int col1, int lane, int wave, char* qs, float (*lds_all)[32 * kLP]) {
+  static_assert(MODE == kMAdd || MODE == kMAddFused, "add modes");
+  constexpr bool NEEDG = MODE == kMAddFused;
+  constexpr int RP = 64, KH = 32, NB = 2;
+  constexpr int EARLY = NEEDG ? 12 : 16;           // requests of a block, of 16, that go out with the round before it
+  constexpr int KIND = kRagged;                    // of edge blocks (takes aligned rows too)
+  const int tid = threadIdx.x, li = lane & 31, h = lane >> 5;
+  const int ph = wave & 3;
+  const int row0 = item_row0 + 32 * (wave >> 2), nrows = min(32, item_rows - 32 * (wave >> 2));   // (nrows <= 0: none)
+  float* lds = lds_all[wave];
+  float pa[KH];
+  if constexpr (NEEDG) {
+#pragma unroll
+    for (int k = 0; k < KH; ++k) pa[k] = 0.0f;
+    if (li < nrows) {
+      const char* src = reinterpret_cast<const char*>(Pb + (size_t)row0 * RP);
+#pragma unroll
+      for (int t = 0; t < KH / 4; ++t) {
+        const Pk<4> x = ldrow<false>(src + 16 * t, (unsigned)(li * RP + KH * h) * 4u);
+        pa[4 * t] = x.v[0]; pa[4 * t + 1] = x.v[1]; pa[4 * t + 2] = x.v[2]; pa[4 * t + 3] = x.v[3];
+      }
+    }
+  }
+  v16f accP[NB], accP2[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { accP[nb][i] = 0.0f; accP2[nb][i] = 0.0f; }
+
+  // 256 rows of Q: thread t moves chunk t % 16 of rows t / 16 + 32 i
+  Pk<4> st[8];
+  const int qrow = tid >> 4;
+  char* const qdst = qs + qrow * (RP * 4) + ((((tid & 15) ^ (qrow & 15))) << 4);
+  auto fetch_q = [&](auto full_tag, const int tid, const int c0, const int i0, const int i1) __attribute__((always_inline)) {
+    unsigned lq = (unsigned)tid * 16u;
+    asm volatile("" : "+v"(lq));
+#pragma unroll
+    for (int i = i0; i < i1; ++i) {
+      if constexpr (decltype(full_tag)::value) {
+        st[i] = ldrow<false>(reinterpret_cast<const char*>(Q + (size_t)(c0 + 32 * i) * RP), lq);
+      } else {
+        const int c = c0 + (tid >> 4) + 32 * i;
+        st[i] = ldrow<false>(reinterpret_cast<const char*>(Q + (size_t)min(c, col1 - 1) * RP), (unsigned)(tid & 15) * 16u);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) st[i].v[v] = keep_if(st[i].v[v], c < col1);
+      }
+    }
+  };
+  auto place_q = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      *reinterpret_cast<float4*>(qdst + i * (32 * RP * 4)) = make_float4(st[i].v[0], st[i].v[1], st[i].v[2], st[i].v[3]);
+  };
+
+  Pk<4> g[8], e[8];
+  // A lane's place in 4 rows of a whole block is one offset from a wave-uniform base.  It is hidden from the optimiser, which
+  // otherwise keeps the sums of the two for all rows, 64 bits each, in registers across the rounds.
+  auto place = [&](const int ln) __attribute__((always_inline)) {
+    unsigned lo = (unsigned)((ln >> 4) * cols + (ln & 15) * 4) * 4u;
+    asm volatile("" : "+v"(lo));
+    return lo;
+  };
+  // Requests k0 .. k1 of the 16 of a whole block: G and E of the block's rows 4 i + sr in turn.  real false: of the first
+  // rows of Q instead, for a round that has no next one (a branch around a request would part the loop in two).
+  auto fetch = [&](const bool real, const int ln, const int c, const int k0, const int k1) __attribute__((always_inline)) {
+    unsigned lo = place(ln);
+    if (!real) lo = (unsigned)ln * 16u;
+#pragma unroll
+    for (int k = k0; k < k1; ++k) {
+      const int i = k >> 1;
+      const size_t off = (size_t)(row0 + 4 * i) * cols + c;
+      const char* base = (k & 1) ? reinterpret_cast<const char*>(M + off) : grad_row<GB16>(G, off);
+      if (!real) base = reinterpret_cast<const char*>(Q);
+      if (k & 1) {
+        e[i] = ldrow<NTS>(base, lo);
+      } else if constexpr (GB16) {                 // kept packed (two registers) until the block is worked on
+        const Pk<2> x = ldrow_bf16_packed<LQSGD_NT_G != 0>(base, lo);
+        g[i].v[0] = x.v[0]; g[i].v[1] = x.v[1];
+      } else {
+        g[i] = ldgrad<LQSGD_NT_G != 0, GB16>(base, lo);
+      }
+    }
+  };
+  auto fetch_edge = [&](const int ln, const int c) __attribute__((always_inline)) {
+    const int sr = ln >> 4, cl = c + (ln & 15) * 4;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const size_t off = (size_t)(row0 + min(4 * i + sr, nrows - 1)) * cols;   // rows beyond nrows repeat the last one, and are never stored
+      g[i] = ldedge<KIND, LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), cl, cols);
+      e[i] = ldedge<KIND, NTS, false>(reinterpret_cast<const char*>(M + off), cl, cols);
+    }
+    if (cl + 4 > cols) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) { edge_fix<1>(g[i].v, cl, cols); edge_fix<1>(e[i].v, cl, cols); }
+    }
+  };
+  // M of the block that g and e hold, to memory and to this wavefront's LDS tile
+  // (late: the block's last requests are made here, between the matrix instructions)
+  auto form = [&](auto full_tag, auto late_tag, const int ln, const int c) __attribute__((always_inline)) {
+    constexpr bool FULL = decltype(full_tag)::value;
+    const int li = ln & 31, h = ln >> 5, sr = ln >> 4, c4 = (ln & 15) * 4;
+    if constexpr (NEEDG) {
+      // rows li and 32 + li of this wavefront's part of Q, ranks 32 h .. 32 h + 31
+      unsigned qb = (unsigned)((64 * ph + li) * (RP * 4) + (((8 * h) ^ (li & 15)) << 4));
+      asm volatile("" : "+v"(qb));                 // (the exclusive ors below stay here, and out of registers across the rounds)
+      v16f gh0, gh1;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) { gh0[i] = 0.0f; gh1[i] = 0.0f; }
+#pragma unroll
+      for (int t = 0; t < KH / 4; ++t) {
+        const float4 q0 = *reinterpret_cast<const float4*>(qs + (qb ^ (16 * t)));
+        const float4 q1 = *reinterpret_cast<const float4*>(qs + (qb ^ (16 * t)) + 32 * RP * 4);
+        gh0 = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[4 * t], q0.x, gh0, 0, 0, 0);
+        gh1 = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[4 * t], q1.x, gh1, 0, 0, 0);
+        gh0 = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[4 * t + 1], q0.y, gh0, 0, 0, 0);
+        gh1 = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[4 * t + 1], q1.y, gh1, 0, 0, 0);
+        gh0 = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[4 * t + 2], q0.z, gh0, 0, 0, 0);
+        gh1 = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[4 * t + 2], q1.z, gh1, 0, 0, 0);
+        gh0 = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[4 * t + 3], q0.w, gh0, 0, 0, 0);
+        gh1 = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[4 * t + 3], q1.w, gh1, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(late_tag)::value) {
+          if (t < 16 - EARLY) fetch(true, ln, c, EARLY + t, EARLY + t + 1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        lds[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP + li] = gh0[v];
+        lds[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP + 32 + li] = gh1[v];
+      }
+      wave_lds_fence();
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float4 t = *reinterpret_cast<const float4*>(lds + (4 * i + sr) * kLP + c4);
+        e[i].v[0] -= t.x; e[i].v[1] -= t.y; e[i].v[2] -= t.z; e[i].v[3] -= t.w;
+      }
+      wave_lds_fence();
+    }
+    const unsigned lo = FULL ? place(ln) : 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      Pk<4> m, gv = g[i];
+      if constexpr (GB16 && FULL) gv = unpack_bf16(g[i].v[0], g[i].v[1]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) m.v[v] = gv.v[v] + e[i].v[v];
+      if constexpr (FULL)
+        strow<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + 4 * i) * cols + c), lo, m);
+      else if (4 * i + sr < nrows)
+        stgroup<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + 4 * i + sr) * cols), (unsigned)(c + c4) * 4u, cols - c - c4, m);
+      *reinterpret_cast<float4*>(lds + (4 * i + sr) * kLP + c4) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
+    }
+    wave_lds_fence();
+  };
+  // between(j): called after the j-th of eight groups of matrix instructions
+  auto product = [&](const int ln, auto&& between) __attribute__((always_inline)) {
+    const int li = ln & 31, h = ln >> 5;
+    // ranks li and 32 + li of row 32 h + kk of this wavefront's part of Q
+    unsigned bq = (unsigned)((64 * ph + 32 * h) * (RP * 4) + li * 4);
+    asm volatile("" : "+v"(bq));
+    auto q_at = [&](int nb, int kk) __attribute__((always_inline)) {
+      return *reinterpret_cast<const float*>(qs + (bq ^ (16 * (kk & 7))) + kk * (RP * 4) + (nb ^ ((kk >> 3) & 1)) * 128);
+    };
+#pragma unroll
+    for (int t = 0; t < 8; t += 2) {
+      const float4 a0 = *reinterpret_cast<const float4*>(lds + li * kLP + 32 * h + 4 * t);
+      const float4 a1 = *reinterpret_cast<const float4*>(lds + li * kLP + 32 * h + 4 * t + 4);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        accP[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, q_at(nb, 4 * t + 0), accP[nb], 0, 0, 0);
+        accP2[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, q_at(nb, 4 * t + 4), accP2[nb], 0, 0, 0);
+        accP[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, q_at(nb, 4 * t + 1), accP[nb], 0, 0, 0);
+        accP2[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, q_at(nb, 4 * t + 5), accP2[nb], 0, 0, 0);
+        accP[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, q_at(nb, 4 * t + 2), accP[nb], 0, 0, 0);
+        accP2[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, q_at(nb, 4 * t + 6), accP2[nb], 0, 0, 0);
+        accP[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, q_at(nb, 4 * t + 3), accP[nb], 0, 0, 0);
+        accP2[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, q_at(nb, 4 * t + 7), accP2[nb], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);         // (keeps the reads of all steps from being drawn together: registers)
+        between(t + nb);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+
+  int c0 = col0;
+  const bool small_offsets = cols < (1 << 26);     // byte offsets within 4 rows fit 32 bits
+  // whole rounds: 64 rows x 256 columns, the next one's requests ahead of this one's P product
+  const int whole = item_rows == 64 && small_offsets ? (col1 - col0) / 256 : 0;
+  if (whole > 0) {
+    fetch_q(std::true_type{}, tid, c0, 0, 8);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(true, lane, c0 + 64 * ph, 0, EARLY);
+    const int cend = col0 + 256 * whole;
+    do {
+      place_q();
+      __syncthreads();
+      form(std::true_type{}, std::bool_constant<NEEDG>{}, lane, c0 + 64 * ph);
+      c0 += 256;
+      // The next round's requests go out between the matrix instructions, a few at a time: made in one go, 24 a wavefront,
+      // they fill what a CU can have outstanding, and all eight wavefronts wait for room before their next matrix instruction.
+      // The rows of Q first: requests complete in order, and these are needed first.
+      product(lane, [&](const int j) __attribute__((always_inline)) {
+        if (j < 4) fetch_q(std::true_type{}, tid, min(c0, cend - 256), 2 * j, 2 * j + 2);
+        else fetch(c0 < cend, lane, c0 + 64 * ph, (j - 4) * (EARLY / 4), (j - 3) * (EARLY / 4));
+      });
+      __syncthreads();
+    } while (c0 < cend);
+  }
+  for (; c0 < col1; c0 += 256) {                   // (the same number of rounds, and of barriers, for all wavefronts)
+    const int c = c0 + 64 * ph;
+    // The lane number is hidden from the optimiser, which otherwise keeps addresses of these rounds in registers that the
+    // whole rounds need.
+    int ln = lane, td = tid;
+    asm volatile("" : "+v"(ln), "+v"(td));
+    fetch_q(std::false_type{}, td, c0, 0, 8);
+    place_q();
+    __syncthreads();
+    if (nrows > 0 && c < col1) {
+      if (nrows == 32 && c + 64 <= col1 && small_offsets) {
+        fetch(true, ln, c, 0, 16);
+        form(std::true_type{}, std::false_type{}, ln, c);
+      } else {
+        fetch_edge(ln, c);
+        form(std::false_type{}, std::false_type{}, ln, c);
+      }
+      product(ln, [](int) {});
+    }
+    __syncthreads();
+  }
+  // P partial of the item = sum over the four wavefronts of its rows, added in wavefront order
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      lds[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP + 32 * nb + li] = accP[nb][v] + accP2[nb][v];
+  __syncthreads();
+  const float (*const part)[32 * kLP] = lds_all + (wave & 4);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int rr = ((tid & 255) >> 6) + 4 * i, k = tid & 63;
+    const float t = ((part[0][rr * kLP + k] + part[1][rr * kLP + k]) + part[2][rr * kLP + k]) + part[3][rr * kLP + k];
+    if (rr < nrows && k < r) Pp[(size_t)(row0 + rr) * r + k] = t;
+  }
+}
+
+template <int MODE, bool GB16, bool NTS>
+__global__ __launch_bounds__(512, 2) void mfma_pair_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
+  __shared__ __attribute__((aligned(256))) char qs[256 * 64 * 4];
+  __shared__ __attribute__((aligned(16))) float lds_all[8][32 * kLP];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & (kWave - 1);
+  if (blockIdx.x == 0) zero_absmax_cells(a, 512);
+  const Tile tl = tiles[reverse ? ntiles - 1 - (int)blockIdx.x : (int)blockIdx.x];   // one item per workgroup
+  const int layer = tl.lw / a.W, worker = tl.lw - layer * a.W;
+  const LayerDesc& ld = a.layers[layer];
+  const float* G = a.grads[(size_t)worker * a.n_all + ld.gidx];
+  float* M = a.E + (size_t)worker * a.m_stride + ld.m_off;
+  float* Pp = a.Ppart + (size_t)worker * a.ppart_stride + ld.ppart_off + (size_t)tl.aux * ld.np_pad;
+  const int col0 = tl.aux * ld.segw;
+  const int col1 = min(ld.cols, col0 + ld.segw);
+  if (ld.kind == kOneColumnPerLane) {            // eight of the item's rows per wavefront
+    const int nr = min(8, tl.nrows - 8 * wave);
+    if (nr > 0)
+      narrow_rows<64, 8, true, MODE == kMAddFused, true, false, GB16>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, nullptr,
+                                                                      ld.cols, ld.r, tl.row0 + 8 * wave, nr, lane, 0, 0.0f);
+    return;
+  }
+  mfma_pair_tile<MODE, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ld.cols, ld.r, tl.row0, tl.nrows,
+                                  col0, col1, lane, wave, qs, lds_all);
+}
+
 // Wavefronts per SIMD the register allocation aims for: two at rank pad 16 (2.65 -> 2.47 ms on
 // 8192^2 x 16 workers), one at rank pad 32, where two would spill (3.0 -> 4.6 ms).
 template <int RP, int MODE, bool GB16 = false, bool NTS = false>
@@ -2391,7 +2681,15 @@ __global__ __launch_bounds__(256, RP <= 16 ? 2 : 1) void mfma_sweep_kernel(DevAr
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & (kWave - 1);
   if ((MODE == kMAdd || MODE == kMAddFused) && blockIdx.x == 0) zero_absmax_cells(a, 256);
-  const Tile tl = tiles[reverse ? ntiles - 1 - (int)blockIdx.x : (int)blockIdx.x];   // one item per workgroup
+  constexpr int PER = RP == 64 ? 2 : 1;            // workgroups per item: 32 rows each
+  const int item = (int)blockIdx.x / PER;
+  Tile tl = tiles[reverse ? ntiles - 1 - item : item];
+  if constexpr (PER == 2) {
+    const int skip = 32 * ((int)blockIdx.x & 1);
+    tl.row0 += skip;
+    tl.nrows = min(32, tl.nrows - skip);
+    if (tl.nrows <= 0) return;
+  }
   const int layer = tl.lw / a.W, worker = tl.lw - layer * a.W;
   const LayerDesc& ld = a.layers[layer];
   const float* G = (MODE == kMAdd || MODE == kMAddFused) ? a.grads[(size_t)worker * a.n_all + ld.gidx] : nullptr;
@@ -3308,9 +3606,27 @@ hipError_t launch_residual(int rp, int mode, const DevArgs& a, const Tile* tiles
 }
 #endif
 
+// Rank pad 64: items of 64 rows go to mfma_pair_kernel, a workgroup each, unless every 32 rows can have a CU of their own:
+// the 32-row form then has twice the workgroups and takes one round of them (sweep 0, microseconds, 32-row form / 64-row form:
+// 64 items, 4096 x 2048, W = 1 66 / 85; 128 items, 4 x 1024^2, W = 2 42 / 49, 4096 x 3072, W = 1 59 / 68; 132 items, 2 x (2100 x
+// 1500), W = 2 107 / 77; 192 items, 4 x 1024^2, W = 3 71 / 51).
+[[maybe_unused]] constexpr int kCus = 256;
 template <int RP, int MODE>
 void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s) {
-  const dim3 grid(ntiles);
+  const dim3 grid(ntiles * (RP == 64 ? 2 : 1));
+  if constexpr (RP == 64) {
+    if (2 * ntiles > kCus) {
+#define LQSGD_LAUNCH_MP(GB, NT) mfma_pair_kernel<MODE, GB, NT><<<dim3(ntiles), dim3(512), 0, s>>>(a, tiles, ntiles, reverse)
+      if (a.g_bf16) {
+        if (a.nt_store) { LQSGD_LAUNCH_MP(true, true); } else { LQSGD_LAUNCH_MP(true, false); }
+      } else {
+        if (a.nt_store) { LQSGD_LAUNCH_MP(false, true); } else { LQSGD_LAUNCH_MP(false, false); }
+      }
+#undef LQSGD_LAUNCH_MP
+      note_kernel("mfma_pair_kernel<%d, %s, %s>", MODE, tf(a.g_bf16), tf(a.nt_store));
+      return;
+    }
+  }
   // the narrow form at rank pad 32, where the wide one runs one wavefront per SIMD (8192^2 x 16, r = 32: 2.77 -> 2.60 ms)
 #define LQSGD_LAUNCH_MA(GB, NT)                                                                                            \
   if constexpr (RP == 32) mfma_sweep32_kernel<RP, MODE, GB, NT><<<grid, dim3(512), 0, s>>>(a, tiles, ntiles, reverse);     \
@@ -3326,7 +3642,7 @@ void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int revers
 
 template <int RP>
 hipError_t launch_mfma_sweep_rp(int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s) {
-  const dim3 grid(ntiles), block(256);
+  const dim3 grid(ntiles * (RP == 64 ? 2 : 1)), block(256);
   switch (mode) {
     case kMAdd: launch_mfma_add<RP, kMAdd>(a, tiles, ntiles, reverse, s); return hipGetLastError();
     case kMAddFused: launch_mfma_add<RP, kMAddFused>(a, tiles, ntiles, reverse, s); return hipGetLastError();

@@ -193,7 +193,7 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
 
   // sweep 0's column segments, and the items it would have with one group of rows in each
   constexpr int cw = kWave * 4;                          // columns of a wavefront's pass over a row
-  const int rowgrp = mfma_a ? 32 : kRowsPerGroup;        // a matrix-core item is one 32-row tile
+  const int rowgrp = RP == 64 ? 64 : mfma_a ? 32 : kRowsPerGroup;   // a matrix-core item is one 32-row tile, at rank pad 64 two
   int64_t items0 = 0, narrow = 0;
   auto cut = [&](LayerDesc& d, int64_t segmax) {
     const int nseg = (int)((d.cols + segmax - 1) / segmax);

@@ -377,3 +377,38 @@ def test_rows_of_any_width_in_sets_of_many_items(rank):
         comp.close()
     for a, b in zip(*outs):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_sixty_four_row_items_add_in_the_order_of_thirty_two_row_ones(bf16):
+    """Rank pad 64: sweep 0 takes items of 64 rows where there are more than 32-row ones for every CU.  The same layers alone (32
+    rows) and in a long list (64 rows), heights around 32 and 64, whole and partial rounds of 256 columns: the same bits."""
+    import torch
+    shapes, W, rank = [(64, 300), (33, 1000), (40, 1023), (64, 256), (32, 770), (31, 700), (63, 516), (64, 61), (64, 1024)], 2, 50
+    _say("case: 64-row items", shapes, bf16)
+    rng = np.random.default_rng(64)
+    Q0 = [rng.standard_normal((c, min(rank, n, c))).astype(f32) for n, c in shapes]
+    Gs = [[[(rng.standard_normal(s) * 1e-3).astype(f32) for s in shapes] for _ in range(W)] for _ in range(3)]
+    got = []
+    for fill in (0, 60):
+        layers = shapes + [(64, 260)] * fill
+        comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, W, 255.0, B.FLAG_BF16_GRADIENTS if bf16 else 0)
+        for l, (n, c) in enumerate(layers):
+            comp.set_q(l, Q0[l] if l < len(shapes) else rng.standard_normal((c, min(rank, n, c))).astype(f32))
+        out = [torch.zeros(s, device="cuda") for s in layers]
+        res, names = [], set()
+        comp.timing_enable(True)
+        for G in Gs:
+            g = [[torch.from_numpy(x).cuda() for x in w] + [torch.ones(64, 260, device="cuda").normal_()] * fill for w in G]
+            if bf16:
+                g = [[x.to(torch.bfloat16) for x in w] for w in g]
+            comp.step(g, out)
+            res += [o.cpu().numpy() for o in out[:len(shapes)]]
+            names.add(comp.launched_kernel(0).split("<")[0])
+        res += [comp.get_state(l, w)[0] for l in range(len(shapes)) for w in range(W)]
+        res += [comp.get_factor(B.FACTOR_P_PRE, l, w) for l in range(len(shapes)) for w in range(W)]
+        assert names == {"mfma_pair_kernel" if fill else "mfma_sweep_kernel"}
+        comp.close()
+        got.append(res)
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
