@@ -2114,274 +2114,7 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
   }
 }
 
-// ---------------------------------------------------------------------------
-// The add modes at rank pad 32 in a narrower form: a wavefront takes 32 rows x 32
-// columns per step instead of 32 x 64, which halves the registers of the
-// streamed tile, of the G-hat operands and of the Q slice, so that two
-// wavefronts fit on a SIMD (with 32 x 64 the fused mode needs more than half
-// the register file and runs one wavefront per SIMD, every load exposed).
-// Eight wavefronts per workgroup keep the 1 KiB-per-row access of the
-// workgroup.  Row layout here: 8 lanes = 128 contiguous bytes of a row, 8 rows
-// per instruction.  G-hat elements come out of the same sequence of matrix
-// instructions as in the 32 x 64 form (the contraction over the ranks does not
-// depend on the column blocking), so the residual modes, which keep that form,
-// still match bit for bit.
-// ---------------------------------------------------------------------------
-constexpr int kLP32 = 36;   // LDS pitch (floats) of a 32 x 32 tile: 16-byte aligned rows
-
-template <int RP, int MODE, bool GB16, bool NTS>
-__device__ __forceinline__ void mfma_tile32(const float* __restrict__ G, float* __restrict__ M,
-                                            const float* Q, const float* Pb, float* __restrict__ Pp,
-                                            int cols, int r, int row0, int nrows, int col0, int col1,
-                                            int lane, int wave, float (*lds_all)[32 * kLP32]) {
-  static_assert(RP == 32 && (MODE == kMAdd || MODE == kMAddFused), "narrow form: add modes at rank pad 32");
-  float* lds = lds_all[wave];
-  constexpr bool NEEDG = (MODE != kMAdd);
-  constexpr int KH = RP / 2;
-  const int li = lane & 31, h = lane >> 5;
-  const int sr = lane >> 3, c4 = (lane & 7) * 4;   // row layout: rows 8 i + sr, columns c4 .. c4 + 3
-  float pa[KH];
-  if constexpr (NEEDG) {
-    const int row = row0 + li;
-    if (li < nrows) {
-      const float4* src = reinterpret_cast<const float4*>(Pb + (size_t)row * RP + KH * h);
-#pragma unroll
-      for (int t = 0; t < KH / 4; ++t) {
-        const float4 x = src[t];
-        pa[4 * t] = x.x; pa[4 * t + 1] = x.y; pa[4 * t + 2] = x.z; pa[4 * t + 3] = x.w;
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < KH; ++k) pa[k] = 0.0f;
-    }
-  }
-  v16f accP, accP2;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) { accP[i] = 0.0f; accP2[i] = 0.0f; }
-
-  // the G and E (or old M) values of one 32 x 32 block at an edge of the layer
-  auto fetch = [&](const int c, Pk<4>* g, Pk<4>* e) {
-    const int cl = c + c4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const size_t off = (size_t)(row0 + min(8 * i + sr, nrows - 1)) * cols;   // rows beyond nrows: never stored
-      g[i] = ldedge<kRagged, LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), cl, cols);
-      e[i] = ldedge<kRagged, NTS, false>(reinterpret_cast<const char*>(M + off), cl, cols);
-    }
-    if (cl + 4 > cols) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { edge_fix<1>(g[i].v, cl, cols); edge_fix<1>(e[i].v, cl, cols); }
-    }
-  };
-  auto block = [&](const int c, Pk<4>* g, Pk<4>* e) {
-    const int cl = c + c4;
-    if constexpr (NEEDG) {
-      float qb[KH];
-      const int col = c + li;
-      if (col < col1) {
-        const float4* src = reinterpret_cast<const float4*>(Q + (size_t)col * RP + KH * h);
-#pragma unroll
-        for (int t = 0; t < KH / 4; ++t) {
-          const float4 x = src[t];
-          qb[4 * t] = x.x; qb[4 * t + 1] = x.y; qb[4 * t + 2] = x.z; qb[4 * t + 3] = x.w;
-        }
-      } else {
-#pragma unroll
-        for (int k = 0; k < KH; ++k) qb[k] = 0.0f;
-      }
-      v16f gh;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) gh[i] = 0.0f;
-#pragma unroll
-      for (int k = 0; k < KH; ++k) gh = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[k], qb[k], gh, 0, 0, 0);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) lds[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP32 + li] = gh[v];
-      wave_lds_fence();
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float4 t = *reinterpret_cast<const float4*>(lds + (8 * i + sr) * kLP32 + c4);
-        e[i].v[0] -= t.x; e[i].v[1] -= t.y; e[i].v[2] -= t.z; e[i].v[3] -= t.w;
-      }
-      wave_lds_fence();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int rr = 8 * i + sr;
-      Pk<4> m;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) m.v[v] = g[i].v[v] + e[i].v[v];
-      if (rr < nrows)
-        stgroup<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + rr) * cols), (unsigned)cl * 4u, cols - cl, m);
-      *reinterpret_cast<float4*>(lds + rr * kLP32 + c4) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
-    }
-    // the Q slice of the P product is fetched only now: the registers of the G-hat operands are free again
-    float bq[16];
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      const int col = c + 16 * h + kk;
-      bq[kk] = col < col1 ? Q[(size_t)col * RP + li] : 0.0f;
-    }
-    wave_lds_fence();
-    {
-      const float4 a0 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h);
-      const float4 a1 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 4);
-      const float4 a2 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 8);
-      const float4 a3 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 12);
-      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, bq[0], accP, 0, 0, 0);
-      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, bq[4], accP2, 0, 0, 0);
-      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, bq[1], accP, 0, 0, 0);
-      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, bq[5], accP2, 0, 0, 0);
-      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, bq[2], accP, 0, 0, 0);
-      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, bq[6], accP2, 0, 0, 0);
-      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, bq[3], accP, 0, 0, 0);
-      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, bq[7], accP2, 0, 0, 0);
-      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.x, bq[8], accP, 0, 0, 0);
-      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.x, bq[12], accP2, 0, 0, 0);
-      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.y, bq[9], accP, 0, 0, 0);
-      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.y, bq[13], accP2, 0, 0, 0);
-      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.z, bq[10], accP, 0, 0, 0);
-      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.z, bq[14], accP2, 0, 0, 0);
-      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.w, bq[11], accP, 0, 0, 0);
-      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.w, bq[15], accP2, 0, 0, 0);
-    }
-    wave_lds_fence();
-  };
-  // Interior blocks (all 32 rows and 32 columns exist) run without bounds tests, as a software
-  // pipeline inside the wavefront: the next block's G and E are requested before this block's matrix
-  // instructions, and the next block's G-hat operand from Q as soon as this block's G-hat is done.
-  // Requests complete in order, so everything a block waits for is requested before the prefetch.
-  int c = col0 + 32 * wave;
-  if (nrows == 32 && c + 32 <= col1 && cols < (1 << 26)) {   // (byte offsets within 8 rows fit 32 bits)
-    const int last = c + ((col1 - 32 - c) / 256) * 256;   // this wavefront's last whole block
-    Pk<4> g[4], e[4], gn[4], en[4];
-    float qb[KH], bq[16];
-    // Addresses are a wave-uniform base (scalar registers, advanced by scalar adds) plus a byte
-    // offset per lane that does not change from block to block.
-    const unsigned goff = (unsigned)(sr * cols + c4) * 4u;      // lane's place in a slab of 8 rows
-    const unsigned qboff = (unsigned)(li * RP + KH * h) * 4u;   // ... in 32 rows of Q (G-hat operand)
-    const unsigned bqoff = (unsigned)(16 * h * RP + li) * 4u;   // ... in 32 rows of Q (P operand)
-    auto fetch_ge = [&](const int cb, Pk<4>* gg, Pk<4>* ee) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const size_t off = (size_t)(row0 + 8 * i) * cols + cb;
-        if constexpr (GB16) {   // kept packed (two registers) until the block is worked on
-          const Pk<2> t = ldrow_bf16_packed<LQSGD_NT_G != 0>(grad_row<GB16>(G, off), goff);
-          gg[i].v[0] = t.v[0]; gg[i].v[1] = t.v[1];
-        } else {
-          gg[i] = ldgrad<LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), goff);
-        }
-        ee[i] = ldrow<NTS>(reinterpret_cast<const char*>(M + off), goff);
-      }
-    };
-    auto fetch_qb = [&](const int cb) {
-      const char* base = reinterpret_cast<const char*>(Q + (size_t)cb * RP);
-#pragma unroll
-      for (int t = 0; t < KH / 4; ++t) {
-        const Pk<4> x = ldrow<false>(base + 16 * t, qboff);
-        qb[4 * t] = x.v[0]; qb[4 * t + 1] = x.v[1]; qb[4 * t + 2] = x.v[2]; qb[4 * t + 3] = x.v[3];
-      }
-    };
-    fetch_ge(c, g, e);
-    if constexpr (NEEDG) fetch_qb(c);
-    // one block; MORE: another whole block follows (a constant, so that no branch joins two
-    // request histories and every wait counts exactly)
-    auto step = [&](auto more_tag, const int c, Pk<4>* g, Pk<4>* e, Pk<4>* gn, Pk<4>* en) {
-      constexpr bool more = decltype(more_tag)::value;
-      {
-        const char* base = reinterpret_cast<const char*>(Q + (size_t)c * RP);
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) bq[kk] = *gptr<float>(base + kk * RP * 4 + bqoff);
-      }
-      if constexpr (more) fetch_ge(c + 256, gn, en);
-      __builtin_amdgcn_sched_barrier(0);   // the requests above stay ahead of the arithmetic below
-      if constexpr (NEEDG) {
-        v16f gh;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) gh[i] = 0.0f;
-#pragma unroll
-        for (int k = 0; k < KH; ++k) gh = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[k], qb[k], gh, 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (more) fetch_qb(c + 256);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) lds[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP32 + li] = gh[v];
-        wave_lds_fence();
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float4 t = *reinterpret_cast<const float4*>(lds + (8 * i + sr) * kLP32 + c4);
-          e[i].v[0] -= t.x; e[i].v[1] -= t.y; e[i].v[2] -= t.z; e[i].v[3] -= t.w;
-        }
-        wave_lds_fence();
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int rr = 8 * i + sr;
-        Pk<4> m, gv = g[i];
-        if constexpr (GB16) gv = unpack_bf16(g[i].v[0], g[i].v[1]);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) m.v[v] = gv.v[v] + e[i].v[v];
-        strow<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + 8 * i) * cols + c), goff, m);
-        *reinterpret_cast<float4*>(lds + rr * kLP32 + c4) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
-      }
-      wave_lds_fence();
-      {
-        const float4 a0 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h);
-        const float4 a1 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 4);
-        const float4 a2 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 8);
-        const float4 a3 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 12);
-        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, bq[0], accP, 0, 0, 0);
-        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, bq[4], accP2, 0, 0, 0);
-        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, bq[1], accP, 0, 0, 0);
-        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, bq[5], accP2, 0, 0, 0);
-        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, bq[2], accP, 0, 0, 0);
-        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, bq[6], accP2, 0, 0, 0);
-        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, bq[3], accP, 0, 0, 0);
-        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, bq[7], accP2, 0, 0, 0);
-        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.x, bq[8], accP, 0, 0, 0);
-        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.x, bq[12], accP2, 0, 0, 0);
-        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.y, bq[9], accP, 0, 0, 0);
-        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.y, bq[13], accP2, 0, 0, 0);
-        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.z, bq[10], accP, 0, 0, 0);
-        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.z, bq[14], accP2, 0, 0, 0);
-        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.w, bq[11], accP, 0, 0, 0);
-        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.w, bq[15], accP2, 0, 0, 0);
-      }
-      wave_lds_fence();
-    };
-    // two blocks per trip, the two register sets changing roles (no copies, so nothing waits for
-    // a prefetch before its values are needed)
-    for (; c + 256 < last; c += 512) {
-      step(std::true_type{}, c, g, e, gn, en);
-      step(std::true_type{}, c + 256, gn, en, g, e);
-    }
-    if (c < last) {
-      step(std::true_type{}, c, g, e, gn, en);
-      step(std::false_type{}, c + 256, gn, en, g, e);
-      c += 512;
-    } else {
-      step(std::false_type{}, c, g, e, gn, en);
-      c += 256;
-    }
-  }
-  for (; c < col1; c += 256) {
-    Pk<4> g[4], e[4];
-    fetch(c, g, e);
-    block(c, g, e);
-  }
-  // P partial of the item = sum over the eight wavefronts, added in wavefront order
-#pragma unroll
-  for (int v = 0; v < 16; ++v) lds[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP32 + li] = accP[v] + accP2[v];
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int e = (int)threadIdx.x + 512 * i;
-    const int rr = e >> 5, k = e & 31;
-    float t = lds_all[0][rr * kLP32 + k];
-#pragma unroll
-    for (int wv = 1; wv < 8; ++wv) t += lds_all[wv][rr * kLP32 + k];
-    if (rr < nrows && k < r) Pp[(size_t)(row0 + rr) * r + k] = t;
-  }
-}
+constexpr int kLP32 = 36;   // LDS pitch (floats) of a 32 x 32 block: 16-byte aligned rows
 
 // ---------------------------------------------------------------------------
 // The add modes at rank pad 64 with the factor operand shared through LDS.
@@ -2673,6 +2406,284 @@ __global__ __launch_bounds__(512, 2) void mfma_pair_kernel(DevArgs a, const Tile
                                   col0, col1, lane, wave, qs, lds_all);
 }
 
+// ---------------------------------------------------------------------------
+// The add modes at rank pad 32, loads and matrix work split differently over the wavefronts of a workgroup.
+//
+// What bounds this sweep is the order in which its streams reach memory (8192 columns, nothing but its loads and stores,
+// microseconds per million elements: pieces of 32 columns a wavefront, 64 rows a workgroup 2.4, 32 rows 2.15; 32 rows in
+// pieces of 256 columns with a barrier a round 1.95 - 2.05).  So in a round of 32 rows x 256 columns wavefront w loads and
+// stores rows 8 w .. 8 w + 7, 1 KiB each, and multiplies columns 64 w .. 64 w + 63; G-hat and M change hands in an LDS
+// tile.  G and E of the next round are requested between the matrix instructions of this one, the 64 rows of Q that
+// a wavefront multiplies with come once, coalesced, through LDS of its own (they used to come twice from L2, in 40 requests a
+// wavefront and round, most of them 4 bytes a lane) and are read there in both operand layouts: chunk x of 16 bytes of row c
+// lies in row c ^ (c / 16 % 2) at x ^ (c / 2 % 8), so that a read of 32 rows' chunks and a read of two rows' ranks both hit all
+// banks.  Two workgroups a CU, so that one's barriers and first requests hide behind the other's work: with eight wavefronts to a
+// workgroup, one to a CU and requests two rounds ahead, items of few rounds wait (16 x 1024^2, W = 8 304 / 354 us; 8192^2,
+// W = 4 615 / 593).  Blocks of 32 columns accumulate on their own and are added at the end in their order.
+// Microseconds at r = 32 unless said otherwise, W = 8, with 32 x 32 blocks per wavefront / now: ResNet-18 set 239 / 216, with
+// bfloat16 gradients 233 / 189; 8192^2, W = 16 2431 / 2246; 4 x (3000 x 5000), r = 20 1892 / 1273; 32 x (512 x 4608) 1446 / 1342;
+// 1024 x 2048 sets as small as 4 x 1024^2, W = 2 29 / 27.
+// ---------------------------------------------------------------------------
+constexpr int kLP256 = 260;  // LDS pitch (floats) of the 32 x 256 tile: 16-byte aligned rows, 4-bank skew per row
+
+template <int MODE, bool GB16, bool NTS>
+__device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, float* __restrict__ M, const float* Q, const float* Pb,
+                                                float* __restrict__ Pp, int cols, int r, int row0, int nrows, int col0, int col1,
+                                                int lane, int wave, char* qs, float* tile) {
+  static_assert(MODE == kMAdd || MODE == kMAddFused, "add modes");
+  constexpr bool NEEDG = MODE == kMAddFused;
+  constexpr int RP = 32, KH = 16;
+  constexpr int NBK = 2, RPW = 8;                  // blocks of 32 columns that a wavefront multiplies, rows that it moves
+  constexpr int KIND = kRagged;                    // of edge rounds (takes aligned rows too)
+  qs += wave * (NBK * 32 * RP * 4);
+  float pa[KH];
+  if constexpr (NEEDG) {
+    const int li = lane & 31, h = lane >> 5;
+#pragma unroll
+    for (int k = 0; k < KH; ++k) pa[k] = 0.0f;
+    if (li < nrows) {
+      const char* src = reinterpret_cast<const char*>(Pb + (size_t)row0 * RP);
+#pragma unroll
+      for (int t = 0; t < KH / 4; ++t) {
+        const Pk<4> x = ldrow<false>(src + 16 * t, (unsigned)(li * RP + KH * h) * 4u);
+        pa[4 * t] = x.v[0]; pa[4 * t + 1] = x.v[1]; pa[4 * t + 2] = x.v[2]; pa[4 * t + 3] = x.v[3];
+      }
+    }
+  }
+  v16f accP[NBK], accP2[NBK];
+#pragma unroll
+  for (int b = 0; b < NBK; ++b)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { accP[b][i] = 0.0f; accP2[b][i] = 0.0f; }
+
+  // its rows of Q: request i moves rows 8 i .. 8 i + 7, 16 bytes a lane
+  Pk<4> st[4 * NBK];
+  auto fetch_q = [&](auto full_tag, const int ln, const int c0) __attribute__((always_inline)) {
+    unsigned lq = (unsigned)ln * 16u;
+    asm volatile("" : "+v"(lq));
+#pragma unroll
+    for (int i = 0; i < 4 * NBK; ++i) {
+      if constexpr (decltype(full_tag)::value) {
+        st[i] = ldrow<false>(reinterpret_cast<const char*>(Q + (size_t)(c0 + 8 * i) * RP), lq);
+      } else {
+        const int c = c0 + 8 * i + (ln >> 3);
+        st[i] = ldrow<false>(reinterpret_cast<const char*>(Q + (size_t)min(c, col1 - 1) * RP), (unsigned)(ln & 7) * 16u);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) st[i].v[v] = keep_if(st[i].v[v], c < col1);
+      }
+    }
+  };
+  auto place_q = [&](const int ln) __attribute__((always_inline)) {
+    unsigned w = (unsigned)((ln >> 3) * (RP * 4) + (((ln & 7) ^ (ln >> 4)) << 4));
+#pragma unroll
+    for (int i = 0; i < 4 * NBK; ++i)
+      *reinterpret_cast<float4*>(qs + (w ^ (128u * ((i >> 1) & 1)) ^ (64u * (i & 1))) + i * (8 * RP * 4)) =
+          make_float4(st[i].v[0], st[i].v[1], st[i].v[2], st[i].v[3]);
+    wave_lds_fence();
+  };
+  // Requests k0 .. k1 of a whole round's: G and E of this wavefront's rows in turn.  real false: of the first
+  // rows of Q instead, for a round that has no next one (a branch around a request would part the loop in two).
+  auto fetch = [&](const bool real, const int c0, Pk<4>* g, Pk<4>* e, const int k0, const int k1) __attribute__((always_inline)) {
+    const unsigned lo = (unsigned)lane * 16u;
+#pragma unroll
+    for (int k = k0; k < k1; ++k) {
+      const int i = k >> 1;
+      const size_t off = (size_t)(row0 + RPW * wave + i) * cols + c0;
+      const char* base = (k & 1) ? reinterpret_cast<const char*>(M + off) : grad_row<GB16>(G, off);
+      if (!real) base = reinterpret_cast<const char*>(Q);
+      if (k & 1) {
+        e[i] = ldrow<NTS>(base, lo);
+      } else if constexpr (GB16) {                 // kept packed (two registers) until the round is worked on
+        const Pk<2> x = ldrow_bf16_packed<LQSGD_NT_G != 0>(base, lo);
+        g[i].v[0] = x.v[0]; g[i].v[1] = x.v[1];
+      } else {
+        g[i] = ldgrad<LQSGD_NT_G != 0, GB16>(base, lo);
+      }
+    }
+  };
+  auto fetch_edge = [&](const int ln, const int c0, Pk<4>* g, Pk<4>* e) __attribute__((always_inline)) {
+    const int cl = c0 + 4 * ln;
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+      const size_t off = (size_t)(row0 + min(RPW * wave + i, nrows - 1)) * cols;   // rows beyond nrows repeat the last one, and are never stored
+      g[i] = ldedge<KIND, LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), cl, cols);
+      e[i] = ldedge<KIND, NTS, false>(reinterpret_cast<const char*>(M + off), cl, cols);
+    }
+    if (cl + 4 > cols) {
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) { edge_fix<1>(g[i].v, cl, cols); edge_fix<1>(e[i].v, cl, cols); }
+    }
+  };
+  // G-hat of this wavefront's 32 columns, into the tile
+  auto reconstruct = [&](const int ln) __attribute__((always_inline)) {
+    const int li = ln & 31, h = ln >> 5;
+    // row li of this wavefront's rows of Q, ranks 16 h .. 16 h + 15
+    const unsigned qb = (unsigned)((li ^ (li >> 4)) * (RP * 4) + (((4 * h) ^ ((li >> 1) & 7)) << 4));
+    v16f gh[NBK];
+#pragma unroll
+    for (int b = 0; b < NBK; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) gh[b][i] = 0.0f;
+#pragma unroll
+    for (int t = 0; t < KH / 4; ++t) {
+      float4 q[NBK];
+#pragma unroll
+      for (int b = 0; b < NBK; ++b) q[b] = *reinterpret_cast<const float4*>(qs + (qb ^ (16 * t)) + b * (32 * RP * 4));
+#pragma unroll
+      for (int b = 0; b < NBK; ++b) gh[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[4 * t], q[b].x, gh[b], 0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < NBK; ++b) gh[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[4 * t + 1], q[b].y, gh[b], 0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < NBK; ++b) gh[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[4 * t + 2], q[b].z, gh[b], 0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < NBK; ++b) gh[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[4 * t + 3], q[b].w, gh[b], 0, 0, 0);
+    }
+#pragma unroll
+    for (int b = 0; b < NBK; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) tile[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP256 + 32 * (NBK * wave + b) + li] = gh[b][v];
+  };
+  // M of this wavefront's four rows, to memory and into the tile
+  auto form = [&](auto full_tag, const int ln, const int c0, Pk<4>* g, Pk<4>* e) __attribute__((always_inline)) {
+    constexpr bool FULL = decltype(full_tag)::value;
+    float* mine = tile + RPW * wave * kLP256 + 4 * ln;
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+      if constexpr (NEEDG) {
+        const float4 t = *reinterpret_cast<const float4*>(mine + i * kLP256);
+        e[i].v[0] -= t.x; e[i].v[1] -= t.y; e[i].v[2] -= t.z; e[i].v[3] -= t.w;
+      }
+      Pk<4> m, gv = g[i];
+      if constexpr (GB16 && FULL) gv = unpack_bf16(g[i].v[0], g[i].v[1]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) m.v[v] = gv.v[v] + e[i].v[v];
+      if constexpr (FULL)
+        strow<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + RPW * wave + i) * cols + c0), (unsigned)ln * 16u, m);
+      else if (RPW * wave + i < nrows)
+        stgroup<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + RPW * wave + i) * cols), (unsigned)(c0 + 4 * ln) * 4u, cols - c0 - 4 * ln, m);
+      *reinterpret_cast<float4*>(mine + i * kLP256) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
+    }
+  };
+  // P += M Q over this wavefront's 32 columns; between(j): called after the j-th of 4 NBK groups of matrix instructions
+  auto product = [&](const int ln, auto&& between) __attribute__((always_inline)) {
+    const int li = ln & 31, h = ln >> 5;
+    // rank li of row 16 h + kk of this wavefront's rows of Q
+    unsigned bq = (unsigned)(16 * h * (RP * 4) + 128 * h + li * 4);
+    asm volatile("" : "+v"(bq));                   // (the exclusive ors below stay here, and out of registers across the rounds)
+    auto q_at = [&](int b, int kk) __attribute__((always_inline)) {
+      return *reinterpret_cast<const float*>(qs + (bq ^ (128u * (kk & 1)) ^ (16u * ((kk >> 1) & 7))) + (32 * b + (kk & ~1)) * (RP * 4));
+    };
+    const float* src = tile + li * kLP256 + 32 * NBK * wave + 16 * h;
+#pragma unroll
+    for (int t = 0; t < 4; t += 2)                 // two accumulators a block (even / odd float4 of the lane's run of columns)
+#pragma unroll
+      for (int b = 0; b < NBK; ++b) {
+        const float4 a0 = *reinterpret_cast<const float4*>(src + 32 * b + 4 * t);
+        const float4 a1 = *reinterpret_cast<const float4*>(src + 32 * b + 4 * t + 4);
+        accP[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, q_at(b, 4 * t + 0), accP[b], 0, 0, 0);
+        accP2[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, q_at(b, 4 * t + 4), accP2[b], 0, 0, 0);
+        accP[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, q_at(b, 4 * t + 1), accP[b], 0, 0, 0);
+        accP2[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, q_at(b, 4 * t + 5), accP2[b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        between(NBK * t + 2 * b);
+        __builtin_amdgcn_sched_barrier(0);
+        accP[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, q_at(b, 4 * t + 2), accP[b], 0, 0, 0);
+        accP2[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, q_at(b, 4 * t + 6), accP2[b], 0, 0, 0);
+        accP[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, q_at(b, 4 * t + 3), accP[b], 0, 0, 0);
+        accP2[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, q_at(b, 4 * t + 7), accP2[b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        between(NBK * t + 2 * b + 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    wave_lds_fence();
+  };
+
+  int c0 = col0;
+  // whole rounds: 32 rows x 256 columns
+  const int cend = nrows == 32 ? col0 + (col1 - col0) / 256 * 256 : col0;
+  if (c0 < cend) {
+    Pk<4> g[RPW], e[RPW];
+    // The tile needs two barriers a round: G-hat is complete before rows are read, M before columns are.  A wavefront's
+    // next G-hat goes to columns that only it reads, and no row is written before all have passed the first barrier again.
+    fetch_q(std::true_type{}, lane, c0 + 32 * NBK * wave);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(true, c0, g, e, 0, 2 * RPW);
+    __builtin_amdgcn_sched_barrier(0);
+    do {
+      place_q(lane);
+      fetch_q(std::true_type{}, lane, min(c0 + 256, cend - 256) + 32 * NBK * wave);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (NEEDG) reconstruct(lane);
+      __syncthreads();
+      form(std::true_type{}, lane, c0, g, e);
+      __syncthreads();
+      c0 += 256;
+      product(lane, [&](const int j) __attribute__((always_inline)) { fetch(c0 < cend, c0, g, e, 2 * j, 2 * j + 2); });
+    } while (c0 < cend);
+  }
+  for (; c0 < col1; c0 += 256) {                   // (the same number of rounds, and of barriers, for all wavefronts)
+    int ln = lane;                                 // hidden from the optimiser (see mfma_pair_tile)
+    asm volatile("" : "+v"(ln));
+    const bool mine = c0 + 32 * NBK * wave < col1;
+    Pk<4> g[RPW], e[RPW];
+    fetch_edge(ln, c0, g, e);
+    if (mine) {
+      fetch_q(std::false_type{}, ln, c0 + 32 * NBK * wave);
+      place_q(ln);
+      if constexpr (NEEDG) reconstruct(ln);
+    }
+    __syncthreads();
+    form(std::false_type{}, ln, c0, g, e);
+    __syncthreads();
+    if (mine) product(ln, [](int) {});
+  }
+  __syncthreads();
+  // P partial of the item = sum over the eight blocks of a round, added in their order
+  const int li = lane & 31, h = lane >> 5;
+#pragma unroll
+  for (int b = 0; b < NBK; ++b) {
+    float* part = tile + (NBK * wave + b) * (32 * kLP32);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) part[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP32 + li] = accP[b][v] + accP2[b][v];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int x = (int)threadIdx.x + 256 * i, rr = x >> 5, k = x & 31;
+    float t = tile[rr * kLP32 + k];
+#pragma unroll
+    for (int wv = 1; wv < 8; ++wv) t += tile[wv * (32 * kLP32) + rr * kLP32 + k];
+    if (rr < nrows && k < r) Pp[(size_t)(row0 + rr) * r + k] = t;
+  }
+}
+
+template <int MODE, bool GB16, bool NTS>
+__global__ __launch_bounds__(256, 2) void mfma_round_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
+  __shared__ __attribute__((aligned(256))) char qs[8 * 32 * 32 * 4];
+  __shared__ __attribute__((aligned(16))) float tile[8 * 32 * kLP32];   // 32 x kLP256 in the rounds, the partial sums after them
+  static_assert(32 * kLP256 <= 8 * 32 * kLP32, "");
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & (kWave - 1);
+  if (blockIdx.x == 0) zero_absmax_cells(a, 256);
+  const Tile tl = tiles[reverse ? ntiles - 1 - (int)blockIdx.x : (int)blockIdx.x];   // one item per workgroup
+  const int layer = tl.lw / a.W, worker = tl.lw - layer * a.W;
+  const LayerDesc& ld = a.layers[layer];
+  const float* G = a.grads[(size_t)worker * a.n_all + ld.gidx];
+  float* M = a.E + (size_t)worker * a.m_stride + ld.m_off;
+  float* Pp = a.Ppart + (size_t)worker * a.ppart_stride + ld.ppart_off + (size_t)tl.aux * ld.np_pad;
+  const int col0 = tl.aux * ld.segw;
+  const int col1 = min(ld.cols, col0 + ld.segw);
+  if (ld.kind == kOneColumnPerLane) {            // eight of the item's rows per wavefront
+    const int nr = min(8, tl.nrows - 8 * wave);
+    if (nr > 0)
+      narrow_rows<32, 8, true, MODE == kMAddFused, true, false, GB16>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, nullptr, ld.cols,
+                                                                      ld.r, tl.row0 + 8 * wave, nr, lane, 0, 0.0f);
+    return;
+  }
+  mfma_round_tile<MODE, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ld.cols, ld.r, tl.row0, tl.nrows,
+                                   col0, col1, lane, wave, qs, tile);
+}
+
 // Wavefronts per SIMD the register allocation aims for: two at rank pad 16 (2.65 -> 2.47 ms on
 // 8192^2 x 16 workers), one at rank pad 32, where two would spill (3.0 -> 4.6 ms).
 template <int RP, int MODE, bool GB16 = false, bool NTS = false>
@@ -2710,31 +2721,6 @@ __global__ __launch_bounds__(256, RP <= 16 ? 2 : 1) void mfma_sweep_kernel(DevAr
   }
   mfma_tile<RP, MODE, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ghat_out, ld.cols, ld.r, tl.row0,
                                  tl.nrows, col0, col1, lane, wave, lds_all, a.update, a.eta);
-}
-
-template <int RP, int MODE, bool GB16, bool NTS>
-__global__ __launch_bounds__(512, 2) void mfma_sweep32_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
-  __shared__ __attribute__((aligned(16))) float lds_all[8][32 * kLP32];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & (kWave - 1);
-  if (blockIdx.x == 0) zero_absmax_cells(a, 512);
-  const Tile tl = tiles[reverse ? ntiles - 1 - (int)blockIdx.x : (int)blockIdx.x];   // one item per workgroup
-  const int layer = tl.lw / a.W, worker = tl.lw - layer * a.W;
-  const LayerDesc& ld = a.layers[layer];
-  const float* G = a.grads[(size_t)worker * a.n_all + ld.gidx];
-  float* M = a.E + (size_t)worker * a.m_stride + ld.m_off;
-  float* Pp = a.Ppart + (size_t)worker * a.ppart_stride + ld.ppart_off + (size_t)tl.aux * ld.np_pad;
-  const int col0 = tl.aux * ld.segw;
-  const int col1 = min(ld.cols, col0 + ld.segw);
-  if (ld.kind == kOneColumnPerLane) {            // four of the item's rows per wavefront
-    const int nr = min(4, tl.nrows - 4 * wave);
-    if (nr > 0)
-      narrow_rows<RP, 4, true, MODE == kMAddFused, true, false, GB16>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, nullptr,
-                                                                      ld.cols, ld.r, tl.row0 + 4 * wave, nr, lane, 0, 0.0f);
-    return;
-  }
-  mfma_tile32<RP, MODE, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ld.cols, ld.r, tl.row0, tl.nrows,
-                                   col0, col1, lane, wave, lds_all);
 }
 
 // Copies of the aggregated factors with rows of RP ranks (zero beyond the layer's rank), as the sweeps
@@ -3627,9 +3613,8 @@ void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int revers
       return;
     }
   }
-  // the narrow form at rank pad 32, where the wide one runs one wavefront per SIMD (8192^2 x 16, r = 32: 2.77 -> 2.60 ms)
 #define LQSGD_LAUNCH_MA(GB, NT)                                                                                            \
-  if constexpr (RP == 32) mfma_sweep32_kernel<RP, MODE, GB, NT><<<grid, dim3(512), 0, s>>>(a, tiles, ntiles, reverse);     \
+  if constexpr (RP == 32) mfma_round_kernel<MODE, GB, NT><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, reverse);     \
   else mfma_sweep_kernel<RP, MODE, GB, NT><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, reverse)
   if (a.g_bf16) {
     if (a.nt_store) { LQSGD_LAUNCH_MA(true, true); } else { LQSGD_LAUNCH_MA(true, false); }
@@ -3637,7 +3622,8 @@ void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int revers
     if (a.nt_store) { LQSGD_LAUNCH_MA(false, true); } else { LQSGD_LAUNCH_MA(false, false); }
   }
 #undef LQSGD_LAUNCH_MA
-  note_kernel("%s<%d, %d, %s, %s>", RP == 32 ? "mfma_sweep32_kernel" : "mfma_sweep_kernel", RP, MODE, tf(a.g_bf16), tf(a.nt_store));
+  if (RP == 32) note_kernel("mfma_round_kernel<%d, %s, %s>", MODE, tf(a.g_bf16), tf(a.nt_store));
+  else note_kernel("mfma_sweep_kernel<%d, %d, %s, %s>", RP, MODE, tf(a.g_bf16), tf(a.nt_store));
 }
 
 template <int RP>

@@ -155,3 +155,10 @@ def test_quantiser_ranges(alpha, scale):
                     assert np.array_equal(k, want), np.abs(k.astype(int) - want).max()
                     assert np.array_equal(s.astype(bool), (x < 0) & (want > 0))
         comp.close()
+
+
+@pytest.mark.parametrize("rank,bits,W", [(20, 8, 2), (32, 0, 2)])
+def test_rounds_of_256_columns(rank, bits, W):
+    """Sweep 0 at rank pad 32 goes by rounds of 32 rows x 256 columns: one and several whole rounds, a partial one behind them and
+    alone, one to three rows more or less than a round has, more than one column segment."""
+    test_ragged_shapes([(96, 256), (65, 512), (95, 768), (97, 300), (66, 1028), (128, 2305), (161, 64)], rank, bits, W)
