@@ -2616,9 +2616,15 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
       if constexpr (NEEDG) reconstruct(lane);
       __syncthreads();
       form(std::true_type{}, lane, c0, g, e);
-      __syncthreads();
       c0 += 256;
-      product(lane, [&](const int j) __attribute__((always_inline)) { fetch(c0 < cend, c0, g, e, 2 * j, 2 * j + 2); });
+      // A round without G-hat is short, and its requests all go out at once (a first iteration of the ResNet-18 set, W = 8: 237 us
+      // spread as below, 208 at once).  With G-hat spread ones are as fast in large sets and faster in small ones (1024 x 576,
+      // r = 20 58 / 62, 4 x 1024^2 79 / 85).
+      if constexpr (!NEEDG) fetch(c0 < cend, c0, g, e, 0, 2 * RPW);
+      __syncthreads();
+      product(lane, [&](const int j) __attribute__((always_inline)) {
+        if constexpr (NEEDG) fetch(c0 < cend, c0, g, e, 2 * j, 2 * j + 2);
+      });
     } while (c0 < cend);
   }
   for (; c0 < col1; c0 += 256) {                   // (the same number of rounds, and of barriers, for all wavefronts)
