@@ -464,8 +464,15 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   // written back underneath the following reads, and streaming both ways wins (8192^2 x 16,
   // 4.3 GB: sweep 0 2.27 -> 2.04 - 2.14 ms).  Measured crossover: 0.55 - 0.7 GB.
   {
+    // Non-temporal stores do not wait for the rest of a line of 128 bytes: rows that start anywhere in a line leave two
+    // partial ones per KiB, written apart.  So not where most elements are in rows that are no multiple of 64 bytes (W = 8,
+    // a step with and without, us: 4 x (3000 x 5000) r = 4 1662 / 1592, r = 16 2084 / 1814, r = 50 2648 / 2527; 4 x (3001 x 5001)
+    // r = 4 1759 / 1620, r = 20 2042 / 1954; rows of 64 bytes, 3000 x 5008, r = 4 1539 / 1549; of 128, 3000 x 4992 1440 / 1476).
+    int64_t askew = 0;
+    for (const LayerDesc& d : p.layers)
+      if (d.cols % 16) askew += (int64_t)d.rows * d.cols;
     const int64_t slab_bytes = 4 * (int64_t)p.W * p.m_stride;
-    a.nt_store = slab_bytes >= ((int64_t)640 << 20) ? 1 : 0;
+    a.nt_store = slab_bytes >= ((int64_t)640 << 20) && 2 * askew <= p.matrix_elements ? 1 : 0;
 #ifdef LQSGD_TUNING     // a tuning build can force the choice and switch the alternating sweep direction off
     if (const char* f = std::getenv("LQSGD_NT_STORE")) {
       if (f[0] == '1') a.nt_store = 1;
