@@ -336,6 +336,17 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
     for (int32_t g = 0; g < gp; g += kXBlockGroups) tilesXP.push_back(XTile{li, g});
     for (int32_t g = 0; g < gq; g += kXBlockGroups) tilesXQ.push_back(XTile{li, g});
   }
+  // Rank pads 32 and 64: few workgroups fit a CU there and an item can take a tenth of the launch, so that the widest go first and
+  // the last ones are short (sweep 0, us, in the layers' order / sorted: ragged set, r = 20, W = 4 48.2 / 43.5; ResNet-18 set, W = 8,
+  // r = 50 277 / 267, r = 32 216 / 216; 64 x 576 .. 512 x 4608, W = 4, r = 64 135 / 129).
+  if (mfma) {
+    auto width = [&](const Tile& t) {
+      const LayerDesc& d = layers[t.lw / W];
+      return std::min(d.segw, d.cols - t.aux * d.segw) * (t.nrows > 32 ? 2 : 1);
+    };
+    std::stable_sort(tilesA.begin(), tilesA.end(), [&](const Tile& x, const Tile& y) { return width(x) > width(y); });
+  }
+
   m_stride = round_up(m_acc, 64);
   p_stride = round_up(p_acc, 64);
   q_stride = round_up(q_acc, 64);
