@@ -1563,8 +1563,8 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 // NB = 2: the rows of P-bar come through LDS, kPRows at a time, once for the four wavefronts of the workgroup, with 16 rows in
 // flight; enter(row) makes `row` and those behind it the ones that `ps` holds, together with the other wavefronts.  (From L2 they
 // are two requests of 4 bytes a lane beside one of 16 for M, and take registers that 8 rows in flight were left with: ResNet-18
-// set, r = 50, W = 8 166 -> 161 us, 8 x (512 x 4608), r = 64 241 -> 209, 16 x 1024^2 185 -> 172, ragged set, W = 4 55 -> 50,
-// 8192^2, W = 8 651 -> 652.)  NB = 1: straight from L2, one request beside one (through LDS 16 x 1024^2, W = 8 128 -> 136 us,
+// set, r = 50, W = 8 168 -> 162 us, 8 x (512 x 4608), r = 64 238 -> 211, 16 x 1024^2 185 -> 173, 8192^2, W = 8 663 - 689 ->
+// 633 - 644.)  NB = 1: straight from L2, one request beside one (through LDS 16 x 1024^2, W = 8 128 -> 136 us,
 // ResNet-18 set 92 -> 90).
 constexpr int kPRows = 256;
 template <int NB, int KIND, typename Enter>
@@ -1585,38 +1585,29 @@ __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const L
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[nb][s][i] = 0.0f;
+  const float* Pb = p_operand(a, ld) + li;         // this lane's rank of each block: rows of 32 NB, zero beyond r
   Pk<4> am[U], an[U];
-  const float* Pb = p_operand(a, ld) + li;         // (NB = 1)
-  float bp[SHARE ? 1 : U], bn[SHARE ? 1 : U];
-  auto fetch = [&](int rb, Pk<4>* m, float* bp) __attribute__((always_inline)) {
+  float bp[NB][U], bn[NB][U];
+  auto fetch = [&](int rb, Pk<4>* m, float (*p)[U]) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int row = min(rb + 2 * u + h, rend - 1);        // (clamped in the last, partial group only)
       m[u] = ldedge<KIND, LQSGD_NT_M != 0, false>(reinterpret_cast<const char*>(M + (size_t)row * cols), cl, cols);
-      if constexpr (!SHARE) bp[u] = Pb[(size_t)row * 32];
+      if constexpr (!SHARE) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) p[nb][u] = Pb[(size_t)row * (32 * NB) + 32 * nb];
+      }
     }
   };
-  // (a row that does not exist counts as zeros on both sides: 0 x Inf would not be zero)
-  auto multiply = [&](auto part_tag, int rb, Pk<4>* m, float* bp) __attribute__((always_inline)) {
-    constexpr bool PART = decltype(part_tag)::value;
-    float p[NB][U];                                // this lane's rank of each block: rows of 32 NB, zero beyond r
+  auto read_p = [&](int rb, float (*p)[U]) __attribute__((always_inline)) {
+    if constexpr (SHARE) {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        if constexpr (SHARE) p[nb][u] = ps[(((rb - tl.row0) & (kPRows - 1)) + 2 * u + h) * (32 * NB) + 32 * nb + li];
-        else p[nb][u] = bp[u];
-      }
-    if constexpr (PART) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const bool ok = rb + 2 * u + h < rend;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) m[u].v[s] = keep_if(m[u].v[s], ok);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) p[nb][u] = keep_if(p[nb][u], ok);
-      }
+        for (int nb = 0; nb < NB; ++nb) p[nb][u] = ps[(((rb - tl.row0) & (kPRows - 1)) + 2 * u + h) * (32 * NB) + 32 * nb + li];
     }
+  };
+  auto multiply = [&](Pk<4>* m, float (*p)[U]) __attribute__((always_inline)) {
     if constexpr (KIND != kAligned) {
 #pragma unroll
       for (int u = 0; u < U; ++u) edge_fix<1>(m[u].v, cl, cols);
@@ -1645,11 +1636,15 @@ __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const L
       // P-bar loads down to their first use, and every group of matrix instructions then waits for
       // its operand and, requests completing in order, for the whole prefetch in front of it)
       __builtin_amdgcn_sched_barrier(0);
-      multiply(std::false_type{}, rb, am, bp);
+      read_p(rb, bp);
+      multiply(am, bp);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         am[u] = an[u];
-        if constexpr (!SHARE) bp[u] = bn[u];
+        if constexpr (!SHARE) {
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) bp[nb][u] = bn[nb][u];
+        }
       }
     }
   }
@@ -1657,7 +1652,17 @@ __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const L
     fetch(rb, am, bp);
     if constexpr (SHARE)
       if ((rb - tl.row0) % kPRows == 0) enter(rb);
-    multiply(std::true_type{}, rb, am, bp);
+    read_p(rb, bp);
+    // a row that does not exist counts as zeros on both sides (0 x Inf would not be zero)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool ok = rb + 2 * u + h < rend;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) am[u].v[s] = keep_if(am[u].v[s], ok);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) bp[nb][u] = keep_if(bp[nb][u], ok);
+    }
+    multiply(am, bp);
   }
   float* Qp = a.Qpart + (size_t)worker * a.qpart_stride + ld.qpart_off + (size_t)(tl.row0 / ld.rbb) * ld.nq_pad;
 #pragma unroll
@@ -1684,34 +1689,37 @@ __global__ __launch_bounds__(256, 2) void back_project_mfma_kernel(DevArgs a, co
   const int layer = tl.lw / a.W, worker = tl.lw - layer * a.W;
   const LayerDesc& ld = a.layers[layer];
   const int c0 = tl.aux * kMfmaCols + wave * 128;
-  __shared__ __attribute__((aligned(16))) float ps[NB == 2 ? kPRows * 32 * NB : 1];
-  const int tid = threadIdx.x, rend = tl.row0 + tl.nrows;
-  // rows of P-bar are contiguous: a linear copy, 16 bytes a thread and request
-  auto enter = [&](int row) __attribute__((always_inline)) {
-    const float* src = p_operand(a, ld) + (size_t)row * (32 * NB);
-    const int n4 = min(kPRows, rend - row) * (8 * NB);
-    if (row > tl.row0) __syncthreads();
-#pragma unroll
-    for (int i0 = 0; i0 < 8 * NB; i0 += 8) {
-      Pk<4> x[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) x[i] = ldrow<false>(reinterpret_cast<const char*>(src), (unsigned)min(tid + 256 * (i0 + i), n4 - 1) * 16u);
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (tid + 256 * (i0 + i) < n4)
-          reinterpret_cast<float4*>(ps)[tid + 256 * (i0 + i)] = make_float4(x[i].v[0], x[i].v[1], x[i].v[2], x[i].v[3]);
-    }
-    __syncthreads();
-  };
-  if (c0 >= ld.cols) {                             // no columns: only its share of the copies
-    if constexpr (NB == 2)
-      for (int row = tl.row0; row < rend; row += kPRows) enter(row);
-    return;
-  }
   // strips of which all 128 columns exist need no care at their end, whatever the alignment of the rows
-  if (c0 + 128 <= ld.cols) back_project_mfma_tile<NB, kAligned>(a, ld, tl, worker, c0, lane, ps, enter);
-  else if (ld.cols >= 4) back_project_mfma_tile<NB, kRagged>(a, ld, tl, worker, c0, lane, ps, enter);
-  else back_project_mfma_tile<NB, kNarrow>(a, ld, tl, worker, c0, lane, ps, enter);
+  auto run = [&](const float* ps, auto&& enter) __attribute__((always_inline)) {
+    if (c0 + 128 <= ld.cols) back_project_mfma_tile<NB, kAligned>(a, ld, tl, worker, c0, lane, ps, enter);
+    else if (ld.cols >= 4) back_project_mfma_tile<NB, kRagged>(a, ld, tl, worker, c0, lane, ps, enter);
+    else back_project_mfma_tile<NB, kNarrow>(a, ld, tl, worker, c0, lane, ps, enter);
+  };
+  if constexpr (NB == 2) {
+    __shared__ __attribute__((aligned(16))) float ps[kPRows * 32 * NB];
+    const int tid = threadIdx.x, rend = tl.row0 + tl.nrows;
+    // rows of P-bar are contiguous: a linear copy, 16 bytes a thread and request
+    auto enter = [&](int row) __attribute__((always_inline)) {
+      const float* src = p_operand(a, ld) + (size_t)row * (32 * NB);
+      const int n4 = min(kPRows, rend - row) * (8 * NB);
+      if (row > tl.row0) __syncthreads();
+#pragma unroll
+      for (int i0 = 0; i0 < 8 * NB; i0 += 8) {
+        Pk<4> x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = ldrow<false>(reinterpret_cast<const char*>(src), (unsigned)min(tid + 256 * (i0 + i), n4 - 1) * 16u);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (tid + 256 * (i0 + i) < n4)
+            reinterpret_cast<float4*>(ps)[tid + 256 * (i0 + i)] = make_float4(x[i].v[0], x[i].v[1], x[i].v[2], x[i].v[3]);
+      }
+      __syncthreads();
+    };
+    if (c0 < ld.cols) run(ps, enter);
+    else for (int row = tl.row0; row < rend; row += kPRows) enter(row);   // no columns: only its share of the copies
+  } else {
+    if (c0 < ld.cols) run(nullptr, [](int) {});
+  }
 }
 
 // ---------------------------------------------------------------------------
