@@ -2458,7 +2458,7 @@ __global__ __launch_bounds__(512, 2) void mfma_pair_kernel(DevArgs a, const Tile
 }
 
 // ---------------------------------------------------------------------------
-// The add modes at rank pad 32, loads and matrix work split differently over the wavefronts of a workgroup.
+// The add modes at rank pads 16 and 32, loads and matrix work split differently over the wavefronts of a workgroup.
 //
 // What bounds this sweep is the order in which its streams reach memory (8192 columns, nothing but its loads and stores,
 // microseconds per million elements: pieces of 32 columns a wavefront, 64 rows a workgroup 2.4, 32 rows 2.15; 32 rows in
@@ -2470,20 +2470,25 @@ __global__ __launch_bounds__(512, 2) void mfma_pair_kernel(DevArgs a, const Tile
 // lies in row c ^ (c / 16 % 2) at x ^ (c / 2 % 8), so that a read of 32 rows' chunks and a read of two rows' ranks both hit all
 // banks.  Two workgroups a CU, so that one's barriers and first requests hide behind the other's work: with eight wavefronts to a
 // workgroup, one to a CU and requests two rounds ahead, items of few rounds wait (16 x 1024^2, W = 8 304 / 354 us; 8192^2,
-// W = 4 615 / 593).  Blocks of 32 columns accumulate on their own and are added at the end in their order.
+// W = 4 615 / 593).  At rank pad 32 blocks of 32 columns accumulate on their own and are added at the end in their order, at rank
+// pad 16 a wavefront's 64 columns.
 // Microseconds at r = 32 unless said otherwise, W = 8, with 32 x 32 blocks per wavefront / now: ResNet-18 set 239 / 216, with
 // bfloat16 gradients 233 / 189; 8192^2, W = 16 2431 / 2246; 4 x (3000 x 5000), r = 20 1892 / 1273; 32 x (512 x 4608) 1446 / 1342;
-// 1024 x 2048 sets as small as 4 x 1024^2, W = 2 29 / 27.
+// sets as small as 4 x 1024^2, W = 2 29 / 27.  At r = 16, with 32 x 64 blocks per wavefront / now: ResNet-18 set 209 / 201, at r = 12
+// with bfloat16 gradients 218 / 162; 8192^2 1091 / 1025; 4 x (3000 x 5000) 1283 / 1246; ragged set (64 x 27 .. 1000 x 2049), r = 12,
+// W = 4 52 / 42; 4 x 1024^2, W = 2 28.6 / 24.7; 8 x (512 x 4608) 339 / 346, the one set measured that lost.
 // ---------------------------------------------------------------------------
 constexpr int kLP256 = 260;  // LDS pitch (floats) of the 32 x 256 tile: 16-byte aligned rows, 4-bank skew per row
 
-template <int MODE, bool GB16, bool NTS>
+template <int RP, int MODE, bool GB16, bool NTS>
 __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, float* __restrict__ M, const float* Q, const float* Pb,
                                                 float* __restrict__ Pp, int cols, int r, int row0, int nrows, int col0, int col1,
                                                 int lane, int wave, char* qs, float* tile) {
-  static_assert(MODE == kMAdd || MODE == kMAddFused, "add modes");
+  static_assert((RP == 16 || RP == 32) && (MODE == kMAdd || MODE == kMAddFused), "add modes at rank pads 16 and 32");
   constexpr bool NEEDG = MODE == kMAddFused;
-  constexpr int RP = 32, KH = 16;
+  constexpr int KH = RP / 2;
+  constexpr int NP = RP == 32 ? 2 : 1;             // sums of P a wavefront keeps: of each block of 32 columns, or of all 64
+  constexpr int LPR = RP / 4, RPQ = 64 / LPR;      // 16-byte chunks of a row of Q, rows that a request moves
   constexpr int NBK = 2, RPW = 8;                  // blocks of 32 columns that a wavefront multiplies, rows that it moves
   constexpr int KIND = kRagged;                    // of edge rounds (takes aligned rows too)
   qs += wave * (NBK * 32 * RP * 4);
@@ -2501,34 +2506,37 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
       }
     }
   }
-  v16f accP[NBK], accP2[NBK];
+  v16f accP[NP], accP2[NP];
 #pragma unroll
-  for (int b = 0; b < NBK; ++b)
+  for (int b = 0; b < NP; ++b)
 #pragma unroll
     for (int i = 0; i < 16; ++i) { accP[b][i] = 0.0f; accP2[b][i] = 0.0f; }
 
-  // its rows of Q: request i moves rows 8 i .. 8 i + 7, 16 bytes a lane
-  Pk<4> st[4 * NBK];
+  // its rows of Q: request i moves rows RPQ i .. RPQ i + RPQ - 1, 16 bytes a lane
+  constexpr int NQ = 64 / RPQ;
+  Pk<4> st[NQ];
   auto fetch_q = [&](auto full_tag, const int ln, const int c0) __attribute__((always_inline)) {
     unsigned lq = (unsigned)ln * 16u;
     asm volatile("" : "+v"(lq));
 #pragma unroll
-    for (int i = 0; i < 4 * NBK; ++i) {
+    for (int i = 0; i < NQ; ++i) {
       if constexpr (decltype(full_tag)::value) {
-        st[i] = ldrow<false>(reinterpret_cast<const char*>(Q + (size_t)(c0 + 8 * i) * RP), lq);
+        st[i] = ldrow<false>(reinterpret_cast<const char*>(Q + (size_t)(c0 + RPQ * i) * RP), lq);
       } else {
-        const int c = c0 + 8 * i + (ln >> 3);
-        st[i] = ldrow<false>(reinterpret_cast<const char*>(Q + (size_t)min(c, col1 - 1) * RP), (unsigned)(ln & 7) * 16u);
+        const int c = c0 + RPQ * i + ln / LPR;
+        st[i] = ldrow<false>(reinterpret_cast<const char*>(Q + (size_t)min(c, col1 - 1) * RP), (unsigned)(ln % LPR) * 16u);
 #pragma unroll
         for (int v = 0; v < 4; ++v) st[i].v[v] = keep_if(st[i].v[v], c < col1);
       }
     }
   };
   auto place_q = [&](const int ln) __attribute__((always_inline)) {
-    unsigned w = (unsigned)((ln >> 3) * (RP * 4) + (((ln & 7) ^ (ln >> 4)) << 4));
+    // (rank pad 16: chunk x of row c lies at x ^ (c / 4 % 4))
+    const unsigned w = RP == 32 ? (unsigned)((ln >> 3) * (RP * 4) + (((ln & 7) ^ (ln >> 4)) << 4))
+                                : (unsigned)((ln >> 2) * (RP * 4) + (((ln & 3) ^ (ln >> 4)) << 4));
 #pragma unroll
-    for (int i = 0; i < 4 * NBK; ++i)
-      *reinterpret_cast<float4*>(qs + (w ^ (128u * ((i >> 1) & 1)) ^ (64u * (i & 1))) + i * (8 * RP * 4)) =
+    for (int i = 0; i < NQ; ++i)
+      *reinterpret_cast<float4*>(qs + (RP == 32 ? w ^ (128u * ((i >> 1) & 1)) ^ (64u * (i & 1)) : w) + i * (RPQ * RP * 4)) =
           make_float4(st[i].v[0], st[i].v[1], st[i].v[2], st[i].v[3]);
     wave_lds_fence();
   };
@@ -2568,8 +2576,9 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
   // G-hat of this wavefront's 32 columns, into the tile
   auto reconstruct = [&](const int ln) __attribute__((always_inline)) {
     const int li = ln & 31, h = ln >> 5;
-    // row li of this wavefront's rows of Q, ranks 16 h .. 16 h + 15
-    const unsigned qb = (unsigned)((li ^ (li >> 4)) * (RP * 4) + (((4 * h) ^ ((li >> 1) & 7)) << 4));
+    // row li of this wavefront's rows of Q, ranks KH h .. KH h + KH - 1
+    const unsigned qb = RP == 32 ? (unsigned)((li ^ (li >> 4)) * (RP * 4) + (((4 * h) ^ ((li >> 1) & 7)) << 4))
+                                 : (unsigned)(li * (RP * 4) + (((2 * h) ^ ((li >> 2) & 3)) << 4));
     v16f gh[NBK];
 #pragma unroll
     for (int b = 0; b < NBK; ++b)
@@ -2618,6 +2627,36 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
   // P += M Q over this wavefront's 32 columns; between(j): called after the j-th of 4 NBK groups of matrix instructions
   auto product = [&](const int ln, auto&& between) __attribute__((always_inline)) {
     const int li = ln & 31, h = ln >> 5;
+    if constexpr (RP == 16) {
+      // rank li % 16 of row 32 h + kk (lanes 16 .. 31: columns of the block that nobody reads)
+      const char* bq = qs + 32 * h * (RP * 4) + (li & 3) * 4;
+      const unsigned ch = (unsigned)((li >> 2) & 3);
+      auto q_at = [&](int kk) __attribute__((always_inline)) {
+        return *reinterpret_cast<const float*>(bq + ((ch ^ ((kk >> 2) & 3)) << 4) + kk * (RP * 4));
+      };
+      const float* src = tile + li * kLP256 + 64 * wave + 32 * h;
+#pragma unroll
+      for (int t = 0; t < 8; t += 2) {
+        const float4 a0 = *reinterpret_cast<const float4*>(src + 4 * t);
+        const float4 a1 = *reinterpret_cast<const float4*>(src + 4 * t + 4);
+        accP[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, q_at(4 * t + 0), accP[0], 0, 0, 0);
+        accP2[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, q_at(4 * t + 4), accP2[0], 0, 0, 0);
+        accP[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, q_at(4 * t + 1), accP[0], 0, 0, 0);
+        accP2[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, q_at(4 * t + 5), accP2[0], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        between(t);
+        __builtin_amdgcn_sched_barrier(0);
+        accP[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, q_at(4 * t + 2), accP[0], 0, 0, 0);
+        accP2[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, q_at(4 * t + 6), accP2[0], 0, 0, 0);
+        accP[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, q_at(4 * t + 3), accP[0], 0, 0, 0);
+        accP2[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, q_at(4 * t + 7), accP2[0], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        between(t + 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      wave_lds_fence();
+      return;
+    } else {
     // rank li of row 16 h + kk of this wavefront's rows of Q
     unsigned bq = (unsigned)(16 * h * (RP * 4) + 128 * h + li * 4);
     asm volatile("" : "+v"(bq));                   // (the exclusive ors below stay here, and out of registers across the rounds)
@@ -2646,6 +2685,7 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
         between(NBK * t + 2 * b + 1);
         __builtin_amdgcn_sched_barrier(0);
       }
+    }
     wave_lds_fence();
   };
 
@@ -2695,11 +2735,11 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
     if (mine) product(ln, [](int) {});
   }
   __syncthreads();
-  // P partial of the item = sum over the eight blocks of a round, added in their order
+  // P partial of the item = sum over the eight blocks of a round (rank pad 16: the four wavefronts), added in their order
   const int li = lane & 31, h = lane >> 5;
 #pragma unroll
-  for (int b = 0; b < NBK; ++b) {
-    float* part = tile + (NBK * wave + b) * (32 * kLP32);
+  for (int b = 0; b < NP; ++b) {
+    float* part = tile + (NP * wave + b) * (32 * kLP32);
 #pragma unroll
     for (int v = 0; v < 16; ++v) part[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP32 + li] = accP[b][v] + accP2[b][v];
   }
@@ -2709,14 +2749,14 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
     const int x = (int)threadIdx.x + 256 * i, rr = x >> 5, k = x & 31;
     float t = tile[rr * kLP32 + k];
 #pragma unroll
-    for (int wv = 1; wv < 8; ++wv) t += tile[wv * (32 * kLP32) + rr * kLP32 + k];
+    for (int wv = 1; wv < 4 * NP; ++wv) t += tile[wv * (32 * kLP32) + rr * kLP32 + k];
     if (rr < nrows && k < r) Pp[(size_t)(row0 + rr) * r + k] = t;
   }
 }
 
-template <int MODE, bool GB16, bool NTS>
+template <int RP, int MODE, bool GB16, bool NTS>
 __global__ __launch_bounds__(256, 2) void mfma_round_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
-  __shared__ __attribute__((aligned(256))) char qs[8 * 32 * 32 * 4];
+  __shared__ __attribute__((aligned(256))) char qs[8 * 32 * RP * 4];
   __shared__ __attribute__((aligned(16))) float tile[8 * 32 * kLP32];   // 32 x kLP256 in the rounds, the partial sums after them
   static_assert(32 * kLP256 <= 8 * 32 * kLP32, "");
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -2733,16 +2773,15 @@ __global__ __launch_bounds__(256, 2) void mfma_round_kernel(DevArgs a, const Til
   if (ld.kind == kOneColumnPerLane) {            // eight of the item's rows per wavefront
     const int nr = min(8, tl.nrows - 8 * wave);
     if (nr > 0)
-      narrow_rows<32, 8, true, MODE == kMAddFused, true, false, GB16>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, nullptr, ld.cols,
+      narrow_rows<RP, 8, true, MODE == kMAddFused, true, false, GB16>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, nullptr, ld.cols,
                                                                       ld.r, tl.row0 + 8 * wave, nr, lane, 0, 0.0f);
     return;
   }
-  mfma_round_tile<MODE, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ld.cols, ld.r, tl.row0, tl.nrows,
+  mfma_round_tile<RP, MODE, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ld.cols, ld.r, tl.row0, tl.nrows,
                                    col0, col1, lane, wave, qs, tile);
 }
 
-// Wavefronts per SIMD the register allocation aims for: two at rank pad 16 (2.65 -> 2.47 ms on
-// 8192^2 x 16 workers), one at rank pad 32, where two would spill (3.0 -> 4.6 ms).
+// Wavefronts per SIMD the register allocation aims for: two at rank pad 16, one from rank pad 32 on, where two would spill.
 template <int RP, int MODE, bool GB16 = false, bool NTS = false>
 __global__ __launch_bounds__(256, RP <= 16 ? 2 : 1) void mfma_sweep_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
   __shared__ __attribute__((aligned(16))) float lds_all[4][32 * kLP];
@@ -3671,7 +3710,7 @@ void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int revers
     }
   }
 #define LQSGD_LAUNCH_MA(GB, NT)                                                                                            \
-  if constexpr (RP == 32) mfma_round_kernel<MODE, GB, NT><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, reverse);     \
+  if constexpr (RP <= 32) mfma_round_kernel<RP, MODE, GB, NT><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, reverse);     \
   else mfma_sweep_kernel<RP, MODE, GB, NT><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, reverse)
   if (a.g_bf16) {
     if (a.nt_store) { LQSGD_LAUNCH_MA(true, true); } else { LQSGD_LAUNCH_MA(true, false); }
@@ -3679,7 +3718,7 @@ void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int revers
     if (a.nt_store) { LQSGD_LAUNCH_MA(false, true); } else { LQSGD_LAUNCH_MA(false, false); }
   }
 #undef LQSGD_LAUNCH_MA
-  if (RP == 32) note_kernel("mfma_round_kernel<%d, %s, %s>", MODE, tf(a.g_bf16), tf(a.nt_store));
+  if constexpr (RP <= 32) note_kernel("mfma_round_kernel<%d, %d, %s, %s>", RP, MODE, tf(a.g_bf16), tf(a.nt_store));
   else note_kernel("mfma_sweep_kernel<%d, %d, %s, %s>", RP, MODE, tf(a.g_bf16), tf(a.nt_store));
 }
 

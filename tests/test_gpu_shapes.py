@@ -162,3 +162,9 @@ def test_rounds_of_256_columns(rank, bits, W):
     """Sweep 0 at rank pad 32 goes by rounds of 32 rows x 256 columns: one and several whole rounds, a partial one behind them and
     alone, one to three rows more or less than a round has, more than one column segment."""
     test_ragged_shapes([(96, 256), (65, 512), (95, 768), (97, 300), (66, 1028), (128, 2305), (161, 64)], rank, bits, W)
+
+
+@pytest.mark.parametrize("rank,bits,W", [(12, 8, 2), (16, 0, 2)])
+def test_rounds_of_256_columns_at_rank_pad_16(rank, bits, W):
+    """The same rounds at rank pad 16, where a wavefront's 64 columns are one sum."""
+    test_ragged_shapes([(96, 256), (65, 512), (95, 768), (97, 300), (66, 1028), (128, 2305), (161, 64)], rank, bits, W)
