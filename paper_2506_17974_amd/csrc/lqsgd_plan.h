@@ -78,7 +78,7 @@ struct Plan {
   int32_t max_rows = 0;         // largest row count of a matrix layer
   int32_t max_rank = 0;         // largest effective rank of a matrix layer
   bool mfma = false;            // sweep 1 runs on the matrix cores (rank pads 32 and 64)
-  bool mfma_a = false;          // sweeps 0 and 2 run on the matrix cores (rank pad >= 16): 32-row work items
+  bool mfma_a = false;          // sweeps 0 and 2 run on the matrix cores (rank pad >= 16): 32-row work items, 64 rows at rank pad 64
   std::vector<LayerDesc> layers;
   std::vector<VecDesc> vecs;
   std::vector<int32_t> kind_of;    // per caller index: >= 0 matrix index, < 0 -(vector index) - 1
