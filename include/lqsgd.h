@@ -245,7 +245,7 @@ int lqsgd_step_update(lqsgd_ctx* ctx, const float* const* grads, float* const* p
  * device memory inside the library (LQSGD_STATIC_SCRATCH_BYTES, 32 MiB, per GPU,
  * held until the process ends; copies of the factors with rows padded to a power
  * of two, which layers of other ranks use, go to a second one of 64 MiB where the
- * first is full).  A configuration that needs more returns
+ * first is full, and a third one of 32 MiB holds Gram matrices of tall factors).  A configuration that needs more returns
  * EUNSUPPORTED and launches nothing (fc 256 x 128 needs under 0.1 MiB, the small
  * CNN 1 MiB, the ResNet-18 set with 8 workers 9 MiB at rank 4 and 17 MiB at rank 8).
  *   cfg, layers, n_layers : as for lqsgd_create (host pointers).

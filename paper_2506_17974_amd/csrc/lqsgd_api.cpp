@@ -51,6 +51,7 @@ struct lqsgd_ctx {
   size_t arena_cap = 0, arena_used = 0;
   unsigned char* operands = nullptr;   // ... and another for padded operand copies and items that it has no room for
   size_t operands_cap = 0, operands_used = 0;
+  float* grams = nullptr;              // ... and one for second-pass Gram matrices, as large as the first block
   DevArgs args{};
   // device copies of the work lists
   Tile* d_tilesA = nullptr; Tile* d_tilesB = nullptr; Tile* d_tilesG = nullptr; Tile* d_tilesBM = nullptr; Tile* d_tilesAG = nullptr; Tile* d_tilesR = nullptr;
@@ -503,7 +504,7 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   constexpr size_t kSlack = kFactorSlack;
   const size_t orth_cells = 2 * W * (size_t)std::max(p.L, 1) * ((p.max_rows + 255) / 256) * p.RP;
   a.E = nullptr; a.Qbar = nullptr; a.orth_table = nullptr; a.status = nullptr;
-  a.chol_table = nullptr; a.chol_part = nullptr; a.chol_redo = nullptr;
+  a.chol_table = nullptr; a.chol_part = nullptr; a.chol_part2 = nullptr; a.chol_redo = nullptr;
   if (!ext) TRY_(dev_alloc(c, &a.E, W * p.m_stride, true));
   TRY_(dev_alloc(c, &a.Ppart, W * p.ppart_stride + kSlack, true));
   TRY_(dev_alloc(c, &a.Ppre, W * p.p_stride + kSlack, true));
@@ -514,6 +515,7 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   // gives the same bits.
   const size_t nslice = (size_t)(p.max_rows + 255) / 256, pairs = W * (size_t)std::max(p.L, 1);
   const size_t ne = (size_t)chol_entries(p.RP);
+  // (table and first-pass matrices; a limit on the second-pass ones as well would give sets near it another method)
   const bool chol_size = ne && pairs * (nslice + 1) * ne * 12 <= ((size_t)1 << 30);
   if (chol_size && nslice >= 8) {
     TRY_(dev_alloc(c, &a.chol_part, pairs * nslice * ne, true));
@@ -538,6 +540,8 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
     a.chol_part = a.Qpart;
     a.chol_redo = reinterpret_cast<int*>(a.Qpart + pairs * nslice * ne);
   }
+  if (a.chol_part && ext) a.chol_part2 = c->grams;
+  if (a.chol_part && !ext) TRY_(dev_alloc(c, &a.chol_part2, pairs * nslice * ne, true));
   if (!ext && a.chol_part && nslice <= 64) TRY_(dev_alloc(c, &a.chol_table, pairs * (nslice + 1) * ne, true));   // the one-launch form's limit
   TRY_(dev_alloc(c, &a.Qw, W * p.q_stride + kSlack, true));
   if (!ext) TRY_(dev_alloc(c, &a.Qbar, (size_t)p.q_stride + kSlack, true));
@@ -1008,9 +1012,9 @@ int lqsgd_step_static(const lqsgd_config* cfg, const lqsgd_layer* layers, int32_
     if (e != hipSuccess) return fail_hip(nullptr, e, "hipGetDevice");
   }
   if (dev < 0 || dev >= kMaxDevices) return fail(nullptr, LQSGD_EUNSUPPORTED, "device index beyond the table of static scratch blocks");
-  void *block = nullptr, *operands = nullptr;
+  void *block = nullptr, *operands = nullptr, *grams = nullptr;
   {
-    hipError_t e = static_scratch(dev, &block, &operands);
+    hipError_t e = static_scratch(dev, &block, &operands, &grams);
     if (e != hipSuccess) return fail_hip(nullptr, e, "hipGetSymbolAddress(scratch)");
   }
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
@@ -1036,6 +1040,7 @@ int lqsgd_step_static(const lqsgd_config* cfg, const lqsgd_layer* layers, int32_
     c->arena_cap = LQSGD_STATIC_SCRATCH_BYTES;
     c->operands = static_cast<unsigned char*>(operands);
     c->operands_cap = LQSGD_STATIC_OPERAND_BYTES;
+    c->grams = static_cast<float*>(grams);
     if ((rc = setup_device(c, cfg->flags))) {
       g_create_error = c->err;
       delete c;

@@ -21,9 +21,10 @@ struct DevArgs {
   float* orth_part;            // [2][L*W][ceil(max_rows/256)][RP] slice partials of the many-workgroup Gram-Schmidt
   unsigned long long* orth_table;      // [2][L*W][ceil(max_rows/256)][RP] tagged partials of its one-launch form
   // Cholesky-QR form of the tall Gram-Schmidt (rank pads >= 8; null if the context has none; at rank pad 64 and fewer than 8
-  // slices the last two lie in Qpart, whose planes are dead while Gram-Schmidt runs):
+  // slices chol_part and chol_redo lie in Qpart, whose planes are dead while Gram-Schmidt runs):
   unsigned long long* chol_table;      // [L*W][ceil(max_rows/256) + 1][NE] tagged Gram matrices of the slices, their total last
-  float* chol_part;            // [L*W][ceil(max_rows/256)][NE] the same matrices in plain memory, for the form of three launches
+  float* chol_part;            // [L*W][ceil(max_rows/256)][NE] the same matrices in plain memory, for the form of three launches: of the
+  float* chol_part2;           // first pass, and of the second
   int* chol_redo;              // [L*W] raised for a pair that has to be done column by column
   int* status;                 // pinned host word the kernels raise when a bounded device-side wait expires
   float* Pbar;                 // aggregated P (shared)
@@ -99,7 +100,7 @@ hipError_t launch_pad_factor(int RP, int which, const DevArgs& a, hipStream_t s)
 
 // The per-GPU blocks of the entry point that allocates nothing, scratch and operand copies: device addresses of
 // those of `device`, which must be the current device on the first call for it.
-hipError_t static_scratch(int device, void** scratch, void** operands);
+hipError_t static_scratch(int device, void** scratch, void** operands, void** grams);
 // Clears `bytes` (a multiple of 16) at the 16-byte aligned device address p with a kernel.
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 

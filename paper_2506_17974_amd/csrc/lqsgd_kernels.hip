@@ -43,6 +43,7 @@
 // never addresses.
 static __device__ __align__(256) unsigned char scratch[LQSGD_STATIC_SCRATCH_BYTES];
 static __device__ __align__(256) unsigned char operands[LQSGD_STATIC_OPERAND_BYTES];
+static __device__ __align__(256) unsigned char grams[LQSGD_STATIC_GRAM_BYTES];
 #endif
 
 namespace lqsgd {
@@ -2865,9 +2866,13 @@ __global__ __launch_bounds__(256) void pad_factor_kernel(DevArgs a, int RP, int 
 //     R^-1 to its row by forward substitution, reading R from LDS.
 // phase -1 runs all of it in one cooperative launch.  Without one, phases 0, 1
 // and 2 are three ordinary launches that pass the slices' Gram matrices through
-// plain memory (cpart) and add them up in the same order, so that both forms
+// plain memory and add them up in the same order, so that both forms
 // give the same bits; pairs that need the column-by-column form raise redo[pair]
-// and the guarded orth_wide_kernel launches that follow do them.
+// and the guarded orth_wide_kernel launches that follow do them.  A launch reads the
+// matrices of one plane (parts_in, all slices of the pair) and writes its own slice's to
+// another (parts_out): the workgroups of a launch have no order, and slices beyond what the
+// chip holds start after others have ended, so that a matrix of the second pass must not
+// lie where a slice may still have to read the first pass's.
 // ---------------------------------------------------------------------------
 // On the CPU, in float32, two passes stay as close to the float64 Gram-Schmidt as float32 Gram-Schmidt
 // itself down to pivot ratios of about 1e-6 (both 1e-6 .. 1e-5 away at ratios 2e-4 .. 1e-5); the floor
@@ -3193,7 +3198,7 @@ __device__ __forceinline__ void chol_store_row(float* F, int row, int rows, int 
 
 template <int RP>
 __global__ __launch_bounds__(256, 2) void orth_chol_kernel(DevArgs a, int nslice_max, int max_rank, int phase,
-                                                        unsigned long long* ctable, float* cpart, int* redo,
+                                                        unsigned long long* ctable, const float* parts_in, float* parts_out, int* redo,
                                                         unsigned long long epoch, unsigned max_polls) {
   using S = CholShape<RP>;
   __shared__ __attribute__((aligned(16))) float pool[S::POOL];
@@ -3212,7 +3217,7 @@ __global__ __launch_bounds__(256, 2) void orth_chol_kernel(DevArgs a, int nslice
   float* orth = a.Porth + (size_t)worker * a.p_stride + ld.p_off;
   float* scale = a.scaleP + (size_t)worker * a.L + layer;
   unsigned long long* tab = ctable + (size_t)lw * (nslice_max + 1) * S::NE;
-  float* parts = cpart + (size_t)lw * nslice_max * S::NE;
+  const size_t parts = (size_t)lw * nslice_max * S::NE;
   float* Ls = pool;                              // [RP][RP], once the total has been read out of pool + 2 NE
   float v[RP];
 #pragma unroll
@@ -3250,7 +3255,7 @@ __global__ __launch_bounds__(256, 2) void orth_chol_kernel(DevArgs a, int nslice
         const unsigned tag = (unsigned)(epoch * 4ull) + 2u * (unsigned)pass;
         chol_exchange<RP>(gsum, tab, slice, nslice, nslice_max, tag + 1u, tag + 2u, pool, a.status, max_polls);
       } else {
-        chol_sum_parts<RP>(parts, nslice, pool);
+        chol_sum_parts<RP>(parts_in + parts, nslice, pool);
       }
       if (wave == 0) {
         const bool ok = chol_factor<RP>(pool + 2 * S::NE, Ls, r, lane);
@@ -3272,7 +3277,7 @@ __global__ __launch_bounds__(256, 2) void orth_chol_kernel(DevArgs a, int nslice
 #pragma unroll
     for (int q = 0; q < S::QN; ++q) {
       const int e = tid + 256 * q;
-      if (e < S::NE) parts[(size_t)slice * S::NE + e] = gsum[q];
+      if (e < S::NE) parts_out[parts + (size_t)slice * S::NE + e] = gsum[q];
     }
     return;
   }
@@ -3519,11 +3524,12 @@ bool try_orth_chol_coop(int nslice, int max_rank, const DevArgs& a, int nblocks,
   DevArgs args = a;
   int phase = -1;
   unsigned long long* table = a.chol_table;
-  float* part = a.chol_part;
+  const float* in = nullptr;
+  float* out = nullptr;
   int* redo = a.chol_redo;
   unsigned long long n = cs->epoch;
   unsigned max_polls = cs->max_polls ? cs->max_polls : kTablePolls;
-  void* params[] = {&args, &nslice, &max_rank, &phase, &table, &part, &redo, &n, &max_polls};
+  void* params[] = {&args, &nslice, &max_rank, &phase, &table, &in, &out, &redo, &n, &max_polls};
   const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<void*>(orth_chol_kernel<RP>), dim3(nblocks), dim3(256),
                                                   params, 0, s);
   if (e != hipSuccess) {
@@ -3555,8 +3561,9 @@ bool launch_orth_chol_coop(int rp, int nslice, int max_rank, const DevArgs& a, i
 // Three launches of the Cholesky-QR kernel, then the column-by-column launches for the pairs that raised their word.
 template <int RP>
 void launch_orth_chol_split(int nslice, int max_rank, const DevArgs& a, int nblocks, hipStream_t s) {
+  float* const planes[4] = {nullptr, a.chol_part, a.chol_part2, nullptr};
   for (int phase = 0; phase < 3; ++phase)
-    orth_chol_kernel<RP><<<dim3(nblocks), dim3(256), 0, s>>>(a, nslice, max_rank, phase, nullptr, a.chol_part, a.chol_redo, 0ull, 0u);
+    orth_chol_kernel<RP><<<dim3(nblocks), dim3(256), 0, s>>>(a, nslice, max_rank, phase, nullptr, planes[phase], planes[phase + 1], a.chol_redo, 0ull, 0u);
   for (int j = 0; j <= max_rank; ++j)
     orth_wide_kernel<RP><<<dim3(nblocks), dim3(256), 0, s>>>(a, j, nslice, a.chol_redo);
   note_kernel("orth_chol_kernel<%d> x 3 launches", RP);
@@ -3597,7 +3604,7 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, Coo
 #else
     constexpr bool chol = true;
 #endif
-    if (chol && rp >= 8 && a.chol_part && a.chol_redo) {
+    if (chol && rp >= 8 && a.chol_part && a.chol_part2 && a.chol_redo) {
       return launch_orth_chol(rp, nslice, max_rank, a, (int)grid.x * nslice, coop, s);
     }
     // (no Cholesky-QR buffers, or a pad below 8)
@@ -3757,31 +3764,34 @@ hipError_t launch_mfma_sweep(int rp, int mode, const DevArgs& a, const Tile* til
 
 #if LQSGD_HAS(0)
 // ---------------------------------------------------------------------------
-// Scratch memory for the entry point that allocates nothing: one block per GPU,
-// part of the loaded code object, held until the process ends.  The name below
-// is a host-side handle only; the block's device address is asked for once per
-// device and that address is what kernels and copies use.  (The array itself
-// is defined at file scope, at the top of this file.)
+// Scratch memory for the entry point that allocates nothing: three blocks per GPU,
+// part of the loaded code object, held until the process ends.  The names below
+// are host-side handles only; the blocks' device addresses are asked for once per
+// device and those addresses are what kernels and copies use.  (The arrays themselves
+// are defined at file scope, at the top of this file.)
 // ---------------------------------------------------------------------------
 
-hipError_t static_scratch(int device, void** scratch_ptr, void** operands_ptr) {
+hipError_t static_scratch(int device, void** scratch_ptr, void** operands_ptr, void** grams_ptr) {
   constexpr int kMaxDev = 64;
-  static void* addr[kMaxDev][2] = {};           // per device; the caller serialises calls
+  static void* addr[kMaxDev][3] = {};           // per device; the caller serialises calls
   if (device < 0 || device >= kMaxDev) return hipErrorInvalidDevice;
-  if (!addr[device][1]) {
+  if (!addr[device][2]) {
     int cur = -1;
     hipError_t e = hipGetDevice(&cur);
     if (e != hipSuccess) return e;
     if (cur != device) return hipErrorInvalidDevice;     // the address belongs to the device that is current
-    void *p = nullptr, *q = nullptr;
+    void *p = nullptr, *q = nullptr, *g = nullptr;
     if ((e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch))) != hipSuccess) return e;
     if ((e = hipGetSymbolAddress(&q, HIP_SYMBOL(operands))) != hipSuccess) return e;
-    if (!p || !q) return hipErrorInvalidSymbol;
+    if ((e = hipGetSymbolAddress(&g, HIP_SYMBOL(grams))) != hipSuccess) return e;
+    if (!p || !q || !g) return hipErrorInvalidSymbol;
     addr[device][0] = p;
     addr[device][1] = q;
+    addr[device][2] = g;
   }
   *scratch_ptr = addr[device][0];
   *operands_ptr = addr[device][1];
+  *grams_ptr = addr[device][2];
   return hipSuccess;
 }
 

@@ -27,6 +27,12 @@ constexpr int kFactorSlack = 64;   // readable floats after the last row of ever
 #ifndef LQSGD_STATIC_OPERAND_BYTES
 #define LQSGD_STATIC_OPERAND_BYTES (64u << 20)
 #endif
+// ... and of the second-pass Gram matrices of tall factors.  The first-pass ones, which are as many, lie in the first block: a
+// configuration that this block had no room for has been refused before.
+#ifndef LQSGD_STATIC_GRAM_BYTES
+#define LQSGD_STATIC_GRAM_BYTES LQSGD_STATIC_SCRATCH_BYTES
+#endif
+static_assert(LQSGD_STATIC_GRAM_BYTES >= LQSGD_STATIC_SCRATCH_BYTES, "second-pass Gram matrices");
 
 // One matrix layer as the kernels see it.  Offsets are in elements (floats)
 // from the start of a per-worker slab unless they say bytes.

@@ -307,3 +307,37 @@ def test_more_tall_factors_than_one_launch_can_hold():
     assert comp.launched_kernel(B.KERNEL_ORTH) == "orth_chol_kernel<16> x 3 launches", comp.launched_kernel(B.KERNEL_ORTH)
     _say("  ", rep)
     comp.close()
+
+
+# Heights of 11 and 13 slices (18 and 20 at rank pad 8), so that a round of resident workgroups ends inside a factor.
+@pytest.mark.parametrize("rank,heights,n_layers,W", [(7, (4400, 4865), 24, 5), (16, (2700, 3300), 40, 5), (30, (2700, 3300), 24, 4),
+                                                     (50, (2700, 3300), 24, 4)])
+def test_every_factor_of_more_slices_than_the_chip_holds(rank, heights, n_layers, W):
+    """The slices of a launch start in any order, some after others have ended: every factor of every worker is what the
+    one-launch form gives for the same layers, a few at a time."""
+    import torch
+    _say("case: more slices than are resident", rank, heights, n_layers, W)
+    cols = 72
+    layers = [(heights[i % 2], cols) for i in range(n_layers)]
+    rp = 8 if rank <= 8 else 16 if rank <= 16 else 32 if rank <= 32 else 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rank)
+    Q = np.random.default_rng(rank).standard_normal((n_layers, cols, rank)).astype(f32)
+    for _ in range(2):
+        G = [[torch.randn(s, device="cuda", generator=gen) * 1e-3 for s in layers] for _ in range(W)]
+
+        def factors(which, name):
+            comp, ml = _make([layers[i] for i in which], (), rank, 8, 8, W)
+            for l, i in zip(ml, which):
+                comp.set_q(l, Q[i])
+            comp.compress(B.PHASE_P, [[g[i] for i in which] for g in G])
+            assert comp.launched_kernel(B.KERNEL_ORTH) == name, comp.launched_kernel(B.KERNEL_ORTH)
+            got = [[comp.get_factor(B.FACTOR_P_ORTH, l, k) for k in range(W)] for l in ml]
+            comp.close()
+            return got
+
+        every = factors(range(n_layers), "orth_chol_kernel<%d> x 3 launches" % rp)
+        for i0 in range(0, n_layers, 4):
+            for i, few in zip(range(i0, i0 + 4), factors(range(i0, i0 + 4), "orth_chol_kernel<%d>" % rp)):
+                for k in range(W):
+                    assert np.all(np.isfinite(few[k])) and np.array_equal(every[i][k], few[k]), "layer %d, worker %d" % (i, k)

@@ -168,3 +168,12 @@ def test_step_static_in_a_block_without_room_for_copies_and_residual_items():
     Es, Qs = _fresh_state(small, 3, 2, rng)
     _one_call(small, [], 3, 8, 2, 0, rng, Es, Qs, "copies in the first block")
     _one_call(full, [], 7, 8, 16, 0, rng, E, Q, "full block again")
+
+
+def test_step_static_with_more_slices_of_tall_factors_than_the_chip_holds():
+    """80 factors of 11 and 13 slices: Gram-Schmidt in three launches, whose workgroups are not all resident at once."""
+    rng = np.random.default_rng(80)
+    layers = [(2700, 40), (3300, 36)] * 8
+    E, Q = _fresh_state(layers, 8, 5, rng)
+    E, Q = _one_call(layers, [], 8, 8, 5, 0, rng, E, Q, "80 tall factors")
+    _one_call(layers, [], 8, 8, 5, 0, rng, E, Q, "80 tall factors again")
