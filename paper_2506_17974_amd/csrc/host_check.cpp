@@ -23,9 +23,30 @@ static lqsgd_config cfg(int rank, int bp, int bq, int W, float alpha = 255.0f, u
   return c;
 }
 
+// The workgroups of 32 rows that go over sweep 0's items and worker 0's: all of them have rows, and together each item's.
+static void check_halves(const lqsgd_config& c, const std::vector<lqsgd_layer>& layers) {
+  lqsgd::Plan p;
+  EXPECT(p.build(&c, layers.data(), (int32_t)layers.size()) == LQSGD_OK);
+  if (!p.mfma_a) return;
+  for (const auto& list : {std::make_pair(&p.tilesA, p.twoA), std::make_pair(&p.tilesAG, p.twoAG)}) {
+    const int n = (int)list.first->size();
+    std::vector<int64_t> rows((size_t)n, 0);
+    for (int b = 0; b < n + list.second; ++b) {
+      const lqsgd::HalfItem h = lqsgd::half_item(b, list.second);
+      EXPECT(h.item >= 0 && h.item < n);
+      if (h.item < 0 || h.item >= n) continue;
+      const int left = (*list.first)[(size_t)h.item].nrows - 32 * h.half;
+      EXPECT(left > 0);
+      rows[(size_t)h.item] += left < 32 ? left : 32;
+    }
+    for (int i = 0; i < n; ++i) EXPECT(rows[(size_t)i] == (*list.first)[(size_t)i].nrows);
+  }
+}
+
 // Every work item of every sweep lies inside its layer, and the items of a sweep cover each
 // (layer, worker) exactly once.
 static void check_tiles(const lqsgd_config& c, const std::vector<lqsgd_layer>& layers) {
+  check_halves(c, layers);
   for (int sweep = 0; sweep < 4; ++sweep) {
     const int64_t n = lqsgd_plan_tiles(&c, layers.data(), (int32_t)layers.size(), sweep, nullptr, 0);
     EXPECT(n >= 0);
@@ -81,7 +102,7 @@ int main() {
       l.flags = vec ? LQSGD_LAYER_VECTOR : LQSGD_LAYER_MATRIX;
       ls.push_back(l);
     }
-    const lqsgd_config c = cfg(1 + (int)(rng() % 64), (int)(rng() % 9), (int)(rng() % 9), 1 + (int)(rng() % 64), 0.5f + (float)(rng() % 1000));
+    const lqsgd_config c = cfg(trial % 4 == 3 ? 33 + (int)(rng() % 32) : 1 + (int)(rng() % 64), (int)(rng() % 9), (int)(rng() % 9), 1 + (int)(rng() % 64), 0.5f + (float)(rng() % 1000));
     EXPECT(lqsgd_plan_query(&c, ls.data(), n, &info) == LQSGD_OK);
     check_tiles(c, ls);
   }

@@ -15,7 +15,7 @@ hipError_t launch_back_project_mfma(int, const DevArgs&, const Tile*, int, const
 hipError_t launch_reduce_q(int, const DevArgs&, const RTile*, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_residual(int, int, const DevArgs&, const Tile*, int, int, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_pad_factor(int, int, const DevArgs&, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_mfma_sweep(int, int, const DevArgs&, const Tile*, int, int, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_mfma_sweep(int, int, const DevArgs&, const Tile*, int, int, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t static_scratch(int, void**, void**, void**) { return hipErrorNotSupported; }
 hipError_t launch_fill_zero(void*, size_t, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_write_pointers(const void**, const void* const*, size_t, hipStream_t) { return hipErrorNotSupported; }

@@ -258,7 +258,7 @@ int run_sweep0(lqsgd_ctx* c) {
   { Timed t(c, LQSGD_KERNEL_ADD_PROJECT);
     if (c->plan.mfma_a)
       HIP_TRY(c, launch_mfma_sweep(c->plan.RP, c->pending ? 1 : 0, c->args, c->d_tilesA, (int)c->plan.tilesA.size(),
-                                   next_dir(c), c->stream));
+                                   c->plan.twoA, next_dir(c), c->stream));
     else
       HIP_TRY(c, launch_add_project(c->plan.RP, c->args, c->d_tilesA, (int)c->plan.tilesA.size(), c->pending ? 1 : 0,
                                     c->plan.narrow_rows ? 1 : 0, next_dir(c), c->stream)); }
@@ -323,13 +323,13 @@ int run_sweep2(lqsgd_ctx* c, bool write_ghat) {
   Timed t(c, LQSGD_KERNEL_RESIDUAL);
   if (c->eager) {
     if (p.mfma_a)
-      HIP_TRY(c, launch_mfma_sweep(p.RP, write_ghat ? 3 : 2, c->args, c->d_tilesA, (int)p.tilesA.size(), next_dir(c), c->stream));
+      HIP_TRY(c, launch_mfma_sweep(p.RP, write_ghat ? 3 : 2, c->args, c->d_tilesA, (int)p.tilesA.size(), p.twoA, next_dir(c), c->stream));
     else
       HIP_TRY(c, launch_residual(p.RP, write_ghat ? 1 : 0, c->args, c->d_tilesR, (int)p.tilesR.size(), p.narrow_rows ? 1 : 0, next_dir(c), c->stream));
   } else {
     if (write_ghat) {
       if (p.mfma_a)
-        HIP_TRY(c, launch_mfma_sweep(p.RP, 4, c->args, c->d_tilesAG, (int)p.tilesAG.size(), 0, c->stream));
+        HIP_TRY(c, launch_mfma_sweep(p.RP, 4, c->args, c->d_tilesAG, (int)p.tilesAG.size(), p.twoAG, 0, c->stream));
       else
         HIP_TRY(c, launch_residual(p.RP, 2, c->args, c->d_tilesG, (int)p.tilesG.size(), 0, 0, c->stream));
     }
@@ -344,7 +344,7 @@ int materialise(lqsgd_ctx* c) {
   if (int rc = refresh_stale(c)) return rc;
   Timed t(c, LQSGD_KERNEL_RESIDUAL);
   if (p.mfma_a)
-    HIP_TRY(c, launch_mfma_sweep(p.RP, 2, c->args, c->d_tilesA, (int)p.tilesA.size(), next_dir(c), c->stream));
+    HIP_TRY(c, launch_mfma_sweep(p.RP, 2, c->args, c->d_tilesA, (int)p.tilesA.size(), p.twoA, next_dir(c), c->stream));
   else
     HIP_TRY(c, launch_residual(p.RP, 0, c->args, c->d_tilesR, (int)p.tilesR.size(), p.narrow_rows ? 1 : 0, next_dir(c), c->stream));
   c->pending = false;

@@ -2784,19 +2784,17 @@ __global__ __launch_bounds__(256, 2) void mfma_round_kernel(DevArgs a, const Til
 
 // Wavefronts per SIMD the register allocation aims for: two at rank pad 16, one from rank pad 32 on, where two would spill.
 template <int RP, int MODE, bool GB16 = false, bool NTS = false>
-__global__ __launch_bounds__(256, RP <= 16 ? 2 : 1) void mfma_sweep_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
+__global__ __launch_bounds__(256, RP <= 16 ? 2 : 1) void mfma_sweep_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int two, int reverse) {
   __shared__ __attribute__((aligned(16))) float lds_all[4][32 * kLP];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & (kWave - 1);
   if ((MODE == kMAdd || MODE == kMAddFused) && blockIdx.x == 0) zero_absmax_cells(a, 256);
-  constexpr int PER = RP == 64 ? 2 : 1;            // workgroups per item: 32 rows each
-  const int item = (int)blockIdx.x / PER;
-  Tile tl = tiles[reverse ? ntiles - 1 - item : item];
-  if constexpr (PER == 2) {
-    const int skip = 32 * ((int)blockIdx.x & 1);
-    tl.row0 += skip;
-    tl.nrows = min(32, tl.nrows - skip);
-    if (tl.nrows <= 0) return;
+  const int block = reverse ? ntiles + two - 1 - (int)blockIdx.x : (int)blockIdx.x;
+  const HalfItem it = RP == 64 ? half_item(block, two) : HalfItem{block, 0};
+  Tile tl = tiles[it.item];
+  if constexpr (RP == 64) {
+    tl.row0 += 32 * it.half;
+    tl.nrows = min(32, tl.nrows - 32 * it.half);
   }
   const int layer = tl.lw / a.W, worker = tl.lw - layer * a.W;
   const LayerDesc& ld = a.layers[layer];
@@ -3695,14 +3693,16 @@ hipError_t launch_residual(int rp, int mode, const DevArgs& a, const Tile* tiles
 }
 #endif
 
-// Rank pad 64: items of 64 rows go to mfma_pair_kernel, a workgroup each, unless every 32 rows can have a CU of their own:
-// the 32-row form then has twice the workgroups and takes one round of them (sweep 0, microseconds, 32-row form / 64-row form:
-// 64 items, 4096 x 2048, W = 1 66 / 85; 128 items, 4 x 1024^2, W = 2 42 / 49, 4096 x 3072, W = 1 59 / 68; 132 items, 2 x (2100 x
-// 1500), W = 2 107 / 77; 192 items, 4 x 1024^2, W = 3 71 / 51).
+// Rank pad 64: items go to mfma_pair_kernel, a workgroup each, unless there is a CU for either half of every item (items of at most
+// 32 rows count as two halves all the same): the 32-row form then has twice the workgroups and takes one round of them (sweep 0,
+// microseconds, 32-row form / 64-row form: 64 items, 4096 x 2048, W = 1 66 / 85; 128 items, 4 x 1024^2, W = 2 42 / 49, 4096 x 3072,
+// W = 1 59 / 68; 132 items, 2 x (2100 x 1500), W = 2 107 / 77; 192 items, 4 x 1024^2, W = 3 71 / 51).  Lists of short items
+// lose nothing by the count, W = 8, r = 50 beside a 64 x 512 layer: 144 items, 17 x (32 x 2048) 67 / 61; 168 items, 20 x (20 x 2048)
+// 74 / 65; 200 items, 24 x (32 x 1024) 40 / 38; 520 items, 64 x (32 x 2048) 169 / 155 (first iterations 123 / 130).
 [[maybe_unused]] constexpr int kCus = 256;
 template <int RP, int MODE>
-void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s) {
-  const dim3 grid(ntiles * (RP == 64 ? 2 : 1));
+void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int two, int reverse, hipStream_t s) {
+  const dim3 grid(ntiles + two);
   if constexpr (RP == 64) {
     if (2 * ntiles > kCus) {
 #define LQSGD_LAUNCH_MP(GB, NT) mfma_pair_kernel<MODE, GB, NT><<<dim3(ntiles), dim3(512), 0, s>>>(a, tiles, ntiles, reverse)
@@ -3718,7 +3718,7 @@ void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int revers
   }
 #define LQSGD_LAUNCH_MA(GB, NT)                                                                                            \
   if constexpr (RP <= 32) mfma_round_kernel<RP, MODE, GB, NT><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, reverse);     \
-  else mfma_sweep_kernel<RP, MODE, GB, NT><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, reverse)
+  else mfma_sweep_kernel<RP, MODE, GB, NT><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, two, reverse)
   if (a.g_bf16) {
     if (a.nt_store) { LQSGD_LAUNCH_MA(true, true); } else { LQSGD_LAUNCH_MA(true, false); }
   } else {
@@ -3730,14 +3730,14 @@ void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int revers
 }
 
 template <int RP>
-hipError_t launch_mfma_sweep_rp(int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s) {
-  const dim3 grid(ntiles * (RP == 64 ? 2 : 1)), block(256);
+hipError_t launch_mfma_sweep_rp(int mode, const DevArgs& a, const Tile* tiles, int ntiles, int two, int reverse, hipStream_t s) {
+  const dim3 grid(ntiles + two), block(256);
   switch (mode) {
-    case kMAdd: launch_mfma_add<RP, kMAdd>(a, tiles, ntiles, reverse, s); return hipGetLastError();
-    case kMAddFused: launch_mfma_add<RP, kMAddFused>(a, tiles, ntiles, reverse, s); return hipGetLastError();
-    case kMResidual: mfma_sweep_kernel<RP, kMResidual><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse); break;
-    case kMResidualGhat: mfma_sweep_kernel<RP, kMResidualGhat><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse); break;
-    case kMGhatOnly: mfma_sweep_kernel<RP, kMGhatOnly><<<grid, block, 0, s>>>(a, tiles, ntiles, reverse); break;
+    case kMAdd: launch_mfma_add<RP, kMAdd>(a, tiles, ntiles, two, reverse, s); return hipGetLastError();
+    case kMAddFused: launch_mfma_add<RP, kMAddFused>(a, tiles, ntiles, two, reverse, s); return hipGetLastError();
+    case kMResidual: mfma_sweep_kernel<RP, kMResidual><<<grid, block, 0, s>>>(a, tiles, ntiles, two, reverse); break;
+    case kMResidualGhat: mfma_sweep_kernel<RP, kMResidualGhat><<<grid, block, 0, s>>>(a, tiles, ntiles, two, reverse); break;
+    case kMGhatOnly: mfma_sweep_kernel<RP, kMGhatOnly><<<grid, block, 0, s>>>(a, tiles, ntiles, two, reverse); break;
     default: return hipErrorInvalidValue;
   }
   note_kernel("mfma_sweep_kernel<%d, %d, false, false>", RP, mode);
@@ -3745,19 +3745,19 @@ hipError_t launch_mfma_sweep_rp(int mode, const DevArgs& a, const Tile* tiles, i
 }
 
 // rank pads 16 and 32 in one part, 64 in another: about the same time to compile
-hipError_t launch_mfma_sweep64(int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s);
+hipError_t launch_mfma_sweep64(int mode, const DevArgs& a, const Tile* tiles, int ntiles, int two, int reverse, hipStream_t s);
 #if LQSGD_HAS(3)
-hipError_t launch_mfma_sweep64(int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse, hipStream_t s) {
-  return launch_mfma_sweep_rp<64>(mode, a, tiles, ntiles, reverse, s);
+hipError_t launch_mfma_sweep64(int mode, const DevArgs& a, const Tile* tiles, int ntiles, int two, int reverse, hipStream_t s) {
+  return launch_mfma_sweep_rp<64>(mode, a, tiles, ntiles, two, reverse, s);
 }
 #endif
 #if LQSGD_HAS(2)
-hipError_t launch_mfma_sweep(int rp, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int reverse,
+hipError_t launch_mfma_sweep(int rp, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int two, int reverse,
                              hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-  if (rp == 16) return launch_mfma_sweep_rp<16>(mode, a, tiles, ntiles, reverse, s);
-  if (rp == 32) return launch_mfma_sweep_rp<32>(mode, a, tiles, ntiles, reverse, s);
-  if (rp == 64) return launch_mfma_sweep64(mode, a, tiles, ntiles, reverse, s);
+  if (rp == 16) return launch_mfma_sweep_rp<16>(mode, a, tiles, ntiles, 0, reverse, s);
+  if (rp == 32) return launch_mfma_sweep_rp<32>(mode, a, tiles, ntiles, 0, reverse, s);
+  if (rp == 64) return launch_mfma_sweep64(mode, a, tiles, ntiles, two, reverse, s);
   return hipErrorInvalidValue;
 }
 #endif

@@ -338,13 +338,21 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
   }
   // Rank pads 32 and 64: few workgroups fit a CU there and an item can take a tenth of the launch, so that the widest go first and
   // the last ones are short (sweep 0, us, in the layers' order / sorted: ragged set, r = 20, W = 4 48.2 / 43.5; ResNet-18 set, W = 8,
-  // r = 50 277 / 267, r = 32 216 / 216; 64 x 576 .. 512 x 4608, W = 4, r = 64 135 / 129).
+  // r = 50 277 / 267, r = 32 216 / 216; 64 x 576 .. 512 x 4608, W = 4, r = 64 135 / 129).  Items of more than 32 rows before the
+  // others (HalfItem).
+  twoA = twoAG = 0;
   if (mfma) {
+    auto two = [](const Tile& t) { return t.nrows > 32; };
     auto width = [&](const Tile& t) {
       const LayerDesc& d = layers[t.lw / W];
-      return std::min(d.segw, d.cols - t.aux * d.segw) * (t.nrows > 32 ? 2 : 1);
+      return std::min(d.segw, d.cols - t.aux * d.segw);
     };
-    std::stable_sort(tilesA.begin(), tilesA.end(), [&](const Tile& x, const Tile& y) { return width(x) > width(y); });
+    std::stable_sort(tilesA.begin(), tilesA.end(), [&](const Tile& x, const Tile& y) {
+      return two(x) != two(y) ? two(x) : width(x) > width(y);
+    });
+    std::stable_partition(tilesAG.begin(), tilesAG.end(), two);
+    twoA = (int32_t)std::count_if(tilesA.begin(), tilesA.end(), two);
+    twoAG = (int32_t)std::count_if(tilesAG.begin(), tilesAG.end(), two);
   }
 
   m_stride = round_up(m_acc, 64);

@@ -412,3 +412,44 @@ def test_sixty_four_row_items_add_in_the_order_of_thirty_two_row_ones(bf16):
         got.append(res)
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+def _schedules(layers, rank, W, kernel, bf16=False, bits=8, iterations=3):
+    """Deferred and eager residuals give the same bits (the eager schedule's sweeps are the ones that the staged tests hold
+    against the oracle); `kernel` is what sweep 0 of the deferred one runs from its second iteration on."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rank + W)
+    Q0 = [torch.randn((c, min(rank, n, c)), generator=gen, device="cuda").cpu().numpy() for n, c in layers]
+    Gs = [[[(torch.randn(s, generator=gen, device="cuda") * 1e-3).to(torch.bfloat16 if bf16 else torch.float32) for s in layers]
+           for _ in range(W)] for _ in range(iterations)]
+    got = []
+    for flags in (0, B.FLAG_EAGER_RESIDUAL):
+        comp = B.Compressor(B.layer_list(layers, ()), rank, bits, bits, W, 255.0, flags | (B.FLAG_BF16_GRADIENTS if bf16 else 0))
+        for l, q in enumerate(Q0):
+            comp.set_q(l, q)
+        out, res = [torch.full(s, 7.0, device="cuda") for s in layers], []
+        for G in Gs:
+            comp.step(G, out)
+            res += [o.clone() for o in out]
+        if not flags:
+            assert comp.launched_kernel(0).startswith(kernel), comp.launched_kernel(0)
+        res += [torch.from_numpy(comp.get_state(l, w)[0]) for l in range(len(layers)) for w in range(W)]
+        res += [torch.from_numpy(comp.get_factor(B.FACTOR_P_PRE, l, w)) for l in range(len(layers)) for w in range(W)]
+        comp.close()
+        got.append(res)
+    for i, (a, b) in enumerate(zip(*got)):
+        assert torch.isfinite(a).all() and torch.equal(a, b), "tensor %d" % i
+    return got[0]
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("layers,W,kernel", [
+    # 64-row items: the last one of a layer of any height, several segments, layers of one short item
+    ([(161, 2305), (200, 1100), (20, 2100), (32, 300), (65, 516), (64, 61), (128, 1024), (97, 63)], 8, "mfma_pair_kernel<1"),
+    # few of them: 32 rows a workgroup
+    ([(161, 1305), (20, 300), (32, 512), (65, 131), (64, 61), (33, 65)], 2, "mfma_sweep_kernel<64, 1"),
+])
+def test_rank_pad_64_items_of_any_height(layers, W, kernel, bf16):
+    _say("case: 64-row items, deferred and eager", layers, W, bf16)
+    _schedules(layers, 50, W, kernel, bf16)
