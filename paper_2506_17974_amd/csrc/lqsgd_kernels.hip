@@ -1568,7 +1568,7 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 // 633 - 644.)  NB = 1: straight from L2, one request beside one (through LDS 16 x 1024^2, W = 8 128 -> 136 us,
 // ResNet-18 set 92 -> 90).
 constexpr int kPRows = 256;
-template <int NB, int KIND, typename Enter>
+template <int NB, int KIND, bool SHORT, typename Enter>
 __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const LayerDesc& ld, const Tile& tl, int worker,
                                                        int c0, int lane, const float* ps, Enter&& enter) {
   constexpr int U = LQSGD_BM_U;                     // pairs of rows per step
@@ -1621,6 +1621,36 @@ __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const L
         for (int s = 0; s < 4; ++s)
           acc[nb][s] = __builtin_amdgcn_mfma_f32_32x32x2f32(m[u].v[s], p[nb][u], acc[nb][s], 0, 0, 0);
   };
+  // a row that does not exist counts as zeros on both sides (0 x Inf would not be zero)
+  auto last_group = [&](int rb, Pk<4>* m, float (*p)[U]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool ok = rb + 2 * u + h < rend;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) m[u].v[s] = keep_if(m[u].v[s], ok);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) p[nb][u] = keep_if(p[nb][u], ok);
+    }
+    multiply(m, p);
+  };
+  // Short items of NB = 2: every prefetch is of rows that are still to come, and the last group, whole or partial, is left to the code
+  // behind the loop (64 layers of 32 x 2048, r = 50, W = 8, two groups an item 88 -> 82 us, 32 layers of 65 rows 85 -> 82; with
+  // 8 rows in flight and P-bar from L2 80 and 79).
+  if constexpr (SHORT) {
+    int rb = tl.row0;
+    fetch(rb, am, bp);
+    enter(rb);
+    for (; rb + 2 * U < rend; rb += 2 * U) {
+      fetch(rb + 2 * U, an, bn);
+      __builtin_amdgcn_sched_barrier(0);           // (see below)
+      read_p(rb, bp);
+      multiply(am, bp);
+#pragma unroll
+      for (int u = 0; u < U; ++u) am[u] = an[u];
+    }
+    read_p(rb, bp);
+    last_group(rb, am, bp);
+  } else {
   // Whole groups of 2 U rows with the next group's loads issued before this group's matrix instructions, so that a
   // wavefront overlaps its own loads with its own arithmetic (the last prefetch re-reads the last group: every load
   // stays unconditional and in bounds), then the rows that are left.
@@ -1654,16 +1684,8 @@ __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const L
     if constexpr (SHARE)
       if ((rb - tl.row0) % kPRows == 0) enter(rb);
     read_p(rb, bp);
-    // a row that does not exist counts as zeros on both sides (0 x Inf would not be zero)
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool ok = rb + 2 * u + h < rend;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) am[u].v[s] = keep_if(am[u].v[s], ok);
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) bp[nb][u] = keep_if(bp[nb][u], ok);
-    }
-    multiply(am, bp);
+    last_group(rb, am, bp);
+  }
   }
   float* Qp = a.Qpart + (size_t)worker * a.qpart_stride + ld.qpart_off + (size_t)(tl.row0 / ld.rbb) * ld.nq_pad;
 #pragma unroll
@@ -1691,10 +1713,11 @@ __global__ __launch_bounds__(256, 2) void back_project_mfma_kernel(DevArgs a, co
   const LayerDesc& ld = a.layers[layer];
   const int c0 = tl.aux * kMfmaCols + wave * 128;
   // strips of which all 128 columns exist need no care at their end, whatever the alignment of the rows
-  auto run = [&](const float* ps, auto&& enter) __attribute__((always_inline)) {
-    if (c0 + 128 <= ld.cols) back_project_mfma_tile<NB, kAligned>(a, ld, tl, worker, c0, lane, ps, enter);
-    else if (ld.cols >= 4) back_project_mfma_tile<NB, kRagged>(a, ld, tl, worker, c0, lane, ps, enter);
-    else back_project_mfma_tile<NB, kNarrow>(a, ld, tl, worker, c0, lane, ps, enter);
+  auto run = [&](auto short_tag, const float* ps, auto&& enter) __attribute__((always_inline)) {
+    constexpr bool SHORT = decltype(short_tag)::value;
+    if (c0 + 128 <= ld.cols) back_project_mfma_tile<NB, kAligned, SHORT>(a, ld, tl, worker, c0, lane, ps, enter);
+    else if (ld.cols >= 4) back_project_mfma_tile<NB, kRagged, SHORT>(a, ld, tl, worker, c0, lane, ps, enter);
+    else back_project_mfma_tile<NB, kNarrow, SHORT>(a, ld, tl, worker, c0, lane, ps, enter);
   };
   if constexpr (NB == 2) {
     __shared__ __attribute__((aligned(16))) float ps[kPRows * 32 * NB];
@@ -1704,22 +1727,30 @@ __global__ __launch_bounds__(256, 2) void back_project_mfma_kernel(DevArgs a, co
       const float* src = p_operand(a, ld) + (size_t)row * (32 * NB);
       const int n4 = min(kPRows, rend - row) * (8 * NB);
       if (row > tl.row0) __syncthreads();
+      auto copy = [&](auto n_tag, const int i0) __attribute__((always_inline)) {
+        constexpr int N = decltype(n_tag)::value;
+        Pk<4> x[N];
 #pragma unroll
-      for (int i0 = 0; i0 < 8 * NB; i0 += 8) {
-        Pk<4> x[8];
+        for (int i = 0; i < N; ++i) x[i] = ldrow<false>(reinterpret_cast<const char*>(src), (unsigned)min(tid + 256 * (i0 + i), n4 - 1) * 16u);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = ldrow<false>(reinterpret_cast<const char*>(src), (unsigned)min(tid + 256 * (i0 + i), n4 - 1) * 16u);
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < N; ++i)
           if (tid + 256 * (i0 + i) < n4)
             reinterpret_cast<float4*>(ps)[tid + 256 * (i0 + i)] = make_float4(x[i].v[0], x[i].v[1], x[i].v[2], x[i].v[3]);
+      };
+      // no more requests than the rows take: an item of 32 rows is over after few others
+      if (n4 <= 512) {
+        copy(std::integral_constant<int, 2>{}, 0);
+      } else {
+        copy(std::integral_constant<int, 8>{}, 0);
+        if (n4 > 2048) copy(std::integral_constant<int, 8>{}, 8);
       }
       __syncthreads();
     };
-    if (c0 < ld.cols) run(ps, enter);
+    if (c0 < ld.cols && tl.nrows < 128) run(std::true_type{}, ps, enter);
+    else if (c0 < ld.cols) run(std::false_type{}, ps, enter);
     else for (int row = tl.row0; row < rend; row += kPRows) enter(row);   // no columns: only its share of the copies
   } else {
-    if (c0 < ld.cols) run(nullptr, [](int) {});
+    if (c0 < ld.cols) run(std::false_type{}, nullptr, [](int) {});
   }
 }
 

@@ -453,3 +453,25 @@ def _schedules(layers, rank, W, kernel, bf16=False, bits=8, iterations=3):
 def test_rank_pad_64_items_of_any_height(layers, W, kernel, bf16):
     _say("case: 64-row items, deferred and eager", layers, W, bf16)
     _schedules(layers, 50, W, kernel, bf16)
+
+
+def test_sweep_one_row_blocks_of_any_height_at_rank_pad_64():
+    """Sweep 1 at rank pad 64: row blocks of less than one group of 16 rows, of whole groups and a rest, around the 128 rows from which
+    items are long, of 256 and a rest; strips without columns beside strips that share the rows of P-bar."""
+    layers = [(h, 300) for h in (9, 16, 17, 31, 32, 33, 65, 100, 127, 128, 129, 144, 150, 255, 256, 257, 300, 520)] + [(80, 520), (200, 1030)]
+    rank, W = 40, 20
+    _say("case: row blocks of sweep 1", layers, rank, W)
+    rng = np.random.default_rng(1)
+    tiles = B.plan_tiles(B.layer_list(layers, ()), rank, 8, 8, W, 1)
+    assert tiles[:, 3].max() == 256 and {9, 127, 128, 129, 255} <= set(tiles[:, 3].tolist())
+    comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, W)
+    Q = [rng.standard_normal((c, min(rank, n, c))).astype(f32) for n, c in layers]
+    ml = list(range(len(layers)))
+    for l in ml:
+        comp.set_q(l, Q[l])
+    E = [[np.zeros(s, f32) for s in layers] for _ in range(W)]
+    rep = pu.StageReport()
+    G = [[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)]
+    pu.staged_iteration(comp, G, pu.to_device(G), E, Q, ml, rep, layers_to_check=ml, workers_to_check=[0, 7, 19])
+    comp.close()
+    _say("  ", rep)
