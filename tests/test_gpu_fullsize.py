@@ -129,3 +129,17 @@ def test_sweep_8192_fused_step_equals_staged_at_full_size(rank):
     want = pb[rows].astype(np.float64) @ qb.astype(np.float64).T
     assert pu.rel_fro(got, want) <= pu.FP_TOL
     fused.close(); staged.close()
+
+
+def test_rank_50_row_blocks_beyond_one_copy_of_p():
+    """Rank pad 64, 8192 x 8292, W = 4: sweep 1's row blocks are of more than 256 rows, so that the rows of P-bar are copied more
+    than once, in workgroups of which three strips of four have no columns too."""
+    w = wl.scaled(wl.sweep_8192(50, 8, workers=4), layers=((8192, 8292),))
+    _say("case: 8192 x 8292 r=50 b=8 W=4")
+    tiles = B.plan_tiles(B.layer_list(w.layers), w.rank, w.bits, w.bits, w.workers, 1)
+    assert tiles[:, 3].max() > 256 and tiles[:, 5].min() == 8292 - 16 * 512
+    _sampled_run(w, [0], [2], steps=1)
+
+
+def test_sweep_8192_fused_step_equals_staged_at_rank_50():
+    test_sweep_8192_fused_step_equals_staged_at_full_size(50)
