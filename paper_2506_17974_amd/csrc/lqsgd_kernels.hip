@@ -2722,6 +2722,74 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
   };
 
   int c0 = col0;
+  // Layers narrower than a round: the item's rows are one run of memory, which the threads share in pieces of 16 bytes whatever
+  // the width.  (A row a request leaves most lanes with another lane's address, and such layers are nothing but partial rounds.
+  // Sweep 0, W = 8, 32 x 64 or 32 x 32 blocks per wavefront / a row a request / now: r = 16 64 x (512 x 64) 96 / 134 / 100 us,
+  // 64 x (512 x 96) 138 / 149 / 113, 48 x (512 x 128) 91 / 118 / 92, 32 x (512 x 130) 80 / 86 / 69, 40 x (512 x 192) 92 / 117 / 87,
+  // at r = 32 135 / 152 / 116, 145 / 167 / 129, 124 / 132 / 105, 118 / 97 / 80, 130 / 128 / 102.)
+  auto narrow = [&](auto n_tag, const int n4) __attribute__((always_inline)) {
+    constexpr int N = decltype(n_tag)::value;
+    int ln = lane, tid = threadIdx.x;              // hidden from the optimiser (see mfma_pair_tile)
+    asm volatile("" : "+v"(ln), "+v"(tid));
+    const bool mine = 32 * NBK * wave < cols;
+    const char* gb = grad_row<GB16>(G, (size_t)row0 * cols);
+    char* mb = reinterpret_cast<char*>(M + (size_t)row0 * cols);
+    Pk<4> g[N], e[N];
+    if (mine) fetch_q(std::false_type{}, ln, 32 * NBK * wave);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const unsigned lo = (unsigned)min(tid + 256 * i, n4 - 1) * 16u;
+      g[i] = ldgrad<LQSGD_NT_G != 0, GB16>(gb, lo);
+      e[i] = ldrow<NTS>(mb, lo);
+    }
+    if (mine) {
+      place_q(ln);
+      if constexpr (NEEDG) reconstruct(ln);
+    }
+    if constexpr (!NEEDG)                          // columns of a wavefront's block that do not exist (G-hat is zero there)
+      for (int x = tid; x < 32 * 64; x += 256) {
+        const int col = cols + (x & 63);
+        if (col < (cols + 63) / 64 * 64) tile[(x >> 6) * kLP256 + col] = 0.0f;
+      }
+    __syncthreads();
+    const float inv = 1.0f / (float)cols;          // (at most 32 rows: half a column is far more than the product's rounding)
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int x = tid + 256 * i;
+      if (x < n4) {
+        const int row = (int)(((float)(4 * x) + 0.5f) * inv), col = 4 * x - row * cols;
+        float* at = tile + row * kLP256 + col;
+        Pk<4> m;
+        if (cols % 4 == 0) {
+          if constexpr (NEEDG) {
+            const float4 t = *reinterpret_cast<const float4*>(at);
+            e[i].v[0] -= t.x; e[i].v[1] -= t.y; e[i].v[2] -= t.z; e[i].v[3] -= t.w;
+          }
+#pragma unroll
+          for (int v = 0; v < 4; ++v) m.v[v] = g[i].v[v] + e[i].v[v];
+          *reinterpret_cast<float4*>(at) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
+        } else {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            float* const a1 = at + v + (col + v >= cols ? kLP256 - cols : 0);
+            if constexpr (NEEDG) e[i].v[v] -= *a1;
+            m.v[v] = g[i].v[v] + e[i].v[v];
+            *a1 = m.v[v];
+          }
+        }
+        strow<NTS>(mb, (unsigned)x * 16u, m);
+      }
+    }
+    __syncthreads();
+    if (mine) product(ln, [](int) {});
+  };
+  if (cols < 256 && nrows * cols % 4 == 0) {       // (else the last piece would reach beyond the layer)
+    const int n4 = nrows * cols / 4;
+    if (n4 <= 512) narrow(std::integral_constant<int, 2>{}, n4);
+    else if (n4 <= 1024) narrow(std::integral_constant<int, 4>{}, n4);
+    else narrow(std::integral_constant<int, 8>{}, n4);
+    c0 = col1;
+  }
   // whole rounds: 32 rows x 256 columns
   const int cend = nrows == 32 ? col0 + (col1 - col0) / 256 * 256 : col0;
   if (c0 < cend) {
@@ -2787,7 +2855,7 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
 }
 
 template <int RP, int MODE, bool GB16, bool NTS>
-__global__ __launch_bounds__(256, 2) void mfma_round_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
+__global__ __launch_bounds__(256, RP == 16 && MODE == kMAdd ? 3 : 2) void mfma_round_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
   __shared__ __attribute__((aligned(256))) char qs[8 * 32 * RP * 4];
   __shared__ __attribute__((aligned(16))) float tile[8 * 32 * kLP32];   // 32 x kLP256 in the rounds, the partial sums after them
   static_assert(32 * kLP256 <= 8 * 32 * kLP32, "");

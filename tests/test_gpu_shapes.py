@@ -168,3 +168,40 @@ def test_rounds_of_256_columns(rank, bits, W):
 def test_rounds_of_256_columns_at_rank_pad_16(rank, bits, W):
     """The same rounds at rank pad 16, where a wavefront's 64 columns are one sum."""
     test_ragged_shapes([(96, 256), (65, 512), (95, 768), (97, 300), (66, 1028), (128, 2305), (161, 64)], rank, bits, W)
+
+
+NARROW = [(64, 64), (33, 100), (96, 252), (31, 255), (70, 68), (32, 130), (65, 192), (37, 77), (128, 4), (61, 129), (3, 253), (40, 40)]
+
+
+@pytest.mark.parametrize("rank,bits,W", [(12, 8, 2), (16, 0, 3), (20, 8, 2), (32, 0, 3)])
+def test_layers_narrower_than_a_round(rank, bits, W):
+    """Rank pads 16 and 32: the rows of an item of fewer than 256 columns are moved as one run of memory, rows of any width and
+    number, the last items' sizes a multiple of four and not."""
+    test_ragged_shapes(NARROW, rank, bits, W)
+
+
+@pytest.mark.parametrize("rank", [12, 20])
+def test_layers_narrower_than_a_round_with_bfloat16_gradients(rank):
+    """The same rows in bfloat16: the bits that the same values give as float32, in first and later iterations."""
+    import torch
+    _say("case: narrow layers, bfloat16", rank)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rank)
+    W = 2
+    Q0 = [torch.randn((c, min(rank, n, c)), generator=gen, device="cuda").cpu().numpy() for n, c in NARROW]
+    Gs = [[[(torch.randn(s, generator=gen, device="cuda") * 1e-3).to(torch.bfloat16) for s in NARROW] for _ in range(W)] for _ in range(3)]
+    got = []
+    for flags in (0, B.FLAG_BF16_GRADIENTS):
+        comp = B.Compressor(B.layer_list(NARROW, ()), rank, 8, 8, W, 255.0, flags)
+        for l, q in enumerate(Q0):
+            comp.set_q(l, q)
+        out, res = [torch.zeros(s, device="cuda") for s in NARROW], []
+        for G in Gs:
+            g = G if flags else [[x.float() for x in w] for w in G]
+            comp.step(g, out)
+            comp.synchronize()
+            res += [o.clone() for o in out]
+        comp.close()
+        got.append(res)
+    for a, b in zip(*got):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
