@@ -474,7 +474,21 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
       if (d.cols % 16) askew += (int64_t)d.rows * d.cols;
     const int64_t slab_bytes = 4 * (int64_t)p.W * p.m_stride;
     a.nt_store = slab_bytes >= ((int64_t)640 << 20) && 2 * askew <= p.matrix_elements ? 1 : 0;
+    // Rank pad 16, deferred residual, float32 gradients, plain stores: whole 64-column blocks per wavefront instead of rounds where
+    // rounds would be left half empty, or where the slabs are about the size of the memory-side cache, in which they leave sweep 1 less
+    // of M (a step by rounds / by blocks, us, W = 8, r = 16: 16 x (512 x 320), 84 MB 147 / 140; 24 x (512 x 384), 151 MB 209 / 196;
+    // 8 x (512 x 448), 59 MB 103 / 101; 64 x (512 x 64) 215 / 213; 16 x (512 x 576), 151 MB 198 / 190, but 8 of them 121 / 121;
+    // 16 x (512 x 832), 218 MB 265 / 251, but 8 of them 152 / 153; 64 x (512 x 256), 268 MB 318 / 305; 16 x (512 x 384) beside 8 and
+    // 12 x (512 x 1024) 280 / 266 and 320 / 315, 8 x (512 x 576) beside 14 of them 318 / 321).  Blocks that are cut off are the
+    // rounds' (6 x (512 x 340) 90 / 95, 10 x (512 x 412) 122 / 129), and so are bfloat16 gradients (ResNet-18 set, r = 12 276 / 336).
+    int64_t blocks = 0;
+    for (const LayerDesc& d : p.layers) {
+      const bool few = d.cols == 64 || (d.cols > 256 && d.cols <= 448), some = d.cols == 256 || (d.cols > 256 && d.cols % 256 != 0);
+      if (d.cols % 64 == 0 && d.cols <= 1024 && (few || (some && slab_bytes >= ((int64_t)112 << 20)))) blocks += (int64_t)d.rows * d.cols;
+    }
+    a.by_blocks = p.RP == 16 && !a.g_bf16 && !a.nt_store && 4 * blocks >= p.matrix_elements ? 1 : 0;
 #ifdef LQSGD_TUNING     // a tuning build can force the choice and switch the alternating sweep direction off
+    if (const char* f = std::getenv("LQSGD_BY_BLOCKS")) a.by_blocks = f[0] == '1' && p.RP == 16 && !a.g_bf16;
     if (const char* f = std::getenv("LQSGD_NT_STORE")) {
       if (f[0] == '1') a.nt_store = 1;
       if (f[0] == '2') a.nt_store = 0;

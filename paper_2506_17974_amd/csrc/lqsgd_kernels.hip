@@ -3815,6 +3815,13 @@ void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int two, i
       return;
     }
   }
+  if constexpr (RP == 16 && MODE == kMAddFused) {
+    if (a.by_blocks) {
+      mfma_sweep_kernel<RP, MODE><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, two, reverse);
+      note_kernel("mfma_sweep_kernel<%d, %d, false, false>", RP, MODE);
+      return;
+    }
+  }
 #define LQSGD_LAUNCH_MA(GB, NT)                                                                                            \
   if constexpr (RP <= 32) mfma_round_kernel<RP, MODE, GB, NT><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, reverse);     \
   else mfma_sweep_kernel<RP, MODE, GB, NT><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, two, reverse)

@@ -475,3 +475,38 @@ def test_sweep_one_row_blocks_of_any_height_at_rank_pad_64():
     pu.staged_iteration(comp, G, pu.to_device(G), E, Q, ml, rep, layers_to_check=ml, workers_to_check=[0, 7, 19])
     comp.close()
     _say("  ", rep)
+
+
+@pytest.mark.parametrize("bits", [8, 0])
+def test_sweep_zero_by_blocks_adds_like_sweep_zero_by_rounds(bits):
+    """Rank pad 16: sets of many half-empty rounds go by 64-column blocks per wavefront.  The same layers beside wide ones, by
+    rounds: the same bits."""
+    import torch
+    shapes, W, rank = [(96, 320), (70, 384), (64, 64), (33, 448), (40, 576), (128, 256), (65, 300), (31, 129), (5, 61)], 3, 13
+    _say("case: blocks and rounds", shapes, bits)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    Q0 = [torch.randn((c, min(rank, n, c)), generator=gen, device="cuda").cpu().numpy() for n, c in shapes]
+    Gs = [[[torch.randn(s, generator=gen, device="cuda") * 1e-3 for s in shapes] for _ in range(W)] for _ in range(3)]
+    got = []
+    for wide in (0, 2):
+        layers = shapes + [(200, 1024)] * wide
+        comp = B.Compressor(B.layer_list(layers, ()), rank, bits, bits, W)
+        for l, (n, c) in enumerate(layers):
+            comp.set_q(l, Q0[l] if l < len(shapes) else torch.randn((c, rank), generator=gen, device="cuda").cpu().numpy())
+        out, res = [torch.zeros(s, device="cuda") for s in layers], []
+        for G in Gs:
+            comp.step([w + [torch.randn(200, 1024, generator=gen, device="cuda")] * wide for w in G], out)
+            res += [o.clone() for o in out[:len(shapes)]]
+        assert comp.launched_kernel(0).startswith("mfma_round_kernel<16, 1" if wide else "mfma_sweep_kernel<16, 1"), comp.launched_kernel(0)
+        res += [torch.from_numpy(comp.get_factor(B.FACTOR_P_PRE, l, w)) for l in range(len(shapes)) for w in range(W)]
+        comp.close()
+        got.append(res)
+    for a, b in zip(*got):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+def test_sweep_zero_by_blocks_in_both_schedules():
+    layers = [(96, 320), (70, 384), (64, 64), (33, 448), (65, 320), (128, 64), (3, 320)]
+    _say("case: blocks, deferred and eager", layers)
+    _schedules(layers, 16, 3, "mfma_sweep_kernel<16, 1")
