@@ -473,7 +473,15 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
     for (const LayerDesc& d : p.layers)
       if (d.cols % 16) askew += (int64_t)d.rows * d.cols;
     const int64_t slab_bytes = 4 * (int64_t)p.W * p.m_stride;
-    a.nt_store = slab_bytes >= ((int64_t)640 << 20) && 2 * askew <= p.matrix_elements ? 1 : 0;
+    const bool rows_whole = 2 * askew <= p.matrix_elements;
+    a.nt_store = slab_bytes >= ((int64_t)640 << 20) && rows_whole ? 1 : 0;
+    // Sweep 0 by rounds (rank pads 16 and 32) with the deferred residual and float32 gradients stores whole KiBs of rows and gains
+    // from 310 MB on (a step plain / non-temporal, us, W = 8, r = 16 and r = 32: 8 x (512 x 2048), 268 MB 287 / 291 and 319 / 323;
+    // 8 x (512 x 2304), 302 MB 302 / 304 and 347 / 343; 5 x (512 x 4096), 336 MB 326 / 318 and 366 / 358; ResNet-18 set, 357 MB
+    // 332 / 326 and 402 / 389; 8 x (512 x 4096), 537 MB 465 / 426 and 587 / 576; 8 x (512 x 4608), 604 MB 523 / 501 and
+    // 604 / 579).  First iterations and bfloat16 gradients do not: ResNet-18 set, first sweep 0 179 / 200, a step with bfloat16
+    // gradients 282 / 296.
+    a.nt_fused = a.nt_store || (p.mfma_a && p.RP <= 32 && !a.g_bf16 && rows_whole && slab_bytes >= ((int64_t)320 << 20)) ? 1 : 0;
     // Rank pad 16, deferred residual, float32 gradients, plain stores: whole 64-column blocks per wavefront instead of rounds where
     // rounds would be left half empty, or where the slabs are about the size of the memory-side cache, in which they leave sweep 1 less
     // of M (a step by rounds / by blocks, us, W = 8, r = 16: 16 x (512 x 320), 84 MB 147 / 140; 24 x (512 x 384), 151 MB 209 / 196;
@@ -486,12 +494,12 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
       const bool few = d.cols == 64 || (d.cols > 256 && d.cols <= 448), some = d.cols == 256 || (d.cols > 256 && d.cols % 256 != 0);
       if (d.cols % 64 == 0 && d.cols <= 1024 && (few || (some && slab_bytes >= ((int64_t)112 << 20)))) blocks += (int64_t)d.rows * d.cols;
     }
-    a.by_blocks = p.RP == 16 && !a.g_bf16 && !a.nt_store && 4 * blocks >= p.matrix_elements ? 1 : 0;
+    a.by_blocks = p.RP == 16 && !a.g_bf16 && !a.nt_fused && 4 * blocks >= p.matrix_elements ? 1 : 0;
 #ifdef LQSGD_TUNING     // a tuning build can force the choice and switch the alternating sweep direction off
     if (const char* f = std::getenv("LQSGD_BY_BLOCKS")) a.by_blocks = f[0] == '1' && p.RP == 16 && !a.g_bf16;
     if (const char* f = std::getenv("LQSGD_NT_STORE")) {
-      if (f[0] == '1') a.nt_store = 1;
-      if (f[0] == '2') a.nt_store = 0;
+      if (f[0] == '1') a.nt_store = a.nt_fused = 1;
+      if (f[0] == '2') a.nt_store = a.nt_fused = 0;
     }
     if (const char* f = std::getenv("LQSGD_FLIP")) c->flip = (f[0] != '0');
 #endif

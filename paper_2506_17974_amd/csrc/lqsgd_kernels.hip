@@ -3802,16 +3802,17 @@ hipError_t launch_residual(int rp, int mode, const DevArgs& a, const Tile* tiles
 template <int RP, int MODE>
 void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int two, int reverse, hipStream_t s) {
   const dim3 grid(ntiles + two);
+  const bool nt = MODE == kMAddFused ? a.nt_fused : a.nt_store;
   if constexpr (RP == 64) {
     if (2 * ntiles > kCus) {
 #define LQSGD_LAUNCH_MP(GB, NT) mfma_pair_kernel<MODE, GB, NT><<<dim3(ntiles), dim3(512), 0, s>>>(a, tiles, ntiles, reverse)
       if (a.g_bf16) {
-        if (a.nt_store) { LQSGD_LAUNCH_MP(true, true); } else { LQSGD_LAUNCH_MP(true, false); }
+        if (nt) { LQSGD_LAUNCH_MP(true, true); } else { LQSGD_LAUNCH_MP(true, false); }
       } else {
-        if (a.nt_store) { LQSGD_LAUNCH_MP(false, true); } else { LQSGD_LAUNCH_MP(false, false); }
+        if (nt) { LQSGD_LAUNCH_MP(false, true); } else { LQSGD_LAUNCH_MP(false, false); }
       }
 #undef LQSGD_LAUNCH_MP
-      note_kernel("mfma_pair_kernel<%d, %s, %s>", MODE, tf(a.g_bf16), tf(a.nt_store));
+      note_kernel("mfma_pair_kernel<%d, %s, %s>", MODE, tf(a.g_bf16), tf(nt));
       return;
     }
   }
@@ -3826,13 +3827,13 @@ void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int two, i
   if constexpr (RP <= 32) mfma_round_kernel<RP, MODE, GB, NT><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, reverse);     \
   else mfma_sweep_kernel<RP, MODE, GB, NT><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, two, reverse)
   if (a.g_bf16) {
-    if (a.nt_store) { LQSGD_LAUNCH_MA(true, true); } else { LQSGD_LAUNCH_MA(true, false); }
+    if (nt) { LQSGD_LAUNCH_MA(true, true); } else { LQSGD_LAUNCH_MA(true, false); }
   } else {
-    if (a.nt_store) { LQSGD_LAUNCH_MA(false, true); } else { LQSGD_LAUNCH_MA(false, false); }
+    if (nt) { LQSGD_LAUNCH_MA(false, true); } else { LQSGD_LAUNCH_MA(false, false); }
   }
 #undef LQSGD_LAUNCH_MA
-  if constexpr (RP <= 32) note_kernel("mfma_round_kernel<%d, %d, %s, %s>", RP, MODE, tf(a.g_bf16), tf(a.nt_store));
-  else note_kernel("mfma_sweep_kernel<%d, %d, %s, %s>", RP, MODE, tf(a.g_bf16), tf(a.nt_store));
+  if constexpr (RP <= 32) note_kernel("mfma_round_kernel<%d, %d, %s, %s>", RP, MODE, tf(a.g_bf16), tf(nt));
+  else note_kernel("mfma_sweep_kernel<%d, %d, %s, %s>", RP, MODE, tf(a.g_bf16), tf(nt));
 }
 
 template <int RP>

@@ -510,3 +510,29 @@ def test_sweep_zero_by_blocks_in_both_schedules():
     layers = [(96, 320), (70, 384), (64, 64), (33, 448), (65, 320), (128, 64), (3, 320)]
     _say("case: blocks, deferred and eager", layers)
     _schedules(layers, 16, 3, "mfma_sweep_kernel<16, 1")
+
+
+# Slabs of W workers in MB (2^20 bytes): the store policy of sweep 0 turns on them and on how the elements' rows start.
+@pytest.mark.parametrize("layers,rank,first,later", [
+    ([(2048, 2048)] * 9, 16, "false>", "false>"),                          # 288 MB
+    ([(2048, 2048)] * 11, 16, "false>", "true>"),                          # 352 MB: with the deferred residual only
+    ([(2048, 2048)] * 11, 20, "false>", "true>"),
+    ([(2048, 2048)] * 11, 50, "false>", "false>"),                         # rank pads 64 and 8 wait for 640 MB
+    ([(2048, 2048)] * 11, 7, "false>", "false>"),
+    ([(2048, 2048)] * 6 + [(2048, 2049)] * 5, 16, "false>", "true>"),      # most elements in rows of whole 64 bytes
+    ([(2048, 2048)] * 5 + [(2048, 2049)] * 6, 16, "false>", "false>"),     # most not
+    ([(2048, 2048)] * 12 + [(2048, 2052)] * 9, 32, "true>", "true>"),      # 672 MB
+    ([(2048, 2048)] * 9 + [(2048, 2052)] * 12, 50, "false>", "false>"),
+])
+def test_store_policy_of_mixed_sets(layers, rank, first, later):
+    """The first iteration and the later ones of the deferred schedule follow their own line; the eager schedule, which takes the
+    former's throughout, gives the same bits."""
+    import torch
+    _say("case: store policy", len(layers), rank, first, later)
+    comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, 2)
+    G = [[torch.zeros(s, device="cuda") for s in layers]] * 2
+    for want in (first, later):
+        comp.step(G)
+        assert comp.launched_kernel(0).endswith(want), comp.launched_kernel(0)
+    comp.close()
+    _schedules(layers, rank, 2, "", iterations=2)
