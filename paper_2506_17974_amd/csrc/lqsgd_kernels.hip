@@ -2572,14 +2572,20 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
           make_float4(st[i].v[0], st[i].v[1], st[i].v[2], st[i].v[3]);
     wave_lds_fence();
   };
-  // Requests k0 .. k1 of a whole round's: G and E of this wavefront's rows in turn.  real false: of the first
-  // rows of Q instead, for a round that has no next one (a branch around a request would part the loop in two).
-  auto fetch = [&](const bool real, const int c0, Pk<4>* g, Pk<4>* e, const int k0, const int k1) __attribute__((always_inline)) {
-    const unsigned lo = (unsigned)lane * 16u;
+  // Requests k0 .. k1 of the round at c0, whole or partial: G and E of this wavefront's rows in turn, lo(c0) its lane's place.
+  // real false: of the first rows of Q instead, for a round that has no next one (a branch around a request would part the
+  // loop in two).  Addresses count from back columns before c0, so that a partial round's last lanes, which load the row's last
+  // four columns (edge_col), stay at or behind them.
+  auto place = [&](const bool real, const int c0, const int back) __attribute__((always_inline)) {
+    unsigned lo = (unsigned)(real ? min(back + 4 * lane, back + col1 - 4 - c0) : 4 * lane) * 4u;
+    asm volatile("" : "+v"(lo));
+    return lo;
+  };
+  auto fetch = [&](const bool real, const unsigned lo, const int c0, const int back, Pk<4>* g, Pk<4>* e, const int k0, const int k1) __attribute__((always_inline)) {
 #pragma unroll
     for (int k = k0; k < k1; ++k) {
       const int i = k >> 1;
-      const size_t off = (size_t)(row0 + RPW * wave + i) * cols + c0;
+      const size_t off = (size_t)(row0 + RPW * wave + i) * cols + (c0 - back);
       const char* base = (k & 1) ? reinterpret_cast<const char*>(M + off) : grad_row<GB16>(G, off);
       if (!real) base = reinterpret_cast<const char*>(Q);
       if (k & 1) {
@@ -2792,13 +2798,13 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
   }
   // whole rounds: 32 rows x 256 columns
   const int cend = nrows == 32 ? col0 + (col1 - col0) / 256 * 256 : col0;
+  Pk<4> g[RPW], e[RPW];
   if (c0 < cend) {
-    Pk<4> g[RPW], e[RPW];
     // The tile needs two barriers a round: G-hat is complete before rows are read, M before columns are.  A wavefront's
     // next G-hat goes to columns that only it reads, and no row is written before all have passed the first barrier again.
     fetch_q(std::true_type{}, lane, c0 + 32 * NBK * wave);
     __builtin_amdgcn_sched_barrier(0);
-    fetch(true, c0, g, e, 0, 2 * RPW);
+    fetch(true, place(true, c0, 0), c0, 0, g, e, 0, 2 * RPW);
     __builtin_amdgcn_sched_barrier(0);
     do {
       place_q(lane);
@@ -2811,10 +2817,15 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
       // A round without G-hat is short, and its requests all go out at once (a first iteration of the ResNet-18 set, W = 8: 237 us
       // spread as below, 208 at once).  With G-hat spread ones are as fast in large sets and faster in small ones (1024 x 576,
       // r = 20 58 / 62, 4 x 1024^2 79 / 85).
-      if constexpr (!NEEDG) fetch(c0 < cend, c0, g, e, 0, 2 * RPW);
+      // The partial round behind the whole ones is requested with the last of them, in a round without G-hat (sweep 0 of a first
+      // iteration, W = 8, us: r = 32 24 x (512 x 320) 104 / 98, 24 x (512 x 448) 120 / 107, 16 x (512 x 832) 126 / 119, 8 x (512 x 4096)
+      // 340 / 308; r = 16 86 / 78, 97 / 91, 118 / 110, 303 / 289; with G-hat 24 x (512 x 448), r = 32 130 / 133).
+      const bool real = c0 < (NEEDG ? cend : col1);
+      const unsigned lo = place(real, c0, 256);
+      if constexpr (!NEEDG) fetch(real, lo, c0, 256, g, e, 0, 2 * RPW);
       __syncthreads();
       product(lane, [&](const int j) __attribute__((always_inline)) {
-        if constexpr (NEEDG) fetch(c0 < cend, c0, g, e, 2 * j, 2 * j + 2);
+        if constexpr (NEEDG) fetch(real, lo, c0, 256, g, e, 2 * j, 2 * j + 2);
       });
     } while (c0 < cend);
   }
@@ -2822,8 +2833,17 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
     int ln = lane;                                 // hidden from the optimiser (see mfma_pair_tile)
     asm volatile("" : "+v"(ln));
     const bool mine = c0 + 32 * NBK * wave < col1;
-    Pk<4> g[RPW], e[RPW];
-    fetch_edge(ln, c0, g, e);
+    if (!NEEDG && c0 == cend && cend > col0) {     // requested by the last whole round
+      if constexpr (GB16)
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) g[i] = unpack_bf16(g[i].v[0], g[i].v[1]);
+      if (c0 + 4 * ln + 4 > cols) {
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) { edge_fix<1>(g[i].v, c0 + 4 * ln, cols); edge_fix<1>(e[i].v, c0 + 4 * ln, cols); }
+      }
+    } else {
+      fetch_edge(ln, c0, g, e);
+    }
     if (mine) {
       fetch_q(std::false_type{}, ln, c0 + 32 * NBK * wave);
       place_q(ln);

@@ -180,22 +180,27 @@ def test_layers_narrower_than_a_round(rank, bits, W):
     test_ragged_shapes(NARROW, rank, bits, W)
 
 
+TAILS = [(96, 257), (64, 258), (65, 300), (32, 511), (33, 770), (70, 2305), (128, 320), (31, 600), (64, 512)]
+
+
+@pytest.mark.parametrize("layers", [NARROW, TAILS])
 @pytest.mark.parametrize("rank", [12, 20])
-def test_layers_narrower_than_a_round_with_bfloat16_gradients(rank):
-    """The same rows in bfloat16: the bits that the same values give as float32, in first and later iterations."""
+def test_bfloat16_gradients_of_narrow_layers_and_partial_rounds(rank, layers):
+    """Items narrower than a round, and partial rounds behind whole ones, in bfloat16: the bits that the same values give as float32,
+    in first and later iterations."""
     import torch
-    _say("case: narrow layers, bfloat16", rank)
+    _say("case: bfloat16 against float32", rank, layers)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(rank)
     W = 2
-    Q0 = [torch.randn((c, min(rank, n, c)), generator=gen, device="cuda").cpu().numpy() for n, c in NARROW]
-    Gs = [[[(torch.randn(s, generator=gen, device="cuda") * 1e-3).to(torch.bfloat16) for s in NARROW] for _ in range(W)] for _ in range(3)]
+    Q0 = [torch.randn((c, min(rank, n, c)), generator=gen, device="cuda").cpu().numpy() for n, c in layers]
+    Gs = [[[(torch.randn(s, generator=gen, device="cuda") * 1e-3).to(torch.bfloat16) for s in layers] for _ in range(W)] for _ in range(3)]
     got = []
     for flags in (0, B.FLAG_BF16_GRADIENTS):
-        comp = B.Compressor(B.layer_list(NARROW, ()), rank, 8, 8, W, 255.0, flags)
+        comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, W, 255.0, flags)
         for l, q in enumerate(Q0):
             comp.set_q(l, q)
-        out, res = [torch.zeros(s, device="cuda") for s in NARROW], []
+        out, res = [torch.zeros(s, device="cuda") for s in layers], []
         for G in Gs:
             g = G if flags else [[x.float() for x in w] for w in G]
             comp.step(g, out)
