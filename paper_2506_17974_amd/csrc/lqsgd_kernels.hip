@@ -1929,8 +1929,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) voi
 }
 
 // ---------------------------------------------------------------------------
-// Sweeps 0 and 2 on the matrix cores, rank pads 16 and 32.
-// One workgroup per work item (32 rows x one column segment); its four
+// Sweeps on the matrix cores by 64-column blocks per wavefront: the residual and G-hat
+// passes at rank pads 16 to 64, sweep 0 of few items at 64 and of half-empty rounds at 16
+// (DevArgs::by_blocks); the other sweeps 0 further below.
+// One workgroup per 32 rows x one column segment; its four
 // wavefronts take the 64-column blocks of the segment in turn, so that the
 // workgroup touches 1 KiB of every row at about the same time (with one item
 // per wavefront, each walking its own segment in 256-byte runs, the same data
@@ -2012,7 +2014,7 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
     const int cl = c + c4;
     // Edge blocks: this lane's row number is hidden from the optimiser, which otherwise computes the addresses of all
     // rows once, ahead of the loop over the blocks, and keeps them in registers that the whole blocks need (rank pad
-    // 16: 92 values spilled, 8192^2 x 8 workers sweep 0 1098 -> 1220 us).
+    // 16, deferred residual: 92 values spilled; 8192^2, W = 8, when that set took this form, sweep 0 1098 -> 1220 us).
     int sr_ = sr;
     if constexpr (!FULL) asm volatile("" : "+v"(sr_));
     const int ncol = FULL ? 4 : cols - cl;       // columns of this lane's group that exist
@@ -2508,7 +2510,10 @@ __global__ __launch_bounds__(512, 2) void mfma_pair_kernel(DevArgs a, const Tile
 // bfloat16 gradients 233 / 189; 8192^2, W = 16 2431 / 2246; 4 x (3000 x 5000), r = 20 1892 / 1273; 32 x (512 x 4608) 1446 / 1342;
 // sets as small as 4 x 1024^2, W = 2 29 / 27.  At r = 16, with 32 x 64 blocks per wavefront / now: ResNet-18 set 209 / 201, at r = 12
 // with bfloat16 gradients 218 / 162; 8192^2 1091 / 1025; 4 x (3000 x 5000) 1283 / 1246; ragged set (64 x 27 .. 1000 x 2049), r = 12,
-// W = 4 52 / 42; 4 x 1024^2, W = 2 28.6 / 24.7; 8 x (512 x 4608) 339 / 346, the one set measured that lost.
+// W = 4 52 / 42; 4 x 1024^2, W = 2 28.6 / 24.7.
+// Sets measured that lost and still do, a step: r = 32 16 x (512 x 576) 230 / 236, 24 x (512 x 320) 226 / 231, r = 16 8 x (512 x 2304)
+// 298 / 303 (all in sweep 1 behind it); a first iteration's sweep 0 at r = 32: 16 x (512 x 2048) 318 / 334, 24 x (512 x 320) 92 / 98
+// (ResNet-18 set 214 / 211, at r = 16 194 / 191).
 // ---------------------------------------------------------------------------
 constexpr int kLP256 = 260;  // LDS pitch (floats) of the 32 x 256 tile: 16-byte aligned rows, 4-bank skew per row
 
@@ -2611,7 +2616,7 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
       for (int i = 0; i < RPW; ++i) { edge_fix<1>(g[i].v, cl, cols); edge_fix<1>(e[i].v, cl, cols); }
     }
   };
-  // G-hat of this wavefront's 32 columns, into the tile
+  // G-hat of this wavefront's 64 columns, into the tile
   auto reconstruct = [&](const int ln) __attribute__((always_inline)) {
     const int li = ln & 31, h = ln >> 5;
     // row li of this wavefront's rows of Q, ranks KH h .. KH h + KH - 1
@@ -2641,7 +2646,7 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
 #pragma unroll
       for (int v = 0; v < 16; ++v) tile[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP256 + 32 * (NBK * wave + b) + li] = gh[b][v];
   };
-  // M of this wavefront's four rows, to memory and into the tile
+  // M of this wavefront's eight rows, to memory and into the tile
   auto form = [&](auto full_tag, const int ln, const int c0, Pk<4>* g, Pk<4>* e) __attribute__((always_inline)) {
     constexpr bool FULL = decltype(full_tag)::value;
     float* mine = tile + RPW * wave * kLP256 + 4 * ln;
@@ -2662,7 +2667,7 @@ __device__ __forceinline__ void mfma_round_tile(const float* __restrict__ G, flo
       *reinterpret_cast<float4*>(mine + i * kLP256) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
     }
   };
-  // P += M Q over this wavefront's 32 columns; between(j): called after the j-th of 4 NBK groups of matrix instructions
+  // P += M Q over this wavefront's 64 columns; between(j): called after the j-th of 4 NBK groups of matrix instructions
   auto product = [&](const int ln, auto&& between) __attribute__((always_inline)) {
     const int li = ln & 31, h = ln >> 5;
     if constexpr (RP == 16) {

@@ -337,8 +337,8 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
     for (int32_t g = 0; g < gq; g += kXBlockGroups) tilesXQ.push_back(XTile{li, g});
   }
   // Rank pads 32 and 64: few workgroups fit a CU there and an item can take a tenth of the launch, so that the widest go first and
-  // the last ones are short (sweep 0, us, in the layers' order / sorted: ragged set, r = 20, W = 4 48.2 / 43.5; ResNet-18 set, W = 8,
-  // r = 50 277 / 267, r = 32 216 / 216; 64 x 576 .. 512 x 4608, W = 4, r = 64 135 / 129).  Items of more than 32 rows before the
+  // the last ones are short (sweep 0 forwards, as it runs there with the deferred residual, us, in the layers' order / sorted: ragged
+  // set, r = 20, W = 4 50 / 44; ResNet-18 set, W = 8, r = 50 271 / 260, r = 32 215 / 211).  Items of more than 32 rows before the
   // others (HalfItem).
   twoA = twoAG = 0;
   if (mfma) {
