@@ -503,8 +503,26 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
       if (d.cols % 64 == 0 && d.cols <= 1024 && (few || (some && slab_bytes >= ((int64_t)112 << 20)))) blocks += (int64_t)d.rows * d.cols;
     }
     a.by_blocks = p.RP == 16 && !a.g_bf16 && !a.nt_fused && 4 * blocks >= p.matrix_elements ? 1 : 0;
+    // Rank pad 32: 32 x 32 blocks per wavefront (1: without a deferred residual, 2: with it, too) where there is a CU an item, with
+    // the residual only if the longest items are uneven, short ones of many rounds or last rounds at most half full, or one narrow
+    // round (figures at mfma_sweep32_kernel; beyond a CU an item, r = 32, W = 8, rounds / blocks: 512 items, 8 x (256 x 1024) 43 / 51,
+    // in a first iteration 43 / 43, 384 items, 24 x (40 x 1024) 37 / 44 and 35 / 35).  Of any length, first iterations only: rows of a
+    // whole round and at most a quarter more that start on lines of 128 bytes (16 x (512 x 288) 66 / 60, 24 x (512 x 320) 96 / 92; but
+    // 16 x (512 x 304) 68 / 74, 16 x (512 x 384) 71 / 72, 8 x (512 x 576) 52 / 53).
+    if (p.RP == 32 && !a.nt_store) {
+      bool wide = false, uneven = false;
+      int64_t quarter = 0;
+      for (const LayerDesc& d : p.layers) {
+        wide = wide || d.cols > 192;
+        uneven = uneven || (d.cols > 768 && d.rows % 32 != 0) || (d.cols > 256 && d.cols % 256 != 0 && d.cols % 256 <= 128);
+        if (d.cols > 256 && d.cols <= 320 && d.cols % 32 == 0) quarter += (int64_t)d.rows * d.cols;
+      }
+      if (p.tilesA.size() <= 256) a.by_blocks = uneven || !wide ? 2 : 1;
+      else if (!a.g_bf16 && 2 * quarter >= p.matrix_elements) a.by_blocks = 1;
+    }
 #ifdef LQSGD_TUNING     // a tuning build can force the choice and switch the alternating sweep direction off
-    if (const char* f = std::getenv("LQSGD_BY_BLOCKS")) a.by_blocks = f[0] == '1' && p.RP == 16 && !a.g_bf16;
+    if (const char* f = std::getenv("LQSGD_BY_BLOCKS"))
+      a.by_blocks = p.RP == 16 && !a.g_bf16 ? f[0] == '1' : p.RP == 32 && !a.nt_store ? f[0] - '0' : 0;
     if (const char* f = std::getenv("LQSGD_NT_STORE")) {
       if (f[0] == '1') a.nt_store = a.nt_fused = 1;
       if (f[0] == '2') a.nt_store = a.nt_fused = 0;

@@ -2511,8 +2511,9 @@ __global__ __launch_bounds__(512, 2) void mfma_pair_kernel(DevArgs a, const Tile
 // sets as small as 4 x 1024^2, W = 2 29 / 27.  At r = 16, with 32 x 64 blocks per wavefront / now: ResNet-18 set 209 / 201, at r = 12
 // with bfloat16 gradients 218 / 162; 8192^2 1091 / 1025; 4 x (3000 x 5000) 1283 / 1246; ragged set (64 x 27 .. 1000 x 2049), r = 12,
 // W = 4 52 / 42; 4 x 1024^2, W = 2 28.6 / 24.7.
-// Sets measured that lost and still do, a step: r = 32 16 x (512 x 576) 230 / 236, 24 x (512 x 320) 226 / 231, r = 16 8 x (512 x 2304)
-// 298 / 303 (all in sweep 1 behind it); a first iteration's sweep 0 at r = 32: 16 x (512 x 2048) 318 / 334, 24 x (512 x 320) 92 / 98
+// Lists that have a CU an item lost and are no longer taken here (mfma_sweep32_kernel).
+// Sets measured that lost and still do, a step: r = 32 16 x (512 x 576) 230 / 235, 24 x (512 x 320) 226 / 229, r = 16 8 x (512 x 2304)
+// 298 / 303 (all in sweep 1 behind it); a first iteration's sweep 0 at r = 32: 16 x (512 x 2048) 318 / 334
 // (ResNet-18 set 214 / 211, at r = 16 194 / 191).
 // ---------------------------------------------------------------------------
 constexpr int kLP256 = 260;  // LDS pitch (floats) of the 32 x 256 tile: 16-byte aligned rows, 4-bank skew per row
@@ -2904,6 +2905,301 @@ __global__ __launch_bounds__(256, RP == 16 && MODE == kMAdd ? 3 : 2) void mfma_r
   }
   mfma_round_tile<RP, MODE, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ld.cols, ld.r, tl.row0, tl.nrows,
                                    col0, col1, lane, wave, qs, tile);
+}
+
+// ---------------------------------------------------------------------------
+// Sweep 0 at rank pad 32 for lists that have a CU an item (DevArgs::by_blocks): 32 x 32 blocks per wavefront.
+//
+// Such a list takes as long as its longest item, and an item as long as its chain of round trips to memory: a round of
+// mfma_round_kernel pays two barriers, and one that is cut short a round trip of its own.  Here eight wavefronts walk the
+// item's blocks on their own, 256 columns apart, with the next block's G, E and operands requested ahead; rows of Q come from
+// L2 in operand layout, too many requests for a full chip.  Blocks of 32 columns accumulate and are added in the same order as
+// there, and G-hat comes out of the same sequence of matrix instructions: the same bits.
+// Sweep 0, r = 32, by rounds / here, us.  Deferred residual: 4 x (256 x 320), W = 4 16.7 / 12.9; 8 x (256 x 576), W = 4 23.0 / 19.3;
+// 16 x (64 x 128), W = 4 9.9 / 8.2; 4 x (31 x 2048), W = 4 25.4 / 24.1; 16 x (20 x 2000), W = 8 32.1 / 27.7; 1000 x 1024, W = 4
+// 27.2 / 24.5.  First iterations: 8 x (256 x 320), W = 4 15.7 / 11.7; 8 x (256 x 576), W = 4 20.4 / 16.3; 4 x (256 x 1024), W = 4
+// 21.0 / 19.4, at W = 8 28.6 / 25.5.  Where the rounds are whole or nearly, they win with the deferred residual (4 x (256 x 1024), W = 4
+// 22.6 / 25.0; 2 x (64 x 988), W = 4 21.6 / 22.8).
+// Row layout: 8 lanes = 128 contiguous bytes of a row, 8 rows per instruction.
+// ---------------------------------------------------------------------------
+template <int MODE, bool GB16>
+__device__ __forceinline__ void mfma_tile32(const float* __restrict__ G, float* __restrict__ M,
+                                            const float* Q, const float* Pb, float* __restrict__ Pp,
+                                            int cols, int r, int row0, int nrows, int col0, int col1,
+                                            int lane, int wave, float (*lds_all)[32 * kLP32]) {
+  static_assert(MODE == kMAdd || MODE == kMAddFused, "add modes");
+  constexpr int RP = 32;
+  float* lds = lds_all[wave];
+  constexpr bool NEEDG = (MODE != kMAdd);
+  constexpr int KH = RP / 2;
+  const int li = lane & 31, h = lane >> 5;
+  const int sr = lane >> 3, c4 = (lane & 7) * 4;   // row layout: rows 8 i + sr, columns c4 .. c4 + 3
+  float pa[KH];
+  if constexpr (NEEDG) {
+    const int row = row0 + li;
+    if (li < nrows) {
+      const float4* src = reinterpret_cast<const float4*>(Pb + (size_t)row * RP + KH * h);
+#pragma unroll
+      for (int t = 0; t < KH / 4; ++t) {
+        const float4 x = src[t];
+        pa[4 * t] = x.x; pa[4 * t + 1] = x.y; pa[4 * t + 2] = x.z; pa[4 * t + 3] = x.w;
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < KH; ++k) pa[k] = 0.0f;
+    }
+  }
+  v16f accP, accP2;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) { accP[i] = 0.0f; accP2[i] = 0.0f; }
+
+  // the G and E (or old M) values of one 32 x 32 block at an edge of the layer
+  auto fetch = [&](const int c, Pk<4>* g, Pk<4>* e) {
+    const int cl = c + c4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const size_t off = (size_t)(row0 + min(8 * i + sr, nrows - 1)) * cols;   // rows beyond nrows: never stored
+      g[i] = ldedge<kRagged, LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), cl, cols);
+      e[i] = ldedge<kRagged, false, false>(reinterpret_cast<const char*>(M + off), cl, cols);
+    }
+    if (cl + 4 > cols) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { edge_fix<1>(g[i].v, cl, cols); edge_fix<1>(e[i].v, cl, cols); }
+    }
+  };
+  auto block = [&](const int c, Pk<4>* g, Pk<4>* e) {
+    const int cl = c + c4;
+    if constexpr (NEEDG) {
+      float qb[KH];
+      const int col = c + li;
+      if (col < col1) {
+        const float4* src = reinterpret_cast<const float4*>(Q + (size_t)col * RP + KH * h);
+#pragma unroll
+        for (int t = 0; t < KH / 4; ++t) {
+          const float4 x = src[t];
+          qb[4 * t] = x.x; qb[4 * t + 1] = x.y; qb[4 * t + 2] = x.z; qb[4 * t + 3] = x.w;
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < KH; ++k) qb[k] = 0.0f;
+      }
+      v16f gh;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) gh[i] = 0.0f;
+#pragma unroll
+      for (int k = 0; k < KH; ++k) gh = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[k], qb[k], gh, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) lds[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP32 + li] = gh[v];
+      wave_lds_fence();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float4 t = *reinterpret_cast<const float4*>(lds + (8 * i + sr) * kLP32 + c4);
+        e[i].v[0] -= t.x; e[i].v[1] -= t.y; e[i].v[2] -= t.z; e[i].v[3] -= t.w;
+      }
+      wave_lds_fence();
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int rr = 8 * i + sr;
+      Pk<4> m;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) m.v[v] = g[i].v[v] + e[i].v[v];
+      if (rr < nrows)
+        stgroup<false>(reinterpret_cast<char*>(M + (size_t)(row0 + rr) * cols), (unsigned)cl * 4u, cols - cl, m);
+      *reinterpret_cast<float4*>(lds + rr * kLP32 + c4) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
+    }
+    // the Q slice of the P product is fetched only now: the registers of the G-hat operands are free again
+    float bq[16];
+#pragma unroll
+    for (int kk = 0; kk < 16; ++kk) {
+      const int col = c + 16 * h + kk;
+      bq[kk] = col < col1 ? Q[(size_t)col * RP + li] : 0.0f;
+    }
+    wave_lds_fence();
+    {
+      const float4 a0 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h);
+      const float4 a1 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 4);
+      const float4 a2 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 8);
+      const float4 a3 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 12);
+      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, bq[0], accP, 0, 0, 0);
+      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, bq[4], accP2, 0, 0, 0);
+      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, bq[1], accP, 0, 0, 0);
+      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, bq[5], accP2, 0, 0, 0);
+      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, bq[2], accP, 0, 0, 0);
+      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, bq[6], accP2, 0, 0, 0);
+      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, bq[3], accP, 0, 0, 0);
+      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, bq[7], accP2, 0, 0, 0);
+      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.x, bq[8], accP, 0, 0, 0);
+      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.x, bq[12], accP2, 0, 0, 0);
+      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.y, bq[9], accP, 0, 0, 0);
+      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.y, bq[13], accP2, 0, 0, 0);
+      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.z, bq[10], accP, 0, 0, 0);
+      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.z, bq[14], accP2, 0, 0, 0);
+      accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.w, bq[11], accP, 0, 0, 0);
+      accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.w, bq[15], accP2, 0, 0, 0);
+    }
+    wave_lds_fence();
+  };
+  // Interior blocks (all 32 rows and 32 columns exist) run without bounds tests, as a software
+  // pipeline inside the wavefront: the next block's G and E are requested before this block's matrix
+  // instructions, and the next block's G-hat operand from Q as soon as this block's G-hat is done.
+  // Requests complete in order, so everything a block waits for is requested before the prefetch.
+  int c = col0 + 32 * wave;
+  if (nrows == 32 && c + 32 <= col1 && cols < (1 << 26)) {   // (byte offsets within 8 rows fit 32 bits)
+    const int last = c + ((col1 - 32 - c) / 256) * 256;   // this wavefront's last whole block
+    Pk<4> g[4], e[4], gn[4], en[4];
+    float qb[KH], bq[16];
+    // Addresses are a wave-uniform base (scalar registers, advanced by scalar adds) plus a byte
+    // offset per lane that does not change from block to block.
+    const unsigned goff = (unsigned)(sr * cols + c4) * 4u;      // lane's place in a slab of 8 rows
+    const unsigned qboff = (unsigned)(li * RP + KH * h) * 4u;   // ... in 32 rows of Q (G-hat operand)
+    const unsigned bqoff = (unsigned)(16 * h * RP + li) * 4u;   // ... in 32 rows of Q (P operand)
+    auto fetch_ge = [&](const int cb, Pk<4>* gg, Pk<4>* ee) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const size_t off = (size_t)(row0 + 8 * i) * cols + cb;
+        if constexpr (GB16) {   // kept packed (two registers) until the block is worked on
+          const Pk<2> t = ldrow_bf16_packed<LQSGD_NT_G != 0>(grad_row<GB16>(G, off), goff);
+          gg[i].v[0] = t.v[0]; gg[i].v[1] = t.v[1];
+        } else {
+          gg[i] = ldgrad<LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), goff);
+        }
+        ee[i] = ldrow<false>(reinterpret_cast<const char*>(M + off), goff);
+      }
+    };
+    auto fetch_qb = [&](const int cb) {
+      const char* base = reinterpret_cast<const char*>(Q + (size_t)cb * RP);
+#pragma unroll
+      for (int t = 0; t < KH / 4; ++t) {
+        const Pk<4> x = ldrow<false>(base + 16 * t, qboff);
+        qb[4 * t] = x.v[0]; qb[4 * t + 1] = x.v[1]; qb[4 * t + 2] = x.v[2]; qb[4 * t + 3] = x.v[3];
+      }
+    };
+    fetch_ge(c, g, e);
+    if constexpr (NEEDG) fetch_qb(c);
+    // one block; MORE: another whole block follows (a constant, so that no branch joins two
+    // request histories and every wait counts exactly)
+    auto step = [&](auto more_tag, const int c, Pk<4>* g, Pk<4>* e, Pk<4>* gn, Pk<4>* en) {
+      constexpr bool more = decltype(more_tag)::value;
+      {
+        const char* base = reinterpret_cast<const char*>(Q + (size_t)c * RP);
+#pragma unroll
+        for (int kk = 0; kk < 16; ++kk) bq[kk] = *gptr<float>(base + kk * RP * 4 + bqoff);
+      }
+      if constexpr (more) fetch_ge(c + 256, gn, en);
+      __builtin_amdgcn_sched_barrier(0);   // the requests above stay ahead of the arithmetic below
+      if constexpr (NEEDG) {
+        v16f gh;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) gh[i] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < KH; ++k) gh = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[k], qb[k], gh, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (more) fetch_qb(c + 256);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) lds[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP32 + li] = gh[v];
+        wave_lds_fence();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float4 t = *reinterpret_cast<const float4*>(lds + (8 * i + sr) * kLP32 + c4);
+          e[i].v[0] -= t.x; e[i].v[1] -= t.y; e[i].v[2] -= t.z; e[i].v[3] -= t.w;
+        }
+        wave_lds_fence();
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int rr = 8 * i + sr;
+        Pk<4> m, gv = g[i];
+        if constexpr (GB16) gv = unpack_bf16(g[i].v[0], g[i].v[1]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) m.v[v] = gv.v[v] + e[i].v[v];
+        strow<false>(reinterpret_cast<char*>(M + (size_t)(row0 + 8 * i) * cols + c), goff, m);
+        *reinterpret_cast<float4*>(lds + rr * kLP32 + c4) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
+      }
+      wave_lds_fence();
+      {
+        const float4 a0 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h);
+        const float4 a1 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 4);
+        const float4 a2 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 8);
+        const float4 a3 = *reinterpret_cast<const float4*>(lds + li * kLP32 + 16 * h + 12);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.x, bq[0], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.x, bq[4], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.y, bq[1], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.y, bq[5], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.z, bq[2], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.z, bq[6], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a0.w, bq[3], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1.w, bq[7], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.x, bq[8], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.x, bq[12], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.y, bq[9], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.y, bq[13], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.z, bq[10], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.z, bq[14], accP2, 0, 0, 0);
+        accP = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.w, bq[11], accP, 0, 0, 0);
+        accP2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a3.w, bq[15], accP2, 0, 0, 0);
+      }
+      wave_lds_fence();
+    };
+    // two blocks per trip, the two register sets changing roles (no copies, so nothing waits for
+    // a prefetch before its values are needed)
+    for (; c + 256 < last; c += 512) {
+      step(std::true_type{}, c, g, e, gn, en);
+      step(std::true_type{}, c + 256, gn, en, g, e);
+    }
+    if (c < last) {
+      step(std::true_type{}, c, g, e, gn, en);
+      step(std::false_type{}, c + 256, gn, en, g, e);
+      c += 512;
+    } else {
+      step(std::false_type{}, c, g, e, gn, en);
+      c += 256;
+    }
+  }
+  for (; c < col1; c += 256) {
+    Pk<4> g[4], e[4];
+    fetch(c, g, e);
+    block(c, g, e);
+  }
+  // P partial of the item = sum over the eight wavefronts, added in wavefront order
+#pragma unroll
+  for (int v = 0; v < 16; ++v) lds[(8 * (v >> 2) + 4 * h + (v & 3)) * kLP32 + li] = accP[v] + accP2[v];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int e = (int)threadIdx.x + 512 * i;
+    const int rr = e >> 5, k = e & 31;
+    float t = lds_all[0][rr * kLP32 + k];
+#pragma unroll
+    for (int wv = 1; wv < 8; ++wv) t += lds_all[wv][rr * kLP32 + k];
+    if (rr < nrows && k < r) Pp[(size_t)(row0 + rr) * r + k] = t;
+  }
+}
+
+template <int MODE, bool GB16>
+__global__ __launch_bounds__(512, 2) void mfma_sweep32_kernel(DevArgs a, const Tile* __restrict__ tiles, int ntiles, int reverse) {
+  __shared__ __attribute__((aligned(16))) float lds_all[8][32 * kLP32];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & (kWave - 1);
+  if (blockIdx.x == 0) zero_absmax_cells(a, 512);
+  const Tile tl = tiles[reverse ? ntiles - 1 - (int)blockIdx.x : (int)blockIdx.x];   // one item per workgroup
+  const int layer = tl.lw / a.W, worker = tl.lw - layer * a.W;
+  const LayerDesc& ld = a.layers[layer];
+  const float* G = a.grads[(size_t)worker * a.n_all + ld.gidx];
+  float* M = a.E + (size_t)worker * a.m_stride + ld.m_off;
+  float* Pp = a.Ppart + (size_t)worker * a.ppart_stride + ld.ppart_off + (size_t)tl.aux * ld.np_pad;
+  const int col0 = tl.aux * ld.segw;
+  const int col1 = min(ld.cols, col0 + ld.segw);
+  if (ld.kind == kOneColumnPerLane) {            // four of the item's rows per wavefront
+    const int nr = min(4, tl.nrows - 4 * wave);
+    if (nr > 0)
+      narrow_rows<32, 4, true, MODE == kMAddFused, true, false, GB16>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, nullptr,
+                                                                      ld.cols, ld.r, tl.row0 + 4 * wave, nr, lane, 0, 0.0f);
+    return;
+  }
+  mfma_tile32<MODE, GB16>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ld.cols, ld.r, tl.row0, tl.nrows,
+                                   col0, col1, lane, wave, lds_all);
 }
 
 // Wavefronts per SIMD the register allocation aims for: two at rank pad 16, one from rank pad 32 on, where two would spill.
@@ -3838,6 +4134,14 @@ void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int two, i
       }
 #undef LQSGD_LAUNCH_MP
       note_kernel("mfma_pair_kernel<%d, %s, %s>", MODE, tf(a.g_bf16), tf(nt));
+      return;
+    }
+  }
+  if constexpr (RP == 32) {
+    if (a.by_blocks > (MODE == kMAddFused ? 1 : 0)) {
+      if (a.g_bf16) mfma_sweep32_kernel<MODE, true><<<grid, dim3(512), 0, s>>>(a, tiles, ntiles, reverse);
+      else mfma_sweep32_kernel<MODE, false><<<grid, dim3(512), 0, s>>>(a, tiles, ntiles, reverse);
+      note_kernel("mfma_sweep32_kernel<%d, %s>", MODE, tf(a.g_bf16));
       return;
     }
   }

@@ -512,6 +512,55 @@ def test_sweep_zero_by_blocks_in_both_schedules():
     _schedules(layers, 16, 3, "mfma_sweep_kernel<16, 1")
 
 
+# (At most 64 rows and 1024 columns: one row block and one segment, however long the list.)
+EVEN = [(64, 256), (64, 512), (32, 1024), (64, 768), (40, 700)]
+UNEVEN = [(64, 320), (60, 640), (33, 1020), (25, 988), (1, 1024), (63, 300), (64, 128), (31, 255), (40, 40), (37, 77), (5, 61), (64, 572)]
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("layers,first,later", [(EVEN, "sweep32", "round"), (UNEVEN, "sweep32", "sweep32"),
+                                                ([(64, 64), (33, 100), (57, 192), (31, 129), (60, 68)], "sweep32", "sweep32")])
+def test_sweep_zero_of_a_cu_an_item_adds_like_sweep_zero_by_rounds(layers, first, later, bf16):
+    """Rank pad 32: lists of at most 256 items go by 32 x 32 blocks per wavefront, with the deferred residual if they are uneven.
+    The same layers in a long list, by rounds: the same bits."""
+    import torch
+    W, rank = 3, 27
+    _say("case: blocks and rounds at rank pad 32", layers, bf16)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    Q0 = [torch.randn((c, min(rank, n, c)), generator=gen, device="cuda").cpu().numpy() for n, c in layers]
+    Gs = [[[(torch.randn(s, generator=gen, device="cuda") * 1e-3).to(dt) for s in layers] for _ in range(W)] for _ in range(3)]
+    more, got = (64, 512), []
+    for longer in (0, 48):
+        ls = layers + [more] * longer
+        comp = B.Compressor(B.layer_list(ls, ()), rank, 8, 8, W, 255.0, B.FLAG_BF16_GRADIENTS if bf16 else 0)
+        for l, (n, c) in enumerate(ls):
+            comp.set_q(l, Q0[l] if l < len(layers) else torch.randn((c, rank), generator=gen, device="cuda").cpu().numpy())
+        out, res = [torch.zeros(s, device="cuda") for s in ls], []
+        fill = [(torch.randn(more, generator=gen, device="cuda") * 1e-3).to(dt) for _ in range(longer)]
+        for it, G in enumerate(Gs):
+            comp.step([w + fill for w in G], out)
+            res += [o.clone() for o in out[:len(layers)]]
+            kernel = "round" if longer else first if it == 0 else later
+            assert comp.launched_kernel(0).startswith("mfma_%s_kernel<" % kernel), comp.launched_kernel(0)
+        res += [torch.from_numpy(comp.get_state(l, w)[0]) for l in range(len(layers)) for w in range(W)]
+        res += [torch.from_numpy(comp.get_factor(B.FACTOR_P_PRE, l, w)) for l in range(len(layers)) for w in range(W)]
+        comp.close()
+        got.append(res)
+    for i, (a, b) in enumerate(zip(*got)):
+        assert torch.isfinite(a).all() and torch.equal(a, b), "tensor %d" % i
+
+
+@pytest.mark.parametrize("layers,kernel", [([(512, 320)] * 9 + [(70, 96)], "mfma_round_kernel<32, 1"),
+                                           (UNEVEN + [(161, 2305)], "mfma_sweep32_kernel<1"),
+                                           (UNEVEN + [(161, 2305), (3000, 512)], "mfma_round_kernel<32, 1")])
+def test_sweep_zero_by_rounds_and_blocks_at_rank_pad_32_in_both_schedules(layers, kernel):
+    """Also a long list whose first iterations alone go by blocks."""
+    _say("case: rank pad 32, deferred and eager", layers)
+    _schedules(layers, 32, 3, kernel)
+
+
 # Slabs of W workers in MB (2^20 bytes): the store policy of sweep 0 turns on them and on how the elements' rows start.
 @pytest.mark.parametrize("layers,rank,first,later", [
     ([(2048, 2048)] * 9, 16, "false>", "false>"),                          # 288 MB
