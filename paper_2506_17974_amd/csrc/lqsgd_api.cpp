@@ -503,26 +503,41 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
       if (d.cols % 64 == 0 && d.cols <= 1024 && (few || (some && slab_bytes >= ((int64_t)112 << 20)))) blocks += (int64_t)d.rows * d.cols;
     }
     a.by_blocks = p.RP == 16 && !a.g_bf16 && !a.nt_fused && 4 * blocks >= p.matrix_elements ? 1 : 0;
-    // Rank pad 32: 32 x 32 blocks per wavefront (1: without a deferred residual, 2: with it, too) where there is a CU an item, with
-    // the residual only if the longest items are uneven, short ones of many rounds or last rounds at most half full, or one narrow
-    // round (figures at mfma_sweep32_kernel; beyond a CU an item, r = 32, W = 8, rounds / blocks: 512 items, 8 x (256 x 1024) 43 / 51,
-    // in a first iteration 43 / 43, 384 items, 24 x (40 x 1024) 37 / 44 and 35 / 35).  Of any length, first iterations only: rows of a
-    // whole round and at most a quarter more that start on lines of 128 bytes (16 x (512 x 288) 66 / 60, 24 x (512 x 320) 96 / 92; but
-    // 16 x (512 x 304) 68 / 74, 16 x (512 x 384) 71 / 72, 8 x (512 x 576) 52 / 53).
-    if (p.RP == 32 && !a.nt_store) {
-      bool wide = false, uneven = false;
-      int64_t quarter = 0;
+    // Lists that have a CU an item take as long as their longest item (figures also at mfma_sweep32_kernel; a step and a first
+    // iteration's sweep 0, W = 4, by rounds / by blocks).
+    if (p.tilesA.size() <= 256 && p.RP <= 32 && !a.nt_fused) {
+      bool half = false, whole = false, low = false, wide = false, segments = false;
       for (const LayerDesc& d : p.layers) {
+        const int last = d.cols > 256 ? d.cols % 256 : 0;
+        half = half || (last > 0 && last <= 128);
+        whole = whole || (last > 0 && last <= 128 && last % 64 == 0);
+        low = low || (d.cols > 768 && d.rows % 32 != 0);
         wide = wide || d.cols > 192;
-        uneven = uneven || (d.cols > 768 && d.rows % 32 != 0) || (d.cols > 256 && d.cols % 256 != 0 && d.cols % 256 <= 128);
-        if (d.cols > 256 && d.cols <= 320 && d.cols % 32 == 0) quarter += (int64_t)d.rows * d.cols;
+        segments = segments || d.cols >= 1024;
       }
-      if (p.tilesA.size() <= 256) a.by_blocks = uneven || !wide ? 2 : 1;
-      else if (!a.g_bf16 && 2 * quarter >= p.matrix_elements) a.by_blocks = 1;
+      // Rank pad 32, 32 x 32 blocks per wavefront: always without a deferred residual (1).  With it, too (2), where rounds would
+      // be cut short: items of fewer than 32 rows and many columns, last rounds at most half full unless some layer has longer
+      // rows than that (4 x (256 x 1088) 87.5 / 88.9, 4 x (256 x 320) beside 2 x (256 x 1024) 86.5 / 89.3), one narrow round.  (More
+      // items, r = 32, W = 8, sweep 0: 512, 8 x (256 x 1024) 43 / 51, in a first iteration 43 / 43; 384, 24 x (40 x 1024) 37 / 44 and
+      // 35 / 35.)
+      if (p.RP == 32) a.by_blocks = low || !wide || (half && !segments) ? 2 : 1;
+      // Rank pad 16, 64-column blocks: also without a deferred residual (2) where last rounds are at most half full (4 x (256 x 576)
+      // 64.7 / 63.1 and 15.9 / 14.7, 4 x (128 x 576) 54.3 / 52.5 and 14.9 / 13.3, 4 x (256 x 640) 63.4 / 62.6 and 16.4 / 15.1; longer rows
+      // 4 x (256 x 1088) 63.9 / 66.6, 4 x (256 x 1920) 72.9 / 74.9).
+      if (p.RP == 16 && !a.g_bf16 && whole && !segments) a.by_blocks = 2;
+    }
+    // Rank pad 32, lists of any length, first iterations only: rows of a whole round and at most a quarter more that start on lines
+    // of 128 bytes (sweep 0, W = 8, 16 x (512 x 288) 66 / 60, 24 x (512 x 320) 96 / 92; but 16 x (512 x 304) 68 / 74, 16 x (512 x 384)
+    // 71 / 72, 8 x (512 x 576) 52 / 53).
+    if (p.RP == 32 && !a.g_bf16 && !a.nt_store && !a.by_blocks) {
+      int64_t quarter = 0;
+      for (const LayerDesc& d : p.layers)
+        if (d.cols > 256 && d.cols <= 320 && d.cols % 32 == 0) quarter += (int64_t)d.rows * d.cols;
+      if (2 * quarter >= p.matrix_elements) a.by_blocks = 1;
     }
 #ifdef LQSGD_TUNING     // a tuning build can force the choice and switch the alternating sweep direction off
     if (const char* f = std::getenv("LQSGD_BY_BLOCKS"))
-      a.by_blocks = p.RP == 16 && !a.g_bf16 ? f[0] == '1' : p.RP == 32 && !a.nt_store ? f[0] - '0' : 0;
+      a.by_blocks = (p.RP == 16 && !a.g_bf16) || p.RP == 32 ? (a.nt_store ? 0 : f[0] - '0') : 0;
     if (const char* f = std::getenv("LQSGD_NT_STORE")) {
       if (f[0] == '1') a.nt_store = a.nt_fused = 1;
       if (f[0] == '2') a.nt_store = a.nt_fused = 0;

@@ -51,8 +51,8 @@ struct DevArgs {
   int32_t update;              // G-hat outputs are parameters to update: w <- w - eta G-hat
   int32_t nt_store;            // sweep 0 streams the residual slabs: non-temporal loads of E and stores of M (the launchers pick the kernels built that way)
   int32_t nt_fused;            // the same for sweep 0 with the deferred residual on the matrix cores
-  int32_t by_blocks;           // sweep 0 by blocks per wavefront, not by rounds.  Rank pad 16: 1 with the deferred residual, of 64
-                               // columns.  Rank pad 32, of 32 columns: 1 without it, 2 with and without
+  int32_t by_blocks;           // sweep 0 by blocks per wavefront, not by rounds.  Rank pad 16, of 64 columns: 1 with the deferred
+                               // residual, 2 with and without.  Rank pad 32, of 32 columns: 1 without it, 2 with and without
   float eta;
 };
 

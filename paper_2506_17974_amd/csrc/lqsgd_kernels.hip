@@ -4145,8 +4145,8 @@ void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int two, i
       return;
     }
   }
-  if constexpr (RP == 16 && MODE == kMAddFused) {
-    if (a.by_blocks) {
+  if constexpr (RP == 16) {
+    if (a.by_blocks > (MODE == kMAddFused ? 0 : 1)) {
       mfma_sweep_kernel<RP, MODE><<<grid, dim3(256), 0, s>>>(a, tiles, ntiles, two, reverse);
       note_kernel("mfma_sweep_kernel<%d, %d, false, false>", RP, MODE);
       return;

@@ -519,6 +519,8 @@ UNEVEN = [(64, 320), (60, 640), (33, 1020), (25, 988), (1, 1024), (63, 300), (64
 
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("layers,first,later", [(EVEN, "sweep32", "round"), (UNEVEN, "sweep32", "sweep32"),
+                                                ([(64, 320), (60, 640), (33, 300), (64, 576)], "sweep32", "sweep32"),
+                                                ([(64, 320), (64, 1024)], "sweep32", "round"),
                                                 ([(64, 64), (33, 100), (57, 192), (31, 129), (60, 68)], "sweep32", "sweep32")])
 def test_sweep_zero_of_a_cu_an_item_adds_like_sweep_zero_by_rounds(layers, first, later, bf16):
     """Rank pad 32: lists of at most 256 items go by 32 x 32 blocks per wavefront, with the deferred residual if they are uneven.
