@@ -2511,7 +2511,7 @@ __global__ __launch_bounds__(512, 2) void mfma_pair_kernel(DevArgs a, const Tile
 // sets as small as 4 x 1024^2, W = 2 29 / 27.  At r = 16, with 32 x 64 blocks per wavefront / now: ResNet-18 set 209 / 201, at r = 12
 // with bfloat16 gradients 218 / 162; 8192^2 1091 / 1025; 4 x (3000 x 5000) 1283 / 1246; ragged set (64 x 27 .. 1000 x 2049), r = 12,
 // W = 4 52 / 42; 4 x 1024^2, W = 2 28.6 / 24.7.
-// Lists that have a CU an item lost and are no longer taken here (mfma_sweep32_kernel).
+// Lists that have a CU an item lost in first iterations and where rounds are cut short, and go by blocks there (mfma_sweep32_kernel).
 // Sets measured that lost and still do, a step: r = 32 16 x (512 x 576) 230 / 235, 24 x (512 x 320) 226 / 229, r = 16 8 x (512 x 2304)
 // 298 / 303 (all in sweep 1 behind it); a first iteration's sweep 0 at r = 32: 16 x (512 x 2048) 318 / 334
 // (ResNet-18 set 214 / 211, at r = 16 194 / 191).
@@ -2918,7 +2918,7 @@ __global__ __launch_bounds__(256, RP == 16 && MODE == kMAdd ? 3 : 2) void mfma_r
 // Sweep 0, r = 32, by rounds / here, us.  Deferred residual: 4 x (256 x 320), W = 4 16.7 / 12.9; 8 x (256 x 576), W = 4 23.0 / 19.3;
 // 16 x (64 x 128), W = 4 9.9 / 8.2; 4 x (31 x 2048), W = 4 25.4 / 24.1; 16 x (20 x 2000), W = 8 32.1 / 27.7; 1000 x 1024, W = 4
 // 27.2 / 24.5.  First iterations: 8 x (256 x 320), W = 4 15.7 / 11.7; 8 x (256 x 576), W = 4 20.4 / 16.3; 4 x (256 x 1024), W = 4
-// 21.0 / 19.4, at W = 8 28.6 / 25.5.  Where the rounds are whole or nearly, they win with the deferred residual (4 x (256 x 1024), W = 4
+// 21.0 / 19.4; 8 x (256 x 1024), W = 4 28.6 / 25.5.  Where the rounds are whole or nearly, they win with the deferred residual (4 x (256 x 1024), W = 4
 // 22.6 / 25.0; 2 x (64 x 988), W = 4 21.6 / 22.8).
 // Row layout: 8 lanes = 128 contiguous bytes of a row, 8 rows per instruction.
 // ---------------------------------------------------------------------------
