@@ -776,21 +776,16 @@ __global__ __launch_bounds__(BS) void orth_reg_kernel(DevArgs a) {
 // holds, and the order in which it goes through them, follow that tree: a lane
 // holds the LL threads of one of its subtrees, in bit-reversed order, so that
 // neighbouring partial sums always meet first.
-// PAIRS: wavefronts added as (0 + 1) + (2 + 3) instead of one after the other.
-// Before and after, microseconds (rows on lanes in the registers, or in memory
-// where they did not fit; columns on lanes): ResNet-18 set 10.2 -> 9.2 at r = 4,
-// 13.5 -> 12.1 at r = 7, 33 -> 20.6 at r = 16, 61 -> 43 at r = 32, 165 -> 95 at
-// r = 50; 1000 rows 421 -> 43 at r = 20, 1400 -> 62 at r = 32, 5200 -> 227 at
-// r = 64; 130 factors of 10000 rows at r = 4 36 -> 27.  (Sums in any order, with
-// 1 / sqrt from the hardware's estimate and the scaled column folded into the
-// factor f, are 3 to 10 % faster.)  More wavefronts with fewer rows each do
-// better up to 16 (r = 32: 38.6 us with 16 x 16 rows, 40.6 with 8 x 32); lane
-// reads instead of LDS for the column cost more (r = 50: 106 against 96 us).
+// It serves heights from 513 rows on at rank pad 4 and from 2049 on at rank pad 8
+// (130 factors of 10000 rows at r = 4: 27 us, rows on lanes 36), and up to 64
+// rows at rank pad 32 where a set has more factors than CUs; elsewhere whole
+// columns per wavefront (orth_colwave_kernel) are faster: their lanes end with
+// their columns, here half of them work on columns that are done.
 // ---------------------------------------------------------------------------
 constexpr int bit_reverse(int x, int bits) { return bits == 0 ? 0 : ((x & 1) << (bits - 1)) | bit_reverse(x >> 1, bits - 1); }
 constexpr int trailing_zeros(int x) { return (x & 1) ? 0 : 1 + trailing_zeros(x >> 1); }
 
-template <int C, int WV, int NI, int NW, bool PAIRS>
+template <int C, int WV, int NI, int NW>
 __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
   constexpr int G = kWave / C;
   constexpr int SUB = NW / WV;                   // wavefronts here per 64 threads of the tree
@@ -798,7 +793,7 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
   constexpr int LL = kWave / SP;                 // threads of a lane's subtree
   constexpr int RPT = LL * NI;                   // NI rows each
   constexpr int STEP = WV > 4 ? kWave * WV : 256;
-  static_assert(NW % WV == 0 && SP <= kWave && RPT % 4 == 0 && (WV >= 4 || NI == 1) && (!PAIRS || WV == 4), "");
+  static_assert(NW % WV == 0 && SP <= kWave && RPT % 4 == 0 && (WV >= 4 || NI == 1), "");
   constexpr int PS = NW + 4;                     // pitch of a column's partials: 16-byte reads of 16 lanes hit all banks once
   __shared__ __attribute__((aligned(16))) float bc[NW][G][RPT];
   __shared__ __attribute__((aligned(16))) float part[2][C][PS];
@@ -813,8 +808,7 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
   float* pre = a.Ppre + (size_t)worker * a.p_stride + ld.p_off;
   float* orth = a.Porth + (size_t)worker * a.p_stride + ld.p_off;
   int row0 = (wave / SUB) * kWave + g * SUB + wave % SUB;
-  // Many rows per lane: the optimiser would keep all their addresses in registers from one use to the next, and spill
-  // (1000 rows at r = 64 255 -> 227 us, 1700 at r = 32 142 -> 106); few rows: it may (r = 7 14.0 -> 12.1 us).
+  // Many rows per lane: the optimiser would keep all their addresses in registers from one use to the next, and spill.
   auto hide_row = [&]() __attribute__((always_inline)) { if constexpr (RPT > 32) asm volatile("" : "+v"(row0)); };
   // row of the lane's value i, from row0
   auto row_of = [](int i) __attribute__((always_inline)) { return bit_reverse(i / NI, log2c(LL)) * SP + (i % NI) * STEP; };
@@ -903,13 +897,9 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
       for (int h = SUB / 2; h >= 1; h /= 2)
 #pragma unroll
         for (int i = 0; i < h; ++i) pw[wv * SUB + i] += pw[wv * SUB + i + h];
-    if constexpr (PAIRS) {
-      s = (pw[0] + pw[SUB]) + (pw[2 * SUB] + pw[3 * SUB]);
-    } else {
-      s = pw[0];
+    s = pw[0];
 #pragma unroll
-      for (int wv = 1; wv < WV; ++wv) s += pw[wv * SUB];
-    }
+    for (int wv = 1; wv < WV; ++wv) s += pw[wv * SUB];
     const float nrm2 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(s), j));
     const float inv = (nrm2 > FLT_MIN) ? 1.0f / sqrtf(nrm2) : 0.0f;
     const float f = -(s * inv);
@@ -945,6 +935,280 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
       orth[row * r + k] = v[i];
       if (copy) copy[row * C + k] = v[i];
       mx = fmaxf(mx, fabsf(v[i]));
+    }
+  }
+  mx = wave_max(mx);
+  if (lane == 0) redmax[wave] = mx;
+  __syncthreads();
+  if (tid == 0 && !a.orth_shared) {
+    float m = redmax[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m = fmaxf(m, redmax[w]);
+    a.scaleP[(size_t)worker * a.L + layer] = m;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// orth, one workgroup per (layer, worker), whole columns to a wavefront: its
+// lanes hold the rows (lane l: rows l, l + 64, ..), and it owns blocks of BC
+// neighbouring columns.  A finished column goes to the other wavefronts through
+// LDS, where each column has a place of its own or, where the factor is larger
+// than LDS, one in a ring; a wavefront waits for a column by its number, takes
+// its products with its own later columns and removes it from them, and when
+// its next block is complete it finishes that block at once.  There is no
+// barrier between columns; the inverse of a column's norm follows the column,
+// so that products with it are taken while it is computed.
+//
+// What bounds it: about 40 vector instructions for each pair of columns on one
+// CU (30 of 47 us at 512 rows, r = 50), then the chain from column to column,
+// a trip through LDS for every BC of them.  Gram-Schmidt of a set, microseconds
+// before (columns on lanes, orth_col_kernel) and now: ResNet-18 set, W = 8,
+// r = 7 12.1 -> 10.2, r = 16 20.4 -> 14.1, r = 32 40 -> 26, r = 50 94 -> 49;
+// ragged set, r = 20 44 -> 23; 2 x (1000 x 640), W = 4, r = 50 179 -> 61;
+// 2 x (1700 x 640), r = 20 73 -> 33; 640 factors of 250 rows at r = 64
+// 210 -> 121.  (8 or 4 wavefronts instead of 16 at r = 32: 31 and 39 us; blocks
+// of 1 and 4 columns at r = 50 56 and 53; pauses in the waiting loops, or a
+// higher priority for the wavefront next in line while it waits: no gain.)
+//
+// The sums are those of orth_col_kernel, to the last bit: c[w] is the chain of
+// rows l + 64 w, + 256, .., the reduction adds lanes 32, 16, .. 1 apart, the
+// NB wavefronts of that order come last, one after the other or in pairs.
+// Waits end: a column waits only for columns before it, its wavefront publishes
+// in order, and all wavefronts of a workgroup are resident.
+// ---------------------------------------------------------------------------
+// Sum over the lanes of each c[w], then over w.
+template <int NB, bool PAIRS>
+__device__ __forceinline__ float column_total(const float (&c)[NB]) {
+  auto swap32 = [](float x, float y) __attribute__((always_inline)) {
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+  };
+  auto swap16 = [](float x, float y) __attribute__((always_inline)) {
+    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+  };
+  float x;
+  if constexpr (NB == 4) {
+    x = swap16(swap32(c[0], c[1]), swap32(c[2], c[3]));        // rows of 16 lanes: c[0], c[2], c[1], c[3]
+  } else {
+    const float u = NB == 2 ? swap32(c[0], c[NB - 1]) : swap32(c[0], c[0]);
+    x = swap16(u, u);
+  }
+  // each step leaves a row of 16 lanes periodic, so that a rotation by half a period is the partner's value
+#define LQSGD_ROR_ADD(N) \
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x120 + (N), 0xf, 0xf, true))
+  LQSGD_ROR_ADD(8);
+  LQSGD_ROR_ADD(4);
+  LQSGD_ROR_ADD(2);
+  LQSGD_ROR_ADD(1);
+#undef LQSGD_ROR_ADD
+  auto at = [&](int l) __attribute__((always_inline)) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), l)); };
+  if constexpr (NB == 4) {
+    return PAIRS ? (at(0) + at(32)) + (at(16) + at(48)) : ((at(0) + at(32)) + at(16)) + at(48);
+  } else {
+    return NB == 2 ? at(0) + at(32) : at(0);
+  }
+}
+
+// C: rank pad.  Up to 64 NB rows (NI = 1) or 256 NI (NB = 4).  BC: neighbouring columns of a wavefront.  NIC: 256-row blocks of the
+// factor that go through LDS at once on their way in and out.  SLOTS: columns in LDS (C: each its own).
+template <int C, int NB, int NI, int NW, int BC, int NIC, int SLOTS, bool PAIRS>
+__global__ __launch_bounds__(64 * NW) void orth_colwave_kernel(DevArgs a) {
+  constexpr int NT = 64 * NW, CPW = C / NW, RPT = NB * NI, BR = kWave * NB;      // BR: rows of a block
+  constexpr int CPIN = NIC * BR + 1, CP = NI * BR;                           // pitches of a column, floats
+  constexpr int POOL = C * CPIN > SLOTS * CP ? C * CPIN : SLOTS * CP;
+  static_assert(CPW >= 1 && CPW % BC == 0 && NI % NIC == 0 && (NI == 1 || NB == 4) && (SLOTS == C || (SLOTS % 2 == 0 && BC <= SLOTS / 2)), "");
+  __shared__ __attribute__((aligned(16))) float pool[POOL];
+  __shared__ float s_inv[C];
+  __shared__ int ready;                          // columns published
+  __shared__ float redmax[NW];
+  const int lw = blockIdx.x;
+  const int layer = lw / a.W, worker = lw - layer * a.W;
+  const LayerDesc& ld = a.layers[layer];
+  const int rows = ld.rows, r = ld.r, nseg = a.orth_shared ? 1 : ld.nseg;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float* Pp = a.Ppart + (size_t)worker * a.ppart_stride + (a.orth_shared ? ld.p_off : ld.ppart_off);
+  float* pre = a.Ppre + (size_t)worker * a.p_stride + ld.p_off;
+  float* orth = a.Porth + (size_t)worker * a.p_stride + ld.p_off;
+  auto col_of = [&](int s) __attribute__((always_inline)) { return (s / BC * NW + wave) * BC + s % BC; };
+  const unsigned magic = r > 1 ? 0xffffffffu / (unsigned)r + 1u : 0u;
+  // row and column of element e of the factor (e < 2^17, r <= 64: exact)
+  auto row_of = [&](int e) __attribute__((always_inline)) { return r > 1 ? (int)__umulhi((unsigned)e, magic) : e; };
+
+  // ---- the factor: planes added in memory order, columns handed out through LDS
+  constexpr int F4 = (NIC * BR * C / 4 + NT - 1) / NT;
+  float v[CPW][RPT];
+  if (tid == 0) ready = 0;
+  if (tid < C) s_inv[tid] = -1.0f;               // (no norm's inverse)
+#pragma unroll
+  for (int ch = 0; ch < NI / NIC; ++ch) {
+    const int row0 = ch * NIC * BR, el0 = row0 * r, el1 = min(rows, row0 + NIC * BR) * r;   // el0 is a multiple of 4
+    if (ch > 0) __syncthreads();
+    if (el0 < el1) {
+      float4 acc[F4], x[F4];
+#pragma unroll
+      for (int i = 0; i < F4; ++i) acc[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      for (int s = 0; s < nseg; ++s) {
+        const float* src = Pp + (size_t)s * ld.np_pad;
+#pragma unroll
+        for (int i = 0; i < F4; ++i) {
+          const int e = el0 + 4 * (tid + NT * i);
+          x[i] = *reinterpret_cast<const float4*>(src + (e < el1 ? e : 0));
+        }
+#pragma unroll
+        for (int i = 0; i < F4; ++i) { acc[i].x += x[i].x; acc[i].y += x[i].y; acc[i].z += x[i].z; acc[i].w += x[i].w; }
+      }
+#pragma unroll
+      for (int i = 0; i < F4; ++i) {
+        const int e = el0 + 4 * (tid + NT * i);
+        if (e < el1) {                           // (what lies beyond goes to rows that are not the factor's and count as zeros)
+          const float t[4] = {acc[i].x, acc[i].y, acc[i].z, acc[i].w};
+          int row = row_of(e), k = e - row * r;
+          row -= row0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            pool[k * CPIN + row] = t[q];
+            if (++k == r) { k = 0; ++row; }
+          }
+          if (e + 4 <= el1) *reinterpret_cast<float4*>(pre + e) = acc[i];
+          else
+            for (int q = 0; q < el1 - e; ++q) pre[e + q] = t[q];
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < CPW; ++s) {
+      const int k = col_of(s);
+#pragma unroll
+      for (int i = 0; i < NIC; ++i)
+#pragma unroll
+        for (int w = 0; w < NB; ++w) {
+          const float t = pool[k * CPIN + i * BR + w * kWave + lane];
+          v[s][(ch * NIC + i) * NB + w] = (k < r && row0 + i * BR + w * kWave + lane < rows) ? t : 0.0f;
+        }
+    }
+  }
+  __syncthreads();
+
+  typedef volatile int __attribute__((address_space(3)))* lds_word;    // (a generic pointer's accesses have no order among DS ones)
+  const lds_word flag = (lds_word)&ready;
+  typedef volatile float __attribute__((address_space(3)))* lds_float;
+  const lds_float invs = (lds_float)s_inv;
+  auto dot = [&](const float (&x)[RPT], const float (&y)[RPT]) __attribute__((always_inline)) {
+    float c[NB];
+#pragma unroll
+    for (int w = 0; w < NB; ++w) c[w] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int w = 0; w < NB; ++w) c[w] = fmaf(x[i * NB + w], y[i * NB + w], c[w]);
+    return column_total<NB, PAIRS>(c);
+  };
+  auto update = [&](float (&y)[RPT], const float (&x)[RPT], float sum, float inv) __attribute__((always_inline)) {
+    const float f = -(sum * inv);
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) y[i] = fmaf(f, x[i] * inv, y[i]);
+  };
+  // Finishes the wavefront's columns s0 .. s0 + BC - 1, from which all earlier ones have been removed: hands each out, the inverse
+  // of its norm after it, removes it from those after it, and normalises it.
+  auto finish = [&](auto s0) __attribute__((always_inline)) {
+    static_for<BC>([&](auto c) __attribute__((always_inline)) {
+      constexpr int s = s0.value + c.value;
+      const int k = col_of(s);
+      if (k < r) {
+        float* to = pool + (SLOTS == C ? k : k % SLOTS) * CP + lane * NB;
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int w = 0; w < NB; ++w) to[i * BR + w] = v[s][i * NB + w];
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // DS operations of a wavefront stay in order
+        __builtin_amdgcn_wave_barrier();
+        *flag = k + 1;
+        float sum[BC];
+#pragma unroll
+        for (int d = c.value; d < BC; ++d) sum[d] = dot(v[s], v[s0.value + d]);
+        const float nrm2 = sum[c.value];
+        const float inv = (nrm2 > FLT_MIN) ? 1.0f / sqrtf(nrm2) : 0.0f;
+        invs[k] = inv;
+#pragma unroll
+        for (int d = c.value + 1; d < BC; ++d) update(v[s0.value + d], v[s], sum[d], inv);
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) v[s][i] *= inv;
+      }
+    });
+  };
+  if (wave == 0) finish(std::integral_constant<int, 0>{});
+  for (int j = 0; j + 1 < r; ++j) {
+    if constexpr (SLOTS < C) {
+      if (j > 0 && j % (SLOTS / 2) == 0) __syncthreads();    // columns before j are done with, and so are their places
+    }
+    if (col_of(CPW - BC) <= j) {                 // the wavefront's columns are all done
+      if constexpr (SLOTS < C) continue;
+      else break;
+    }
+    while (__builtin_amdgcn_readfirstlane(*flag) <= j) {}
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    float b[RPT];
+    const float* from = pool + (SLOTS == C ? j : j % SLOTS) * CP + lane * NB;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int w = 0; w < NB; ++w) b[i * NB + w] = from[i * BR + w];
+    float inv = -1.0f;
+    static_for<CPW / BC>([&](auto q) __attribute__((always_inline)) {
+      constexpr int s0 = q.value * BC;
+      const int k0 = col_of(s0);
+      if (k0 > j && k0 < r) {
+        if (k0 == j + 1) __builtin_amdgcn_s_setprio(3);
+        float sum[BC];
+#pragma unroll
+        for (int c = 0; c < BC; ++c) sum[c] = dot(b, v[s0 + c]);
+        while (inv < 0.0f) inv = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(invs[j])));
+#pragma unroll
+        for (int c = 0; c < BC; ++c) update(v[s0 + c], b, sum[c], inv);
+        if (k0 == j + 1) {
+          finish(std::integral_constant<int, s0>{});
+          __builtin_amdgcn_s_setprio(0);
+        }
+      }
+    });
+  }
+
+  // ---- back to memory, in its order
+  float mx = 0.0f;
+  float* copy = a.orth_shared && a.padded ? a.Pop + ld.pop_off : nullptr;   // the sweeps' copy of an orthonormalised aggregate
+#pragma unroll
+  for (int ch = 0; ch < NI / NIC; ++ch) {
+    const int row0 = ch * NIC * BR, el0 = row0 * r, el1 = min(rows, row0 + NIC * BR) * r;
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < CPW; ++s) {
+      const int k = col_of(s);
+#pragma unroll
+      for (int i = 0; i < NIC; ++i)
+#pragma unroll
+        for (int w = 0; w < NB; ++w) pool[k * CPIN + i * BR + w * kWave + lane] = v[s][(ch * NIC + i) * NB + w];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < F4; ++i) {
+      const int e = el0 + 4 * (tid + NT * i);
+      if (e < el1) {
+        float t[4];
+        int row = row_of(e), k = e - row * r;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {              // (rows beyond the factor's are zeros)
+          t[q] = pool[k * CPIN + row - row0];
+          mx = fmaxf(mx, fabsf(t[q]));
+          if (copy && e + q < el1) copy[row * C + k] = t[q];
+          if (++k == r) { k = 0; ++row; }
+        }
+        if (e + 4 <= el1) *reinterpret_cast<float4*>(orth + e) = make_float4(t[0], t[1], t[2], t[3]);
+        else
+          for (int q = 0; q < el1 - e; ++q) orth[e + q] = t[q];
+      }
     }
   }
   mx = wave_max(mx);
@@ -3814,49 +4078,69 @@ bool launch_orth_reg(const DevArgs& a, int max_rows, dim3 grid, hipStream_t s) {
   return false;
 }
 
-// Columns on lanes: workgroups of up to 16 wavefronts, up to 64 rows per lane; the sums are those of 256 threads with
-// rows on lanes (1024 threads beyond 2048 rows), their wavefronts added in pairs from rank pad 16 and 513 rows on.
+// Whole columns to a wavefront (OW) or columns on lanes (OC); the sums are those of 256 threads with rows on lanes (1024
+// threads beyond 2048 rows), their wavefronts added in pairs from rank pad 16 and 513 rows on.
 template <int C>
 bool launch_orth_col(const DevArgs& a, int max_rows, dim3 grid, hipStream_t s) {
-#define LQSGD_LAUNCH_OC(ROWS, WV, NI, NW, PAIRS)                                                     \
+#define LQSGD_LAUNCH_OC(ROWS, WV, NI, NW)                                                            \
   if (max_rows <= (ROWS)) {                                                                          \
     static_assert((ROWS) <= ((WV) > 4 ? 64 * (WV) : (NI) > 1 ? 256 : 64 * (WV)) * (NI), "");         \
-    orth_col_kernel<C, WV, NI, NW, PAIRS><<<grid, dim3(64 * (NW)), 0, s>>>(a);                       \
-    note_kernel("orth_col_kernel<%d, %d, %d, %d, %s>", C, WV, NI, NW, tf(PAIRS));                    \
+    orth_col_kernel<C, WV, NI, NW><<<grid, dim3(64 * (NW)), 0, s>>>(a);                              \
+    note_kernel("orth_col_kernel<%d, %d, %d, %d>", C, WV, NI, NW);                                   \
     return true;                                                                                     \
   }
+#define LQSGD_LAUNCH_OW(ROWS, NB, NI, NW, BC, NIC, SLOTS, PAIRS)                                                \
+  if (max_rows <= (ROWS)) {                                                                                     \
+    static_assert((ROWS) == 64 * (NB) * (NI), "");                                                              \
+    orth_colwave_kernel<C, NB, NI, NW, BC, NIC, SLOTS, PAIRS><<<grid, dim3(64 * (NW)), 0, s>>>(a);              \
+    note_kernel("orth_colwave_kernel<%d, %d, %d, %d, %d, %d, %d, %s>", C, NB, NI, NW, BC, NIC, SLOTS, tf(PAIRS)); \
+    return true;                                                                                                \
+  }
+  // More factors than CUs: what counts is the work of a factor, not its chain (640 of them, one wavefront a column or block / as
+  // chosen: 512 rows at r = 16 27 / 24 us, 120 rows 18 / 14; 60 rows at r = 40 41 / 37; 64 rows at r = 30 28 / 23.5.  168 of them at
+  // r = 16 14.1 / 15.1).
+  const bool many = grid.x > 256;
   if constexpr (C == 4) {
-    LQSGD_LAUNCH_OC(512, 4, 2, 4, false)
-    LQSGD_LAUNCH_OC(1024, 4, 4, 8, false)
-    LQSGD_LAUNCH_OC(2048, 4, 8, 8, false)
-    LQSGD_LAUNCH_OC(4096, 16, 4, 16, false)
-    LQSGD_LAUNCH_OC(8192, 16, 8, 16, false)
-    LQSGD_LAUNCH_OC(11264, 16, 11, 16, false)
+    LQSGD_LAUNCH_OW(512, 4, 2, 4, 1, 2, 4, false)        // (500 rows 8.6 -> 8.3 us, but 1000 rows 8.1 -> 9.0, 1700 9.7 -> 12.4)
+    LQSGD_LAUNCH_OC(1024, 4, 4, 8)
+    LQSGD_LAUNCH_OC(2048, 4, 8, 8)
+    LQSGD_LAUNCH_OC(4096, 16, 4, 16)
+    LQSGD_LAUNCH_OC(8192, 16, 8, 16)
+    LQSGD_LAUNCH_OC(11264, 16, 11, 16)
   } else if constexpr (C == 8) {
-    LQSGD_LAUNCH_OC(256, 4, 1, 4, false)
-    LQSGD_LAUNCH_OC(512, 4, 2, 8, false)
-    LQSGD_LAUNCH_OC(1024, 4, 4, 8, false)
-    LQSGD_LAUNCH_OC(2048, 4, 8, 16, false)
-    LQSGD_LAUNCH_OC(4096, 16, 4, 16, false)
+    LQSGD_LAUNCH_OW(256, 4, 1, 8, 1, 1, 8, false)
+    LQSGD_LAUNCH_OW(512, 4, 2, 8, 1, 2, 8, false)
+    LQSGD_LAUNCH_OW(1024, 4, 4, 8, 1, 4, 8, false)
+    LQSGD_LAUNCH_OW(2048, 4, 8, 8, 1, 4, 8, false)
+    LQSGD_LAUNCH_OC(4096, 16, 4, 16)
   } else if constexpr (C == 16) {
-    LQSGD_LAUNCH_OC(128, 2, 1, 4, false)
-    LQSGD_LAUNCH_OC(256, 4, 1, 8, false)
-    LQSGD_LAUNCH_OC(512, 4, 2, 8, false)
-    LQSGD_LAUNCH_OC(1024, 4, 4, 16, true)
-    LQSGD_LAUNCH_OC(1792, 4, 7, 16, true)
+    if (!many) {
+      LQSGD_LAUNCH_OW(128, 2, 1, 16, 1, 1, 16, false)
+      LQSGD_LAUNCH_OW(256, 4, 1, 16, 1, 1, 16, false)
+      LQSGD_LAUNCH_OW(512, 4, 2, 16, 1, 2, 16, false)
+      LQSGD_LAUNCH_OW(1024, 4, 4, 16, 1, 2, 16, true)
+      LQSGD_LAUNCH_OW(1792, 4, 7, 16, 1, 7, 16, true)
+    }
+    LQSGD_LAUNCH_OW(128, 2, 1, 8, 2, 1, 16, false)
+    LQSGD_LAUNCH_OW(256, 4, 1, 8, 2, 1, 16, false)
+    LQSGD_LAUNCH_OW(512, 4, 2, 8, 2, 2, 16, false)
+    LQSGD_LAUNCH_OW(1024, 4, 4, 8, 2, 2, 16, true)
+    LQSGD_LAUNCH_OW(1792, 4, 7, 8, 2, 7, 16, true)
   } else if constexpr (C == 32) {
-    LQSGD_LAUNCH_OC(64, 1, 1, 4, false)
-    LQSGD_LAUNCH_OC(128, 2, 1, 8, false)
-    LQSGD_LAUNCH_OC(256, 4, 1, 8, false)
-    LQSGD_LAUNCH_OC(512, 4, 2, 16, false)
-    LQSGD_LAUNCH_OC(1024, 4, 4, 16, true)
-    LQSGD_LAUNCH_OC(1792, 4, 7, 16, true)
+    if (many) { LQSGD_LAUNCH_OC(64, 1, 1, 4) }
+    LQSGD_LAUNCH_OW(64, 1, 1, 16, 2, 1, 32, false)
+    LQSGD_LAUNCH_OW(128, 2, 1, 16, 2, 1, 32, false)
+    LQSGD_LAUNCH_OW(256, 4, 1, 16, 2, 1, 32, false)
+    LQSGD_LAUNCH_OW(512, 4, 2, 16, 2, 2, 32, false)
+    LQSGD_LAUNCH_OW(1024, 4, 4, 16, 2, 2, 32, true)
+    LQSGD_LAUNCH_OW(1792, 4, 7, 16, 2, 1, 16, true)
   } else {
-    LQSGD_LAUNCH_OC(64, 1, 1, 8, false)
-    LQSGD_LAUNCH_OC(128, 2, 1, 8, false)
-    LQSGD_LAUNCH_OC(256, 4, 1, 16, false)
-    LQSGD_LAUNCH_OC(512, 4, 2, 16, false)
-    LQSGD_LAUNCH_OC(1024, 4, 4, 16, true)
+    if (many) { LQSGD_LAUNCH_OW(64, 1, 1, 8, 2, 1, 64, false) }
+    LQSGD_LAUNCH_OW(64, 1, 1, 16, 2, 1, 64, false)
+    LQSGD_LAUNCH_OW(128, 2, 1, 16, 2, 1, 64, false)
+    LQSGD_LAUNCH_OW(256, 4, 1, 16, 2, 1, 64, false)
+    LQSGD_LAUNCH_OW(512, 4, 2, 16, 2, 2, 64, false)
+    LQSGD_LAUNCH_OW(1024, 4, 4, 16, 2, 2, 32, true)
   }
 #undef LQSGD_LAUNCH_OC
   return false;

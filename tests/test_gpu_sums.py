@@ -93,6 +93,27 @@ def test_gram_schmidt_sums_of_many_tall_factors(rank, rows):
     comp.close()
 
 
+# more factors than CUs (a workgroup each then has fewer wavefronts, or columns on lanes), odd ranks, which leave a wavefront's
+# block of columns half empty, and layers narrower than the rank beside them
+@pytest.mark.parametrize("rank,rows", [(7, 500), (8, 1500), (9, 128), (13, 256), (15, 300), (16, 1000), (11, 1500), (17, 64), (31, 65),
+                                       (25, 400), (33, 50), (64, 64), (41, 128), (63, 300), (49, 1000)])
+def test_gram_schmidt_sums_of_more_factors_than_cus(rank, rows):
+    import torch
+    _say("case: order of sums, more factors than CUs", rank, rows)
+    rng = np.random.default_rng(rank * 7919 + rows)
+    layers, W = [(rows, rank + 8)] * 34 + [(rows, 1), (rows - 1, 3), (5, rank + 8)], 8
+    comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, W)
+    for l, (n, c) in enumerate(layers):
+        comp.set_q(l, rng.standard_normal((c, min(rank, n, c))).astype(f32))
+    D = [torch.from_numpy((rng.standard_normal(rows * (rank + 8)) * 1e-3).astype(f32)).cuda() for _ in range(3)]
+    comp.compress(B.PHASE_P, [[D[(l + w) % 3][:n * c].view(n, c) for l, (n, c) in enumerate(layers)] for w in range(W)])
+    assert comp.launched_kernel(B.KERNEL_ORTH).startswith("orth_col")
+    for l, w in ((0, 0), (20, 3), (33, 7), (34, 1), (35, 2), (36, 5)):
+        want = _gram_schmidt(comp.get_factor(B.FACTOR_P_PRE, l, w), 256, rank > 8 and rows > 512)
+        assert np.array_equal(comp.get_factor(B.FACTOR_P_ORTH, l, w), want), (l, w)
+    comp.close()
+
+
 @pytest.mark.parametrize("rank", [2, 4, 7, 20, 50])
 def test_gram_schmidt_of_a_column_whose_squared_norm_overflows(rank):
     """Finite values whose squares leave the range of floats: the column becomes zero and the others, whose products with it
