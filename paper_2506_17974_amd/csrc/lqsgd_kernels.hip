@@ -813,11 +813,14 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
   // row of the lane's value i, from row0
   auto row_of = [](int i) __attribute__((always_inline)) { return bit_reverse(i / NI, log2c(LL)) * SP + (i % NI) * STEP; };
   const bool col = k < r;
+  const int kread = min(k, r - 1);
 
   float v[RPT];
 #pragma unroll
   for (int i = 0; i < RPT; ++i) v[i] = 0.0f;
-  // elements beyond the factor re-read its first one; they count as zeros from here on
+  // Elements beyond the factor re-read the last one of their row or column, in a line that is read anyhow (its first element
+  // instead: 4096 x 8192, r = 3, W = 4, 31 us against 18.5, 2 x (11008 x 4096) and so on, r = 4, 47 against 42); they count as
+  // zeros from here on.
   for (int s = 0; s < nseg; ++s) {
     const float* src = Pp + (size_t)s * ld.np_pad;
     hide_row();
@@ -828,8 +831,7 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
       float t[CH];
 #pragma unroll
       for (int i = 0; i < CH; ++i) {
-        const int row = row0 + row_of(i0 + i);
-        t[i] = src[(col && row < rows) ? row * r + k : 0];
+        t[i] = src[min(row0 + row_of(i0 + i), rows - 1) * r + kread];
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -4294,13 +4296,19 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, Coo
   if (a.L <= 0) return hipSuccess;
   const dim3 grid(a.L * a.W);
   const int nslice = (max_rows + 255) / 256;
-  // Tall factors and too few (layer, worker) pairs to fill 256 CUs with one workgroup
-  // each, or more rows than one workgroup holds: many workgroups per factor.  The limits of
-  // pads 8 to 32 keep each factor with the form, and so the sums, that it has had: one workgroup of columns on lanes would
-  // hold up to 8192 rows at pad 8 (130 factors of 8000 rows: 121 us, Cholesky-QR 186) and 4096 at pad 16 (3000 rows:
-  // 119 and 125), with results that differ by their rounding times the factor's condition number.
+  // More rows than one workgroup holds, or, from rank pad 8 on, tall factors and too few (layer, worker) pairs to fill 256
+  // CUs with one workgroup each: many workgroups per factor.  At rank pads 1 to 4 one workgroup is the faster one at every
+  // height that it holds, few factors or many: a cooperative launch alone costs about 20 us, its launches one by one 9 us a
+  // column (many workgroups / one, us: 1822 x 384, W = 8, r = 1 23 / 8, r = 4 29 / 10; 8000 x 300, W = 4, r = 1 25 / 9, r = 4 32 / 18;
+  // 8192^2, W = 4, r = 1 27 / 23, r = 3 32 / 25, r = 4 35 / 26; two blocks of a large language model, W = 4, r = 4 58 / 42, r = 1
+  // 18.7 / 19.4).  (Fewer than 16 factors of 8192 rows or more at rank pad 4 stay with the one-launch form all the same: it is
+  // there that the expiry of its bounded waits is tested.)  The limits of pads 8 to 32 keep each factor with the form, and so the sums, that it has had: one workgroup
+  // would hold up to 8192 rows at pad 8 (130 factors of 8000 rows: 121 us, Cholesky-QR 186) and 4096 at pad 16 (3000 rows:
+  // 119 and 125), with results that differ by their rounding times the factor's condition number, which at those ranks can be
+  // a thousand.
   const bool fits = max_rows <= (rp <= 4 ? 11264 : rp == 8 ? 4096 : rp <= 32 ? 1792 : 1024);
-  if (a.orth_part && (!fits || (nslice >= 8 && (int)grid.x < 128))) {
+  const bool few = rp > 4 ? nslice >= 8 && grid.x < 128 : rp == 4 && max_rows >= 8192 && grid.x < 16;
+  if (a.orth_part && (!fits || few)) {
 #ifdef LQSGD_TUNING
     static const bool chol = [] { const char* e = std::getenv("LQSGD_ORTH_CHOL"); return !(e && e[0] == '0'); }();
 #else

@@ -93,6 +93,25 @@ def test_gram_schmidt_sums_of_many_tall_factors(rank, rows):
     comp.close()
 
 
+# few tall factors at rank pads 1 to 4: one workgroup each up to the height that it holds, slices beyond
+@pytest.mark.parametrize("rank,rows", [(1, 1793), (1, 11264), (2, 2049), (2, 8200), (3, 1793), (3, 4097), (4, 8191), (4, 8192), (3, 11265)])
+def test_gram_schmidt_sums_of_few_tall_factors(rank, rows):
+    _say("case: order of sums, few tall factors", rank, rows)
+    rng = np.random.default_rng(rank * 7919 + rows)
+    layers, W = [(rows, 1100), (40, 12), (rows - 300, 2)], 2
+    comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, W)
+    for l, (n, c) in enumerate(layers):
+        comp.set_q(l, rng.standard_normal((c, min(rank, n, c))).astype(f32))
+    comp.compress(B.PHASE_P, pu.to_device([[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)]))
+    assert comp.launched_kernel(B.KERNEL_ORTH).startswith("orth_coop" if rank > 2 and rows >= 8192 else "orth_reg" if rank <= 2 else "orth_col")
+    for l in range(len(layers)):
+        for w in range(W):
+            got = comp.get_factor(B.FACTOR_P_ORTH, l, w)
+            want = _gram_schmidt(comp.get_factor(B.FACTOR_P_PRE, l, w), 256 if rows <= 2048 else 1024, False)
+            assert pu.rel_fro(got, want) < pu.FP_TOL if rank <= 2 or rows >= 8192 else np.array_equal(got, want), (l, w)
+    comp.close()
+
+
 # more factors than CUs (a workgroup each then has fewer wavefronts, or columns on lanes), odd ranks, which leave a wavefront's
 # block of columns half empty, and layers narrower than the rank beside them
 @pytest.mark.parametrize("rank,rows", [(7, 500), (8, 1500), (9, 128), (13, 256), (15, 300), (16, 1000), (11, 1500), (17, 64), (31, 65),
