@@ -462,7 +462,7 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   HIP_TRY(c, hipGetDevice(&c->device));
   const Plan& p = c->plan;
   DevArgs& a = c->args;
-  a.W = p.W; a.L = p.L; a.n_all = p.n_all; a.rank_pad = p.RP; a.bits_p = p.cfg.bits_p; a.bits_q = p.cfg.bits_q;
+  a.W = p.W; a.L = p.L; a.n_all = p.n_all; a.rank_pad = p.RP; a.slices = p.slices; a.bits_p = p.cfg.bits_p; a.bits_q = p.cfg.bits_q;
   a.alpha = p.cfg.alpha;
   a.agg_first = p.agg_first ? 1 : 0; a.orth_shared = 0; a.update = 0; a.eta = 0.0f;
   a.g_bf16 = (flags & LQSGD_FLAG_BF16_GRADIENTS) ? 1 : 0;

@@ -25,7 +25,7 @@ struct DevArgs {
   unsigned long long* chol_table;      // [L*W][ceil(max_rows/256) + 1][NE] tagged Gram matrices of the slices, their total last
   float* chol_part;            // [L*W][ceil(max_rows/256)][NE] the same matrices in plain memory, for the form of three launches: of the
   float* chol_part2;           // first pass, and of the second
-  int* chol_redo;              // [L*W] raised for a pair that has to be done column by column
+  int* chol_redo;              // [L*W] bit 0 raised for a pair that has to be done column by column, bit 1 of the first word for any
   int* status;                 // pinned host word the kernels raise when a bounded device-side wait expires
   float* Pbar;                 // aggregated P (shared)
   float* Qpart;                // sweep-1 partial products, per worker
@@ -45,6 +45,7 @@ struct DevArgs {
   float alpha;                 // log scale of Eq. (5)
   int32_t quant_fast;          // alpha is such that the hardware log2 finds a code to within one level
   float qscale_p, qscale_q;    // (2^b - 1) / log2(1 + alpha) for b_p, b_q
+  int32_t slices;              // slices of 256 rows of one worker's factors (Plan::slices)
   int32_t agg_first;           // aggregate-first order: scaleP is an atomic-max accumulator (sweep 0 zeroes it)
   int32_t orth_shared;         // the Gram-Schmidt kernels run once per layer, in place on the plane at Ppart + p_off
   int32_t g_bf16;              // the gradient tensors hold bfloat16 values (G-hat / parameters stay fp32)

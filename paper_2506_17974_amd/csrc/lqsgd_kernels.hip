@@ -1234,19 +1234,47 @@ __global__ __launch_bounds__(64 * NW) void orth_colwave_kernel(DevArgs a) {
 // between columns is the kernel boundary.  Launch 0 sums the sweep-0 partials,
 // launch r finishes with absmax(P_w) through an integer atomic max.
 // only_if (optional): one word per (layer, worker) pair, written by an earlier
-// kernel; the launches skip the pairs whose word is zero.
+// kernel; the launches skip the pairs whose lowest bit is zero, and do nothing
+// where the first word is.
 // ---------------------------------------------------------------------------
+// The factor and the slice that workgroup `block` has: the slices of all factors in a row, a layer's workers one after the other.
+// (A grid of the tallest factor's slices for every factor is mostly empty where heights differ, and too many for one cooperative
+// launch: 10 layers of up to 6848 rows, r = 21, W = 4, 1080 workgroups for 284 slices, Gram-Schmidt 150 us in three launches, 79 in
+// one; 4000 x 300 beside 10 x (500 x 600), r = 40, W = 8 477 and 160.)
+__device__ __forceinline__ void slice_of(const DevArgs& a, int block, int nslice_max, int& lw, int& slice) {
+  if (a.slices == a.L * nslice_max) {            // all as tall
+    lw = block / nslice_max;
+    slice = block - lw * nslice_max;
+    return;
+  }
+  const int lane = threadIdx.x & (kWave - 1);
+  int layer = -1;
+  for (int base = 0; base < a.L; base += kWave) {
+    const bool at_or_before = base + lane < a.L && a.W * a.layers[base + lane].slice0 <= block;
+    const int n = __popcll(__ballot(at_or_before));
+    layer += n;
+    if (n < kWave) break;
+  }
+  layer = __builtin_amdgcn_readfirstlane(layer);
+  const int in_layer = block - a.W * a.layers[layer].slice0, n = (a.layers[layer].rows + 255) >> 8;
+  const int worker = in_layer / n;
+  lw = layer * a.W + worker;
+  slice = in_layer - worker * n;
+}
+
 template <int RP>
 __global__ __launch_bounds__(256) void orth_wide_kernel(DevArgs a, int j, int nslice_max, const int* only_if) {
   __shared__ float red[4][RP];
   __shared__ float redmax[4];
-  const int lw = blockIdx.x / nslice_max, slice = blockIdx.x - lw * nslice_max;
-  if (only_if && only_if[lw] == 0) return;       // this pair was finished by the Cholesky-QR kernels
+  if (only_if && only_if[0] == 0) return;        // no pair has to be done column by column
+  int lw, slice;
+  slice_of(a, blockIdx.x, nslice_max, lw, slice);
+  if (only_if && (only_if[lw] & 1) == 0) return; // this pair was finished by the Cholesky-QR kernels
   const int layer = lw / a.W, worker = lw - layer * a.W;
   const LayerDesc& ld = a.layers[layer];
   const int rows = ld.rows, r = ld.r;
   const int nslice = (rows + 255) >> 8;
-  if (slice >= nslice || j > r) return;
+  if (j > r) return;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
   const int row = slice * 256 + tid;
   const bool live = row < rows;
@@ -1452,12 +1480,12 @@ __global__ __launch_bounds__(256) void orth_coop_kernel(DevArgs a, int nslice_ma
   __shared__ float tot_s[RP];
   __shared__ float gather_s[kCoopMaxSlices * RP];
   __shared__ float redmax[4];
-  const int lw = blockIdx.x / nslice_max, slice = blockIdx.x - lw * nslice_max;
+  int lw, slice;
+  slice_of(a, blockIdx.x, nslice_max, lw, slice);
   const int layer = lw / a.W, worker = lw - layer * a.W;
   const LayerDesc& ld = a.layers[layer];
   const int rows = ld.rows, r = ld.r;
   const int nslice = (rows + 255) >> 8;
-  if (slice >= nslice) return;                   // workgroup-uniform
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
   const int row = slice * 256 + tid;
   const bool live = row < rows;
@@ -3888,13 +3916,13 @@ __global__ __launch_bounds__(256, 2) void orth_chol_kernel(DevArgs a, int nslice
   __shared__ __attribute__((aligned(16))) float pool[S::POOL];
   __shared__ float redmax[4];
   __shared__ int flag;
-  const int lw = blockIdx.x / nslice_max, slice = blockIdx.x - lw * nslice_max;
+  int lw, slice;
+  slice_of(a, blockIdx.x, nslice_max, lw, slice);
   const int layer = lw / a.W, worker = lw - layer * a.W;
   const LayerDesc& ld = a.layers[layer];
   const int rows = ld.rows, r = ld.r;
   const int nslice = (rows + 255) >> 8;
-  if (slice >= nslice) return;                   // workgroup-uniform
-  if (phase == 2 && redo[lw] != 0) return;       // raised in phase 1, or by a faster slice just now: the pair is done again anyway
+  if (phase == 2 && (redo[lw] & 1)) return;       // raised in phase 1, or by a faster slice just now: the pair is done again anyway
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
   const int row = slice * 256 + tid;
   float* pre = a.Ppre + (size_t)worker * a.p_stride + ld.p_off;
@@ -3967,7 +3995,10 @@ __global__ __launch_bounds__(256, 2) void orth_chol_kernel(DevArgs a, int nslice
   }
   if (!good) {
     if (phase > 0) {
-      if (slice == 0 && tid == 0) redo[lw] = 1;
+      if (slice == 0 && tid == 0) {
+        atomicOr(redo + lw, 1);
+        atomicOr(redo, 2);                       // some pair
+      }
       return;
     }
     // one launch: column by column from the sum of the planes, as orth_coop_kernel does
@@ -4315,12 +4346,12 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, Coo
     constexpr bool chol = true;
 #endif
     if (chol && rp >= 8 && a.chol_part && a.chol_part2 && a.chol_redo) {
-      return launch_orth_chol(rp, nslice, max_rank, a, (int)grid.x * nslice, coop, s);
+      return launch_orth_chol(rp, nslice, max_rank, a, a.W * a.slices, coop, s);
     }
     // (no Cholesky-QR buffers, or a pad below 8)
-    if (launch_orth_coop(rp, nslice, max_rank, a, (int)grid.x * nslice, coop, s)) return hipSuccess;
+    if (launch_orth_coop(rp, nslice, max_rank, a, a.W * a.slices, coop, s)) return hipSuccess;
     for (int j = 0; j <= max_rank; ++j) {
-      LQSGD_RP_SWITCH_ORTH(rp, (orth_wide_kernel<RP><<<dim3(grid.x * nslice), dim3(256), 0, s>>>(a, j, nslice, nullptr)));
+      LQSGD_RP_SWITCH_ORTH(rp, (orth_wide_kernel<RP><<<dim3(a.W * a.slices), dim3(256), 0, s>>>(a, j, nslice, nullptr)));
     }
     note_kernel("orth_wide_kernel<%d> x %d launches", rp, max_rank + 1);
     return hipGetLastError();

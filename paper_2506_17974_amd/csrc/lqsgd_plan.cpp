@@ -103,6 +103,7 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
 
   int max_r = 1;
   max_rows = 0;
+  slices = 0;
   matrix_elements = 0;
   for (int i = 0; i < n_layers; ++i) {
     const lqsgd_layer& l = ls[i];
@@ -145,6 +146,8 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
       d.nq_pad = (int32_t)round_up(d.nq_el, 16);
       max_r = std::max(max_r, d.r);
       max_rows = std::max(max_rows, d.rows);
+      d.slice0 = slices;
+      slices += (d.rows + 255) / 256;
       matrix_elements += (int64_t)d.rows * d.cols;
       kind_of.push_back((int32_t)layers.size());
       layers.push_back(d);

@@ -45,6 +45,7 @@ struct LayerDesc {
   int32_t np_el, nq_el;         // rows*r, cols*r
   int32_t np_pad, nq_pad;       // the same rounded up to 16 elements (stride of the partial planes)
   int32_t direct_q;             // sweep 1 covers all rows in one block and writes Q_w (and its absmax) itself: no partial planes, no reduce
+  int32_t slice0;               // slices of 256 rows in the layers before (Gram-Schmidt by slices)
   int64_t pop_off, qop_off;     // into the factors the sweeps read: copies with rows padded to RP ranks (Plan::padded), or p_off / q_off
   int64_t m_off;                // into E / M          (worker stride m_stride)
   int64_t p_off;                // into rows x r slabs (worker stride p_stride)
@@ -83,6 +84,7 @@ struct Plan {
   int32_t RP = 0;               // register rank: smallest of 1, 2, 4, .. 64 >= max layer rank
   int32_t max_rows = 0;         // largest row count of a matrix layer
   int32_t max_rank = 0;         // largest effective rank of a matrix layer
+  int32_t slices = 0;           // slices of 256 rows of all matrix layers
   bool mfma = false;            // sweep 1 runs on the matrix cores (rank pads 32 and 64)
   bool mfma_a = false;          // sweeps 0 and 2 run on the matrix cores (rank pad >= 16): 32-row work items, 64 rows at rank pad 64
   std::vector<LayerDesc> layers;

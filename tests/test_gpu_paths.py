@@ -289,6 +289,36 @@ def test_tall_gram_schmidt_by_cholesky_qr(layers, rank, W, special):
         assert np.array_equal(x, y), "the one-launch and the three-launch form differ"
 
 
+def test_slices_of_factors_of_any_height():
+    """A workgroup finds its factor among the slices of all: heights of one to ten slices, more layers than a wavefront has lanes,
+    and a pair in the middle (zero gradient) that is done column by column, in one launch and in several."""
+    _say("case: slices of mixed heights")
+    layers, rank, W = [(2100, 20)] + [(40 + 7 * i, 12) for i in range(80)] + [(2500, 24), (256, 16), (257, 16)], 8, 1
+    rng = np.random.default_rng(80)
+    Q = [rng.standard_normal((c, min(rank, r, c))).astype(f32) for r, c in layers]
+    G = _random_inputs(rng, layers, W)
+    G[0][81][:] = 0.0
+    Gd = pu.to_device(G)
+    got = {}
+    for flags, name in ((0, "orth_chol_kernel<8>"), (B.FLAG_NO_COOPERATIVE_LAUNCH, "orth_chol_kernel<8> x 3 launches")):
+        comp, ml = _make(layers, (), rank, 8, 8, W, flags=flags)
+        for l in ml:
+            comp.set_q(l, Q[l])
+        comp.compress(B.PHASE_P, Gd)
+        assert comp.launched_kernel(B.KERNEL_ORTH) == name, comp.launched_kernel(B.KERNEL_ORTH)
+        got[flags] = [comp.get_factor(B.FACTOR_P_ORTH, l, k) for l in ml for k in range(W)]
+        for i, (l, k) in enumerate((l, k) for l in ml for k in range(W)):
+            p = got[flags][i]
+            if (l, k) == (81, 0):
+                assert not p.any()
+            else:
+                want = orc.orthonormalize(comp.get_factor(B.FACTOR_P_PRE, l, k))
+                assert pu.rel_fro(p, want) < pu.FP_TOL, (l, k)
+        comp.close()
+    for x, y in zip(got[0], got[B.FLAG_NO_COOPERATIVE_LAUNCH]):
+        assert np.array_equal(x, y)
+
+
 def test_more_tall_factors_than_one_launch_can_hold():
     """100 (layer, worker) pairs of 16 slices each are more workgroups than fit the chip at once: the
     Cholesky-QR Gram-Schmidt has to take its three-launch form by itself (no flag), and the sampled
