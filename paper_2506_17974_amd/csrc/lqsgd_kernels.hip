@@ -1554,14 +1554,11 @@ __global__ __launch_bounds__(256) void exchange_kernel(DevArgs a, const XTile* _
   const int bits = phase ? a.bits_q : a.bits_p;
   const int lv = (1 << bits) - 1;
   const int tid = threadIdx.x;
+  float thr0 = 0.0f, lev0 = 0.0f;
   if (bits > 0) {
-    const float* thr = phase ? a.thrQ : a.thrP;
-    const float* lev = phase ? a.levQ : a.levP;
-    if (tid < lv) s_tab[1 + tid] = thr[tid];
-    if (tid <= lv) s_lev[tid] = lev[tid];
-    if (tid < 2) s_tab[tid * (lv + 1)] = __uint_as_float(0x7fc00000u);
+    thr0 = gptr<float>(phase ? a.thrQ : a.thrP)[min(tid, max(lv - 1, 0))];
+    lev0 = gptr<float>(phase ? a.levQ : a.levP)[min(tid, lv)];
   }
-  __syncthreads();
   const XTile tl = tiles[blockIdx.x];
   const LayerDesc& ld = a.layers[tl.layer];
   const int n_el = phase ? ld.nq_el : ld.np_el;
@@ -1580,19 +1577,39 @@ __global__ __launch_bounds__(256) void exchange_kernel(DevArgs a, const XTile* _
   const float* scale = phase ? a.scaleQ : a.scaleP;
   const float qscale = phase ? a.qscale_q : a.qscale_p;
 
+  // A worker's group and its absmax.  The first ones are requested before the tables are waited for, and each worker's while the
+  // one before it is quantised: at low ranks this kernel is nothing but a chain of trips to memory.
+  float4 lo = make_float4(0.0f, 0.0f, 0.0f, 0.0f), hi = lo;
+  float s_next = 0.0f;
+  auto request = [&](int w) __attribute__((always_inline)) {
+    if (gvalid && w < a.W) {
+      if (MODE != kMeanOnly || bits == 0) {
+        lo = reinterpret_cast<const float4*>(fac + (size_t)w * fstride)[0];
+        hi = reinterpret_cast<const float4*>(fac + (size_t)w * fstride)[1];
+      }
+      if (bits > 0) s_next = scale[(size_t)w * a.L + tl.layer];
+    }
+  };
+  request(slot);
+  __builtin_amdgcn_sched_barrier(0);
+  if (bits > 0) {
+    if (tid < lv) s_tab[1 + tid] = thr0;
+    if (tid <= lv) s_lev[tid] = lev0;
+    if (tid < 2) s_tab[tid * (lv + 1)] = __uint_as_float(0x7fc00000u);
+    __syncthreads();
+  }
+
   float acc = 0.0f;
   for (int wbase = 0; wbase < a.W; wbase += 8) {
     const int w = wbase + slot;
     float val[kXGroup];
 #pragma unroll
     for (int i = 0; i < kXGroup; ++i) val[i] = 0.0f;
+    float x[kXGroup] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    const float s = s_next;
+    request(w + 8);
     if (gvalid && w < a.W) {
-      float x[kXGroup];
       if (MODE != kMeanOnly || bits == 0) {
-        const float4 lo = reinterpret_cast<const float4*>(fac + (size_t)w * fstride)[0];
-        const float4 hi = reinterpret_cast<const float4*>(fac + (size_t)w * fstride)[1];
-        x[0] = lo.x; x[1] = lo.y; x[2] = lo.z; x[3] = lo.w;
-        x[4] = hi.x; x[5] = hi.y; x[6] = hi.z; x[7] = hi.w;
 #pragma unroll
         for (int i = 0; i < kXGroup; ++i)
           if (i >= nvalid) x[i] = 0.0f;
@@ -1601,7 +1618,6 @@ __global__ __launch_bounds__(256) void exchange_kernel(DevArgs a, const XTile* _
 #pragma unroll
         for (int i = 0; i < kXGroup; ++i) val[i] = x[i];
       } else {
-        const float s = scale[(size_t)w * a.L + tl.layer];
         if (MODE != kMeanOnly) {
           uint8_t* mp = mag + (size_t)w * mstride;
           uint8_t* sp = sgn + (size_t)w * sstride;
