@@ -1998,15 +1998,37 @@ __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const L
   }
   }
   float* Qp = a.Qpart + (size_t)worker * a.qpart_stride + ld.qpart_off + (size_t)(tl.row0 / ld.rbb) * ld.nq_pad;
+  // Value v of component s is column c0 + 32 (v / 4) + 4 (v % 4) + s + 16 h.
+  if constexpr (SHORT || KIND != kAligned) {
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb)
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
+      for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int col = c0 + 4 * (8 * (v >> 2) + 4 * h + (v & 3)) + s;
-        if (col < cols && 32 * nb + li < r) Qp[(size_t)col * r + 32 * nb + li] = acc[nb][s][v];
+        for (int v = 0; v < 16; ++v) {
+          const int col = c0 + 4 * (8 * (v >> 2) + 4 * h + (v & 3)) + s;
+          if (col < cols && 32 * nb + li < r) Qp[(size_t)col * r + 32 * nb + li] = acc[nb][s][v];
+        }
+  } else {
+    // Whole strips of items that are not over after a few groups: a wave-uniform row of Q_w plus one byte offset a lane, no tests.
+    // With an address and a test of its own for each of the 64 NB values the stores were a fifth of an item of 256 rows (sweep 1, us:
+    // ResNet-18 set, W = 8, r = 50 156 -> 130, 12 x (512 x 4608) 313 -> 294, 3 of them at r = 32 63 -> 60, 8192^2, W = 4, r = 64
+    // 323 -> 313; short items are no faster for it where they are few: 20 x (100 x 300), r = 50 26.1 / 26.9).
+    unsigned lane_off = (unsigned)(16 * h * r + li) * 4u;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+      if (32 * nb + li < r) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int col = c0 + 32 * (v >> 2) + 4 * (v & 3) + s;
+            char* at = reinterpret_cast<char*>(Qp + (unsigned)(col * r + 32 * nb));
+            asm volatile("" : "+v"(lane_off));   // (else the optimiser adds it to Qp first, and has 64-bit sums to do again)
+            *gptr<float>(at + lane_off) = acc[nb][s][v];
+          }
       }
+  }
 }
 
 template <int NB>
