@@ -23,12 +23,12 @@ static lqsgd_config cfg(int rank, int bp, int bq, int W, float alpha = 255.0f, u
   return c;
 }
 
-// The workgroups of 32 rows that go over sweep 0's items and worker 0's: all of them have rows, and together each item's.
+// The workgroups of 32 rows that go over sweep 0's items: all of them have rows, and together each item's.
 static void check_halves(const lqsgd_config& c, const std::vector<lqsgd_layer>& layers) {
   lqsgd::Plan p;
   EXPECT(p.build(&c, layers.data(), (int32_t)layers.size()) == LQSGD_OK);
   if (!p.mfma_a) return;
-  for (const auto& list : {std::make_pair(&p.tilesA, p.twoA), std::make_pair(&p.tilesAG, p.twoAG)}) {
+  for (const auto& list : {std::make_pair(&p.tilesA, p.twoA)}) {
     const int n = (int)list.first->size();
     std::vector<int64_t> rows((size_t)n, 0);
     for (int b = 0; b < n + list.second; ++b) {

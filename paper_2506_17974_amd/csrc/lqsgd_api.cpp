@@ -337,7 +337,7 @@ int run_sweep2(lqsgd_ctx* c, bool write_ghat) {
   } else {
     if (write_ghat) {
       if (p.mfma_a)
-        HIP_TRY(c, launch_mfma_sweep(p.RP, 4, c->args, c->d_tilesAG, (int)p.tilesAG.size(), p.twoAG, 0, c->stream));
+        HIP_TRY(c, launch_mfma_sweep(p.RP, 4, c->args, c->d_tilesAG, (int)p.tilesAG.size(), 0, 0, c->stream));
       else
         HIP_TRY(c, launch_residual(p.RP, 2, c->args, c->d_tilesG, (int)p.tilesG.size(), 0, 0, c->stream));
     }
@@ -437,8 +437,9 @@ int64_t lqsgd_plan_tiles(const lqsgd_config* cfg, const lqsgd_layer* layers, int
       o[2] = t.row0;
       o[3] = t.nrows;
       if (as0) {
-        o[4] = t.aux * d.segw;
-        o[5] = std::min(d.cols, o[4] + d.segw) - o[4];
+        const int w = sweep == 3 ? kGhatCols : d.segw;
+        o[4] = t.aux * w;
+        o[5] = std::min(d.cols, o[4] + w) - o[4];
       } else {
         const int cw = bm ? kMfmaCols : sweep == 1 ? d.bcw : kWave * 4;
         o[4] = t.aux * cw;

@@ -114,8 +114,8 @@ hipError_t launch_write_pointers(const void** dst, const void* const* src, size_
 
 // Sweeps 0 and 2 on the matrix cores (rank pad 16, 32 or 64), over the work list of
 // sweep 0 (32-row items, at rank pad 64 of 64 rows).  mode: 0 = M = G + E and P partials, 1 = the same with the deferred
-// residual applied on the fly, 2 = residual, 3 = residual + G-hat, 4 = G-hat only (worker 0's items).
-// two: Plan::twoA / twoAG.
+// residual applied on the fly, 2 = residual, 3 = residual + G-hat, 4 = G-hat only, over a list of its own (Plan::tilesAG).
+// two: Plan::twoA, 0 for that list.
 hipError_t launch_mfma_sweep(int RP, int mode, const DevArgs& a, const Tile* tiles, int ntiles, int two, int reverse, hipStream_t s);
 
 }  // namespace lqsgd

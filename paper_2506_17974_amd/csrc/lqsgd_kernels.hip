@@ -2286,9 +2286,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) voi
 //   columns); it takes the same LDS tile the other way to meet G and M in row
 //   layout for  M_new = G + (M_old - G-hat).
 // Modes: kMAdd (first iteration: M = G + E), kMAddFused (deferred residual),
-// kMResidual / kMResidualGhat / kMGhatOnly (the residual sweep; G-hat uses the
-// very same instruction sequence as in kMAddFused, so deferring the residual
-// does not change a bit of the result).
+// kMResidual / kMResidualGhat (the residual sweep; G-hat uses the very same
+// instruction sequence as in kMAddFused and in mfma_ghat_kernel, which kMGhatOnly
+// launches, so deferring the residual does not change a bit of the result).
 // ---------------------------------------------------------------------------
 enum MfmaMode { kMAdd = 0, kMAddFused = 1, kMResidual = 2, kMResidualGhat = 3, kMGhatOnly = 4 };
 constexpr int kLP = 68;   // LDS pitch (floats): 16-byte aligned rows, 4-bank skew per row
@@ -2309,7 +2309,6 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
   float* lds = lds_all[wave];
   constexpr bool ADD = (MODE == kMAdd || MODE == kMAddFused);
   constexpr bool NEEDG = (MODE != kMAdd);
-  constexpr bool HASM = (MODE != kMGhatOnly);
   constexpr int KH = RP / 2;                       // ranks per half-wavefront
   constexpr int NB = (RP + 31) / 32;               // blocks of 32 ranks in the P product (2 at rank pad 64)
   // (the rows of Q and Pb hold RP ranks; r is only the row length of the P partials this item writes)
@@ -2361,10 +2360,10 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
       const size_t off = FULL ? (size_t)(row0 + 4 * i) * cols + c : (size_t)(row0 + min(rr, nrows - 1)) * cols;
       if constexpr (FULL) {
         if constexpr (ADD) g[i] = ldgrad<LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), lo);
-        if constexpr (HASM) e[i] = ldrow<(ADD ? NTS : LQSGD_NT_E != 0)>(reinterpret_cast<const char*>(M + off), lo);
+        e[i] = ldrow<(ADD ? NTS : LQSGD_NT_E != 0)>(reinterpret_cast<const char*>(M + off), lo);
       } else {
         if constexpr (ADD) g[i] = ldedge<KIND, LQSGD_NT_G != 0, GB16>(grad_row<GB16>(G, off), cl, cols);
-        if constexpr (HASM) e[i] = ldedge<KIND, (ADD ? NTS : LQSGD_NT_E != 0), false>(reinterpret_cast<const char*>(M + off), cl, cols);
+        e[i] = ldedge<KIND, (ADD ? NTS : LQSGD_NT_E != 0), false>(reinterpret_cast<const char*>(M + off), cl, cols);
       }
     }
     if constexpr (!FULL) {
@@ -2372,12 +2371,12 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           if constexpr (ADD) edge_fix<1>(g[i].v, cl, cols);
-          if constexpr (HASM) edge_fix<1>(e[i].v, cl, cols);
+          edge_fix<1>(e[i].v, cl, cols);
         }
       }
     }
     Pk<4> wp[8];                                 // the parameters to update
-    if constexpr (MODE == kMResidualGhat || MODE == kMGhatOnly) {
+    if constexpr (MODE == kMResidualGhat) {
       if (update && ghat_out) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -2448,10 +2447,8 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
       for (int i = 0; i < 8; ++i) {
         const int rr = 4 * i + sr_;
         const float4 t = *reinterpret_cast<const float4*>(lds + rr * kLP + c4);
-        if constexpr (HASM) {
-          e[i].v[0] -= t.x; e[i].v[1] -= t.y; e[i].v[2] -= t.z; e[i].v[3] -= t.w;
-        }
-        if (MODE == kMGhatOnly || (MODE == kMResidualGhat && ghat_out)) {
+        e[i].v[0] -= t.x; e[i].v[1] -= t.y; e[i].v[2] -= t.z; e[i].v[3] -= t.w;
+        if (MODE == kMResidualGhat && ghat_out) {
           if constexpr (FULL) {
             const Pk<4> o{{t.x, t.y, t.z, t.w}};
             emit_ghat<kAligned>(ghat_out + (size_t)(row0 + 4 * i) * cols + c, (int)(lo >> 2), 0, o, update, eta, wp[i]);
@@ -2463,21 +2460,19 @@ __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __
       }
       wave_lds_fence();
     }
-    if constexpr (HASM) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int rr = 4 * i + sr_;
-        Pk<4> m;
+    for (int i = 0; i < 8; ++i) {
+      const int rr = 4 * i + sr_;
+      Pk<4> m;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) m.v[v] = ADD ? g[i].v[v] + e[i].v[v] : e[i].v[v];
-        if constexpr (FULL)
-          strow<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + 4 * i) * cols + c), lo, m);
-        else if (rr < nrows)
-          stgroup<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + rr) * cols), (unsigned)cl * 4u, ncol, m);
+      for (int v = 0; v < 4; ++v) m.v[v] = ADD ? g[i].v[v] + e[i].v[v] : e[i].v[v];
+      if constexpr (FULL)
+        strow<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + 4 * i) * cols + c), lo, m);
+      else if (rr < nrows)
+        stgroup<NTS>(reinterpret_cast<char*>(M + (size_t)(row0 + rr) * cols), (unsigned)cl * 4u, ncol, m);
 
-        if constexpr (ADD)
-          *reinterpret_cast<float4*>(lds + rr * kLP + c4) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
-      }
+      if constexpr (ADD)
+        *reinterpret_cast<float4*>(lds + rr * kLP + c4) = make_float4(m.v[0], m.v[1], m.v[2], m.v[3]);
     }
     if constexpr (BQ_LATE) {
       __builtin_amdgcn_sched_barrier(0);
@@ -3554,20 +3549,163 @@ __global__ __launch_bounds__(256, RP <= 16 ? 2 : 1) void mfma_sweep_kernel(DevAr
   float* M = a.E + (size_t)worker * a.m_stride + ld.m_off;
   float* Pp = a.Ppart + (size_t)worker * a.ppart_stride + ld.ppart_off + (size_t)tl.aux * ld.np_pad;
   float* ghat_out = nullptr;
-  if ((MODE == kMResidualGhat || MODE == kMGhatOnly) && worker == 0 && a.ghat) ghat_out = a.ghat[ld.gidx];
-  if (MODE == kMGhatOnly && !ghat_out) return;
+  if (MODE == kMResidualGhat && worker == 0 && a.ghat) ghat_out = a.ghat[ld.gidx];
   const int col0 = tl.aux * ld.segw;
   const int col1 = min(ld.cols, col0 + ld.segw);
   if (ld.kind == kOneColumnPerLane) {            // eight of the item's rows per wavefront
     constexpr bool ADD = MODE == kMAdd || MODE == kMAddFused;
     const int nr = min(8, tl.nrows - 8 * wave);
     if (nr > 0)
-      narrow_rows<RP, 8, ADD, MODE == kMAddFused, MODE != kMGhatOnly, MODE == kMResidualGhat || MODE == kMGhatOnly, GB16>(
+      narrow_rows<RP, 8, ADD, MODE == kMAddFused, true, MODE == kMResidualGhat, GB16>(
           G, M, q_operand(a, ld), p_operand(a, ld), Pp, ghat_out, ld.cols, ld.r, tl.row0 + 8 * wave, nr, lane, a.update, a.eta);
     return;
   }
   mfma_tile<RP, MODE, GB16, NTS>(G, M, q_operand(a, ld), p_operand(a, ld), Pp, ghat_out, ld.cols, ld.r, tl.row0,
                                  tl.nrows, col0, col1, lane, wave, lds_all, a.update, a.eta);
+}
+
+// ---------------------------------------------------------------------------
+// The G-hat pass on the matrix cores: G-hat = P-bar Q-bar^T of one layer, or the
+// parameters it updates.  One workgroup per block of rows x 256 columns; a
+// wavefront keeps the rows of Q-bar of its 64 columns in registers and goes down
+// the rows 32 at a time.  The 32 rows of P-bar come once, coalesced, through LDS
+// for all four wavefronts, the next ones requested while these are multiplied.
+// (Sweep 2's blocks, which this pass used to share, fetch 64 rows of Q-bar for
+// every 32 x 64 of G-hat, 16 bytes of 64 rows at a time.)  The block leaves in
+// the matrix cores' own layout, 128 bytes of two rows a store, non-temporal
+// unless it is parameters that the next pass of the network reads (plain stores:
+// ResNet-18 set, r = 50 24.6 us, r = 32 16.3).  The products are those of
+// mfma_tile in the same order, so G-hat is what the other passes subtract, to
+// the last bit.  Blocks of sweep 2 / this kernel, us: ResNet-18 set, r = 50
+// 35.4 -> 22.3, r = 32 20.4 -> 14.2, r = 16 15.7 -> 12.4, ragged set, r = 20
+// 13.2 -> 9.2, 2 x (208 x 2000), r = 41 19.7 -> 9.0, 8192^2, r = 64 139 -> 85,
+// r = 32 67 -> 51.  Bound by the stores where items are many, else by the chain
+// of one item: tile, layer, factors, products, stores.
+// ---------------------------------------------------------------------------
+template <int RP, bool UPDATE>
+__global__ __launch_bounds__(256) void mfma_ghat_kernel(DevArgs a, const Tile* __restrict__ tiles) {
+  constexpr int KH = RP / 2, PITCH = RP + 4, F4 = (8 * RP + 255) / 256;      // pitch: 16 rows' reads of 16 bytes hit all banks once
+  __shared__ __attribute__((aligned(16))) float ps[2][32 * PITCH];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & (kWave - 1), tid = threadIdx.x;
+  const Tile tl = tiles[blockIdx.x];
+  const LayerDesc& ld = a.layers[tl.lw / a.W];
+  float* out = a.ghat ? a.ghat[ld.gidx] : nullptr;
+  if (!out) return;
+  const float* Q = q_operand(a, ld);
+  const float* Pb = p_operand(a, ld);
+  const int cols = ld.cols;
+  if (ld.kind == kOneColumnPerLane) {            // eight rows a wavefront at a time
+    for (int i = 8 * wave; i < tl.nrows; i += 32)
+      narrow_rows<RP, 8, false, false, false, true, false>(nullptr, nullptr, Q, Pb, nullptr, out, cols, ld.r, tl.row0 + i,
+                                                           min(8, tl.nrows - i), lane, a.update, a.eta);
+    return;
+  }
+  const int li = lane & 31, h = lane >> 5;
+  const int c = tl.aux * kGhatCols + 64 * wave;
+  // the block's rows of P-bar, 16 bytes a thread and request; the last one again where they end
+  const char* src = reinterpret_cast<const char*>(Pb + (size_t)tl.row0 * RP);
+  const int n4 = tl.nrows * (RP / 4);
+  Pk<4> x[F4];
+  auto request = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < F4; ++i) x[i] = ldrow<false>(src, (unsigned)min(t * 8 * RP + tid + 256 * i, n4 - 1) * 16u);
+  };
+  auto to_lds = [&](float* to) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < F4; ++i) {
+      const int e = tid + 256 * i;
+      if (8 * RP >= 256 || e < 8 * RP)
+        *reinterpret_cast<float4*>(to + e / (RP / 4) * PITCH + e % (RP / 4) * 4) = make_float4(x[i].v[0], x[i].v[1], x[i].v[2], x[i].v[3]);
+    }
+  };
+  request(0);
+  float qb[2][KH];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int first = min(c, cols - 1), col = min(32 * b + li, cols - 1 - first);
+#pragma unroll
+    for (int t = 0; t < KH / 4; ++t) {
+      const Pk<4> q = ldrow<false>(reinterpret_cast<const char*>(Q + (size_t)first * RP) + 16 * t, (unsigned)(col * RP + KH * h) * 4u);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) qb[b][4 * t + v] = q.v[v];
+    }
+  }
+  to_lds(ps[0]);
+  __syncthreads();
+  const int nt = (tl.nrows + 31) / 32;
+  const bool small = cols < (1 << 26);           // byte offsets within 8 rows fit 32 bits
+  unsigned lane_off = (unsigned)(4 * h * cols + li) * 4u;
+  for (int t = 0; t < nt; ++t) {
+    if (t + 1 < nt) request(t + 1);
+    const int left = tl.nrows - 32 * t;
+    float* o = out + (size_t)(tl.row0 + 32 * t) * cols + c;
+    const bool whole = left >= 32 && c + 64 <= cols && small;
+    if (c < cols) {
+      float w[UPDATE ? 2 : 1][16];
+      auto parameters = [&](auto whole_tag) __attribute__((always_inline)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            const int row = 8 * (v >> 2) + (v & 3);
+            if constexpr (decltype(whole_tag)::value) {
+              w[b][v] = *gptr<const float>(reinterpret_cast<const char*>(o + (size_t)row * cols + 32 * b) + lane_off);
+            } else {
+              const size_t at = (size_t)min(row + 4 * h, left - 1) * cols + min(32 * b + li, cols - 1 - c);
+              w[b][v] = o[at];
+            }
+          }
+      };
+      if constexpr (UPDATE) {
+        if (whole) parameters(std::true_type{}); else parameters(std::false_type{});
+      }
+      float pa[KH];
+#pragma unroll
+      for (int k = 0; k < KH / 4; ++k) {
+        const float4 p = *reinterpret_cast<const float4*>(ps[t & 1] + li * PITCH + KH * h + 4 * k);
+        pa[4 * k] = p.x; pa[4 * k + 1] = p.y; pa[4 * k + 2] = p.z; pa[4 * k + 3] = p.w;
+      }
+      v16f gh[2];
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) gh[b][i] = 0.0f;
+#pragma unroll
+      for (int k = 0; k < KH; ++k)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) gh[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[k], qb[b][k], gh[b], 0, 0, 0);
+      if constexpr (UPDATE) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) gh[b][v] = fmaf(-a.eta, gh[b][v], w[b][v]);
+      }
+      if (whole) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            char* at = reinterpret_cast<char*>(o + (size_t)(8 * (v >> 2) + (v & 3)) * cols + 32 * b);
+            asm volatile("" : "+v"(lane_off));   // (one offset for all rows, not a 64-bit address for each)
+            if constexpr (!UPDATE) __builtin_nontemporal_store(gh[b][v], gptr<float>(at + lane_off));
+            else *gptr<float>(at + lane_off) = gh[b][v];
+          }
+      } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int row = 8 * (v >> 2) + 4 * h + (v & 3);
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+            if (row < left && c + 32 * b + li < cols) o[(size_t)row * cols + 32 * b + li] = gh[b][v];
+        }
+      }
+    }
+    if (t + 1 < nt) {
+      to_lds(ps[(t + 1) & 1]);
+      __syncthreads();
+    }
+  }
 }
 
 // Copies of the aggregated factors with rows of RP ranks (zero beyond the layer's rank), as the sweeps
@@ -4534,7 +4672,11 @@ hipError_t launch_mfma_sweep_rp(int mode, const DevArgs& a, const Tile* tiles, i
     case kMAddFused: launch_mfma_add<RP, kMAddFused>(a, tiles, ntiles, two, reverse, s); return hipGetLastError();
     case kMResidual: mfma_sweep_kernel<RP, kMResidual><<<grid, block, 0, s>>>(a, tiles, ntiles, two, reverse); break;
     case kMResidualGhat: mfma_sweep_kernel<RP, kMResidualGhat><<<grid, block, 0, s>>>(a, tiles, ntiles, two, reverse); break;
-    case kMGhatOnly: mfma_sweep_kernel<RP, kMGhatOnly><<<grid, block, 0, s>>>(a, tiles, ntiles, two, reverse); break;
+    case kMGhatOnly:
+      if (a.update) mfma_ghat_kernel<RP, true><<<dim3(ntiles), block, 0, s>>>(a, tiles);
+      else mfma_ghat_kernel<RP, false><<<dim3(ntiles), block, 0, s>>>(a, tiles);
+      note_kernel("mfma_ghat_kernel<%d, %s>", RP, tf(a.update));
+      return hipGetLastError();
     default: return hipErrorInvalidValue;
   }
   note_kernel("mfma_sweep_kernel<%d, %d, false, false>", RP, mode);

@@ -255,6 +255,17 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
     return (int32_t)(1024 * std::min<int64_t>(8, std::max<int64_t>(1, total * W / (1024 * 512))));
   };
   const int32_t rq_chunk = reduce_chunk(true), rp_chunk = reduce_chunk(false);
+  // Rows of an item of the G-hat pass on the matrix cores: 32 where that leaves few items for a CU, as many as save operand reads
+  // where there are plenty (us at 32 / 64 / 128 rows: 100 x 300, 20 of them, r = 50, 160 items of 32 rows, 8.8 / 11.4 / 16.5; 1024^2, 6 of
+  // them, r = 64, 768 15.0 / 16.5 / 17.6; ResNet-18 set, 1360, r = 50 25.8 / 22.3 / 25.9, r = 32 16.0 / 14.2 / 16.5; 11008 x 4096,
+  // 5504, r = 32 44.8 / 38.1 / 36.7; 8192^2, 8192, r = 64 108 / 88 / 86; rank pad 16 reads half as much: ResNet-18 set 12.4 / 13.1 /
+  // 12.9, 8192^2 43 / 45 / 48).
+  auto ghat_items = [&](int64_t rows) {
+    int64_t n = 0;
+    for (const LayerDesc& d : layers) n += ((d.rows + rows - 1) / rows) * ((d.cols + kGhatCols - 1) / kGhatCols);
+    return n;
+  };
+  const int32_t rows_g = (int32_t)env_i64("LQSGD_TILE_AG", RP <= 16 || ghat_items(32) < 1024 ? 32 : ghat_items(64) < 2048 ? 64 : 128);
   for (int li = 0; li < L; ++li) {
     LayerDesc& d = layers[li];
     // Groups of rows per item.  Counted in whole passes of 256 columns, a row of 21 costs a pass like one of 256, and a
@@ -309,7 +320,6 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
       for (int32_t row0 = 0; row0 < d.rows; row0 += trows)
         for (int32_t s = 0; s < d.nseg; ++s) {
           tilesA.push_back(Tile{lw, row0, std::min(trows, d.rows - row0), s});
-          if (w == 0) tilesAG.push_back(tilesA.back());
         }
       for (int32_t rb = 0; rb < nrb_v; ++rb)
         for (int32_t ch = 0; ch < nchunk_b; ++ch)
@@ -321,6 +331,8 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
           for (int32_t ch = 0; ch < nchunk; ++ch)
             tilesR.push_back(Tile{lw, row0, std::min(rbr, d.rows - row0), ch});
       }
+      for (int32_t row0 = 0; w == 0 && mfma_a && row0 < d.rows; row0 += rows_g)
+        for (int32_t s = 0; s * kGhatCols < d.cols; ++s) tilesAG.push_back(Tile{lw, row0, std::min(rows_g, d.rows - row0), s});
       if (w == 0) {
         const int32_t rbg = (int32_t)std::min<int64_t>(round_up(std::max<int64_t>(1, tgtG / (d.kind == 2 ? kWave : cw)), 4), round_up(d.rows, 4));
         for (int32_t row0 = 0; row0 < d.rows; row0 += rbg)
@@ -343,7 +355,7 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
   // the last ones are short (sweep 0 forwards, as it runs there with the deferred residual, us, in the layers' order / sorted: ragged
   // set, r = 20, W = 4 50 / 44; ResNet-18 set, W = 8, r = 50 271 / 260, r = 32 215 / 211).  Items of more than 32 rows before the
   // others (HalfItem).
-  twoA = twoAG = 0;
+  twoA = 0;
   if (mfma) {
     auto two = [](const Tile& t) { return t.nrows > 32; };
     auto width = [&](const Tile& t) {
@@ -353,9 +365,7 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
     std::stable_sort(tilesA.begin(), tilesA.end(), [&](const Tile& x, const Tile& y) {
       return two(x) != two(y) ? two(x) : width(x) > width(y);
     });
-    std::stable_partition(tilesAG.begin(), tilesAG.end(), two);
     twoA = (int32_t)std::count_if(tilesA.begin(), tilesA.end(), two);
-    twoAG = (int32_t)std::count_if(tilesAG.begin(), tilesAG.end(), two);
   }
 
   m_stride = round_up(m_acc, 64);

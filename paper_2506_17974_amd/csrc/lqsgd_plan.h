@@ -13,6 +13,7 @@ namespace lqsgd {
 
 constexpr int kWave = 64;
 constexpr int kRowsPerGroup = 8;   // rows a wavefront carries through one column pass of sweep 0
+constexpr int kGhatCols = 256;     // columns of an item of the G-hat pass on the matrix cores
 constexpr int kMfmaCols = 512;     // columns one workgroup of the matrix-core sweep 1 covers (4 waves x 4 strips x 32)
 constexpr int kXGroup = 8;         // elements one lane quantises / packs (b bytes + 1 sign byte)
 constexpr int kXBlockGroups = 32;  // groups of 8 elements one exchange workgroup covers
@@ -92,8 +93,8 @@ struct Plan {
   std::vector<int32_t> kind_of;    // per caller index: >= 0 matrix index, < 0 -(vector index) - 1
   std::vector<Tile> tilesA, tilesB;
   std::vector<Tile> tilesR;        // residual sweep of the vector path: row block x 256 columns, all workers
-  std::vector<Tile> tilesAG;       // worker 0's items of tilesA (G-hat pass of the matrix-core path)
-  int32_t twoA = 0, twoAG = 0;     // rank pad 64: items of more than 32 rows, the first ones of these lists
+  std::vector<Tile> tilesAG;       // G-hat pass of the matrix-core path: worker 0, a block of rows x kGhatCols
+  int32_t twoA = 0;                // rank pad 64: items of more than 32 rows, the first ones of tilesA
   std::vector<Tile> tilesBM;       // sweep 1 on the matrix cores (rank pads 32 and 64): row block x 512-column group
   std::vector<Tile> tilesG;        // one pass over every layer of worker 0 (G-hat only): row block x 256 columns
   std::vector<XTile> tilesXP, tilesXQ;

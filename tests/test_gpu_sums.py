@@ -627,3 +627,40 @@ def test_store_policy_of_mixed_sets(layers, rank, first, later):
         assert comp.launched_kernel(0).endswith(want), comp.launched_kernel(0)
     comp.close()
     _schedules(layers, rank, 2, "", iterations=2)
+
+
+# the G-hat pass of rank pads 16 to 64 beside the eager schedule's, which takes G-hat from the residual sweep: edges of its 32 rows and
+# 64 and 256 columns, rows that are no multiple of four, one column a lane (21), and sets whose items are 64 and 128 rows
+GHAT_EDGES = [(1, 300), (31, 63), (32, 64), (33, 65), (97, 255), (64, 256), (70, 257), (130, 513), (40, 21), (300, 1), (65, 4)]
+
+
+@pytest.mark.parametrize("update", [False, True])
+@pytest.mark.parametrize("rank,layers", [(r, GHAT_EDGES) for r in (9, 16, 27, 32, 41, 64)] +
+                         [(r, [(2111, 4100), (65, 130)]) for r in (12, 32, 50)] + [(r, [(4097, 8200)]) for r in (20, 64)])
+def test_ghat_pass_writes_what_the_residual_sweep_subtracts(rank, layers, update):
+    import torch
+    _say("case: G-hat pass", rank, layers[:3], update)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rank)
+    G = [[torch.randn(s, generator=gen, device="cuda") * 1e-3 for s in layers]]
+    Q = [np.random.default_rng(rank).standard_normal((c, min(rank, r, c))).astype(f32) for r, c in layers]
+    start = [torch.randn(s, generator=gen, device="cuda") for s in layers]
+    got = []
+    for flags in (0, B.FLAG_EAGER_RESIDUAL):
+        comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, 1, 255.0, flags)
+        for l, q in enumerate(Q):
+            comp.set_q(l, q)
+        flat = torch.full((sum(t.numel() + 128 for t in start) + 64,), 7.0, device="cuda")
+        out, at = [], 64
+        for t in start:                          # (with untouched values around every layer's)
+            out.append(flat[at:at + t.numel()].view(t.shape))
+            out[-1].copy_(t)
+            at += -(-t.numel() // 64) * 64 + 64
+        for _ in range(2):
+            comp.step_update(G, out, 0.1) if update else comp.step(G, out)
+        comp.synchronize()
+        if flags == 0:
+            assert comp.launched_kernel(B.KERNEL_RESIDUAL).startswith("mfma_ghat_kernel")
+        got.append(flat.cpu().numpy())
+        comp.close()
+    assert np.array_equal(got[0], got[1])
