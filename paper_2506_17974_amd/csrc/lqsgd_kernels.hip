@@ -1877,10 +1877,19 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 // set, r = 50, W = 8 168 -> 162 us, 8 x (512 x 4608), r = 64 238 -> 211, 16 x 1024^2 185 -> 173, 8192^2, W = 8 663 - 689 ->
 // 633 - 644.)  NB = 1: straight from L2, one request beside one (through LDS 16 x 1024^2, W = 8 128 -> 136 us,
 // ResNet-18 set 92 -> 90).
+__device__ __forceinline__ void wave_lds_fence() {
+  // LDS traffic between the lanes of one wavefront: the hardware keeps DS
+  // operations of a wavefront in order; this only stops the compiler.
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 constexpr int kPRows = 256;
+// Rank pad 64: whether the list is one that waits for single items (see the end of back_project_mfma_tile).
+__device__ __forceinline__ bool few_items() { return gridDim.x <= 512; }
 template <int NB, int KIND, bool SHORT, typename Enter>
 __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const LayerDesc& ld, const Tile& tl, int worker,
-                                                       int c0, int lane, const float* ps, Enter&& enter) {
+                                                       int c0, int lane, const float* ps, float* stage, Enter&& enter) {
   constexpr int U = LQSGD_BM_U;                     // pairs of rows per step
   constexpr bool SHARE = NB == 2;
   static_assert(kPRows % (2 * U) == 0, "");
@@ -1997,23 +2006,33 @@ __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const L
     last_group(rb, am, bp);
   }
   }
-  float* Qp = a.Qpart + (size_t)worker * a.qpart_stride + ld.qpart_off + (size_t)(tl.row0 / ld.rbb) * ld.nq_pad;
-  // Value v of component s is column c0 + 32 (v / 4) + 4 (v % 4) + s + 16 h.
-  if constexpr (SHORT || KIND != kAligned) {
+  // Where the sums leave: straight from the registers, 4 bytes a lane, or through LDS, 64 columns at a time, whose rows of r ranks are
+  // one run of memory there as in Q_w or its partial plane, so that a store is 1 KiB and there are no tests but at its end.  With an
+  // address and a test of its own for each of the 64 NB values the register form was a fifth of an item of 256 rows, and most of the
+  // code, which a short item runs once.  Whole strips of long items at rank pad 64 do without both (a wave-uniform row of Q_w plus
+  // one byte offset a lane; sweep 1, us, ResNet-18 set, W = 8, r = 50 156 -> 130, 12 x (512 x 4608) 313 -> 292, 8192^2, W = 4, r = 64
+  // 323 -> 308; through LDS, behind a barrier of the workgroup, 149, 297 and 310).  The others go through LDS, at rank pad 64 in lists of up
+  // to 512 items, which wait for single items (a step, us, r = 50, W = 8 registers / LDS: 20 x (100 x 300) 130.5 / 129.3, 64 x 512, 30 of
+  // them 113.2 / 111.7; but the ResNet-18 set, 1800 items, 476 / 488, for the barrier).
+  // Where a layer has one row block these are the sums themselves, and their absmax is taken here, a pass over a copy less (a step:
+  // ResNet-18 set, W = 8, r = 50 482 -> 476, r = 32 350 -> 347, 8 x (256 x 4096), r = 50 366 -> 349, 2 x (60 x 300), r = 20 48.3 -> 44.7).
+  const bool through_lds = NB == 1 || few_items();
+  if (SHARE && through_lds) __syncthreads();     // (the rows of P-bar make room)
+  const bool direct = ld.direct_q != 0;
+  float* Qp = direct ? a.Qw + (size_t)worker * a.q_stride + ld.q_off
+                     : a.Qpart + (size_t)worker * a.qpart_stride + ld.qpart_off + (size_t)(tl.row0 / ld.rbb) * ld.nq_pad;
+  float mx = 0.0f;
+  auto absmax = [&]() __attribute__((always_inline)) {           // (values beyond the columns or ranks are zeros)
+    if (direct) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+      for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
+        for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int col = c0 + 4 * (8 * (v >> 2) + 4 * h + (v & 3)) + s;
-          if (col < cols && 32 * nb + li < r) Qp[(size_t)col * r + 32 * nb + li] = acc[nb][s][v];
-        }
-  } else {
-    // Whole strips of items that are not over after a few groups: a wave-uniform row of Q_w plus one byte offset a lane, no tests.
-    // With an address and a test of its own for each of the 64 NB values the stores were a fifth of an item of 256 rows (sweep 1, us:
-    // ResNet-18 set, W = 8, r = 50 156 -> 130, 12 x (512 x 4608) 313 -> 294, 3 of them at r = 32 63 -> 60, 8192^2, W = 4, r = 64
-    // 323 -> 313; short items are no faster for it where they are few: 20 x (100 x 300), r = 50 26.1 / 26.9).
+          for (int v = 0; v < 16; ++v) mx = fmaxf(mx, fabsf(acc[nb][s][v]));
+    }
+  };
+  if constexpr (NB == 2 && !SHORT && KIND == kAligned) {
     unsigned lane_off = (unsigned)(16 * h * r + li) * 4u;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
@@ -2028,6 +2047,58 @@ __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const L
             *gptr<float>(at + lane_off) = acc[nb][s][v];
           }
       }
+    absmax();
+  } else if (!through_lds) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int col = c0 + 4 * (8 * (v >> 2) + 4 * h + (v & 3)) + s;
+          if (col < cols && 32 * nb + li < r) Qp[(size_t)col * r + 32 * nb + li] = acc[nb][s][v];
+        }
+    absmax();
+  } else {
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int c = c0 + 64 * half;
+      if (c < cols) {
+        wave_lds_fence();
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+          if (32 * nb + li < r) {
+            float* to = stage + 16 * h * r + 32 * nb + li;
+#pragma unroll
+            for (int v = 8 * half; v < 8 * half + 8; ++v)
+#pragma unroll
+              for (int s = 0; s < 4; ++s) to[(32 * ((v >> 2) & 1) + 4 * (v & 3) + s) * r] = acc[nb][s][v];
+          }
+        wave_lds_fence();
+        const int n = min(64, cols - c) * r;
+        float* dst = Qp + (size_t)c * r;
+#pragma unroll 4
+        for (int e = 4 * lane; e < n; e += 4 * kWave) {
+          const float4 t = *reinterpret_cast<const float4*>(stage + e);
+          if (e + 4 <= n) {
+            *reinterpret_cast<float4*>(dst + e) = t;
+            mx = fmaxf(mx, fmaxf(fmaxf(fabsf(t.x), fabsf(t.y)), fmaxf(fabsf(t.z), fabsf(t.w))));
+          } else {
+            const float x[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+              if (e + q < n) {
+                dst[e + q] = x[q];
+                mx = fmaxf(mx, fabsf(x[q]));
+              }
+          }
+        }
+      }
+    }
+  }
+  if (direct) {
+    mx = wave_max(mx);
+    if (lane == 0) atomicMax(reinterpret_cast<unsigned int*>(a.scaleQ + (size_t)worker * a.L + tl.lw / a.W), __float_as_uint(mx));
   }
 }
 
@@ -2044,15 +2115,19 @@ __global__ __launch_bounds__(256, 2) void back_project_mfma_kernel(DevArgs a, co
   const int layer = tl.lw / a.W, worker = tl.lw - layer * a.W;
   const LayerDesc& ld = a.layers[layer];
   const int c0 = tl.aux * kMfmaCols + wave * 128;
+  // rows of P-bar (NB = 2), at the end 64 columns' sums of each wavefront
+  constexpr int STAGE = 64 * 32 * NB;
+  static_assert(kPRows * 32 * NB >= 4 * STAGE, "");
+  __shared__ __attribute__((aligned(16))) float ps[NB == 2 ? kPRows * 32 * NB : 4 * STAGE];
+  float* stage = ps + wave * STAGE;
   // strips of which all 128 columns exist need no care at their end, whatever the alignment of the rows
   auto run = [&](auto short_tag, const float* ps, auto&& enter) __attribute__((always_inline)) {
     constexpr bool SHORT = decltype(short_tag)::value;
-    if (c0 + 128 <= ld.cols) back_project_mfma_tile<NB, kAligned, SHORT>(a, ld, tl, worker, c0, lane, ps, enter);
-    else if (ld.cols >= 4) back_project_mfma_tile<NB, kRagged, SHORT>(a, ld, tl, worker, c0, lane, ps, enter);
-    else back_project_mfma_tile<NB, kNarrow, SHORT>(a, ld, tl, worker, c0, lane, ps, enter);
+    if (c0 + 128 <= ld.cols) back_project_mfma_tile<NB, kAligned, SHORT>(a, ld, tl, worker, c0, lane, ps, stage, enter);
+    else if (ld.cols >= 4) back_project_mfma_tile<NB, kRagged, SHORT>(a, ld, tl, worker, c0, lane, ps, stage, enter);
+    else back_project_mfma_tile<NB, kNarrow, SHORT>(a, ld, tl, worker, c0, lane, ps, stage, enter);
   };
   if constexpr (NB == 2) {
-    __shared__ __attribute__((aligned(16))) float ps[kPRows * 32 * NB];
     const int tid = threadIdx.x, rend = tl.row0 + tl.nrows;
     // rows of P-bar are contiguous: a linear copy, 16 bytes a thread and request
     auto enter = [&](int row) __attribute__((always_inline)) {
@@ -2080,7 +2155,10 @@ __global__ __launch_bounds__(256, 2) void back_project_mfma_kernel(DevArgs a, co
     };
     if (c0 < ld.cols && tl.nrows < 128) run(std::true_type{}, ps, enter);
     else if (c0 < ld.cols) run(std::false_type{}, ps, enter);
-    else for (int row = tl.row0; row < rend; row += kPRows) enter(row);   // no columns: only its share of the copies
+    else {                                       // no columns: only its share of the copies
+      for (int row = tl.row0; row < rend; row += kPRows) enter(row);
+      if (few_items()) __syncthreads();          // (the others' before they hand out their sums)
+    }
   } else {
     if (c0 < ld.cols) run(std::false_type{}, nullptr, [](int) {});
   }
@@ -2293,12 +2371,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 8))) voi
 enum MfmaMode { kMAdd = 0, kMAddFused = 1, kMResidual = 2, kMResidualGhat = 3, kMGhatOnly = 4 };
 constexpr int kLP = 68;   // LDS pitch (floats): 16-byte aligned rows, 4-bank skew per row
 
-__device__ __forceinline__ void wave_lds_fence() {
-  // LDS traffic between the lanes of one wavefront: the hardware keeps DS
-  // operations of a wavefront in order; this only stops the compiler.
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 
 template <int RP, int MODE, bool GB16, bool NTS>
 __device__ __forceinline__ void mfma_tile(const float* __restrict__ G, float* __restrict__ M,

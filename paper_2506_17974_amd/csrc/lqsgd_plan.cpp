@@ -295,14 +295,14 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
       d.rbb = rbb_v;
     }
     d.nrb = (d.rows + d.rbb - 1) / d.rbb;
-    d.direct_q = (!mfma && d.nrb == 1) ? 1 : 0;
+    d.direct_q = d.nrb == 1 ? 1 : 0;
     const int nchunk = (d.cols + cw - 1) / cw, nchunk_b = (d.cols + d.bcw - 1) / d.bcw;
 
     d.m_off = m_acc;   m_acc += round_up((int64_t)d.rows * d.cols, 64);
     d.p_off = p_acc;   p_acc += round_up(d.np_el, 64);
     d.q_off = q_acc;   q_acc += round_up(d.nq_el, 64);
     d.ppart_off = pp_acc; pp_acc += (int64_t)d.nseg * d.np_pad;
-    d.qpart_off = qp_acc; qp_acc += d.direct_q ? 0 : (int64_t)d.nrb * d.nq_pad;   // no partial planes where sweep 1 stores Q_w itself
+    d.qpart_off = qp_acc; qp_acc += d.direct_q && !mfma ? 0 : (int64_t)d.nrb * d.nq_pad;   // no partial planes where sweep 1 stores Q_w itself (rank pads 32 and 64 keep the room: Gram-Schmidt has a use for it)
     d.pop_off = ppd_acc; ppd_acc += round_up((int64_t)d.rows * RP, 64);
     d.qop_off = qpd_acc; qpd_acc += round_up((int64_t)d.cols * RP, 64);
     if (d.r < RP) padded = true;

@@ -664,3 +664,34 @@ def test_ghat_pass_writes_what_the_residual_sweep_subtracts(rank, layers, update
         got.append(flat.cpu().numpy())
         comp.close()
     assert np.array_equal(got[0], got[1])
+
+
+# rank pads 32 and 64: layers of one row block, whose sums and absmax sweep 1 stores itself, beside taller ones; strips of 128 columns that
+# end early, ranks clipped by a layer; lists of few items and of many
+SWEEP_ONE = [(5, 640), (64, 130), (63, 1), (100, 300), (128, 512), (256, 257), (300, 1025), (97, 60)]
+
+
+@pytest.mark.parametrize("rank,copies,W", [(20, 1, 2), (32, 1, 1), (32, 12, 4), (33, 1, 2), (50, 1, 2), (50, 12, 4), (64, 1, 1)])
+def test_sweep_one_stores_sums_and_absmax(rank, copies, W):
+    import torch
+    _say("case: sweep 1, sums and absmax", rank, copies, W)
+    layers = SWEEP_ONE * copies
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rank + copies)
+    comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, W)
+    rng = np.random.default_rng(rank)
+    for l, (r, c) in enumerate(layers):
+        comp.set_q(l, rng.standard_normal((c, min(rank, r, c))).astype(f32))
+    G = [[torch.randn(s, generator=gen, device="cuda") * 1e-3 for s in layers] for _ in range(W)]
+    comp.compress(B.PHASE_P, G)
+    comp.decompress(B.PHASE_P)
+    comp.compress(B.PHASE_Q)
+    for l in list(range(8)) + list(range(len(layers) - 8, len(layers))):
+        p = comp.get_factor(B.FACTOR_P_BAR, l).astype(np.float64)
+        for w in range(W):
+            q = comp.get_factor(B.FACTOR_Q_W, l, w)
+            m = G[w][l].cpu().numpy().astype(np.float64)
+            bound = (np.abs(m).T @ np.abs(p)) * (m.shape[0] + 2) * 2.0 ** -24          # a sum of that many terms, in any order
+            assert (np.abs(q - m.T @ p) <= bound + 1e-30).all(), (l, w)
+            assert comp.get_packet(B.PHASE_Q, l, w)[2] == np.abs(q).max(), (l, w)
+    comp.close()
