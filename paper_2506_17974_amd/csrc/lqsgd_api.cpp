@@ -43,6 +43,7 @@ struct lqsgd_ctx {
   bool pending = false;     // E buffer holds M; E = M - P-bar Q-bar^T not applied yet
   CoopState coop;           // one-launch Gram-Schmidt: launch count, device capacity, wait bound
   int* status = nullptr;    // pinned, device-visible: non-zero once a bounded device-side wait has expired
+  char* bounce = nullptr;   // kBounceBytes of pinned memory behind it (fetch)
   std::string err;
   std::vector<void*> allocs;
   // When set, device memory is carved out of this caller-provided block instead of being allocated
@@ -153,6 +154,19 @@ int sync_stream(lqsgd_ctx* c) {
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   if (c->status && *static_cast<volatile int*>(c->status) != 0)
     return fail(c, LQSGD_EHIP, "a device-side barrier wait expired; results of this context are invalid");
+  return LQSGD_OK;
+}
+
+// Device values for the host, once the stream is done.  Up to kBounceBytes they are copied behind the work on the stream into pinned
+// memory and from there, with one wait for both: a factor of 16 KB 17 -> 12 us, of 64 KB 34 -> 11, and about 10 less where the stream is still
+// at work; of 512 KB and more the runtime's own staging is as fast.
+constexpr size_t kBounceBytes = 256 << 10;
+int fetch(lqsgd_ctx* c, void* host, const void* src, size_t bytes) {
+  const bool bounce = c->bounce && bytes <= kBounceBytes;
+  if (bounce) HIP_TRY(c, hipMemcpyAsync(c->bounce, src, bytes, hipMemcpyDeviceToHost, c->stream));
+  if (int rcs = sync_stream(c)) return rcs;
+  if (bounce) std::memcpy(host, c->bounce, bytes);
+  else HIP_TRY(c, hipMemcpy(host, src, bytes, hipMemcpyDeviceToHost));
   return LQSGD_OK;
 }
 
@@ -588,9 +602,10 @@ int setup_device(lqsgd_ctx* c, uint32_t flags) {
   if (!ext) {
     TRY_(dev_alloc(c, &a.orth_table, orth_cells, true));
     void* hp = nullptr;
-    hipError_t e = hipHostMalloc(&hp, sizeof(int), hipHostMallocDefault);
+    hipError_t e = hipHostMalloc(&hp, 256 + kBounceBytes, hipHostMallocDefault);      // status word, memory for fetch()
     if (e != hipSuccess) { fail_hip(c, e, "hipHostMalloc"); return LQSGD_ENOMEM; }
     c->status = static_cast<int*>(hp);
+    c->bounce = static_cast<char*>(hp) + 256;
     *c->status = 0;
     a.status = c->status;
   }
@@ -950,9 +965,7 @@ int lqsgd_get_factor(lqsgd_ctx* c, int32_t which, int32_t layer, int32_t worker,
     const int k = c->plan.kind_of[layer];
     if (k >= 0) return fail(c, LQSGD_ESHAPE, "layer is not a VECTOR layer");
     const VecDesc& vd = c->plan.vecs[-k - 1];
-    if (int rcs = sync_stream(c)) return rcs;
-    HIP_TRY(c, hipMemcpy(host, a.vmean + vd.off, (size_t)vd.len * sizeof(float), hipMemcpyDeviceToHost));
-    return LQSGD_OK;
+    return fetch(c, host, a.vmean + vd.off, (size_t)vd.len * sizeof(float));
   }
   const LayerDesc* ld = nullptr;
   int rc = check_matrix_layer(c, layer, &ld);
@@ -974,9 +987,7 @@ int lqsgd_get_factor(lqsgd_ctx* c, int32_t which, int32_t layer, int32_t worker,
     case LQSGD_FACTOR_Q_BAR: src = a.Qbar + ld->q_off; n = ld->nq_el; break;
     default: return fail(c, LQSGD_EINVAL, "unknown factor id");
   }
-  if (int rcs = sync_stream(c)) return rcs;
-  HIP_TRY(c, hipMemcpy(host, src, n * sizeof(float), hipMemcpyDeviceToHost));
-  return LQSGD_OK;
+  return fetch(c, host, src, n * sizeof(float));
 }
 
 int lqsgd_set_factor(lqsgd_ctx* c, int32_t which, int32_t layer, const float* host) {
