@@ -1674,7 +1674,7 @@ __global__ __launch_bounds__(256) void exchange_kernel(DevArgs a, const XTile* _
 // Columns a lane of sweep 1 holds.
 template <int KIND>
 constexpr int lane_cols() { return KIND == kNarrow ? 1 : 4; }
-template <int RP, int KIND>
+template <int RP, int KIND, bool WHOLE_GROUP>
 __device__ __forceinline__ void back_project_rows(const float* __restrict__ M, const float* Pb, int cols,
                                                   int ra, int rb, int c, float (&acc)[lane_cols<KIND>() * RP]) {
   constexpr int U = LQSGD_B_U, V = lane_cols<KIND>();
@@ -1702,6 +1702,34 @@ __device__ __forceinline__ void back_project_rows(const float* __restrict__ M, c
       for (int v = 0; v < V; ++v)
 #pragma unroll
         for (int k = 0; k < RP; ++k) acc[v * RP + k] = fmaf(m[u].v[v], p[k], acc[v * RP + k]);
+    }
+  }
+  if constexpr (WHOLE_GROUP) {
+    // The last, partial group in flight as a whole, from three rows on: those beyond it repeat its last one and are left out.  One at
+    // a time, each a trip to memory, they were most of a small item (a step, us: 731 x 300 and 300 x 600, r = 7, W = 3 47.2 -> 45.4;
+    // 401 x 400, 3 of them, r = 6, W = 9 54.3 -> 52.5; 1000^2, 8 of them, r = 8, W = 8 245 -> 240).  Lower rank pads lose a wavefront
+    // a SIMD to its registers (3001 x 5000, r = 4, W = 4 410 -> 414) and gain nothing.
+    if (rb - i > 2) {
+      Pk<V> m[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) m[u] = load(min(i + u, rb - 1));
+      if constexpr (KIND == kRagged) {
+        if (c + 4 > cols) {
+#pragma unroll
+          for (int u = 0; u < U; ++u) edge_fix<1>(m[u].v, c, cols);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (i + u < rb) {
+          float p[RP];
+          load_row_uniform<RP>(Pb, i + u, p);
+#pragma unroll
+          for (int v = 0; v < V; ++v)
+#pragma unroll
+            for (int k = 0; k < RP; ++k) acc[v * RP + k] = fmaf(m[u].v[v], p[k], acc[v * RP + k]);
+        }
+      i = rb;
     }
   }
   for (; i < rb; ++i) {
@@ -1740,9 +1768,9 @@ __device__ __forceinline__ void back_project_tile(const DevArgs& a, const LayerD
       // hundreds of rows apart read the 8192^2 set at 6.0 TB/s, interleaved at 6.6 TB/s).
       const int rend = tl.row0 + tl.nrows;
       for (int g0 = tl.row0 + wave * LQSGD_B_U; g0 < rend; g0 += 4 * LQSGD_B_U)
-        back_project_rows<RP, KIND>(M, Pb, cols, g0, min(g0 + LQSGD_B_U, rend), c, acc);
+        back_project_rows<RP, KIND, false>(M, Pb, cols, g0, min(g0 + LQSGD_B_U, rend), c, acc);
     } else {
-      back_project_rows<RP, KIND>(M, Pb, cols, ra, rb, c, acc);
+      back_project_rows<RP, KIND, RP >= 8>(M, Pb, cols, ra, rb, c, acc);
     }
   }
   // A layer whose rows fit one row block: this item holds the whole sum, Q_w is stored directly
