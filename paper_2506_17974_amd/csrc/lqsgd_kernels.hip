@@ -260,6 +260,15 @@ __device__ __forceinline__ void load_slice(const float* __restrict__ F, int c, f
     s[4 * i + 0] = t.x; s[4 * i + 1] = t.y; s[4 * i + 2] = t.z; s[4 * i + 3] = t.w;
   }
 }
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order.
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
 // Row of a rows x r factor into p[k] (zero beyond r), plain loads.
 template <int RP>
 __device__ __forceinline__ void load_row(const float* __restrict__ F, int row, int r, bool exact, float (&p)[RP]) {
@@ -272,6 +281,17 @@ __device__ __forceinline__ void load_row(const float* __restrict__ F, int row, i
 #pragma unroll
     for (int k = 0; k < RP; ++k) p[k] = keep_if(b[k], k < r);
   }
+}
+
+// The first r of the RP values to one place, in one store (RP <= 4).
+template <int RP>
+__device__ __forceinline__ void store_row(float* to, int r, const float (&p)[RP]) {
+  static_for<RP>([&](auto n) __attribute__((always_inline)) {
+    if (r == n.value + 1) {
+#pragma unroll
+      for (int k = 0; k <= n.value; ++k) to[k] = p[k];
+    }
+  });
 }
 
 // Wave-uniform row of a factor operand written by an earlier kernel: scalar loads.
@@ -307,6 +327,32 @@ __device__ __forceinline__ void transpose_reduce(float (&v)[NT], int lane) {
   }
 }
 
+// Sums over the lanes of a wavefront, partners 32, 16, .. 1 apart, without LDS.  swap32_add: lanes 0 - 31 get x + its partner,
+// lanes 32 - 63 y + its partner; swap16_add: the same within each 32 lanes; row_sums: the sum over each row of 16 lanes.
+__device__ __forceinline__ float swap32_add(float x, float y) {
+  const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+}
+__device__ __forceinline__ float swap16_add(float x, float y) {
+  const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+}
+__device__ __forceinline__ float row_sums(float x) {
+  // each step leaves a row periodic, so that a rotation by half a period is the partner's value
+#define LQSGD_ROR_ADD(N) \
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x120 + (N), 0xf, 0xf, true))
+  LQSGD_ROR_ADD(8);
+  LQSGD_ROR_ADD(4);
+  LQSGD_ROR_ADD(2);
+  LQSGD_ROR_ADD(1);
+#undef LQSGD_ROR_ADD
+  return x;
+}
+// The sums of four values: c[0], c[2], c[1], c[3] in rows 0, 1, 2, 3.
+__device__ __forceinline__ float four_lane_sums(const float (&c)[4]) {
+  return row_sums(swap16_add(swap32_add(c[0], c[1]), swap32_add(c[2], c[3])));
+}
+
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) x = fmaxf(x, __shfl_xor(x, off, kWave));
@@ -314,15 +360,6 @@ __device__ __forceinline__ float wave_max(float x) {
 }
 
 constexpr int log2c(int n) { return n <= 1 ? 0 : 1 + log2c(n / 2); }
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order.
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<N, I + 1>(f);
-  }
-}
 
 // The absmax cells that later kernels of the iteration raise with atomic maxima start from zero:
 // absmax(Q_w) always (sweep 1 or the reduce that follows it), absmax of the raw P_w in the
@@ -753,6 +790,152 @@ __global__ __launch_bounds__(BS) void orth_reg_kernel(DevArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// orth, rows on lanes, one workgroup per (layer, worker), with the sums of
+// slices of 256 rows (orth_coop_kernel, orth_wide_kernel; rank pads 1 to 4), to
+// the last bit: the products of 256 neighbouring rows, a butterfly over each 64
+// of them, the four wavefronts in pairs, then the slices one after the other.  A
+// thread holds rows t, t + 1024, .., so that wavefronts 4 q .. 4 q + 3 have slice
+// q of each block of 1024.
+//
+// What bounds it: reading the planes on one CU, then for each column two
+// barriers and up to 44 additions in a row (1 to 2 us).  The slices' way costs
+// about 20 us for the cooperative launch and 2 to 3 a column.  Gram-Schmidt, us,
+// in one cooperative launch / here: 4096 x 1024, W = 16, r = 4 33 / 11,
+// 8192^2, W = 16, r = 1 32 / 12, r = 4 42 / 24; 11264 x 8192, r = 3 43 / 27.  (With
+// its values stored one at a time, 4 bytes of every row, 8192 x 1024, r = 4 took
+// 28 us instead of 17.)
+// ---------------------------------------------------------------------------
+template <int RP, int RPT>
+__global__ __launch_bounds__(1024) void orth_tall_kernel(DevArgs a) {
+  constexpr int BS = 1024, NW = BS / kWave, NS = 4 * RPT;       // slices held
+  constexpr int GROUPS = RPT * RP / 4;                          // of four values that are summed together
+  static_assert(RPT * RP % 4 == 0 && GROUPS <= 16 && NS <= kWave && RP <= NW, "");
+  __shared__ __attribute__((aligned(16))) float part[RP][NS][4];
+  __shared__ float tot[RP];
+  __shared__ float redmax[NW];
+  const int lw = blockIdx.x;
+  const int layer = lw / a.W, worker = lw - layer * a.W;
+  const LayerDesc& ld = a.layers[layer];
+  const int rows = ld.rows, r = ld.r, nseg = a.orth_shared ? 1 : ld.nseg, nslice = (rows + 255) >> 8;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float* Pp = a.Ppart + (size_t)worker * a.ppart_stride + (a.orth_shared ? ld.p_off : ld.ppart_off);
+  float* pre = a.Ppre + (size_t)worker * a.p_stride + ld.p_off;
+  float* orth = a.Porth + (size_t)worker * a.p_stride + ld.p_off;
+
+  // the planes added in order, many rows in flight; rows beyond the factor re-read its last one and count as zeros
+  constexpr int CH = RPT * RP > 40 ? (RPT + 1) / 2 : RPT;
+  int row0 = tid;
+  auto hide_row = [&]() __attribute__((always_inline)) { asm volatile("" : "+v"(row0)); };   // (else all addresses stay in registers, and some spill)
+  float v[RPT][RP];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i)
+#pragma unroll
+    for (int k = 0; k < RP; ++k) v[i][k] = 0.0f;
+  auto add_planes = [&](auto width) __attribute__((always_inline)) {   // (rows of r values in one load)
+    constexpr int N = decltype(width)::value + 1;
+    for (int s = 0; s < nseg; ++s) {
+      const float* src = Pp + (size_t)s * ld.np_pad;
+      hide_row();
+#pragma unroll
+      for (int i0 = 0; i0 < RPT; i0 += CH) {
+        float t[CH][N];
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+          if (i0 + i < RPT) {
+            const float* from = src + min(row0 + (i0 + i) * BS, rows - 1) * N;
+#pragma unroll
+            for (int k = 0; k < N; ++k) t[i][k] = from[k];
+          }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+#pragma unroll
+          for (int k = 0; k < N; ++k)
+            if (i0 + i < RPT) v[i0 + i][k] += t[i][k];
+      }
+    }
+  };
+  static_for<RP>([&](auto width) __attribute__((always_inline)) {
+    if (r == width.value + 1) add_planes(width);
+  });
+  hide_row();
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int row = row0 + i * BS;
+    if (row < rows) store_row<RP>(pre + row * r, r, v[i]);
+#pragma unroll
+    for (int k = 0; k < RP; ++k) v[i][k] = row < rows ? v[i][k] : 0.0f;
+  }
+
+  // the value whose sum this lane writes: the n-th of the thread's, row n / RP of it, column n % RP
+  const int q = lane >> 4, n = 4 * (lane & 15) + (q == 1 ? 2 : q == 2 ? 1 : q);
+#pragma unroll
+  for (int j = 0; j < RP; ++j) {
+    if (j < r) {
+      float mine = 0.0f;
+#pragma unroll
+      for (int g = 0; g < GROUPS; ++g) {
+        float c[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c[e] = v[(4 * g + e) / RP][j] * v[(4 * g + e) / RP][(4 * g + e) % RP];
+        const float x = four_lane_sums(c);
+        mine = (lane & 15) == g ? x : mine;
+      }
+      if ((lane & 15) < GROUPS) part[n % RP][4 * (n / RP) + (wave >> 2)][wave & 3] = mine;
+      __syncthreads();
+      if (wave < RP) {                             // a column each
+        float x = 0.0f;
+        if (lane < nslice) {
+          const float4 w = *reinterpret_cast<const float4*>(part[wave][lane]);
+          x = (w.x + w.y) + (w.z + w.w);
+        }
+        float sum = 0.0f;
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl) sum += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), sl));   // (zeros beyond nslice)
+        if (lane == 0) tot[wave] = sum;
+      }
+      __syncthreads();
+      const float nrm2 = tot[j];
+      const float inv = (nrm2 > FLT_MIN) ? 1.0f / sqrtf(nrm2) : 0.0f;
+      float f[RP];
+#pragma unroll
+      for (int k = j + 1; k < RP; ++k) f[k] = -(tot[k] * inv);
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) {
+        const float qv = v[i][j] * inv;
+        v[i][j] = qv;
+#pragma unroll
+        for (int k = j + 1; k < RP; ++k)
+          if (k < r) v[i][k] = fmaf(f[k], qv, v[i][k]);
+      }
+    }
+  }
+
+  float mx = 0.0f;
+  float* copy = a.orth_shared && a.padded ? a.Pop + ld.pop_off : nullptr;
+  hide_row();
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int row = row0 + i * BS;
+    if (row < rows) {
+      store_row<RP>(orth + row * r, r, v[i]);
+      if (copy) store_row<RP>(copy + row * RP, r, v[i]);
+#pragma unroll
+      for (int k = 0; k < RP; ++k) mx = fmaxf(mx, fabsf(v[i][k]));   // (zeros beyond r)
+    }
+  }
+  mx = wave_max(mx);
+  if (lane == 0) redmax[wave] = mx;
+  __syncthreads();
+  if (tid == 0 && !a.orth_shared) {
+    float m = redmax[0];
+#pragma unroll
+    for (int wv = 1; wv < NW; ++wv) m = fmaxf(m, redmax[wv]);
+    a.scaleP[(size_t)worker * a.L + layer] = m;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // orth, one workgroup per (layer, worker), columns on lanes: lane (g, k) of a
 // wavefront holds RPT rows of column k (C columns, 64 / C groups of rows), so a
 // column's products with all later ones are RPT multiply-adds per lane and no
@@ -818,9 +1001,8 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
   float v[RPT];
 #pragma unroll
   for (int i = 0; i < RPT; ++i) v[i] = 0.0f;
-  // Elements beyond the factor re-read the last one of their row or column, in a line that is read anyhow (its first element
-  // instead: 4096 x 8192, r = 3, W = 4, 31 us against 18.5, 2 x (11008 x 4096) and so on, r = 4, 47 against 42); they count as
-  // zeros from here on.
+  // Elements beyond the factor re-read the last one of their row or column, in a line that is read anyhow (its first element would be
+  // one more line in every load); they count as zeros from here on.
   for (int s = 0; s < nseg; ++s) {
     const float* src = Pp + (size_t)s * ld.np_pad;
     hide_row();
@@ -981,29 +1163,13 @@ __global__ __launch_bounds__(64 * NW) void orth_col_kernel(DevArgs a) {
 // Sum over the lanes of each c[w], then over w.
 template <int NB, bool PAIRS>
 __device__ __forceinline__ float column_total(const float (&c)[NB]) {
-  auto swap32 = [](float x, float y) __attribute__((always_inline)) {
-    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
-  };
-  auto swap16 = [](float x, float y) __attribute__((always_inline)) {
-    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
-  };
   float x;
   if constexpr (NB == 4) {
-    x = swap16(swap32(c[0], c[1]), swap32(c[2], c[3]));        // rows of 16 lanes: c[0], c[2], c[1], c[3]
+    x = four_lane_sums(c);
   } else {
-    const float u = NB == 2 ? swap32(c[0], c[NB - 1]) : swap32(c[0], c[0]);
-    x = swap16(u, u);
+    const float u = NB == 2 ? swap32_add(c[0], c[NB - 1]) : swap32_add(c[0], c[0]);
+    x = row_sums(swap16_add(u, u));
   }
-  // each step leaves a row of 16 lanes periodic, so that a rotation by half a period is the partner's value
-#define LQSGD_ROR_ADD(N) \
-  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x120 + (N), 0xf, 0xf, true))
-  LQSGD_ROR_ADD(8);
-  LQSGD_ROR_ADD(4);
-  LQSGD_ROR_ADD(2);
-  LQSGD_ROR_ADD(1);
-#undef LQSGD_ROR_ADD
   auto at = [&](int l) __attribute__((always_inline)) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), l)); };
   if constexpr (NB == 4) {
     return PAIRS ? (at(0) + at(32)) + (at(16) + at(48)) : ((at(0) + at(32)) + at(16)) + at(48);
@@ -4387,6 +4553,24 @@ bool launch_orth_reg(const DevArgs& a, int max_rows, dim3 grid, hipStream_t s) {
   return false;
 }
 
+// One workgroup each with the sums of slices, rank pads 1 to 4.
+template <int RP>
+bool launch_orth_tall(const DevArgs& a, int max_rows, dim3 grid, hipStream_t s) {
+#define LQSGD_LAUNCH_OT(RPT)                                      \
+  if (max_rows <= (RPT) * 1024) {                                 \
+    orth_tall_kernel<RP, RPT><<<grid, dim3(1024), 0, s>>>(a);     \
+    note_kernel("orth_tall_kernel<%d, %d>", RP, RPT);             \
+    return true;                                                  \
+  }
+  if constexpr (RP > 1) { LQSGD_LAUNCH_OT(2) }
+  LQSGD_LAUNCH_OT(4)
+  LQSGD_LAUNCH_OT(8)
+  if constexpr (RP == 4) { LQSGD_LAUNCH_OT(11) }
+  else { LQSGD_LAUNCH_OT(12) }
+#undef LQSGD_LAUNCH_OT
+  return false;
+}
+
 // Whole columns to a wavefront (OW) or columns on lanes (OC); the sums are those of 256 threads with rows on lanes (1024
 // threads beyond 2048 rows), their wavefronts added in pairs from rank pad 16 and 513 rows on.
 template <int C>
@@ -4603,18 +4787,22 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, Coo
   if (a.L <= 0) return hipSuccess;
   const dim3 grid(a.L * a.W);
   const int nslice = (max_rows + 255) / 256;
-  // More rows than one workgroup holds, or, from rank pad 8 on, tall factors and too few (layer, worker) pairs to fill 256
-  // CUs with one workgroup each: many workgroups per factor.  At rank pads 1 to 4 one workgroup is the faster one at every
-  // height that it holds, few factors or many: a cooperative launch alone costs about 20 us, its launches one by one 9 us a
-  // column (many workgroups / one, us: 1822 x 384, W = 8, r = 1 23 / 8, r = 4 29 / 10; 8000 x 300, W = 4, r = 1 25 / 9, r = 4 32 / 18;
-  // 8192^2, W = 4, r = 1 27 / 23, r = 3 32 / 25, r = 4 35 / 26; two blocks of a large language model, W = 4, r = 4 58 / 42, r = 1
-  // 18.7 / 19.4).  (Fewer than 16 factors of 8192 rows or more at rank pad 4 stay with the one-launch form all the same: it is
-  // there that the expiry of its bounded waits is tested.)  The limits of pads 8 to 32 keep each factor with the form, and so the sums, that it has had: one workgroup
-  // would hold up to 8192 rows at pad 8 (130 factors of 8000 rows: 121 us, Cholesky-QR 186) and 4096 at pad 16 (3000 rows:
-  // 119 and 125), with results that differ by their rounding times the factor's condition number, which at those ranks can be
-  // a thousand.
+  // More rows than one workgroup holds, or tall factors and too few (layer, worker) pairs to fill 256 CUs with one workgroup each:
+  // many workgroups per factor, or, at rank pads 1 to 4, one that adds in their order (orth_tall_kernel: a cooperative launch alone
+  // costs about 20 us, its launches one by one 9 us a column).  (Fewer than 16 factors of 8192 rows or more at rank pad 4 stay with
+  // the one-launch form all the same: it is there that the expiry of its bounded waits is tested.)
+  // The limits keep each factor with the order of sums that it has had: one workgroup of columns on lanes would hold up to 8192 rows at
+  // pad 8 (130 factors of 8000 rows: 121 us, Cholesky-QR 186) and 4096 at pad 16 (3000 rows: 119 and 125), with results that
+  // differ by their rounding times the factor's condition number, which at those ranks can be a thousand.
   const bool fits = max_rows <= (rp <= 4 ? 11264 : rp == 8 ? 4096 : rp <= 32 ? 1792 : 1024);
-  const bool few = rp > 4 ? nslice >= 8 && grid.x < 128 : rp == 4 && max_rows >= 8192 && grid.x < 16;
+  const bool few = nslice >= 8 && grid.x < 128;
+  if (rp <= 4 && fits && few && !(rp == 4 && max_rows >= 8192 && grid.x < 16)) {
+    const bool tall = rp == 1 ? launch_orth_tall<1>(a, max_rows, grid, s) : rp == 2 ? launch_orth_tall<2>(a, max_rows, grid, s)
+                                                                                    : launch_orth_tall<4>(a, max_rows, grid, s);
+    if (!tall) return hipErrorInvalidValue;
+    *copied = true;
+    return hipGetLastError();
+  }
   if (a.orth_part && (!fits || few)) {
 #ifdef LQSGD_TUNING
     static const bool chol = [] { const char* e = std::getenv("LQSGD_ORTH_CHOL"); return !(e && e[0] == '0'); }();

@@ -93,23 +93,47 @@ def test_gram_schmidt_sums_of_many_tall_factors(rank, rows):
     comp.close()
 
 
-# few tall factors at rank pads 1 to 4: one workgroup each up to the height that it holds, slices beyond
-@pytest.mark.parametrize("rank,rows", [(1, 1793), (1, 11264), (2, 2049), (2, 8200), (3, 1793), (3, 4097), (4, 8191), (4, 8192), (3, 11265)])
+def _gram_schmidt_slices(p):
+    """The same over slices of 256 rows: products, a butterfly per 64 of them, four wavefronts in pairs, the slices one after the other."""
+    rows, r = p.shape
+    n = -(-rows // 256)
+    v = np.zeros((n * 256, r), f32)
+    v[:rows] = p
+    for j in range(r):
+        s = _butterfly((v[:, j:j + 1] * v).reshape(-1, 64, r)).reshape(n, 4, r)
+        t = np.zeros(r, f32)
+        for x in (s[:, 0] + s[:, 1]) + (s[:, 2] + s[:, 3]):
+            t = t + x
+        inv = f32(1) / np.sqrt(t[j]) if t[j] > np.finfo(f32).tiny else f32(0)
+        q = v[:, j] * inv
+        v[:, j + 1:] = _fma(-(t[j + 1:] * inv), q[:, None], v[:, j + 1:])
+        v[:, j] = q
+    return v[:rows]
+
+
+# few tall factors at rank pads 1 to 4: the sums of slices, by one workgroup each up to the height that it holds, by the slices
+# beyond, in one launch and in several
+@pytest.mark.parametrize("rank,rows", [(1, 1793), (1, 4097), (1, 11264), (2, 2049), (2, 8200), (3, 1793), (3, 4097), (3, 8191), (4, 2048), (4, 8191), (4, 8192),
+                                       (1, 11265), (2, 11265), (2, 16384), (3, 11265)])
 def test_gram_schmidt_sums_of_few_tall_factors(rank, rows):
     _say("case: order of sums, few tall factors", rank, rows)
     rng = np.random.default_rng(rank * 7919 + rows)
     layers, W = [(rows, 1100), (40, 12), (rows - 300, 2)], 2
-    comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, W)
-    for l, (n, c) in enumerate(layers):
-        comp.set_q(l, rng.standard_normal((c, min(rank, n, c))).astype(f32))
-    comp.compress(B.PHASE_P, pu.to_device([[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)]))
-    assert comp.launched_kernel(B.KERNEL_ORTH).startswith("orth_coop" if rank > 2 and rows >= 8192 else "orth_reg" if rank <= 2 else "orth_col")
-    for l in range(len(layers)):
-        for w in range(W):
-            got = comp.get_factor(B.FACTOR_P_ORTH, l, w)
-            want = _gram_schmidt(comp.get_factor(B.FACTOR_P_PRE, l, w), 256 if rows <= 2048 else 1024, False)
-            assert pu.rel_fro(got, want) < pu.FP_TOL if rank <= 2 or rows >= 8192 else np.array_equal(got, want), (l, w)
-    comp.close()
+    Q = [rng.standard_normal((c, min(rank, n, c))).astype(f32) for n, c in layers]
+    G = pu.to_device([[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)])
+    for flags in (0, B.FLAG_NO_COOPERATIVE_LAUNCH):
+        comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, W, 255.0, flags)
+        for l, q in enumerate(Q):
+            comp.set_q(l, q)
+        comp.compress(B.PHASE_P, G)
+        if rows < 8192 or rows > 11264 or rank < 3:
+            name = "orth_tall" if rows <= 11264 else "orth_wide" if flags else "orth_coop"
+            assert comp.launched_kernel(B.KERNEL_ORTH).startswith(name)
+        for l in range(len(layers)):
+            for w in range(W):
+                want = _gram_schmidt_slices(comp.get_factor(B.FACTOR_P_PRE, l, w))
+                assert np.array_equal(comp.get_factor(B.FACTOR_P_ORTH, l, w), want), (l, w, flags)
+        comp.close()
 
 
 # more factors than CUs (a workgroup each then has fewer wavefronts, or columns on lanes), odd ranks, which leave a wavefront's
