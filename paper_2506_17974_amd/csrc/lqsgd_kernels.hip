@@ -875,10 +875,20 @@ __global__ __launch_bounds__(1024) void orth_tall_kernel(DevArgs a) {
       float mine = 0.0f;
 #pragma unroll
       for (int g = 0; g < GROUPS; ++g) {
-        float c[4];
+        float x;
+        if constexpr (RP == 1) {                   // (see column_products)
+          auto squares = [&](int i) __attribute__((always_inline)) {
+            const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i][0]), __float_as_uint(v[i + 1][0]), false, false);
+            const float lo = __uint_as_float(t[0]), hi = __uint_as_float(t[1]);
+            return fmaf(lo, lo, hi * hi);
+          };
+          x = row_sums(swap16_add(squares(4 * g), squares(4 * g + 2)));
+        } else {
+          float c[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) c[e] = v[(4 * g + e) / RP][j] * v[(4 * g + e) / RP][(4 * g + e) % RP];
-        const float x = four_lane_sums(c);
+          for (int e = 0; e < 4; ++e) c[e] = v[(4 * g + e) / RP][j] * v[(4 * g + e) / RP][(4 * g + e) % RP];
+          x = four_lane_sums(c);
+        }
         mine = (lane & 15) == g ? x : mine;
       }
       if ((lane & 15) < GROUPS) part[n % RP][4 * (n / RP) + (wave >> 2)][wave & 3] = mine;
@@ -1428,6 +1438,20 @@ __device__ __forceinline__ void slice_of(const DevArgs& a, int block, int nslice
   slice = in_layer - worker * n;
 }
 
+// Products of a column with all columns, summed over a wavefront's lanes as transpose_reduce does.  A single product (RP = 1) meets
+// its partner's before it is rounded.
+template <int RP>
+__device__ __forceinline__ void column_products(float vj, const float (&v)[RP], float (&s)[RP], int lane) {
+#pragma unroll
+  for (int k = 0; k < RP; ++k) s[k] = vj * v[k];
+  if constexpr (RP == 1) {
+    s[0] = fmaf(vj, v[0], __shfl_xor(s[0], 32, kWave));
+    transpose_reduce<1, 1, 16>(s, lane);
+  } else {
+    transpose_reduce<RP, RP, 32>(s, lane);
+  }
+}
+
 template <int RP>
 __global__ __launch_bounds__(256) void orth_wide_kernel(DevArgs a, int j, int nslice_max, const int* only_if) {
   __shared__ float red[4][RP];
@@ -1518,9 +1542,7 @@ __global__ __launch_bounds__(256) void orth_wide_kernel(DevArgs a, int j, int ns
     for (int k = 0; k < RP; ++k)
       if (k == j) vj = v[k];
     float s[RP];
-#pragma unroll
-    for (int k = 0; k < RP; ++k) s[k] = vj * v[k];
-    transpose_reduce<RP, RP, 32>(s, lane);
+    column_products<RP>(vj, v, s, lane);
     if ((lane & (kWave / RP - 1)) == 0) red[wave][lane >> (6 - log2c(RP))] = s[0];
     __syncthreads();
     if (tid < RP)
@@ -1585,9 +1607,7 @@ __device__ __forceinline__ void coop_columns(float (&v)[RP], int r, int lw, int 
     for (int k = 0; k < RP; ++k)
       if (k == j) vj = v[k];
     float s[RP];
-#pragma unroll
-    for (int k = 0; k < RP; ++k) s[k] = vj * v[k];
-    transpose_reduce<RP, RP, 32>(s, lane);
+    column_products<RP>(vj, v, s, lane);
     if ((lane & (kWave / RP - 1)) == 0) red[wave * RP + (lane >> (6 - log2c(RP)))] = s[0];
     __syncthreads();
     if (tid < RP) {
