@@ -715,7 +715,8 @@ int lqsgd_create(const lqsgd_config* cfg, const lqsgd_layer* layers, int32_t n_l
   }
   c->stream = static_cast<hipStream_t>(hip_stream);
   // The bound of the device-side waits of the one-launch Gram-Schmidt can be shortened for a test
-  // of the expiry path (read once, here; nothing else in the library reads the environment).
+  // of the expiry path (read once, here; nothing else in the library reads the environment).  Tall factors at rank
+  // pads 1 to 4 then take the form that waits, with the same bits (launch_orth).
   if (const char* e = std::getenv("LQSGD_TABLE_POLLS")) {
     const long v = std::strtol(e, nullptr, 10);
     if (v >= 1) c->coop.max_polls = (unsigned)v;

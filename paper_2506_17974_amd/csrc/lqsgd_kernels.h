@@ -76,7 +76,7 @@ struct CoopState {
   unsigned long long epoch = 0;   // launches made so far: makes the tags in `a.orth_table` unique
   int capacity = -1;              // workgroups of that kernel that fit the context's device at once (-1: not asked yet)
   int chol_capacity = -1;         // the same for the Cholesky-QR kernel
-  unsigned max_polls = 0;         // bound of a device-side wait; 0 = the default (about a second)
+  unsigned max_polls = 0;         // bound of a device-side wait; 0 = the default (about a second), not set from outside
 };
 // Entries of the r x r Gram matrix that the slices of a factor exchange at rank pad RP (NE above); 0 if
 // the Cholesky-QR form does not exist at that pad.

@@ -4809,14 +4809,15 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, Coo
   const int nslice = (max_rows + 255) / 256;
   // More rows than one workgroup holds, or tall factors and too few (layer, worker) pairs to fill 256 CUs with one workgroup each:
   // many workgroups per factor, or, at rank pads 1 to 4, one that adds in their order (orth_tall_kernel: a cooperative launch alone
-  // costs about 20 us, its launches one by one 9 us a column).  (Fewer than 16 factors of 8192 rows or more at rank pad 4 stay with
-  // the one-launch form all the same: it is there that the expiry of its bounded waits is tested.)
+  // costs about 20 us, its launches one by one 9 us a column; W = 4, r = 4, slices / one workgroup, us: 2048 x 1024 29 / 8.6, 8192 x 1024
+  // 33 / 15, 8192^2 35 / 24).  A bound of the waits that was set from outside asks for the form that waits: same bits, and its expiry
+  // can be tested at any height.
   // The limits keep each factor with the order of sums that it has had: one workgroup of columns on lanes would hold up to 8192 rows at
   // pad 8 (130 factors of 8000 rows: 121 us, Cholesky-QR 186) and 4096 at pad 16 (3000 rows: 119 and 125), with results that
   // differ by their rounding times the factor's condition number, which at those ranks can be a thousand.
   const bool fits = max_rows <= (rp <= 4 ? 11264 : rp == 8 ? 4096 : rp <= 32 ? 1792 : 1024);
   const bool few = nslice >= 8 && grid.x < 128;
-  if (rp <= 4 && fits && few && !(rp == 4 && max_rows >= 8192 && grid.x < 16)) {
+  if (rp <= 4 && fits && few && !(coop && coop->max_polls)) {
     const bool tall = rp == 1 ? launch_orth_tall<1>(a, max_rows, grid, s) : rp == 2 ? launch_orth_tall<2>(a, max_rows, grid, s)
                                                                                     : launch_orth_tall<4>(a, max_rows, grid, s);
     if (!tall) return hipErrorInvalidValue;

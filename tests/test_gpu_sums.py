@@ -117,27 +117,27 @@ def _gram_schmidt_slices(p, single):
 
 
 # few tall factors at rank pads 1 to 4: the sums of slices, by one workgroup each up to the height that it holds, by the slices
-# beyond, in one launch and in several
-@pytest.mark.parametrize("rank,rows", [(1, 1793), (1, 4097), (1, 11264), (2, 2049), (2, 8200), (3, 1793), (3, 4097), (3, 8191), (4, 2048), (4, 8191), (4, 8192),
+# beyond (or where a bound of their waits is set), in one launch and in several
+@pytest.mark.parametrize("rank,rows", [(1, 1793), (1, 4097), (1, 11264), (2, 2049), (2, 8200), (3, 1793), (3, 4097), (3, 8191), (3, 11264), (4, 2048), (4, 8191), (4, 8192),
                                        (1, 11265), (2, 11265), (2, 16384), (3, 11265)])
-def test_gram_schmidt_sums_of_few_tall_factors(rank, rows):
+def test_gram_schmidt_sums_of_few_tall_factors(monkeypatch, rank, rows):
     _say("case: order of sums, few tall factors", rank, rows)
     rng = np.random.default_rng(rank * 7919 + rows)
     layers, W = [(rows, 1100), (40, 12), (rows - 300, 2)], 2
     Q = [rng.standard_normal((c, min(rank, n, c))).astype(f32) for n, c in layers]
     G = pu.to_device([[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)])
-    for flags in (0, B.FLAG_NO_COOPERATIVE_LAUNCH):
+    for flags, polls in ((0, ""), (B.FLAG_NO_COOPERATIVE_LAUNCH, ""), (0, str(1 << 20))):
+        monkeypatch.setenv("LQSGD_TABLE_POLLS", polls)
         comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, W, 255.0, flags)
         for l, q in enumerate(Q):
             comp.set_q(l, q)
         comp.compress(B.PHASE_P, G)
-        if rows < 8192 or rows > 11264 or rank < 3:
-            name = "orth_tall" if rows <= 11264 else "orth_wide" if flags else "orth_coop"
-            assert comp.launched_kernel(B.KERNEL_ORTH).startswith(name)
+        name = "orth_tall" if rows <= 11264 and not polls else "orth_wide" if flags else "orth_coop"
+        assert comp.launched_kernel(B.KERNEL_ORTH).startswith(name)
         for l in range(len(layers)):
             for w in range(W):
                 want = _gram_schmidt_slices(comp.get_factor(B.FACTOR_P_PRE, l, w), rank == 1)
-                assert np.array_equal(comp.get_factor(B.FACTOR_P_ORTH, l, w), want), (l, w, flags)
+                assert np.array_equal(comp.get_factor(B.FACTOR_P_ORTH, l, w), want), (l, w, flags, polls)
         comp.close()
 
 
