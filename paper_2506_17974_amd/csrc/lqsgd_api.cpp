@@ -292,7 +292,7 @@ int run_sweep0(lqsgd_ctx* c) {
   } else {
     Timed t(c, LQSGD_KERNEL_ORTH);
     bool copied = false;
-    HIP_TRY(c, launch_orth(c->plan.RP, c->plan.max_rows, c->plan.max_rank, c->args, coop_state(c), &copied, c->stream));
+    HIP_TRY(c, launch_orth(c->plan.RP, c->plan.max_rows, c->plan.max_rank, c->plan.plane_rows, c->args, coop_state(c), &copied, c->stream));
   }
   return LQSGD_OK;
 }
@@ -307,7 +307,7 @@ int run_orth_shared(lqsgd_ctx* c) {
   a.Ppre = c->args.Porth;
   a.Porth = c->args.Pbar;
   bool copied = false;
-  HIP_TRY(c, launch_orth(c->plan.RP, c->plan.max_rows, c->plan.max_rank, a, coop_state(c), &copied, c->stream));
+  HIP_TRY(c, launch_orth(c->plan.RP, c->plan.max_rows, c->plan.max_rank, c->plan.max_rows, a, coop_state(c), &copied, c->stream));
   return copied ? LQSGD_OK : refresh_padded(c, 0);
 }
 int run_exchange(lqsgd_ctx* c, int mode, int phase) {

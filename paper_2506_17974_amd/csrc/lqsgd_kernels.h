@@ -83,7 +83,8 @@ struct CoopState {
 int chol_entries(int RP);
 // coop: NULL disables the one-launch forms.
 // *copied: whether the launch has written the padded copy Pop of an aggregate (orth_shared) too, where there is one.
-hipError_t launch_orth(int RP, int max_rows, int max_rank, const DevArgs& a, CoopState* coop, bool* copied, hipStream_t s);
+// plane_rows: Plan::plane_rows, or max_rows where there is one plane.
+hipError_t launch_orth(int RP, int max_rows, int max_rank, int64_t plane_rows, const DevArgs& a, CoopState* coop, bool* copied, hipStream_t s);
 hipError_t launch_exchange(int mode, int phase, const DevArgs& a, const XTile* tiles, int ntiles, hipStream_t s);
 // Sweep 1 also runs the plain mean of the 1-D tensors (nvtiles extra workgroups).  Layers whose
 // items cover all their rows (LayerDesc::direct_q) get Q_w and its absmax from this sweep itself.

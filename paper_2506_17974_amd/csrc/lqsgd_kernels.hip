@@ -4802,7 +4802,7 @@ hipError_t launch_orth_chol(int rp, int nslice, int max_rank, const DevArgs& a, 
 hipError_t launch_orth_chol(int rp, int nslice, int max_rank, const DevArgs& a, int nblocks, CoopState* coop, hipStream_t s);
 
 #if LQSGD_HAS(4)
-hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, CoopState* coop, bool* copied, hipStream_t s) {
+hipError_t launch_orth(int rp, int max_rows, int max_rank, int64_t plane_rows, const DevArgs& a, CoopState* coop, bool* copied, hipStream_t s) {
   *copied = a.L <= 0;
   if (a.L <= 0) return hipSuccess;
   const dim3 grid(a.L * a.W);
@@ -4810,14 +4810,18 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, const DevArgs& a, Coo
   // More rows than one workgroup holds, or tall factors and too few (layer, worker) pairs to fill 256 CUs with one workgroup each:
   // many workgroups per factor, or, at rank pads 1 to 4, one that adds in their order (orth_tall_kernel: a cooperative launch alone
   // costs about 20 us, its launches one by one 9 us a column; W = 4, r = 4, slices / one workgroup, us: 2048 x 1024 29 / 8.6, 8192 x 1024
-  // 33 / 15, 8192^2 35 / 24).  A bound of the waits that was set from outside asks for the form that waits: same bits, and its expiry
+  // 33 / 15, 8192^2 35 / 24).  It reads all planes on one CU, the slices on 8 to 44, so that many planes of many rows go to them: up to
+  // 2^17 rows of planes one workgroup is the faster one or as fast (W = 1 and 4, slices / one workgroup, us: 2048 rows x 32 planes,
+  // r = 4 45 / 27, 4096 x 32, r = 1 35 / 27, r = 4 50 / 44, 8192 x 16, r = 2 34 / 29, r = 4, W = 4 41 / 34, though W = 1 43 / 49, 11264 x 8, r = 4
+  // 36 / 32), beyond it the slices soon are (8192 x 32, r = 2 38 / 41, r = 4 46 / 53, 11264 x 32, r = 2 38 / 59, 8192 x 126, r = 1 55 / 90,
+  // r = 4 95 / 166).  A bound of the waits that was set from outside asks for the form that waits: same bits, and its expiry
   // can be tested at any height.
   // The limits keep each factor with the order of sums that it has had: one workgroup of columns on lanes would hold up to 8192 rows at
   // pad 8 (130 factors of 8000 rows: 121 us, Cholesky-QR 186) and 4096 at pad 16 (3000 rows: 119 and 125), with results that
   // differ by their rounding times the factor's condition number, which at those ranks can be a thousand.
   const bool fits = max_rows <= (rp <= 4 ? 11264 : rp == 8 ? 4096 : rp <= 32 ? 1792 : 1024);
   const bool few = nslice >= 8 && grid.x < 128;
-  if (rp <= 4 && fits && few && !(coop && coop->max_polls)) {
+  if (rp <= 4 && fits && few && plane_rows <= (1 << 17) && !(coop && coop->max_polls)) {
     const bool tall = rp == 1 ? launch_orth_tall<1>(a, max_rows, grid, s) : rp == 2 ? launch_orth_tall<2>(a, max_rows, grid, s)
                                                                                     : launch_orth_tall<4>(a, max_rows, grid, s);
     if (!tall) return hipErrorInvalidValue;

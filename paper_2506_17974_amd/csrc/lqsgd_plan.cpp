@@ -104,6 +104,7 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
   int max_r = 1;
   max_rows = 0;
   slices = 0;
+  plane_rows = 0;
   matrix_elements = 0;
   for (int i = 0; i < n_layers; ++i) {
     const lqsgd_layer& l = ls[i];
@@ -302,6 +303,7 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
     d.p_off = p_acc;   p_acc += round_up(d.np_el, 64);
     d.q_off = q_acc;   q_acc += round_up(d.nq_el, 64);
     d.ppart_off = pp_acc; pp_acc += (int64_t)d.nseg * d.np_pad;
+    plane_rows = std::max(plane_rows, (int64_t)d.rows * d.nseg);
     d.qpart_off = qp_acc; qp_acc += d.direct_q && !mfma ? 0 : (int64_t)d.nrb * d.nq_pad;   // no partial planes where sweep 1 stores Q_w itself (rank pads 32 and 64 keep the room: Gram-Schmidt has a use for it)
     d.pop_off = ppd_acc; ppd_acc += round_up((int64_t)d.rows * RP, 64);
     d.qop_off = qpd_acc; qpd_acc += round_up((int64_t)d.cols * RP, 64);

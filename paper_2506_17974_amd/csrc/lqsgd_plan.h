@@ -86,6 +86,7 @@ struct Plan {
   int32_t max_rows = 0;         // largest row count of a matrix layer
   int32_t max_rank = 0;         // largest effective rank of a matrix layer
   int32_t slices = 0;           // slices of 256 rows of all matrix layers
+  int64_t plane_rows = 0;       // largest rows * nseg of a matrix layer: what Gram-Schmidt adds up of one factor
   bool mfma = false;            // sweep 1 runs on the matrix cores (rank pads 32 and 64)
   bool mfma_a = false;          // sweeps 0 and 2 run on the matrix cores (rank pad >= 16): 32-row work items, 64 rows at rank pad 64
   std::vector<LayerDesc> layers;

@@ -141,6 +141,26 @@ def test_gram_schmidt_sums_of_few_tall_factors(monkeypatch, rank, rows):
         comp.close()
 
 
+# the same beside layers of many columns: planes of 2^17 rows together by one workgroup, of more by the slices
+@pytest.mark.parametrize("rank,rows,cols,name", [(1, 2048, 65536, "orth_tall"), (1, 2048, 65537, "orth_coop"), (4, 4097, 32000, "orth_coop"),
+                                                 (3, 4000, 32768, "orth_tall")])
+def test_gram_schmidt_of_many_planes(rank, rows, cols, name):
+    import torch
+    _say("case: order of sums, many planes", rank, rows, cols)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows)
+    layers = [(rows, cols), (70, 30)]
+    comp = B.Compressor(B.layer_list(layers, ()), rank, 8, 8, 1)
+    for l, (n, c) in enumerate(layers):
+        comp.set_q(l, np.random.default_rng(l).standard_normal((c, rank)).astype(f32))
+    comp.compress(B.PHASE_P, [[torch.randn(s, generator=gen, device="cuda") * 1e-3 for s in layers]])
+    assert comp.launched_kernel(B.KERNEL_ORTH).startswith(name)
+    for l in range(len(layers)):
+        want = _gram_schmidt_slices(comp.get_factor(B.FACTOR_P_PRE, l, 0), rank == 1)
+        assert np.array_equal(comp.get_factor(B.FACTOR_P_ORTH, l, 0), want), l
+    comp.close()
+
+
 # more factors than CUs (a workgroup each then has fewer wavefronts, or columns on lanes), odd ranks, which leave a wavefront's
 # block of columns half empty, and layers narrower than the rank beside them
 @pytest.mark.parametrize("rank,rows", [(7, 500), (8, 1500), (9, 128), (13, 256), (15, 300), (16, 1000), (11, 1500), (17, 64), (31, 65),
