@@ -157,11 +157,11 @@ int sync_stream(lqsgd_ctx* c) {
   return LQSGD_OK;
 }
 
-// Device values for the host, once the stream is done.  Up to kBounceBytes they are copied behind the work on the stream into pinned
-// memory and from there, with one wait for both: a factor of 16 KB 17 -> 12 us, of 64 KB 34 -> 11, and about 10 less where the stream is still
-// at work; of 128 KB and more the runtime's own staging is as fast, and memory for them would make contexts slower to create (256 KB
-// 60 to 150 us).
-constexpr size_t kBounceBytes = (64 << 10) - 256;
+// Device values for the host, once the stream is done.  Up to 64 KiB they are copied behind the work on the stream into pinned
+// memory and from there, with one wait for both (us, on an idle stream: 16 KiB 17 -> 12, just under 64 KiB 35 -> 11, 64 KiB 11 -> 11; a step
+// of 1024 x 64, r = 16 and its 64 KiB P-bar 69.7 -> 66.6).  From 64 KiB on the runtime's own staging is as fast, and memory for more would
+// make contexts slower to create (256 KiB 60 to 150 us).
+constexpr size_t kBounceBytes = 64 << 10;
 int fetch(lqsgd_ctx* c, void* host, const void* src, size_t bytes) {
   const bool bounce = c->bounce && bytes <= kBounceBytes;
   if (bounce) HIP_TRY(c, hipMemcpyAsync(c->bounce, src, bytes, hipMemcpyDeviceToHost, c->stream));

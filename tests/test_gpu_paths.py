@@ -371,3 +371,25 @@ def test_every_factor_of_more_slices_than_the_chip_holds(rank, heights, n_layers
             for i, few in zip(range(i0, i0 + 4), factors(range(i0, i0 + 4), "orth_chol_kernel<%d>" % rp)):
                 for k in range(W):
                     assert np.all(np.isfinite(few[k])) and np.array_equal(every[i][k], few[k]), "layer %d, worker %d" % (i, k)
+
+
+@pytest.mark.parametrize("rows", [1023, 1024, 1025])
+def test_factors_read_back_around_64_kib(rows):
+    """Factors of 64 KiB and a row less come through the context's pinned memory, of a row more do not; what is read is the step's just
+    enqueued, never the one's before."""
+    _say("case: factors read back", rows)
+    layers, rank, W = [(rows, 40), (50, 30)], 16, 2
+    rng = np.random.default_rng(rows)
+    comp, ml = _make(layers, (), rank, 0, 0, W)
+    for l in ml:
+        comp.set_q(l, rng.standard_normal((layers[l][1], rank)).astype(f32))
+    before = None
+    for _ in range(3):
+        comp.step(pu.to_device(_random_inputs(rng, layers, W)))
+        bar = [comp.get_factor(B.FACTOR_P_BAR, l) for l in ml]
+        for l in ml:
+            p = [comp.get_factor(B.FACTOR_P_ORTH, l, w) for w in range(W)]
+            assert np.array_equal(bar[l], (p[0] + p[1]) / f32(W))
+            assert before is None or not np.array_equal(bar[l], before[l])
+        before = bar
+    comp.close()
