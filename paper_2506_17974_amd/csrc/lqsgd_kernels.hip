@@ -84,6 +84,7 @@ typedef const float __attribute__((address_space(4)))* const_fp;
 #ifndef LQSGD_B_INTERLEAVE  // sweep 1: row blocks of at least this many rows are split between the wavefronts in groups of LQSGD_B_U rows
 #define LQSGD_B_INTERLEAVE 512
 #endif
+[[maybe_unused]] constexpr int kCus = 256;
 // Dynamic LDS that sweep 0 asks for, and does not use, to keep it at two workgroups a CU, two wavefronts a SIMD: where rows
 // fill a wavefront's pass more of them read slower (ResNet-18 set, r = 4: 187 / 174.7 / 177 / 177 us at 1 / 2 / 3 / 4).  Rows
 // much narrower than a pass wait for memory instead, and take what the registers allow (1000000 x 16, r = 4, W = 8: 1980 us
@@ -325,6 +326,13 @@ __device__ __forceinline__ void transpose_reduce(float (&v)[NT], int lane) {
       transpose_reduce<NT, 1, OFF / 2>(v, lane);
     }
   }
+}
+
+__device__ __forceinline__ void wave_lds_fence() {
+  // LDS traffic between the lanes of one wavefront: the hardware keeps DS
+  // operations of a wavefront in order; this only stops the compiler.
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // Sums over the lanes of a wavefront, partners 32, 16, .. 1 apart, without LDS.  swap32_add: lanes 0 - 31 get x + its partner,
@@ -2091,19 +2099,11 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 // set, r = 50, W = 8 168 -> 162 us, 8 x (512 x 4608), r = 64 238 -> 211, 16 x 1024^2 185 -> 173, 8192^2, W = 8 663 - 689 ->
 // 633 - 644.)  NB = 1: straight from L2, one request beside one (through LDS 16 x 1024^2, W = 8 128 -> 136 us,
 // ResNet-18 set 92 -> 90).
-__device__ __forceinline__ void wave_lds_fence() {
-  // LDS traffic between the lanes of one wavefront: the hardware keeps DS
-  // operations of a wavefront in order; this only stops the compiler.
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 constexpr int kPRows = 256;
-// Rank pad 64: whether the list is one that waits for single items (see the end of back_project_mfma_tile).
-__device__ __forceinline__ bool few_items() { return gridDim.x <= 512; }
+// few: rank pad 64, a list that waits for single items (see the end).
 template <int NB, int KIND, bool SHORT, typename Enter>
 __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const LayerDesc& ld, const Tile& tl, int worker,
-                                                       int c0, int lane, const float* ps, float* stage, Enter&& enter) {
+                                                       int c0, int lane, bool few, const float* ps, float* stage, Enter&& enter) {
   constexpr int U = LQSGD_BM_U;                     // pairs of rows per step
   constexpr bool SHARE = NB == 2;
   static_assert(kPRows % (2 * U) == 0, "");
@@ -2226,11 +2226,11 @@ __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const L
   // code, which a short item runs once.  Whole strips of long items at rank pad 64 do without both (a wave-uniform row of Q_w plus
   // one byte offset a lane; sweep 1, us, ResNet-18 set, W = 8, r = 50 156 -> 130, 12 x (512 x 4608) 313 -> 292, 8192^2, W = 4, r = 64
   // 323 -> 308; through LDS, behind a barrier of the workgroup, 149, 297 and 310).  The others go through LDS, at rank pad 64 in lists of up
-  // to 512 items, which wait for single items (a step, us, r = 50, W = 8 registers / LDS: 20 x (100 x 300) 130.5 / 129.3, 64 x 512, 30 of
+  // to two items a CU, which wait for single items (a step, us, r = 50, W = 8 registers / LDS: 20 x (100 x 300) 130.5 / 129.3, 64 x 512, 30 of
   // them 113.2 / 111.7; but the ResNet-18 set, 1800 items, 476 / 488, for the barrier).
   // Where a layer has one row block these are the sums themselves, and their absmax is taken here, a pass over a copy less (a step:
   // ResNet-18 set, W = 8, r = 50 482 -> 476, r = 32 350 -> 347, 8 x (256 x 4096), r = 50 366 -> 349, 2 x (60 x 300), r = 20 48.3 -> 44.7).
-  const bool through_lds = NB == 1 || few_items();
+  const bool through_lds = NB == 1 || few;
   if (SHARE && through_lds) __syncthreads();     // (the rows of P-bar make room)
   const bool direct = ld.direct_q != 0;
   float* Qp = direct ? a.Qw + (size_t)worker * a.q_stride + ld.q_off
@@ -2329,6 +2329,7 @@ __global__ __launch_bounds__(256, 2) void back_project_mfma_kernel(DevArgs a, co
   const int layer = tl.lw / a.W, worker = tl.lw - layer * a.W;
   const LayerDesc& ld = a.layers[layer];
   const int c0 = tl.aux * kMfmaCols + wave * 128;
+  const bool few = ntiles <= 2 * kCus;
   // rows of P-bar (NB = 2), at the end 64 columns' sums of each wavefront
   constexpr int STAGE = 64 * 32 * NB;
   static_assert(kPRows * 32 * NB >= 4 * STAGE, "");
@@ -2337,9 +2338,9 @@ __global__ __launch_bounds__(256, 2) void back_project_mfma_kernel(DevArgs a, co
   // strips of which all 128 columns exist need no care at their end, whatever the alignment of the rows
   auto run = [&](auto short_tag, const float* ps, auto&& enter) __attribute__((always_inline)) {
     constexpr bool SHORT = decltype(short_tag)::value;
-    if (c0 + 128 <= ld.cols) back_project_mfma_tile<NB, kAligned, SHORT>(a, ld, tl, worker, c0, lane, ps, stage, enter);
-    else if (ld.cols >= 4) back_project_mfma_tile<NB, kRagged, SHORT>(a, ld, tl, worker, c0, lane, ps, stage, enter);
-    else back_project_mfma_tile<NB, kNarrow, SHORT>(a, ld, tl, worker, c0, lane, ps, stage, enter);
+    if (c0 + 128 <= ld.cols) back_project_mfma_tile<NB, kAligned, SHORT>(a, ld, tl, worker, c0, lane, few, ps, stage, enter);
+    else if (ld.cols >= 4) back_project_mfma_tile<NB, kRagged, SHORT>(a, ld, tl, worker, c0, lane, few, ps, stage, enter);
+    else back_project_mfma_tile<NB, kNarrow, SHORT>(a, ld, tl, worker, c0, lane, few, ps, stage, enter);
   };
   if constexpr (NB == 2) {
     const int tid = threadIdx.x, rend = tl.row0 + tl.nrows;
@@ -2371,7 +2372,7 @@ __global__ __launch_bounds__(256, 2) void back_project_mfma_kernel(DevArgs a, co
     else if (c0 < ld.cols) run(std::false_type{}, ps, enter);
     else {                                       // no columns: only its share of the copies
       for (int row = tl.row0; row < rend; row += kPRows) enter(row);
-      if (few_items()) __syncthreads();          // (the others' before they hand out their sums)
+      if (few) __syncthreads();                  // (the others' before they hand out their sums)
     }
   } else {
     if (c0 < ld.cols) run(std::false_type{}, nullptr, [](int) {});
@@ -4931,7 +4932,6 @@ hipError_t launch_residual(int rp, int mode, const DevArgs& a, const Tile* tiles
 // W = 1 59 / 68; 132 items, 2 x (2100 x 1500), W = 2 107 / 77; 192 items, 4 x 1024^2, W = 3 71 / 51).  Lists of short items
 // lose nothing by the count, W = 8, r = 50 beside a 64 x 512 layer: 144 items, 17 x (32 x 2048) 67 / 61; 168 items, 20 x (20 x 2048)
 // 74 / 65; 200 items, 24 x (32 x 1024) 40 / 38; 520 items, 64 x (32 x 2048) 169 / 155 (first iterations 123 / 130).
-[[maybe_unused]] constexpr int kCus = 256;
 template <int RP, int MODE>
 void launch_mfma_add(const DevArgs& a, const Tile* tiles, int ntiles, int two, int reverse, hipStream_t s) {
   const dim3 grid(ntiles + two);

@@ -744,3 +744,32 @@ def test_sweep_one_stores_sums_and_absmax(rank, copies, W):
             assert (np.abs(q - m.T @ p) <= bound + 1e-30).all(), (l, w)
             assert comp.get_packet(B.PHASE_Q, l, w)[2] == np.abs(q).max(), (l, w)
     comp.close()
+
+
+@pytest.mark.parametrize("rank,copies", [(50, 20), (50, 42), (20, 20)])
+def test_matrix_layers_beside_many_vectors(rank, copies):
+    """Sweep 1 of lists of up to two items a CU and more, with hundreds of 1-D tensors' workgroups in the same launch and without: the
+    same bits, and the vectors' means."""
+    import torch
+    _say("case: sweep 1 beside vectors", rank, copies)
+    layers, W, n = [(100, 300), (64, 600)] * copies, 8, 300
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rank)
+    D = [torch.randn(64 * 600, generator=gen, device="cuda") * 1e-3 for _ in range(3)]
+    V = [torch.randn(1500, generator=gen, device="cuda") for _ in range(W)]
+    got = []
+    for vectors in ((), (1500,) * n):
+        comp = B.Compressor(B.layer_list(layers, vectors), rank, 8, 8, W)
+        for l, (r, c) in enumerate(layers):
+            comp.set_q(l, np.random.default_rng(l).standard_normal((c, min(rank, r, c))).astype(f32))
+        G = [[D[(l + w) % 3][:r * c].view(r, c) for l, (r, c) in enumerate(layers)] + [V[w]] * len(vectors) for w in range(W)]
+        out = [torch.zeros(s, device="cuda") for s in layers] + [torch.zeros(1500, device="cuda") for _ in vectors]
+        for _ in range(2):
+            comp.step(G, out)
+        comp.synchronize()
+        got.append([t.cpu().numpy() for t in out])
+        comp.close()
+    for x, y in zip(got[0], got[1]):
+        assert np.array_equal(x, y)
+    mean = sum(v.cpu().numpy().astype(np.float64) for v in V) / W
+    assert all(np.allclose(x, mean, rtol=0, atol=1e-6) for x in got[1][len(layers):])
