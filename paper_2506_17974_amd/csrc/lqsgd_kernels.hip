@@ -2228,7 +2228,7 @@ __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const L
   // 323 -> 308; through LDS, behind a barrier of the workgroup, 149, 297 and 310).  The others go through LDS, at rank pad 64 in lists of up
   // to two items a CU, which wait for single items (a step, us, r = 50, W = 8 registers / LDS: 20 x (100 x 300) 130.5 / 129.3, 64 x 512, 30 of
   // them 113.2 / 111.7; but the ResNet-18 set, 1800 items, 476 / 488, for the barrier).
-  // Where a layer has one row block these are the sums themselves, and their absmax is taken here, a pass over a copy less (a step:
+  // Where a layer has one row block these are the sums themselves, and their absmax is taken here if a quantiser reads it, a pass over a copy less (a step:
   // ResNet-18 set, W = 8, r = 50 482 -> 476, r = 32 350 -> 347, 8 x (256 x 4096), r = 50 366 -> 349, 2 x (60 x 300), r = 20 48.3 -> 44.7).
   const bool through_lds = NB == 1 || few;
   if (SHARE && through_lds) __syncthreads();     // (the rows of P-bar make room)
@@ -2236,8 +2236,9 @@ __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const L
   float* Qp = direct ? a.Qw + (size_t)worker * a.q_stride + ld.q_off
                      : a.Qpart + (size_t)worker * a.qpart_stride + ld.qpart_off + (size_t)(tl.row0 / ld.rbb) * ld.nq_pad;
   float mx = 0.0f;
+  const bool raise = direct && a.bits_q > 0;
   auto absmax = [&]() __attribute__((always_inline)) {           // (values beyond the columns or ranks are zeros)
-    if (direct) {
+    if (raise) {
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -2310,7 +2311,7 @@ __device__ __forceinline__ void back_project_mfma_tile(const DevArgs& a, const L
       }
     }
   }
-  if (direct) {
+  if (raise) {
     mx = wave_max(mx);
     if (lane == 0) atomicMax(reinterpret_cast<unsigned int*>(a.scaleQ + (size_t)worker * a.L + tl.lw / a.W), __float_as_uint(mx));
   }
