@@ -58,7 +58,7 @@ int64_t Plan::block_bytes() const {
   n += granules(sizeof(LayerDesc) * L) + granules(sizeof(VecDesc) * V) + 4 * granules(4 * 256);
   n += granules(sizeof(Tile) * tilesA.size()) + granules(sizeof(Tile) * tilesB.size()) + granules(sizeof(Tile) * tilesBM.size());
   n += granules(sizeof(XTile) * tilesXP.size()) + granules(sizeof(XTile) * tilesXQ.size());
-  n += granules(sizeof(RTile) * tilesRQ.size()) + granules(sizeof(RTile) * tilesRP.size()) + granules(sizeof(VTile) * tilesV.size());
+  n += granules(sizeof(RTile) * (tilesRQ.size() + spared_rq)) + granules(sizeof(RTile) * tilesRP.size()) + granules(sizeof(VTile) * tilesV.size());
   return n;
 }
 
@@ -105,6 +105,7 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
   max_rows = 0;
   slices = 0;
   plane_rows = 0;
+  spared_rq = 0;
   matrix_elements = 0;
   for (int i = 0; i < n_layers; ++i) {
     const lqsgd_layer& l = ls[i];
@@ -345,6 +346,7 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
         for (int32_t rb = 0; rb < d.nrb; ++rb)
           for (int32_t cg = 0; cg < (d.cols + kMfmaCols - 1) / kMfmaCols; ++cg)
             tilesBM.push_back(Tile{lw, rb * d.rbb, std::min(d.rbb, d.rows - rb * d.rbb), cg});
+      if (d.direct_q && mfma) spared_rq += (d.nq_el + rq_chunk - 1) / rq_chunk;
       if (!d.direct_q)
         for (int32_t e = 0; e < d.nq_el; e += rq_chunk) tilesRQ.push_back(RTile{lw, e, std::min(rq_chunk, d.nq_el - e)});
       if (agg_first)

@@ -100,6 +100,7 @@ struct Plan {
   std::vector<Tile> tilesG;        // one pass over every layer of worker 0 (G-hat only): row block x 256 columns
   std::vector<XTile> tilesXP, tilesXQ;
   std::vector<RTile> tilesRQ;
+  int64_t spared_rq = 0;           // ... of layers of one row block at rank pads 32 and 64, which need none; block_bytes() counts them
   std::vector<RTile> tilesRP;      // aggregate-first order: reduce of the P partials (1024 elements each)
   bool agg_first = false;          // LQSGD_FLAG_AGGREGATE_FIRST
   bool narrow_rows = false;        // most elements are in layers of fewer than 256 columns

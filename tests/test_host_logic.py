@@ -215,3 +215,11 @@ def test_work_lists_of_ragged_sets_cover_each_element_once(sweep, rank, shapes):
         assert widest == (64 if few else 256)
     if sweep == 0 and rank < 9:
         assert widest <= 256 if few else widest > 256
+
+
+@pytest.mark.parametrize("layers,rank,W,items", [([(128, 4285)] * 2, 50, 8, [160, 288, 160]), ([(256, 3045)] * 8, 64, 2, [192, 384, 192]),
+                                                 ([(128, 27711)], 64, 2, [112, 220, 112])])
+def test_split_of_sets_a_few_kilobytes_beyond_the_static_block(layers, rank, W, items):
+    """Rank pads 32 and 64: a layer of one row block needs no reduce items, but the rule that decides a set's split (and with it the
+    order of its sums) and what the entry point that allocates nothing takes goes on counting them."""
+    assert list(B.plan_query(B.layer_list(layers, ()), rank, 8, 8, W).tiles) == items
