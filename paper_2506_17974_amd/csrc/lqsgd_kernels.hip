@@ -4614,7 +4614,7 @@ bool launch_orth_col(const DevArgs& a, int max_rows, dim3 grid, hipStream_t s) {
   // More factors than CUs: what counts is the work of a factor, not its chain (640 of them, one wavefront a column or block / as
   // chosen: 512 rows at r = 16 27 / 24 us, 120 rows 18 / 14; 60 rows at r = 40 41 / 37; 64 rows at r = 30 28 / 23.5.  168 of them at
   // r = 16 14.1 / 15.1).
-  const bool many = grid.x > 256;
+  const bool many = grid.x > kCus;
   if constexpr (C == 4) {
     LQSGD_LAUNCH_OW(512, 4, 2, 4, 1, 2, 4, false)        // (500 rows 8.6 -> 8.3 us, but 1000 rows 8.1 -> 9.0, 1700 9.7 -> 12.4)
     LQSGD_LAUNCH_OC(1024, 4, 4, 8)
@@ -4658,6 +4658,7 @@ bool launch_orth_col(const DevArgs& a, int max_rows, dim3 grid, hipStream_t s) {
     LQSGD_LAUNCH_OW(1024, 4, 4, 16, 2, 2, 32, true)
   }
 #undef LQSGD_LAUNCH_OC
+#undef LQSGD_LAUNCH_OW
   return false;
 }
 
@@ -4809,7 +4810,7 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, int64_t plane_rows, c
   if (a.L <= 0) return hipSuccess;
   const dim3 grid(a.L * a.W);
   const int nslice = (max_rows + 255) / 256;
-  // More rows than one workgroup holds, or tall factors and too few (layer, worker) pairs to fill 256 CUs with one workgroup each:
+  // More rows than one workgroup holds, or tall factors and too few (layer, worker) pairs to fill the CUs with one workgroup each:
   // many workgroups per factor, or, at rank pads 1 to 4, one that adds in their order (orth_tall_kernel: a cooperative launch alone
   // costs about 20 us, its launches one by one 9 us a column; W = 4, r = 4, slices / one workgroup, us: 2048 x 1024 29 / 8.6, 8192 x 1024
   // 33 / 15, 8192^2 35 / 24).  It reads all planes on one CU, the slices on 8 to 44, so that many planes of many rows go to them: up to
@@ -4822,7 +4823,7 @@ hipError_t launch_orth(int rp, int max_rows, int max_rank, int64_t plane_rows, c
   // pad 8 (130 factors of 8000 rows: 121 us, Cholesky-QR 186) and 4096 at pad 16 (3000 rows: 119 and 125), with results that
   // differ by their rounding times the factor's condition number, which at those ranks can be a thousand.
   const bool fits = max_rows <= (rp <= 4 ? 11264 : rp == 8 ? 4096 : rp <= 32 ? 1792 : 1024);
-  const bool few = nslice >= 8 && grid.x < 128;
+  const bool few = nslice >= 8 && grid.x < kCus / 2;
   if (rp <= 4 && fits && few && plane_rows <= (1 << 17) && !(coop && coop->max_polls)) {
     const bool tall = rp == 1 ? launch_orth_tall<1>(a, max_rows, grid, s) : rp == 2 ? launch_orth_tall<2>(a, max_rows, grid, s)
                                                                                     : launch_orth_tall<4>(a, max_rows, grid, s);

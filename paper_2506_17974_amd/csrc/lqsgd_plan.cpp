@@ -305,7 +305,7 @@ int Plan::build_split(const lqsgd_config* c, const lqsgd_layer* ls, int32_t n_la
     d.q_off = q_acc;   q_acc += round_up(d.nq_el, 64);
     d.ppart_off = pp_acc; pp_acc += (int64_t)d.nseg * d.np_pad;
     plane_rows = std::max(plane_rows, (int64_t)d.rows * d.nseg);
-    d.qpart_off = qp_acc; qp_acc += d.direct_q && !mfma ? 0 : (int64_t)d.nrb * d.nq_pad;   // no partial planes where sweep 1 stores Q_w itself (rank pads 32 and 64 keep the room: Gram-Schmidt has a use for it)
+    d.qpart_off = qp_acc; qp_acc += d.direct_q && !mfma ? 0 : (int64_t)d.nrb * d.nq_pad;   // no partial planes where sweep 1 stores Q_w itself.  Rank pads 32 and 64 keep their room: it is part of block_bytes(), by which build() chooses a set's split, and its sums with it; at pad 64 Gram matrices lie there besides
     d.pop_off = ppd_acc; ppd_acc += round_up((int64_t)d.rows * RP, 64);
     d.qop_off = qpd_acc; qpd_acc += round_up((int64_t)d.cols * RP, 64);
     if (d.r < RP) padded = true;
