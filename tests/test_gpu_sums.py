@@ -141,6 +141,43 @@ def test_gram_schmidt_sums_of_few_tall_factors(monkeypatch, rank, rows):
         comp.close()
 
 
+# in place on the aggregate (whose padded copy the sweeps then read), and on caller-held state
+@pytest.mark.parametrize("rank", [1, 2, 3])
+def test_gram_schmidt_of_a_tall_aggregate(rank):
+    import torch
+    _say("case: tall aggregate", rank)
+    layers, W = [(2500, 300), (40, 12), (1800, 2)], 3
+    rng = np.random.default_rng(rank)
+    Q = [rng.standard_normal((c, min(rank, n, c))).astype(f32) for n, c in layers]
+    G = pu.to_device([[(rng.standard_normal(s) * 1e-3).astype(f32) for s in layers] for _ in range(W)])
+    comp = B.Compressor(B.layer_list(layers, ()), rank, 0, 0, W, 255.0, B.FLAG_AGGREGATE_FIRST)
+    for l, q in enumerate(Q):
+        comp.set_q(l, q)
+    out = [torch.zeros(s, device="cuda") for s in layers]
+    comp.step(G, out)
+    assert comp.launched_kernel(B.KERNEL_ORTH).startswith("orth_tall")
+    for l in range(len(layers)):
+        p, q = comp.get_factor(B.FACTOR_P_BAR, l), comp.get_factor(B.FACTOR_Q_BAR, l).astype(np.float64)
+        assert np.array_equal(p, _gram_schmidt_slices(comp.get_factor(B.FACTOR_P_MEAN, l), rank == 1)), l
+        mean = sum(g[l].cpu().numpy().astype(np.float64) for g in G) / W
+        assert pu.rel_fro(q, mean.T @ p.astype(np.float64)) < pu.FP_TOL
+        assert pu.rel_fro(out[l].cpu().numpy(), p.astype(np.float64) @ q.T) < pu.FP_TOL
+    comp.close()
+    layers_c = B.layer_list(layers, ())
+    info = B.plan_query(layers_c, rank, 0, 0, W, 255.0, B.FLAG_AGGREGATE_FIRST)
+    residual = torch.zeros((W, info.residual_stride), device="cuda")
+    warm = torch.zeros(info.warm_q_floats, device="cuda")
+    at = 0
+    for q in Q:
+        warm[at:at + q.size].copy_(torch.from_numpy(q).reshape(-1))
+        at += -(-q.size // 64) * 64
+    same = [torch.zeros(s, device="cuda") for s in layers]
+    B.step_static(layers_c, rank, 0, 0, W, 255.0, B.FLAG_AGGREGATE_FIRST, G, residual, warm, same)
+    torch.cuda.synchronize()
+    for x, y in zip(out, same):
+        assert torch.equal(x, y)
+
+
 # the same beside layers of many columns: planes of 2^17 rows together by one workgroup, of more by the slices
 @pytest.mark.parametrize("rank,rows,cols,name", [(1, 2048, 65536, "orth_tall"), (1, 2048, 65537, "orth_coop"), (4, 4097, 32000, "orth_coop"),
                                                  (3, 4000, 32768, "orth_tall")])
