@@ -89,7 +89,8 @@ typedef struct {
 #define LQSGD_FLAG_BF16_GRADIENTS 4u
 /* Never launch a kernel cooperatively.  The Gram-Schmidt of tall factors with few
  * (layer, worker) pairs normally runs as one cooperative launch whose workgroups
- * exchange partial sums while it runs; with this flag it takes its form of
+ * exchange partial sums while it runs (up to rank 4 only factors of more than 11264
+ * rows or of many column segments do); with this flag it takes its form of
  * several ordinary launches (same bits, slower: 0.2 ms instead of 0.1 ms at
  * 8192 rows, rank 32, 16 workers).  For processes in which cooperative launches
  * are unwelcome -- e.g. under rocprofv3, whose exit handler has been seen to
